@@ -284,6 +284,8 @@ int rosaq_stream_probe(const void* src_dev, size_t src_bytes, const void* shared
  *   "rot_splits"  the dense rotation of calls of 17 to 64 rows as n = 2-16 slabs of the contraction
  *             whose partial tiles a second launch adds (0, 1 = the single-launch rotation, the
  *             default; a count whose slabs exceed 32 k-steps also keeps the single launch)
+ *   "wide"    the 128 x 256 tile kernel for many rows (main GEMM and dense rotation): 0 = heuristic, 1 = never,
+ *             2 = every launch of more than 64 rows
  *   "stages"  3 = whole call (default), 1 = prologue kernels only, 2 = main GEMM only
  *             (2 reuses the rotated activations a previous call left in the workspace)
  * For benchmarks and tests only: the settings are process-wide and not synchronised, so no other
@@ -295,6 +297,7 @@ int rosaq_tune(const char* key, int32_t value);
  * would get: M rows, `channels` output channels in total over the layers of the launch (each layer
  * rounded up to whole 16-channel tiles by the caller: pass the sum of 16 * ceil(N_i / 16)),
  * `in_features` = D, `bits` 3 or 4 (16 for an all-fp16 layer), under the current rosaq_tune settings.
+ * (Calls of many rows may run as the fixed 128 x 256 tiles of tune key "wide" instead.)
  * shape_out (HOST, 5 ints) receives mt, nt (tiles of 16 rows / 16 channels per workgroup), waves per
  * workgroup, units in flight per wave and the number of workgroups that split one tile's contraction
  * (given a workspace of rosaq_workspace_bytes_batch size).  Errors: ROSAQ_ERR_NULL, ROSAQ_ERR_SHAPE (M, channels < 1,

@@ -313,8 +313,9 @@ static int run_prologue(const rosaq_packed_t* p, const WsPlan& w, const void* x_
   a.M = M;
   a.ks_s = c.D / kKStep; a.G = 0; a.KS = c.D / kKStep; a.KS_out = c.D / kKStep;
   a.bits = 4; a.out_frag = 1;
+  // "rot_splits" selects the slab launches above, never a ticketed split: no room for partial tiles is offered
   GemmTune tune = g_tune_rot;
-  tune.splits = 1;           // "rot_splits" selects the slab launches above, never a ticketed split
+  tune.splits = 0;
   return launch_gemm(a, tune, hip_stream);
 }
 
@@ -677,6 +678,10 @@ int rosaq_tune(const char* key, int32_t value) {
     if (!std::strcmp(k, "nt")) { g_tune_rot.nt = value; return ROSAQ_OK; }
     if (!std::strcmp(k, "depth")) { g_tune_rot.depth = value; return ROSAQ_OK; }
     return fail(ROSAQ_ERR_ARG, "unknown tuning key");
+  }
+  if (!std::strcmp(key, "wide")) {
+    if (value < 0 || value > 2) return fail(ROSAQ_ERR_ARG, "wide must be 0, 1 or 2");
+    g_tune.wide = g_tune_rot.wide = value; return ROSAQ_OK;
   }
   if (!std::strcmp(key, "depth")) {
     if (value < 0 || value > 4) return fail(ROSAQ_ERR_ARG, "depth must be 0 to 4");

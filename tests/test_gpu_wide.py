@@ -1,0 +1,97 @@
+"""The kernel for many rows (128 x 256 outputs per workgroup, activations shared through LDS), forced with the tuning
+key "wide" at the sizes where it can go wrong: one unit of the contraction, fewer units than ring buffers, fp16 units
+only, a last row group and a last channel chunk that are partly or almost wholly padding."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from oracle import rosaq_oracle as O
+from paper_2506_13472_amd import binding as B
+from paper_2506_13472_amd import torch_glue as T
+from test_gpu_parity import check_output, make_case, run_gpu
+from test_gpu_swiglu import check_swiglu, run, run_mlp, run_two_calls, synth_down
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def wide():
+    B.rosaq_tune("wide", 2)
+    yield
+    B.rosaq_tune("wide", 0)
+
+
+@pytest.mark.parametrize("mode,bits,M,D,N,K", [(O.MODE_NONE, 4, 128, 128, 256, 0),        # one low-bit unit, one full tile
+                                               (O.MODE_NONE, 3, 65, 128, 40, 128),        # one fp16 unit, K = D
+                                               (O.MODE_NONE, 3, 129, 256, 257, 128),      # one row and one channel over
+                                               (O.MODE_HEADWISE, 4, 200, 384, 130, 128),
+                                               (O.MODE_HEADWISE, 3, 320, 640, 600, 0),    # an odd number of 64-row blocks
+                                               (O.MODE_FULL, 4, 300, 512, 512, 256),      # fp16 form as the dense rotation
+                                               (O.MODE_FULL, 3, 72, 384, 272, 384)])
+def test_wide_against_oracle(mode, bits, M, D, N, K):
+    print(f"case wide mode={mode} bits={bits} M={M} D={D} N={N} K={K}", flush=True)
+    lay, Q, lam = make_case(500 + M, M, D, N, 300, mode)
+    ref = O.pack(lay["W"], Q, lam, K, bits, mode)
+    p = B.rosaq_pack_weights(lay["W"], Q, lam, K, bits, mode)
+    y = run_gpu(p, lay["x"])
+    check_output(y, lay["x"], Q, ref)
+    # a row stride that keeps rows off 16-byte boundaries goes through the element-wise store: same values
+    x = torch.from_numpy(lay["x"]).cuda()
+    odd = torch.full((M, N + 3), 7.0, dtype=torch.float16, device="cuda")
+    T.linear(p, x, odd[:, :N])
+    torch.cuda.synchronize()
+    got = odd.cpu().numpy()
+    assert np.array_equal(np.ascontiguousarray(got[:, :N]).view(np.uint16), y.view(np.uint16))
+    assert np.all(got[:, N:] == 7.0)
+    p.free()
+
+
+def test_wide_batch_straddles_layers():
+    print("case wide batch", flush=True)
+    lay, Q, lam = make_case(510, 150, 256, 200, 300, O.MODE_HEADWISE)
+    Ws = [lay["W"], lay["W"][:72].copy(), (lay["W"][::-1] * np.float16(0.5)).astype(np.float16)]
+    refs = [O.pack(W, Q, lam, 128, 4, O.MODE_HEADWISE) for W in Ws]
+    ps = [B.rosaq_pack_weights(W, Q, lam, 128, 4, B.Q_HEADWISE) for W in Ws]
+    ys = T.linear_batch(ps, torch.from_numpy(lay["x"]).cuda())
+    torch.cuda.synchronize()
+    for y, ref in zip(ys, refs):
+        check_output(y.cpu().numpy(), lay["x"], Q, ref)
+    for p in ps:
+        p.free()
+
+
+@pytest.mark.parametrize("bits,M,D,F,N,Kd", [(4, 150, 384, 384, 72, 128), (3, 260, 256, 640, 300, 0)])
+def test_wide_gated_block(bits, M, D, F, N, Kd):
+    print(f"case wide gated bits={bits} M={M} D={D} F={F} N={N}", flush=True)
+    lay, Q, lam = make_case(520 + M, M, D, F, 300, O.MODE_FULL)
+    Wu = (lay["W"][::-1] * np.float16(1.5)).astype(np.float16)
+    lam_d = np.abs(np.random.default_rng(5).standard_normal(F)) + 0.1
+    refs = [O.pack(W, Q, lam, 128, bits, O.MODE_FULL) for W in (lay["W"], Wu)]
+    pg, pu = (B.rosaq_pack_weights(W, Q, lam, 128, bits, B.Q_FULL) for W in (lay["W"], Wu))
+    pd = B.rosaq_pack_weights(synth_down(530, N, F), None, lam_d, Kd, bits, B.Q_NONE)
+    try:
+        check_swiglu(run(pg, pu, lay["x"]), lay["x"], Q, refs[0], refs[1])
+        _, y2 = run_two_calls(pg, pu, pd, lay["x"])
+        y = run_mlp(pg, pu, pd, lay["x"])
+        assert np.array_equal(y.view(np.uint16), y2.view(np.uint16))
+    finally:
+        for p in (pg, pu, pd):
+            p.free()
+
+
+def test_wide_is_the_default_where_it_fills_the_chip():
+    """2048 x 8192 outputs: the heuristic's own choice equals the forced kernel bit for bit and gemm_kernel's result
+    up to the order of the fp32 sums."""
+    print("case wide default", flush=True)
+    lay, Q, lam = make_case(540, 64, 1024, 8192, 64, O.MODE_NONE)
+    p = B.rosaq_pack_weights(lay["W"], Q, lam, 128, 4, B.Q_NONE)
+    x = np.tile(lay["x"], (32, 1))
+    y = run_gpu(p, x)
+    B.rosaq_tune("wide", 0)
+    assert np.array_equal(run_gpu(p, x).view(np.uint16), y.view(np.uint16))
+    B.rosaq_tune("wide", 1)
+    y1 = run_gpu(p, x).astype(np.float64)
+    assert np.linalg.norm(y - y1) <= 1e-3 * np.linalg.norm(y1)
+    assert not np.array_equal(y1.astype(np.float16).view(np.uint16), y.view(np.uint16))
+    p.free()
