@@ -1,18 +1,29 @@
 // PCA of the calibration activations on the GPU (Sec. 3.1 Eq. 4; per attention head Sec. 3.1.1,
 // Eq. 6): the eigenvectors of C = X^T X / n_cal are the right singular vectors of X, its
 // eigenvalues the squared column norms of X V / n_cal.  One-sided Jacobi: plane rotations are
-// applied to pairs of columns of X (kept transposed, Y[c][:] = column c, so that a column is
-// contiguous) until all columns are mutually orthogonal; the same rotations accumulate in V.
-// C itself is never formed, and a rotation touches two rows of Y and of V only, so the disjoint
-// pairs of a round run on one workgroup each with no exchange at all -- one launch per round,
-// Db - 1 rounds per sweep.  A layer-wise rotation is one problem of dimension D; a head-wise one
-// is D / 128 independent problems of dimension 128 that share every launch.
-// Calibration-time code: it allocates its own scratch and waits for the result.
+// applied to pairs of columns of X until all columns are mutually orthogonal; the same rotations
+// accumulate in V.  C itself is never formed.
+//
+// The rotations are applied in blocks (block one-sided Jacobi).  The columns of a problem are cut into blocks of
+// 32; a round pairs the blocks (round-robin), and for every pair of blocks
+//   gram_kernel    forms the 64 x 64 matrix of inner products of the pair's columns (fp64 MFMA),
+//   rotate_kernel  finds the plane rotations from it: 32 rounds that meet each column of one block with each of
+//                  the other (63, all pairs, in a sweep's first round), applied to the 64 x 64 matrix from both sides
+//                  and accumulated into an orthogonal 64 x 64 matrix J, all in LDS,
+//   apply_kernel   multiplies the pair's columns of X V and of V by J (fp64 MFMA).
+// That makes D_b / 32 - 1 rounds of three launches per sweep where rotating one pair of columns at a
+// time takes D_b - 1 launches that stream all of X V and V each: 32 heads of 128 channels, 512 rows
+// 15.1 -> 2.3 ms, one problem of 1024 channels, 2048 rows 161 -> 25 ms.  Bound now by rotate_kernel, whose 32 dependent
+// rounds take 1.1 us each (128 KiB of LDS traffic, two barriers and the chain of the angles), 60 % of the time.
+//
+// Columns are kept contiguous: Z[c] = [column c of X V (n_pad rows, zero padded) | row c of V^T].
+// A layer-wise rotation is one problem of dimension D; a head-wise one is D / 128 independent problems of
+// dimension 128 that share every launch.  Calibration-time code: it allocates its own scratch and
+// waits for the result.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <cmath>
-#include <numeric>
 #include <string>
 #include <vector>
 
@@ -20,107 +31,336 @@
 
 namespace rosaq {
 
-// Y[c][r] = X[r][c] in fp64 (rows padded with zeros to n_pad); Vt of every block = I
-// (Vt[c][j], c the global channel, j the channel inside c's block of Db).
-__global__ __launch_bounds__(256) void hestenes_init_kernel(const _Float16* __restrict__ X, int64_t ldx,
-                                                            int n_cal, int n_pad, int Db,
-                                                            double* __restrict__ Y, double* __restrict__ Vt) {
-  const int c = blockIdx.x;
-  for (int r = threadIdx.x; r < n_pad; r += 256)
-    Y[static_cast<size_t>(c) * n_pad + r] = r < n_cal ? static_cast<double>(X[static_cast<int64_t>(r) * ldx + c]) : 0.0;
-  for (int j = threadIdx.x; j < Db; j += 256) Vt[static_cast<size_t>(c) * Db + j] = j == c % Db ? 1.0 : 0.0;
+typedef double doublex2 __attribute__((ext_vector_type(2)));
+typedef double doublex4 __attribute__((ext_vector_type(4)));
+
+constexpr int kPcaBlock = 32;                // columns per block
+constexpr int kPcaPanel = 2 * kPcaBlock;     // columns of a pair of blocks
+constexpr int kPcaTiles = 10;                // 16 x 16 tiles on and above the diagonal of the panel's matrix
+
+// One calibration set on the device.
+struct PcaDev {
+  double* Z;          // [D][pitch]
+  double* part;       // inner products of the pairs' columns: [pair][chunk][10 tiles][256]
+  double* J;          // [pair][64][64], J^T: row c' holds the weights of the old columns in new column c'
+  double* gamma2;     // [rounds][pairs]: sum of squared inner products of a pair of blocks
+  double* diag2;      // [pairs]: sum of squared squared norms, first round of a sweep
+  int* done;          // [problems]: converged
+  int n_pad, pitch, Db, chunk_rows, chunks;
+};
+
+// Pair k of a round-robin tournament of `n` players in `round`: player n - 1 stays, the others move one seat
+// per round; seat k meets seat n - 1 - k.  Lower number first.
+__device__ __forceinline__ void tournament(int n, int round, int k, int& a, int& b) {
+  const int other = n - 1 - k;
+  const int x = (k + round) % (n - 1), y = other == n - 1 ? n - 1 : (other + round) % (n - 1);
+  a = x < y ? x : y;
+  b = x < y ? y : x;
 }
 
-// One round: workgroup (block b, seat k) rotates the pair (p, q) that the round-robin tournament
-// assigns to seat k (player Db - 1 stays, the others move one seat per round; seat k meets seat
-// Db - 1 - k).
-//   alpha = |y_p|^2, beta = |y_q|^2, gamma = y_p . y_q;  zeta = (beta - alpha) / (2 gamma),
-//   t = sign(zeta) / (|zeta| + sqrt(1 + zeta^2)), c = 1 / sqrt(1 + t^2), s = c t,
-//   (y_p, y_q) <- (c y_p - s y_q, s y_p + c y_q), the same for the rows p, q of Vt.
-// Pairs that are orthogonal to round-off (|gamma| <= eps sqrt(alpha beta)) are left alone.
-// gamma^2 of every pair (before its rotation) and, in the first round of a sweep, alpha^2 + beta^2
-// go to slots that a later launch adds up in a fixed order.
-__global__ __launch_bounds__(256) void hestenes_round_kernel(double* __restrict__ Y, double* __restrict__ Vt,
-                                                             int n_pad, int Db, int round,
-                                                             double* __restrict__ gamma2,
-                                                             double* __restrict__ diag2) {
-  __shared__ double red[3][4];
-  const int half = Db / 2;
-  const int blk = blockIdx.x / half, k = blockIdx.x - blk * half, tid = threadIdx.x;
-  auto player = [&](int seat) { return seat == Db - 1 ? Db - 1 : (seat + round) % (Db - 1); };
-  const int a = player(k), b = player(Db - 1 - k);
-  const size_t p = static_cast<size_t>(blk) * Db + (a < b ? a : b), q = static_cast<size_t>(blk) * Db + (a < b ? b : a);
-  double* yp = Y + p * n_pad;
-  double* yq = Y + q * n_pad;
-  double al = 0.0, be = 0.0, ga = 0.0;
-  for (int r = tid; r < n_pad; r += 256) {
-    const double u = yp[r], v = yq[r];
-    al = __builtin_fma(u, u, al); be = __builtin_fma(v, v, be); ga = __builtin_fma(u, v, ga);
+// First global column of each block of pair `pair` in `round`.
+__device__ __forceinline__ int pair_columns(const PcaDev& p, int pair, int round, int& c0, int& c1) {
+  const int blocks = p.Db / kPcaBlock, half = blocks / 2;
+  const int problem = pair / half;
+  int a, b;
+  tournament(blocks, round, pair - problem * half, a, b);
+  c0 = problem * p.Db + a * kPcaBlock;
+  c1 = problem * p.Db + b * kPcaBlock;
+  return problem;
+}
+
+// Z[c] = [X[:, c] in fp64, zero padded | unit vector of c's channel inside its problem]; 64 x 64 tiles of X are
+// turned through LDS so that both sides move whole lines.
+__global__ __launch_bounds__(256) void pca_init_kernel(const _Float16* __restrict__ X, int64_t ldx, int n_cal, PcaDev p) {
+  __shared__ _Float16 tile[64][66];
+  const int c0 = blockIdx.x * 64, r0 = blockIdx.y * 64;
+  if (r0 < p.n_pad) {
+    for (int i = threadIdx.x; i < 64 * 64; i += 256) {
+      const int r = i >> 6, c = i & 63;
+      tile[r][c] = r0 + r < n_cal ? X[static_cast<int64_t>(r0 + r) * ldx + c0 + c] : static_cast<_Float16>(0.0f);
+    }
+    __syncthreads();
+  }
+  for (int i = threadIdx.x; i < 64 * 64; i += 256) {
+    const int c = i >> 6, r = i & 63;
+    const double v = r0 < p.n_pad ? static_cast<double>(tile[r][c]) : (r0 - p.n_pad + r == (c0 + c) % p.Db ? 1.0 : 0.0);
+    p.Z[static_cast<size_t>(c0 + c) * p.pitch + r0 + r] = v;
+  }
+}
+
+// Inner products of a pair's 64 columns over a chunk of rows: four waves take 16 rows each in turn, lane (i, q) holding
+// rows 4 q .. 4 q + 3 of column i of each group of 16 columns (the order of the contraction is free).
+__global__ __launch_bounds__(256) void gram_kernel(PcaDev p, int round) {
+  __shared__ double red[kPcaTiles * 256];
+  int c0, c1;
+  if (p.done[pair_columns(p, blockIdx.x, round, c0, c1)]) return;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int r_lo = blockIdx.y * p.chunk_rows, r_hi = min(r_lo + p.chunk_rows, p.n_pad);
+  const double* col[4];
+#pragma unroll
+  for (int t = 0; t < 4; ++t)
+    col[t] = p.Z + static_cast<size_t>((t < 2 ? c0 : c1) + (t & 1) * 16 + (lane & 15)) * p.pitch + 4 * (lane >> 4);
+  doublex4 acc[kPcaTiles];
+#pragma unroll
+  for (int i = 0; i < kPcaTiles; ++i) acc[i] = doublex4{0.0, 0.0, 0.0, 0.0};
+  for (int r = r_lo + 16 * wave; r < r_hi; r += 64) {
+    doublex2 v[4][2];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      v[t][0] = *reinterpret_cast<const doublex2*>(col[t] + r);
+      v[t][1] = *reinterpret_cast<const doublex2*>(col[t] + r + 2);
+    }
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      int i = 0;
+#pragma unroll
+      for (int ta = 0; ta < 4; ++ta)
+#pragma unroll
+        for (int tb = ta; tb < 4; ++tb, ++i)
+          acc[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(v[ta][s >> 1][s & 1], v[tb][s >> 1][s & 1], acc[i], 0, 0, 0);
+    }
+  }
+  // the waves' sums meet in wave order
+  for (int w = 0; w < 4; ++w) {
+    if (wave == w) {
+#pragma unroll
+      for (int i = 0; i < kPcaTiles; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          double* d = &red[i * 256 + e * 64 + lane];
+          *d = w == 0 ? acc[i][e] : *d + acc[i][e];
+        }
+    }
+    __syncthreads();
+  }
+  double* out = p.part + (static_cast<size_t>(blockIdx.x) * p.chunks + blockIdx.y) * (kPcaTiles * 256);
+  for (int i = threadIdx.x; i < kPcaTiles * 256; i += 256) out[i] = red[i];
+}
+
+__device__ __forceinline__ double fast_rsqrt(double x) {   // x > 0; two Newton steps on the hardware's estimate
+  double y = __builtin_amdgcn_rsq(x);
+  y = y * __builtin_fma(-0.5 * x * y, y, 1.5);
+  return y * __builtin_fma(-0.5 * x * y, y, 1.5);
+}
+__device__ __forceinline__ double fast_rcp(double x) {
+  double y = __builtin_amdgcn_rcp(x);
+  y = y * __builtin_fma(-x, y, 2.0);
+  return y * __builtin_fma(-x, y, 2.0);
+}
+
+// The rotations of a pair of blocks.  With alpha = |y_p|^2, beta = |y_q|^2, gamma = y_p . y_q:
+//   d = beta - alpha, t = sign(d) 2 gamma / (|d| + sqrt(d^2 + 4 gamma^2)), c = 1 / sqrt(1 + t^2), s = c t,
+//   (y_p, y_q) <- (c y_p - s y_q, s y_p + c y_q);
+// columns that are orthogonal to round-off (|gamma| <= eps sqrt(alpha beta)) are left alone.  Of a round's 32 rotations
+// one wave computes the angles; then thread (a, b) turns the 2 x 2 block of rows (p_a, q_a) and columns (p_b, q_b).
+__global__ __launch_bounds__(1024) void rotate_kernel(PcaDev p, int round, int pairs) {
+  __shared__ double G[kPcaPanel][kPcaPanel];
+  __shared__ double Jt[kPcaPanel][kPcaPanel];
+  __shared__ doublex2 cs[kPcaBlock];
+  __shared__ double red[2][16];
+  int c0, c1;
+  if (p.done[pair_columns(p, blockIdx.x, round, c0, c1)]) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  {
+    const double* part = p.part + static_cast<size_t>(blockIdx.x) * p.chunks * (kPcaTiles * 256);
+    for (int i = tid; i < kPcaTiles * 256; i += 1024) {
+      double v = 0.0;
+      for (int ch = 0; ch < p.chunks; ++ch) v += part[static_cast<size_t>(ch) * (kPcaTiles * 256) + i];
+      // accumulator e of lane l of a 16 x 16 tile: row 4 e + l / 16, column l % 16
+      const int tile = i >> 8, e = (i >> 6) & 3, l = i & 63;
+      const int ta = tile < 4 ? 0 : (tile < 7 ? 1 : (tile < 9 ? 2 : 3));
+      const int tb = tile - (ta == 0 ? 0 : (ta == 1 ? 3 : (ta == 2 ? 5 : 6)));
+      const int r = ta * 16 + 4 * e + (l >> 4), c = tb * 16 + (l & 15);
+      G[r][c] = v;
+      G[c][r] = v;                       // inside a diagonal tile both orders of an element hold the same sum
+    }
+    for (int i = tid; i < kPcaPanel * kPcaPanel; i += 1024) Jt[i >> 6][i & 63] = (i >> 6) == (i & 63) ? 1.0 : 0.0;
+  }
+  __syncthreads();
+  // what the convergence test needs, before anything is rotated: gamma^2 between the blocks, in a sweep's first round also
+  // inside them, and alpha^2
+  const bool all_pairs = round == 0;
+  double g2 = 0.0, d2 = 0.0;
+  for (int i = tid; i < kPcaPanel * kPcaPanel; i += 1024) {
+    const int r = i >> 6, c = i & 63;
+    const double v = G[r][c];
+    if (r < c && (all_pairs || (r < kPcaBlock && c >= kPcaBlock))) g2 = __builtin_fma(v, v, g2);
+    if (r == c) d2 = __builtin_fma(v, v, d2);
   }
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    al += __shfl_down(al, o, 64); be += __shfl_down(be, o, 64); ga += __shfl_down(ga, o, 64);
-  }
-  if ((tid & 63) == 0) { red[0][tid >> 6] = al; red[1][tid >> 6] = be; red[2][tid >> 6] = ga; }
+  for (int o = 32; o > 0; o >>= 1) { g2 += __shfl_down(g2, o, 64); d2 += __shfl_down(d2, o, 64); }
+  if (lane == 0) { red[0][wave] = g2; red[1][wave] = d2; }
   __syncthreads();
-  al = (red[0][0] + red[0][1]) + (red[0][2] + red[0][3]);
-  be = (red[1][0] + red[1][1]) + (red[1][2] + red[1][3]);
-  ga = (red[2][0] + red[2][1]) + (red[2][2] + red[2][3]);
   if (tid == 0) {
-    gamma2[blockIdx.x] = ga * ga;
-    if (diag2 != nullptr) diag2[blockIdx.x] = al * al + be * be;
+    double a = 0.0, b = 0.0;
+    for (int w = 0; w < 16; ++w) { a += red[0][w]; b += red[1][w]; }
+    p.gamma2[static_cast<size_t>(round) * pairs + blockIdx.x] = a;
+    if (all_pairs) p.diag2[blockIdx.x] = b;
   }
-  if (!(fabs(ga) > 2.220446049250313e-16 * sqrt(al * be))) return;   // also alpha or beta zero, NaN
-  const double zeta = (be - al) / (2.0 * ga);
-  const double t = zeta == 0.0 ? 1.0 : copysign(1.0, zeta) / (fabs(zeta) + hypot(1.0, zeta));
-  const double c = 1.0 / sqrt(1.0 + t * t), s = c * t;
-  for (int r = tid; r < n_pad; r += 256) {
-    const double u = yp[r], v = yq[r];
-    yp[r] = c * u - s * v;
-    yq[r] = s * u + c * v;
+
+  const int a = tid >> 5, b = tid & 31;
+  const int rounds = all_pairs ? kPcaPanel - 1 : kPcaBlock;
+  for (int r = 0; r < rounds; ++r) {
+    auto columns = [&](int k, int& x, int& y) {
+      if (all_pairs) tournament(kPcaPanel, r, k, x, y);
+      else { x = k; y = kPcaBlock + ((k + r) & (kPcaBlock - 1)); }
+    };
+    int pa, qa, pb, qb;
+    columns(a, pa, qa);
+    columns(b, pb, qb);
+    if (wave == 0) {                     // both halves of the wave compute the same
+      const double al = G[pb][pb], be = G[qb][qb], ga = G[pb][qb];
+      doublex2 v = {1.0, 0.0};
+      const double ab = al * be;
+      if (ab > 0.0 && ga * ga > 4.930380657631324e-32 * ab) {    // false too where one is NaN
+        const double d = be - al, g = 2.0 * ga;
+        const double h2 = __builtin_fma(d, d, g * g);
+        const double t = copysign(1.0, d) * g * fast_rcp(fabs(d) + h2 * fast_rsqrt(h2));
+        const double c = fast_rsqrt(__builtin_fma(t, t, 1.0));
+        v = doublex2{c, c * t};
+      }
+      if (lane < kPcaBlock) cs[b] = v;
+    }
+    __syncthreads();
+    const doublex2 ra = cs[a], rb = cs[b];
+    const double pp = G[pa][pb], pq = G[pa][qb], qp = G[qa][pb], qq = G[qa][qb];
+    const double pp1 = rb.x * pp - rb.y * pq, pq1 = rb.y * pp + rb.x * pq;      // columns
+    const double qp1 = rb.x * qp - rb.y * qq, qq1 = rb.y * qp + rb.x * qq;
+    G[pa][pb] = ra.x * pp1 - ra.y * qp1;                                        // rows
+    G[pa][qb] = ra.x * pq1 - ra.y * qq1;
+    G[qa][pb] = ra.y * pp1 + ra.x * qp1;
+    G[qa][qb] = ra.y * pq1 + ra.x * qq1;
+#pragma unroll
+    for (int i = b; i < kPcaPanel; i += 32) {
+      const double u = Jt[pa][i], v = Jt[qa][i];
+      Jt[pa][i] = ra.x * u - ra.y * v;
+      Jt[qa][i] = ra.y * u + ra.x * v;
+    }
+    __syncthreads();
   }
-  double* vp = Vt + p * Db;
-  double* vq = Vt + q * Db;
-  for (int j = tid; j < Db; j += 256) {
-    const double u = vp[j], v = vq[j];
-    vp[j] = c * u - s * v;
-    vq[j] = s * u + c * v;
-  }
+  double* out = p.J + static_cast<size_t>(blockIdx.x) * (kPcaPanel * kPcaPanel);
+  for (int i = tid; i < kPcaPanel * kPcaPanel; i += 1024) out[i] = Jt[i >> 6][i & 63];
 }
 
-// Per block b: out[2 b] = sum over rounds and seats of gamma2, out[2 b + 1] = sum over seats of
-// diag2.  One workgroup per block; every thread adds its strided share in order and the 256
-// shares are added in a fixed tree, so the sums do not depend on scheduling.
-__global__ __launch_bounds__(256) void hestenes_sum_kernel(const double* __restrict__ gamma2, int rounds,
-                                                           const double* __restrict__ diag2, int half,
-                                                           int seats_total, double* __restrict__ out) {
+// Columns c' of a pair <- sum over c of J[c][c'] column c, for 64 entries of Z: a wave owns 16 entries of all 64
+// columns, which it reads before it writes any.
+__global__ __launch_bounds__(256) void apply_kernel(PcaDev p, int round) {
+  __shared__ double Jt[kPcaPanel][kPcaPanel + 2];
+  int c0, c1;
+  if (p.done[pair_columns(p, blockIdx.x, round, c0, c1)]) return;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int i16 = lane & 15, q = lane >> 4;
+  const double* J = p.J + static_cast<size_t>(blockIdx.x) * (kPcaPanel * kPcaPanel);
+  const int row = blockIdx.y * 64 + wave * 16 + i16;
+  auto column = [&](int c) { return p.Z + static_cast<size_t>((c < kPcaBlock ? c0 : c1 - kPcaBlock) + c) * p.pitch + row; };
+  double z[16];                                       // columns 16 q + s of this entry
+#pragma unroll
+  for (int s = 0; s < 16; ++s) z[s] = *column(16 * q + s);
+  for (int i = threadIdx.x; i < kPcaPanel * kPcaPanel; i += 256) Jt[i >> 6][i & 63] = J[i];
+  __syncthreads();
+  doublex4 acc[4];
+#pragma unroll
+  for (int t = 0; t < 4; ++t) acc[t] = doublex4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int s = 0; s < 16; ++s)
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+      acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(Jt[t * 16 + i16][16 * q + s], z[s], acc[t], 0, 0, 0);
+#pragma unroll
+  for (int t = 0; t < 4; ++t)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) *column(t * 16 + 4 * e + q) = acc[t][e];
+}
+
+// End of a sweep, one workgroup per problem: converged when the off-diagonal part of the implied second
+// moment is below tol times its norm (2 sum gamma^2 <= tol^2 (sum alpha^2 + 2 sum gamma^2), measured over the
+// sweep).  Every thread adds its strided share in order and the shares are added in a fixed tree, so the sums do not
+// depend on scheduling.  done: 1 = converged, 2 = not a number.
+__global__ __launch_bounds__(256) void pca_check_kernel(PcaDev p, int rounds, int half, int pairs, double tol) {
   __shared__ double sh[2][256];
-  const int blk = blockIdx.x;
+  const int problem = blockIdx.x;
+  if (p.done[problem]) return;
   double g = 0.0, d = 0.0;
   for (int i = threadIdx.x; i < rounds * half; i += 256)
-    g += gamma2[static_cast<size_t>(i / half) * seats_total + blk * half + i % half];
-  for (int i = threadIdx.x; i < half; i += 256) d += diag2[blk * half + i];
+    g += p.gamma2[static_cast<size_t>(i / half) * pairs + problem * half + i % half];
+  for (int i = threadIdx.x; i < half; i += 256) d += p.diag2[problem * half + i];
   sh[0][threadIdx.x] = g; sh[1][threadIdx.x] = d;
   __syncthreads();
   for (int w = 128; w > 0; w >>= 1) {
     if (threadIdx.x < w) { sh[0][threadIdx.x] += sh[0][threadIdx.x + w]; sh[1][threadIdx.x] += sh[1][threadIdx.x + w]; }
     __syncthreads();
   }
-  if (threadIdx.x == 0) { out[2 * blk] = sh[0][0]; out[2 * blk + 1] = sh[1][0]; }
+  if (threadIdx.x == 0) {
+    const double off2 = 2.0 * sh[0][0], norm2 = sh[1][0] + off2;
+    if (!(off2 == off2)) p.done[problem] = 2;
+    else if (off2 <= tol * tol * norm2) p.done[problem] = 1;
+  }
 }
 
-// lambda_c = |y_c|^2 / n_cal
-__global__ __launch_bounds__(256) void hestenes_norms_kernel(const double* __restrict__ Y, int n_pad, int n_cal,
-                                                             double* __restrict__ lam) {
-  __shared__ double red[4];
-  const int c = blockIdx.x;
-  double a = 0.0;
-  for (int r = threadIdx.x; r < n_pad; r += 256) { const double u = Y[static_cast<size_t>(c) * n_pad + r]; a = __builtin_fma(u, u, a); }
+// lambda_c = |y_c|^2 / n_cal, and the sign that makes column c's entry of largest magnitude (the first of equals) positive.
+__global__ __launch_bounds__(256) void pca_norms_kernel(PcaDev p, int n_cal, double* __restrict__ lam,
+                                                        double* __restrict__ sign) {
+  __shared__ double red[4], big[4];
+  __shared__ int at[4];
+  const int c = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const double* z = p.Z + static_cast<size_t>(c) * p.pitch;
+  double a = 0.0, m = -1.0;
+  int where = 0;
+  for (int r = threadIdx.x; r < p.n_pad; r += 256) a = __builtin_fma(z[r], z[r], a);
+  for (int j = threadIdx.x; j < p.Db; j += 256) {
+    const double v = fabs(z[p.n_pad + j]);
+    if (v > m) { m = v; where = j; }
+  }
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) a += __shfl_down(a, o, 64);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = a;
+  for (int o = 32; o > 0; o >>= 1) {
+    a += __shfl_down(a, o, 64);
+    const double m2 = __shfl_down(m, o, 64);
+    const int w2 = __shfl_down(where, o, 64);
+    if (m2 > m || (m2 == m && w2 < where)) { m = m2; where = w2; }
+  }
+  if (lane == 0) { red[wave] = a; big[wave] = m; at[wave] = where; }
   __syncthreads();
-  if (threadIdx.x == 0) lam[c] = ((red[0] + red[1]) + (red[2] + red[3])) / static_cast<double>(n_cal);
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < 4; ++w)
+      if (big[w] > big[0] || (big[w] == big[0] && at[w] < at[0])) { big[0] = big[w]; at[0] = at[w]; }
+    lam[c] = ((red[0] + red[1]) + (red[2] + red[3])) / static_cast<double>(n_cal);
+    sign[c] = z[p.n_pad + at[0]] < 0.0 ? -1.0 : 1.0;
+  }
+}
+
+// Column c's place among its problem's eigenvalues, descending, ties in column order; eig sorted.
+__global__ __launch_bounds__(64) void pca_order_kernel(const double* __restrict__ lam, int Db, int* __restrict__ order,
+                                                       double* __restrict__ eig) {
+  __shared__ double sh[64];
+  const int c = blockIdx.x * 64 + threadIdx.x;      // 64 columns of one problem
+  const int base = c / Db * Db;
+  const double v = lam[c];
+  int rank = 0;
+  for (int j0 = base; j0 < base + Db; j0 += 64) {
+    __syncthreads();
+    sh[threadIdx.x] = lam[j0 + threadIdx.x];
+    __syncthreads();
+#pragma unroll 16
+    for (int j = 0; j < 64; ++j) rank += sh[j] > v || (sh[j] == v && j0 + j < c) ? 1 : 0;
+  }
+  order[base + rank] = c;
+  eig[base + rank] = fmax(v, 0.0);
+}
+
+// Q[problem][i][j] = entry i of the eigenvector of rank j, fp32: 64 x 64 tiles turned through LDS.
+__global__ __launch_bounds__(256) void pca_write_kernel(PcaDev p, const int* __restrict__ order,
+                                                        const double* __restrict__ sign, float* __restrict__ Q) {
+  __shared__ float tile[64][65];
+  const int tiles = p.Db / 64;
+  const int problem = blockIdx.y / tiles, j0 = (blockIdx.y % tiles) * 64, i0 = blockIdx.x * 64;
+  for (int k = threadIdx.x; k < 64 * 64; k += 256) {
+    const int c = order[problem * p.Db + j0 + (k >> 6)];
+    tile[k >> 6][k & 63] = static_cast<float>(sign[c] * p.Z[static_cast<size_t>(c) * p.pitch + p.n_pad + i0 + (k & 63)]);
+  }
+  __syncthreads();
+  float* out = Q + static_cast<size_t>(problem) * p.Db * p.Db;
+  for (int k = threadIdx.x; k < 64 * 64; k += 256)
+    out[static_cast<size_t>(i0 + (k >> 6)) * p.Db + j0 + (k & 63)] = tile[k & 63][k >> 6];
 }
 
 static int pca_fail(hipError_t e, const char* what) {
@@ -128,88 +368,92 @@ static int pca_fail(hipError_t e, const char* what) {
   return ROSAQ_ERR_HIP;
 }
 
-// D / Db independent PCA problems of dimension Db on the channels [b Db, (b + 1) Db): sweeps of
-// Db - 1 rounds until, in every block, the off-diagonal part of the implied second moment is below
-// tol times its norm (2 sum gamma^2 <= tol^2 (sum alpha^2 + 2 sum gamma^2), measured over a
-// sweep).  Then the host bookkeeping of Eq. 4's "columns sorted by eigenvalue" per block:
-// descending order (ties keep the lower column first), each eigenvector signed so that its entry
-// of largest magnitude is positive.  Q_host is [D / Db][Db][Db], block b holding its eigenvectors
+// D / Db independent PCA problems of dimension Db on the channels [b Db, (b + 1) Db): sweeps until every problem
+// has converged (a converged one's kernels return at once), then Eq. 4's "columns sorted by eigenvalue" per
+// problem: descending order (ties keep the lower column first), each eigenvector signed so that its entry
+// of largest magnitude is positive.  Q_host is [D / Db][Db][Db], problem b holding its eigenvectors
 // as columns (for Db = D that is the row-major D x D rotation).
 static int pca_blocks_device(const void* X_dev, int n_cal, int D, int Db, int64_t ldx, float* Q_host,
                              double* eig_host, void* stream, const char* who) {
   hipStream_t st = static_cast<hipStream_t>(stream);
-  const int n_pad = (n_cal + 3) / 4 * 4, blocks = D / Db, half = Db / 2, rounds = Db - 1;
-  const int seats = blocks * half;
-  // host bookkeeping first: if it cannot be had, nothing on the device has been allocated yet
-  std::vector<double> stats(static_cast<size_t>(blocks) * 2), V, lam(D);
-  std::vector<int> order(Db);
-  double *dY = nullptr, *dV = nullptr, *dG = nullptr, *dD = nullptr, *dS = nullptr, *dL = nullptr;
-  hipError_t e = hipMalloc(&dY, static_cast<size_t>(D) * n_pad * 8);
-  if (e == hipSuccess) e = hipMalloc(&dV, static_cast<size_t>(D) * Db * 8);
-  if (e == hipSuccess) e = hipMalloc(&dG, static_cast<size_t>(rounds) * seats * 8);
-  if (e == hipSuccess) e = hipMalloc(&dD, static_cast<size_t>(seats) * 8);
-  if (e == hipSuccess) e = hipMalloc(&dS, static_cast<size_t>(blocks) * 2 * 8);
-  if (e == hipSuccess) e = hipMalloc(&dL, static_cast<size_t>(D) * 8);
-  constexpr int kMaxSweeps = 60;
+  const int problems = D / Db, blocks = Db / kPcaBlock, half = blocks / 2, rounds = blocks - 1;
+  const int pairs = problems * half;
+  std::vector<int> done(problems);   // before anything is allocated on the device
+  PcaDev p{};
+  p.n_pad = (n_cal + 63) / 64 * 64;
+  p.pitch = p.n_pad + Db;
+  p.Db = Db;
+  // rows of a chunk: enough workgroups for the chip, no more than eight partial sums per pair
+  const int want = std::max(1, std::min(8, 512 / pairs));
+  p.chunk_rows = ((p.n_pad / 64 + want - 1) / want) * 64;
+  p.chunks = (p.n_pad + p.chunk_rows - 1) / p.chunk_rows;
+  const size_t sizes[] = {static_cast<size_t>(D) * p.pitch * 8, static_cast<size_t>(pairs) * p.chunks * kPcaTiles * 256 * 8,
+                          static_cast<size_t>(pairs) * kPcaPanel * kPcaPanel * 8, static_cast<size_t>(rounds) * pairs * 8,
+                          static_cast<size_t>(pairs) * 8, static_cast<size_t>(problems) * 4, static_cast<size_t>(D) * 8,
+                          static_cast<size_t>(D) * 8, static_cast<size_t>(D) * 8, static_cast<size_t>(D) * 4,
+                          static_cast<size_t>(D) * Db * 4};
+  constexpr int kParts = sizeof(sizes) / sizeof(sizes[0]);
+  size_t offs[kParts], total = 0;
+  for (int i = 0; i < kParts; ++i) { offs[i] = total; total += (sizes[i] + 255) / 256 * 256; }
+  char* mem = nullptr;
+  hipError_t e = hipMalloc(reinterpret_cast<void**>(&mem), total);
+  if (e != hipSuccess) return pca_fail(e, who);
+  p.Z = reinterpret_cast<double*>(mem + offs[0]);
+  p.part = reinterpret_cast<double*>(mem + offs[1]);
+  p.J = reinterpret_cast<double*>(mem + offs[2]);
+  p.gamma2 = reinterpret_cast<double*>(mem + offs[3]);
+  p.diag2 = reinterpret_cast<double*>(mem + offs[4]);
+  p.done = reinterpret_cast<int*>(mem + offs[5]);
+  double* lam = reinterpret_cast<double*>(mem + offs[6]);
+  double* sign = reinterpret_cast<double*>(mem + offs[7]);
+  double* eig = reinterpret_cast<double*>(mem + offs[8]);
+  int* order = reinterpret_cast<int*>(mem + offs[9]);
+  float* Q = reinterpret_cast<float*>(mem + offs[10]);
+
+  constexpr int kMaxSweeps = 60, kBlindSweeps = 5;   // no calibration set converges in fewer: the host does not look before
   constexpr double kTol = 1e-13;
   bool converged = false;
+  e = hipMemsetAsync(p.done, 0, sizes[5], st);
   if (e == hipSuccess) {
-    hipLaunchKernelGGL(hestenes_init_kernel, dim3(D), dim3(256), 0, st, static_cast<const _Float16*>(X_dev), ldx,
-                       n_cal, n_pad, Db, dY, dV);
+    hipLaunchKernelGGL(pca_init_kernel, dim3(D / 64, p.pitch / 64), dim3(256), 0, st,
+                       static_cast<const _Float16*>(X_dev), ldx, n_cal, p);
     e = hipGetLastError();
   }
   for (int sweep = 0; e == hipSuccess && sweep < kMaxSweeps && !converged; ++sweep) {
     for (int r = 0; r < rounds && e == hipSuccess; ++r) {
-      hipLaunchKernelGGL(hestenes_round_kernel, dim3(seats), dim3(256), 0, st, dY, dV, n_pad, Db, r,
-                         dG + static_cast<size_t>(r) * seats, r == 0 ? dD : nullptr);
+      hipLaunchKernelGGL(gram_kernel, dim3(pairs, p.chunks), dim3(256), 0, st, p, r);
+      hipLaunchKernelGGL(rotate_kernel, dim3(pairs), dim3(1024), 0, st, p, r, pairs);
+      hipLaunchKernelGGL(apply_kernel, dim3(pairs, p.pitch / 64), dim3(256), 0, st, p, r);
       e = hipGetLastError();
     }
     if (e != hipSuccess) break;
-    hipLaunchKernelGGL(hestenes_sum_kernel, dim3(blocks), dim3(256), 0, st, dG, rounds, dD, half, seats, dS);
+    hipLaunchKernelGGL(pca_check_kernel, dim3(problems), dim3(256), 0, st, p, rounds, half, pairs, kTol);
     e = hipGetLastError();
-    if (e == hipSuccess) e = hipMemcpyAsync(stats.data(), dS, stats.size() * 8, hipMemcpyDeviceToHost, st);
+    if (e != hipSuccess || sweep + 1 < kBlindSweeps) continue;
+    e = hipMemcpyAsync(done.data(), p.done, sizes[5], hipMemcpyDeviceToHost, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) break;
     converged = true;
-    for (int b = 0; b < blocks; ++b) {
-      // ||C_b||_F^2 n_cal^2 = sum alpha^2 + 2 sum gamma^2 at the start of the sweep; off^2 = 2 sum gamma^2
-      const double off2 = 2.0 * stats[2 * b], norm2 = stats[2 * b + 1] + 2.0 * stats[2 * b];
-      if (!(off2 == off2)) { e = hipErrorUnknown; break; }
-      if (!(off2 <= kTol * kTol * norm2)) converged = false;
+    for (int v : done) {
+      if (v == 2) { e = hipErrorUnknown; break; }
+      if (v == 0) converged = false;
     }
   }
-  if (e == hipSuccess) {
-    hipLaunchKernelGGL(hestenes_norms_kernel, dim3(D), dim3(256), 0, st, dY, n_pad, n_cal, dL);
+  if (e == hipSuccess && converged) {
+    hipLaunchKernelGGL(pca_norms_kernel, dim3(D), dim3(256), 0, st, p, n_cal, lam, sign);
+    hipLaunchKernelGGL(pca_order_kernel, dim3(D / 64), dim3(64), 0, st, lam, Db, order, eig);
+    hipLaunchKernelGGL(pca_write_kernel, dim3(Db / 64, D / 64), dim3(256), 0, st, p, order, sign, Q);
     e = hipGetLastError();
+    if (e == hipSuccess) e = hipMemcpyAsync(Q_host, Q, sizes[10], hipMemcpyDeviceToHost, st);
+    if (e == hipSuccess) e = hipMemcpyAsync(eig_host, eig, sizes[8], hipMemcpyDeviceToHost, st);
   }
-  if (e == hipSuccess) {
-    try { V.resize(static_cast<size_t>(D) * Db); } catch (const std::bad_alloc&) { e = hipErrorOutOfMemory; }
-  }
-  if (e == hipSuccess) e = hipMemcpyAsync(V.data(), dV, static_cast<size_t>(D) * Db * 8, hipMemcpyDeviceToHost, st);
-  if (e == hipSuccess) e = hipMemcpyAsync(lam.data(), dL, static_cast<size_t>(D) * 8, hipMemcpyDeviceToHost, st);
-  if (e == hipSuccess) e = hipStreamSynchronize(st);
-  for (double* q : {dY, dV, dG, dD, dS, dL})
-    if (q) (void)hipFree(q);
+  const hipError_t es = hipStreamSynchronize(st);   // also before the scratch is freed
+  if (e == hipSuccess) e = es;
+  (void)hipFree(mem);
   if (e != hipSuccess) return pca_fail(e, who);
   if (!converged) {
     set_error("one-sided Jacobi did not converge within 60 sweeps");
     return ROSAQ_ERR_NOCONVERGE;
-  }
-  for (int b = 0; b < blocks; ++b) {
-    const double* lb = &lam[static_cast<size_t>(b) * Db];
-    std::iota(order.begin(), order.end(), 0);
-    std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return lb[x] > lb[y]; });
-    float* Qb = Q_host + static_cast<size_t>(b) * Db * Db;
-    for (int j = 0; j < Db; ++j) {
-      const int src = order[j];
-      const double* v = &V[(static_cast<size_t>(b) * Db + src) * Db];    // row src of Vt = eigenvector src
-      eig_host[static_cast<size_t>(b) * Db + j] = std::max(lb[src], 0.0);
-      int big = 0;
-      for (int i = 1; i < Db; ++i)
-        if (std::fabs(v[i]) > std::fabs(v[big])) big = i;
-      const double sign = v[big] < 0.0 ? -1.0 : 1.0;
-      for (int i = 0; i < Db; ++i) Qb[static_cast<size_t>(i) * Db + j] = static_cast<float>(sign * v[i]);
-    }
   }
   return ROSAQ_OK;
 }
