@@ -2,6 +2,7 @@
 // the per-call launch sequence.  No arithmetic of the method happens here.
 #include <hip/hip_runtime_api.h>
 
+#include <atomic>
 #include <climits>
 #include <cstdlib>
 #include <cstring>
@@ -104,13 +105,37 @@ static int check_desc(const rosaq_pack_desc* d) {
     }                                                                           \
   } while (0)
 
-// The offline step with the layer on the GPU: upload W (and Q), rotate in fp64 (Eq. 1), then one
+// What one offline step on the GPU holds besides the handle's own buffer; given back on every way out.
+struct PackScratch {
+  char* mem = nullptr;
+  hipStream_t copies = nullptr;      // uploads and downloads run beside the kernels
+  hipStream_t work = nullptr;        // the caller's stream
+  std::vector<hipEvent_t> events;
+  hipError_t event(hipEvent_t* e) {
+    events.push_back(nullptr);
+    const hipError_t r = hipEventCreateWithFlags(&events.back(), hipEventDisableTiming);
+    *e = events.back();
+    return r;
+  }
+  ~PackScratch() {
+    if (copies) { (void)hipStreamSynchronize(copies); (void)hipStreamDestroy(copies); }
+    if (mem) { (void)hipStreamSynchronize(work); (void)hipFree(mem); }
+    for (hipEvent_t e : events) if (e) (void)hipEventDestroy(e);
+  }
+};
+
+// The offline step with the layer on the GPU: upload Q and W, rotate in fp64 (Eq. 1), then one
 // pass from the rotated fp16 weight to the fragment images the kernels read and to the canonical
 // arrays (Sec. 3.2-3.3, Eq. 3), which come back to the host for rosaq_packed_export.  Only the
-// input checks and the ranking of D eigenvalues stay on the host.
+// ranking of D eigenvalues stays on the host.
+// The rows go through in chunks: while the GPU works on one, the next is uploaded and finished ones are
+// downloaded on a second stream, and the pages of the arrays they go to are touched by several threads
+// (a download into untouched memory runs at 4 GB/s, into touched memory at 16).  Inf / NaN in W and Q and the rotation's
+// fingerprint are found by kernels on the uploaded copies; a byte-wise hash of a 4096 x 4096 rotation on the host
+// alone took 54 ms.  11008 x 4096 INT3 with a dense rotation, export included: 79 -> 13 ms.
 static int pack_device(const rosaq_pack_desc& d, hipStream_t st, rosaq_packed* p) {
   std::string err;
-  int rc = pack_validate(d, &err);
+  int rc = pack_validate_eigenvalues(d, &err);
   if (rc != ROSAQ_OK) return fail(rc, err);
   pack_select(d, &p->c);
   Canonical& c = p->c;
@@ -122,7 +147,7 @@ static int pack_device(const rosaq_pack_desc& d, hipStream_t st, rosaq_packed* p
   const size_t wS_bytes = ntiles * ks_s * 64 * 16, wq_bytes = ntiles * G * rec_dwords * 4;
   const size_t qf_bytes = !keep_q ? 0 : (headwise ? (D / kHeadDim) * 8 * 4 * 64 * 16
                                                   : (D / kTileN) * (D / kKStep) * 64 * 16);
-  const size_t q_bytes = !rotate ? 0 : (headwise ? D * kHeadDim : D * D) * sizeof(float);
+  const size_t q_words = !rotate ? 0 : (headwise ? D * kHeadDim : D * D);
 
   // the handle's device buffer: [wS | wq | qf | perm | pos]
   struct Part { size_t bytes; void** dst; };
@@ -143,58 +168,104 @@ static int pack_device(const rosaq_pack_desc& d, hipStream_t st, rosaq_packed* p
   p->d_perm = static_cast<int32_t*>(d_perm);
   p->d_pos = static_cast<int32_t*>(d_pos);
 
-  // host arrays the canonical form comes back into (sized before the scratch exists: an allocation
-  // failure here must not leave it behind)
+  // host arrays the canonical form comes back into
   c.W_S.resize(N * K); c.codes.resize(N * C); c.scales.resize(N * G); c.zeros.resize(N * G);
-  // scratch of this call: [W | What | Q | W_S | codes | scales | zeros | flag]
-  const size_t sizes[] = {N * D * 2, rotate ? N * D * 2 : 0, q_bytes, N * K * 2, N * C, N * G * 2, N * G * 2, 256};
+  // chunks: at most eight, at least 8 MiB of W each, of a number of rows whose 128 x 128 tiles of the rotation come to
+  // two whole workgroups per compute unit
+  const size_t round_rows = 128 * ((512 * 128 + D - 1) / D);
+  const size_t chunk = align_up(std::max<size_t>((N + 7) / 8, (size_t{4} << 20) / D), rotate && !headwise ? round_rows : 128);
+  const size_t chunks = (N + chunk - 1) / chunk;
+  PackScratch t;
+  t.work = st;
+  t.events.reserve(2 * chunks);
+  // scratch of this call: [W | What | Q | W_S | codes | scales | zeros | flags and hash]
+  const size_t sizes[] = {N * D * 2, rotate ? N * D * 2 : 0, q_words * 4, N * K * 2, N * C, N * G * 2, N * G * 2, 256};
   size_t offs[8], tmp_total = 0;
   for (int i = 0; i < 8; ++i) { offs[i] = tmp_total; tmp_total += align_up(std::max<size_t>(sizes[i], 16), 256); }
-  char* tmp = nullptr;
-  ROSAQ_HIP(hipMalloc(reinterpret_cast<void**>(&tmp), tmp_total));
-  unsigned flag = 0;
-  hipError_t e = static_cast<size_t>(d.ldw) == D
-                     ? hipMemcpyAsync(tmp + offs[0], d.W, N * D * 2, hipMemcpyHostToDevice, st)
-                     : hipMemcpy2DAsync(tmp + offs[0], D * 2, d.W, static_cast<size_t>(d.ldw) * 2, D * 2, N,
-                                        hipMemcpyHostToDevice, st);
-  if (e == hipSuccess && rotate) e = hipMemcpyAsync(tmp + offs[2], d.Q, q_bytes, hipMemcpyHostToDevice, st);
-  if (e == hipSuccess) e = hipMemcpyAsync(d_perm, c.perm.data(), D * 4, hipMemcpyHostToDevice, st);
-  if (e == hipSuccess) e = hipMemcpyAsync(d_pos, c.pos.data(), D * 4, hipMemcpyHostToDevice, st);
-  if (e == hipSuccess) e = hipMemsetAsync(tmp + offs[7], 0, 256, st);
-  rc = ROSAQ_OK;
-  const char* what = tmp + offs[0];
-  if (e == hipSuccess && rotate) {
-    rc = launch_rotate_weights_f64(tmp + offs[0], tmp + offs[2], tmp + offs[1], static_cast<int>(N),
-                                   static_cast<int>(D), headwise ? 1 : 0, st);
-    what = tmp + offs[1];
-  }
-  if (e == hipSuccess && rc == ROSAQ_OK) {
+  ROSAQ_HIP(hipMalloc(reinterpret_cast<void**>(&t.mem), tmp_total));
+  ROSAQ_HIP(hipStreamCreateWithFlags(&t.copies, hipStreamNonBlocking));
+  char* const w_dev = t.mem + offs[0];
+  char* const what = rotate ? t.mem + offs[1] : w_dev;
+  char* const q_dev = t.mem + offs[2];
+  char* const flags = t.mem + offs[7];           // words: rotated weight, W, Q; then Q's hash in 64 bits
+  ROSAQ_HIP(hipMemsetAsync(flags, 0, 256, st));
+  ROSAQ_HIP(hipMemcpyAsync(d_perm, c.perm.data(), D * 4, hipMemcpyHostToDevice, t.copies));
+  ROSAQ_HIP(hipMemcpyAsync(d_pos, c.pos.data(), D * 4, hipMemcpyHostToDevice, t.copies));
+  if (rotate) ROSAQ_HIP(hipMemcpyAsync(q_dev, d.Q, q_words * 4, hipMemcpyHostToDevice, t.copies));
+  std::vector<hipEvent_t> finished(chunks);
+  for (size_t i = 0; i < chunks; ++i) {
+    const size_t n0 = i * chunk, rows = std::min(chunk, N - n0), tile0 = n0 / kTileN;
+    char* const w = w_dev + n0 * D * 2;
+    if (static_cast<size_t>(d.ldw) == D)
+      ROSAQ_HIP(hipMemcpyAsync(w, d.W + n0 * D, rows * D * 2, hipMemcpyHostToDevice, t.copies));
+    else
+      ROSAQ_HIP(hipMemcpy2DAsync(w, D * 2, d.W + n0 * static_cast<size_t>(d.ldw), static_cast<size_t>(d.ldw) * 2, D * 2,
+                                 rows, hipMemcpyHostToDevice, t.copies));
+    hipEvent_t uploaded;
+    ROSAQ_HIP(t.event(&uploaded));
+    ROSAQ_HIP(hipEventRecord(uploaded, t.copies));
+    ROSAQ_HIP(hipStreamWaitEvent(st, uploaded, 0));
+    if (i == 0 && rotate && (rc = launch_check_rotation(q_dev, q_words, flags + 8, flags + 16, st)) != ROSAQ_OK) return rc;
+    if (i == 0 && keep_q && (rc = launch_rotation_image(q_dev, c.D, headwise ? 1 : 0, p->d_perm, p->d_qf, st)) != ROSAQ_OK)
+      return rc;
+    if ((rc = launch_check_weight(w, rows * D, flags + 4, st)) != ROSAQ_OK) return rc;
+    if (rotate && (rc = launch_rotate_weights_f64(w, q_dev, what + n0 * D * 2, static_cast<int>(rows), c.D,
+                                                  headwise ? 1 : 0, st)) != ROSAQ_OK)
+      return rc;
     QuantPackArgs a{};
-    a.what16 = what; a.N = c.N; a.D = c.D; a.K = c.K; a.bits = c.bits; a.perm = p->d_perm;
-    a.wS_image = p->d_wS; a.wq_image = p->d_wq;
-    a.W_S = tmp + offs[3]; a.codes = tmp + offs[4]; a.scales = tmp + offs[5]; a.zeros = tmp + offs[6];
-    a.flag = tmp + offs[7];
-    rc = launch_quantize_pack(a, st);
+    a.what16 = what + n0 * D * 2; a.N = static_cast<int>(rows); a.D = c.D; a.K = c.K; a.bits = c.bits; a.perm = p->d_perm;
+    a.wS_image = static_cast<char*>(p->d_wS) + tile0 * ks_s * 64 * 16;
+    a.wq_image = static_cast<char*>(p->d_wq) + tile0 * G * rec_dwords * 4;
+    a.W_S = t.mem + offs[3] + n0 * K * 2; a.codes = t.mem + offs[4] + n0 * C;
+    a.scales = t.mem + offs[5] + n0 * G * 2; a.zeros = t.mem + offs[6] + n0 * G * 2;
+    a.flag = flags;
+    if ((rc = launch_quantize_pack(a, st)) != ROSAQ_OK) return rc;
+    ROSAQ_HIP(t.event(&finished[i]));
+    ROSAQ_HIP(hipEventRecord(finished[i], st));
   }
-  if (e == hipSuccess && rc == ROSAQ_OK && keep_q)
-    rc = launch_rotation_image(tmp + offs[2], c.D, headwise ? 1 : 0, p->d_perm, p->d_qf, st);
-  if (e == hipSuccess && rc == ROSAQ_OK) {
-    if (N * K) e = hipMemcpyAsync(c.W_S.data(), tmp + offs[3], N * K * 2, hipMemcpyDeviceToHost, st);
-    if (e == hipSuccess && N * C) e = hipMemcpyAsync(c.codes.data(), tmp + offs[4], N * C, hipMemcpyDeviceToHost, st);
-    if (e == hipSuccess && N * G) e = hipMemcpyAsync(c.scales.data(), tmp + offs[5], N * G * 2, hipMemcpyDeviceToHost, st);
-    if (e == hipSuccess && N * G) e = hipMemcpyAsync(c.zeros.data(), tmp + offs[6], N * G * 2, hipMemcpyDeviceToHost, st);
-    if (e == hipSuccess) e = hipMemcpyAsync(&flag, tmp + offs[7], 4, hipMemcpyDeviceToHost, st);
+  struct Array { char* host; size_t dev, row_bytes; };
+  const Array arrays[] = {{reinterpret_cast<char*>(c.codes.data()), offs[4], C}, {reinterpret_cast<char*>(c.W_S.data()), offs[3], K * 2},
+                          {reinterpret_cast<char*>(c.scales.data()), offs[5], G * 2}, {reinterpret_cast<char*>(c.zeros.data()), offs[6], G * 2}};
+  for (const Array& a : arrays) {
+    constexpr size_t kPage = 4096;
+    const size_t pages = N * a.row_bytes / kPage;
+    parallel_rows(static_cast<int>(pages / 64), [&](int lo, int hi) {
+      for (size_t pg = static_cast<size_t>(lo) * 64; pg < static_cast<size_t>(hi) * 64; ++pg) a.host[pg * kPage] = 0;
+    });
   }
-  const hipError_t es = hipStreamSynchronize(st);   // also before the scratch is freed
-  if (e == hipSuccess) e = es;
-  (void)hipFree(tmp);
-  if (rc != ROSAQ_OK) return rc;
-  if (e != hipSuccess) {
-    set_error(std::string("offline step on the device: ") + hipGetErrorString(e));
-    return ROSAQ_ERR_HIP;
+  for (size_t i = 0; i < chunks; ++i) {
+    const size_t n0 = i * chunk, rows = std::min(chunk, N - n0);
+    ROSAQ_HIP(hipStreamWaitEvent(t.copies, finished[i], 0));
+    for (const Array& a : arrays)
+      if (a.row_bytes)
+        ROSAQ_HIP(hipMemcpyAsync(a.host + n0 * a.row_bytes, t.mem + a.dev + n0 * a.row_bytes, rows * a.row_bytes,
+                                 hipMemcpyDeviceToHost, t.copies));
   }
-  if (flag) return fail(ROSAQ_ERR_NONFINITE, "rotated weight overflows fp16");
+  uint32_t found[6];
+  ROSAQ_HIP(hipMemcpyAsync(found, flags, sizeof(found), hipMemcpyDeviceToHost, t.copies));
+  ROSAQ_HIP(hipStreamSynchronize(t.copies));
+  ROSAQ_HIP(hipStreamSynchronize(st));
+  if (found[1]) return fail(ROSAQ_ERR_NONFINITE, "W contains NaN/Inf");
+  if (found[2]) return fail(ROSAQ_ERR_NONFINITE, "Q contains NaN/Inf");
+  if (found[0]) return fail(ROSAQ_ERR_NONFINITE, "rotated weight overflows fp16");
+  std::memcpy(&p->rot_fingerprint, &found[4], 8);
   return ROSAQ_OK;
+}
+
+// The same hash of the rotation for a layer that stays on the host.
+static uint64_t rotation_hash_host(const float* Q, size_t words) {
+  std::atomic<uint64_t> sum{0};
+  constexpr size_t kSlice = 4096;
+  parallel_rows(static_cast<int>((words + kSlice - 1) / kSlice), [&](int lo, int hi) {
+    uint64_t h = 0;
+    for (size_t i = static_cast<size_t>(lo) * kSlice; i < std::min(words, static_cast<size_t>(hi) * kSlice); ++i) {
+      uint32_t w;
+      std::memcpy(&w, Q + i, 4);
+      h += rotation_hash_word(i, w);
+    }
+    sum.fetch_add(h, std::memory_order_relaxed);
+  });
+  return sum.load();
 }
 
 static int check_call(const rosaq_packed_t* p, const void* x, int32_t M, int64_t ldx, void* y,
@@ -354,20 +425,18 @@ int rosaq_pack_weights(const rosaq_pack_desc* desc, void* hip_stream, rosaq_pack
     if (desc->host_only) {
       rc = pack_host(*desc, &p->c, &err);
       if (rc != ROSAQ_OK) set_error(err);
+      else if (desc->q_mode != ROSAQ_Q_NONE)
+        p->rot_fingerprint = rotation_hash_host(desc->Q, static_cast<size_t>(desc->in_features) *
+                                                             (desc->q_mode == ROSAQ_Q_FULL ? desc->in_features : kHeadDim));
     } else {
       rc = pack_device(*desc, static_cast<hipStream_t>(hip_stream), p);
     }
   } catch (const std::exception&) { rc = fail(ROSAQ_ERR_NOMEM, "out of host memory"); }
   if (rc != ROSAQ_OK) { rosaq_free(p); return rc; }
-  {
-    uint64_t h = fnv1a(1469598103934665603ull, &desc->q_mode, sizeof(desc->q_mode));
-    h = fnv1a(h, p->c.perm.data(), p->c.perm.size() * sizeof(int32_t));
-    if (desc->q_mode == ROSAQ_Q_FULL)
-      h = fnv1a(h, desc->Q, sizeof(float) * desc->in_features * static_cast<size_t>(desc->in_features));
-    else if (desc->q_mode == ROSAQ_Q_HEADWISE)
-      h = fnv1a(h, desc->Q, sizeof(float) * desc->in_features * static_cast<size_t>(kHeadDim));
-    p->rot_fingerprint = h;
-  }
+  // the storage order's bytes and the rotation's hash (left in the handle by the device path)
+  uint64_t h = fnv1a(1469598103934665603ull, &desc->q_mode, sizeof(desc->q_mode));
+  h = fnv1a(h, p->c.perm.data(), p->c.perm.size() * sizeof(int32_t));
+  p->rot_fingerprint = fnv1a(h, &p->rot_fingerprint, sizeof(p->rot_fingerprint));
   if (desc->rotation_absorbed) p->c.q_mode = ROSAQ_Q_NONE;   // run time sees rotated activations
   *out = p;
   return ROSAQ_OK;
@@ -607,11 +676,22 @@ int rosaq_packed_export(const rosaq_packed_t* p, int32_t* salient_idx, uint16_t*
                         uint16_t* scales, uint16_t* zeros) {
   if (!p) return fail(ROSAQ_ERR_NULL, "handle is NULL");
   const Canonical& c = p->c;
-  if (salient_idx) std::memcpy(salient_idx, c.salient_idx.data(), c.salient_idx.size() * 4);
-  if (W_S) std::memcpy(W_S, c.W_S.data(), c.W_S.size() * 2);
-  if (codes) std::memcpy(codes, c.codes.data(), c.codes.size());
-  if (scales) std::memcpy(scales, c.scales.data(), c.scales.size() * 2);
-  if (zeros) std::memcpy(zeros, c.zeros.data(), c.zeros.size() * 2);
+  // by several threads: a caller's fresh 45 MB array costs one thread 10 ms in page faults
+  auto copy = [](void* dst, const void* src, size_t bytes) {
+    constexpr size_t kSlice = size_t{256} << 10;
+    if (!dst) return;
+    parallel_rows(static_cast<int>((bytes + kSlice - 1) / kSlice), [&](int lo, int hi) {
+      const size_t from = lo * kSlice, to = std::min(bytes, hi * kSlice);
+      if (from < to) std::memcpy(static_cast<char*>(dst) + from, static_cast<const char*>(src) + from, to - from);
+    });
+  };
+  try {
+    copy(salient_idx, c.salient_idx.data(), c.salient_idx.size() * 4);
+    copy(W_S, c.W_S.data(), c.W_S.size() * 2);
+    copy(codes, c.codes.data(), c.codes.size());
+    copy(scales, c.scales.data(), c.scales.size() * 2);
+    copy(zeros, c.zeros.data(), c.zeros.size() * 2);
+  } catch (const std::exception&) { return fail(ROSAQ_ERR_NOMEM, "out of host memory"); }
   return ROSAQ_OK;
 }
 

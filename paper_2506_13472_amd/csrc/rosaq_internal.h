@@ -2,7 +2,11 @@
 #pragma once
 #include <cstddef>
 #include <cstdint>
+#include <functional>
+#include <memory>
+#include <new>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "rosaq.h"
@@ -19,6 +23,20 @@ constexpr int kMBlock = 64;    // rows of x handled by one workgroup pass (4 MFM
 uint16_t f64_to_f16(double v);  // round-half-to-even, one rounding, overflow -> inf
 double f16_to_f64(uint16_t h);
 
+// A vector whose resize() leaves its elements unwritten: the canonical arrays are filled by copies from the
+// GPU, and writing tens of megabytes of zeros first costs more than the copy.
+template <class T> struct NoInit : std::allocator<T> {
+  NoInit() = default;
+  template <class U> NoInit(const NoInit<U>&) {}
+  template <class U> struct rebind { using other = NoInit<U>; };
+  template <class U> void construct(U* p) { ::new (static_cast<void*>(p)) U; }
+  template <class U, class... A> void construct(U* p, A&&... a) { ::new (static_cast<void*>(p)) U(std::forward<A>(a)...); }
+};
+template <class T> using HostArray = std::vector<T, NoInit<T>>;
+
+// Runs fn over [0, n) in slices on several threads (rosaq_pack.cpp).
+void parallel_rows(int n, const std::function<void(int, int)>& fn);
+
 // Host-side result of the offline step (Eq. 3): canonical arrays in storage order.
 struct Canonical {
   int N = 0, D = 0, K = 0, bits = 0, q_mode = 0;
@@ -26,15 +44,15 @@ struct Canonical {
   std::vector<int32_t> salient_idx;   // [K] ascending
   std::vector<int32_t> perm;          // [D] storage position -> rotated channel
   std::vector<int32_t> pos;           // [D] rotated channel -> storage position
-  std::vector<uint16_t> W_S;          // [N x K] fp16
-  std::vector<uint8_t> codes;         // [N x (D-K)]
-  std::vector<uint16_t> scales;       // [N x G] fp16
-  std::vector<uint16_t> zeros;        // [N x G] fp16 (integer valued)
+  HostArray<uint16_t> W_S;            // [N x K] fp16
+  HostArray<uint8_t> codes;           // [N x (D-K)]
+  HostArray<uint16_t> scales;         // [N x G] fp16
+  HostArray<uint16_t> zeros;          // [N x G] fp16 (integer valued)
 };
 
-// Pieces of the offline step that also serve the device path: input checks, and the salient set
+// Pieces of the offline step that also serve the device path: the eigenvalue check, and the salient set
 // with the storage order (fills the shape fields, salient_idx, perm, pos).
-int pack_validate(const rosaq_pack_desc& d, std::string* err);
+int pack_validate_eigenvalues(const rosaq_pack_desc& d, std::string* err);
 void pack_select(const rosaq_pack_desc& d, Canonical* c);
 
 // Sec. 3.1-3.3 on the host.  Returns ROSAQ_OK or an error code with `err` filled.
@@ -116,12 +134,23 @@ size_t rotate_slab_part_bytes(int D, int slabs);
 int launch_rotate_slabs(const void* x, int64_t ldx, int M, int D, const void* qf, int slabs, void* part,
                         void* xf_out, void* zero_ptr, int zero_count, void* stream);
 
-int launch_rotate_weights_f64(const void* W_dev, const void* Q_dev, void* out_dev, int N, int D,
-                              int headwise, void* stream);
 int launch_stream_probe(const void* src, const void* shared, int workgroups, int threads, int w_kib,
                         int x_kib, int shared_kib, void* sink, void* stream);
 
-// Offline step on the device (rosaq_quant.hip): What16 [N x D] fp16 (device) -> fragment images and
+// Word i's share of a rotation's hash; the hash of a rotation is the sum over its fp32 words, modulo 2^64, so that
+// any number of threads can add it up (host and GPU give the same).
+#ifdef __HIPCC__
+__host__ __device__
+#endif
+inline uint64_t rotation_hash_word(uint64_t i, uint32_t w) {
+  uint64_t x = (i << 32) + i * 0x9e3779b97f4a7c15ull + w;
+  x ^= x >> 33; x *= 0xff51afd7ed558ccdull;
+  x ^= x >> 33; x *= 0xc4ceb9fe1a85ec53ull;
+  return x ^ (x >> 33);
+}
+
+// Offline step on the device (rosaq_quant.hip): What16 = fp16(W Q); input checks that set a word when W / Q holds Inf
+// or NaN (and add Q's hash to a 64-bit word); What16 [N x D] fp16 (device) -> fragment images and
 // canonical arrays (all device pointers; `flag` is one word that is set if What16 holds Inf / NaN).
 struct QuantPackArgs {
   const void* what16;
@@ -136,6 +165,10 @@ struct QuantPackArgs {
   void* flag;
 };
 int launch_quantize_pack(const QuantPackArgs& a, void* stream);
+int launch_rotate_weights_f64(const void* W_dev, const void* Q_dev, void* out_dev, int N, int D,
+                              int headwise, void* stream);
+int launch_check_weight(const void* W_dev, size_t elements, void* flag, void* stream);
+int launch_check_rotation(const void* Q_dev, size_t words, void* flag, void* hash, void* stream);
 int launch_rotation_image(const void* Q_dev, int D, int headwise, const int32_t* perm_dev, void* qf_image,
                           void* stream);
 

@@ -63,6 +63,8 @@ void tile_kernel(const double* a, int lda, const double* b, int ldb, double* o, 
   }
 }
 
+}  // namespace
+
 // Runs fn over [0, n) in slices on up to 32 threads.  An exception thrown by a slice (an
 // allocation that fails) is carried to the calling thread and thrown again there after every
 // thread has joined; if a thread cannot be started the remaining rows run on the calling thread.
@@ -96,6 +98,8 @@ void parallel_rows(int n, const std::function<void(int, int)>& fn) {
   for (auto& t : th) t.join();
   if (first) std::rethrow_exception(first);
 }
+
+namespace {
 
 // Dense rotation: out [N x D] fp64 = W (fp16) * Q (fp32 [D x D] row-major).
 void rotate_full(const rosaq_pack_desc& d, std::vector<double>* out) {
@@ -206,10 +210,16 @@ void pack_select(const rosaq_pack_desc& d, Canonical* c) {
 }
 
 // Input checks that need the data: every eigenvalue, weight and rotation entry finite.
-int pack_validate(const rosaq_pack_desc& d, std::string* err) {
-  const int N = d.out_features, D = d.in_features;
-  for (int i = 0; i < D; ++i)
+int pack_validate_eigenvalues(const rosaq_pack_desc& d, std::string* err) {
+  for (int i = 0; i < d.in_features; ++i)
     if (!std::isfinite(d.eigenvalues[i])) { *err = "eigenvalues contain NaN/Inf"; return ROSAQ_ERR_NONFINITE; }
+  return ROSAQ_OK;
+}
+
+static int pack_validate(const rosaq_pack_desc& d, std::string* err) {
+  const int N = d.out_features, D = d.in_features;
+  const int rc = pack_validate_eigenvalues(d, err);
+  if (rc != ROSAQ_OK) return rc;
   std::atomic<bool> bad{false};
   parallel_rows(N, [&](int lo, int hi) {
     bool local = false;

@@ -1,5 +1,5 @@
-// Offline step on the GPU (Sec. 3.2-3.3, Eq. 3): from the rotated weight What16 = fp16(W Q),
-// already in device memory, to the packed layer in one pass -- the fp16 salient block, per
+// Offline step on the GPU (Sec. 3.1-3.3, Eq. 1-3): What16 = fp16(W Q), then from there to the packed layer in
+// one pass -- the fp16 salient block, per
 // (output row, group) min / max, scale, zero point and codes -- written straight into the
 // fragment-ordered images the run-time kernels read, plus the layout-independent arrays that
 // rosaq_packed_export returns.  Scale and zero point are computed in fp64 exactly as the host
@@ -7,12 +7,129 @@
 // fp32), so the result is bit-identical to the host path.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <string>
 
 #include "rosaq_device.h"
 #include "rosaq_internal.h"
 
 namespace rosaq {
+
+// ---- What = W Q in fp64, one rounding to fp16 (Eq. 1) ---------------------------------------------
+// out[n][c] = fp16( sum_k W[n][k] * Q[k][c] ), W fp16 [N x D].  Q fp32: dense [D x D], or (headwise) blocks
+// [D/128][128][128] of a block-diagonal rotation, where the sum runs over the 128 channels of c's head
+// only (Eq. 5-6).
+// A workgroup owns 128 x 128 outputs, each of its four waves 64 x 64 as v_mfma_f64_16x16x4: per four channels a wave
+// reads eight fragments from LDS for sixteen MFMAs of 64 cycles, so that the matrix cores bound it (78.6 TFLOP/s in
+// fp64; on the vector units the operands' way through LDS did).  The next 16 channels are requested before the current
+// ones are multiplied and converted to fp64 once, on their way into the other LDS buffer.
+// W 11008 x 4096, dense Q: 11.5 -> 6.6 ms (56 TFLOP/s).
+constexpr int kF64Tile = 128, kF64Step = 16, kF64Pitch = kF64Tile + 16;   // the pad puts a fragment's k on other banks
+typedef double doublex4 __attribute__((ext_vector_type(4)));
+typedef _Float16 half8v __attribute__((ext_vector_type(8)));
+typedef float floatx4v __attribute__((ext_vector_type(4)));
+
+__global__ __launch_bounds__(256, 2) void rotate_weights_f64_kernel(const _Float16* __restrict__ W,
+                                                                    const float* __restrict__ Q,
+                                                                    uint16_t* __restrict__ out, int N, int D,
+                                                                    int headwise) {
+  __shared__ double sa[2][kF64Step][kF64Pitch];   // [k][row]
+  __shared__ double sb[2][kF64Step][kF64Pitch];   // [k][column]
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int n0 = blockIdx.y * kF64Tile, c0 = blockIdx.x * kF64Tile;
+  const int kb = headwise ? c0 : 0, steps = (headwise ? kHeadDim : D) / kF64Step;
+  const float* Qb = headwise ? Q + static_cast<size_t>(c0) * kHeadDim : Q + c0;      // row 0 of the sum
+  const int q_pitch = headwise ? kHeadDim : D;
+  const int ar = tid >> 1, ak = (tid & 1) * 8;       // this thread's 8 channels of a row of W
+  const int bk = tid >> 4, bc = (tid & 15) * 8;      // and its 8 columns of a row of Q
+  const _Float16* a_src = W + static_cast<size_t>(n0 + ar < N ? n0 + ar : N - 1) * D + kb + ak;
+  const float* b_src = Qb + static_cast<size_t>(bk) * q_pitch + bc;
+  half8v a;
+  floatx4v b[2];
+  auto load = [&](int s) {
+    a = *reinterpret_cast<const half8v*>(a_src + s * kF64Step);
+    const floatx4v* q = reinterpret_cast<const floatx4v*>(b_src + static_cast<size_t>(s) * kF64Step * q_pitch);
+    b[0] = q[0];
+    b[1] = q[1];
+  };
+  auto stage = [&](int buf) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) sa[buf][ak + e][ar] = static_cast<double>(a[e]);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) sb[buf][bk][bc + e] = static_cast<double>(b[e >> 2][e & 3]);
+  };
+  const int r0 = (wave >> 1) * 64, k0 = (wave & 1) * 64;   // this wave's quarter of the tile
+  doublex4 acc[4][4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = doublex4{0.0, 0.0, 0.0, 0.0};
+  load(0);
+  stage(0);
+  __syncthreads();
+  for (int s = 0; s < steps; ++s) {
+    const int buf = s & 1;
+    if (s + 1 < steps) load(s + 1);
+#pragma unroll
+    for (int k = 0; k < kF64Step; k += 4) {
+      double fa[4], fb[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        fa[i] = sa[buf][k + (lane >> 4)][r0 + i * 16 + (lane & 15)];
+        fb[i] = sb[buf][k + (lane >> 4)][k0 + i * 16 + (lane & 15)];
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[i], fb[j], acc[i][j], 0, 0, 0);
+    }
+    if (s + 1 < steps) stage(buf ^ 1);
+    __syncthreads();
+  }
+  // accumulator e of lane l: row 4 e + l / 16, column l % 16
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int n = n0 + r0 + i * 16 + 4 * e + (lane >> 4);
+      if (n >= N) continue;
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        out[static_cast<size_t>(n) * D + c0 + k0 + j * 16 + (lane & 15)] = f64_to_f16_bits(acc[i][j][e]);
+    }
+}
+
+// Input checks of the offline step, on the copies that are on the GPU anyway: W holds Inf / NaN; Q holds Inf / NaN, and
+// Q's hash (rotation_hash_word, summed: the order of the additions does not matter).
+__global__ __launch_bounds__(256) void check_weight_kernel(const uint4* __restrict__ W, size_t pieces,
+                                                           unsigned* __restrict__ flag) {
+  bool bad = false;
+  for (size_t i = static_cast<size_t>(blockIdx.x) * 256 + threadIdx.x; i < pieces; i += static_cast<size_t>(gridDim.x) * 256) {
+    const uint4 v = W[i];
+    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) bad |= (w[k] & 0x7c00u) == 0x7c00u || (w[k] & 0x7c000000u) == 0x7c000000u;
+  }
+  if (bad) atomicOr(flag, 1u);
+}
+__global__ __launch_bounds__(256) void check_rotation_kernel(const uint32_t* __restrict__ Q, size_t words,
+                                                             unsigned* __restrict__ flag,
+                                                             unsigned long long* __restrict__ hash) {
+  __shared__ unsigned long long sh[4];
+  bool bad = false;
+  unsigned long long h = 0;
+  for (size_t i = static_cast<size_t>(blockIdx.x) * 256 + threadIdx.x; i < words; i += static_cast<size_t>(gridDim.x) * 256) {
+    const uint32_t w = Q[i];
+    bad |= (w & 0x7f800000u) == 0x7f800000u;
+    h += rotation_hash_word(i, w);
+  }
+  if (bad) atomicOr(flag, 1u);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) h += __shfl_down(h, o, 64);
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = h;
+  __syncthreads();
+  if (threadIdx.x == 0) atomicAdd(hash, sh[0] + sh[1] + sh[2] + sh[3]);
+}
 
 // One wave per (16-channel tile, group) record.  Lane l owns output row 16 tile + l % 16 and, for
 // each of the group's four k-steps t, the eight storage columns 128 g + 32 t + 8 (l / 16) + e:
@@ -174,6 +291,33 @@ __global__ __launch_bounds__(256) void rotation_image_kernel(const float* __rest
 static int quant_fail(hipError_t e, const char* what) {
   set_error(std::string(what) + ": " + hipGetErrorString(e));
   return ROSAQ_ERR_HIP;
+}
+
+int launch_rotate_weights_f64(const void* W_dev, const void* Q_dev, void* out_dev, int N, int D,
+                              int headwise, void* stream) {
+  hipLaunchKernelGGL(rotate_weights_f64_kernel, dim3(D / kF64Tile, (N + kF64Tile - 1) / kF64Tile), dim3(256), 0,
+                     static_cast<hipStream_t>(stream), static_cast<const _Float16*>(W_dev),
+                     static_cast<const float*>(Q_dev), static_cast<uint16_t*>(out_dev), N, D, headwise);
+  const hipError_t e = hipGetLastError();
+  return e == hipSuccess ? ROSAQ_OK : quant_fail(e, "rotate_weights_f64_kernel launch");
+}
+
+int launch_check_weight(const void* W_dev, size_t elements, void* flag, void* stream) {
+  const size_t pieces = elements / 8;             // rows are whole groups of 128
+  const unsigned wgs = static_cast<unsigned>(std::min<size_t>((pieces + 255) / 256, 2048));
+  hipLaunchKernelGGL(check_weight_kernel, dim3(wgs), dim3(256), 0, static_cast<hipStream_t>(stream),
+                     static_cast<const uint4*>(W_dev), pieces, static_cast<unsigned*>(flag));
+  const hipError_t e = hipGetLastError();
+  return e == hipSuccess ? ROSAQ_OK : quant_fail(e, "check_weight_kernel launch");
+}
+
+int launch_check_rotation(const void* Q_dev, size_t words, void* flag, void* hash, void* stream) {
+  const unsigned wgs = static_cast<unsigned>(std::min<size_t>((words + 255) / 256, 2048));
+  hipLaunchKernelGGL(check_rotation_kernel, dim3(wgs), dim3(256), 0, static_cast<hipStream_t>(stream),
+                     static_cast<const uint32_t*>(Q_dev), words, static_cast<unsigned*>(flag),
+                     static_cast<unsigned long long*>(hash));
+  const hipError_t e = hipGetLastError();
+  return e == hipSuccess ? ROSAQ_OK : quant_fail(e, "check_rotation_kernel launch");
 }
 
 int launch_quantize_pack(const QuantPackArgs& a, void* stream) {
