@@ -13,8 +13,9 @@
 //   apply_kernel   multiplies the pair's columns of X V and of V by J (fp64 MFMA).
 // That makes D_b / 32 - 1 rounds of three launches per sweep where rotating one pair of columns at a
 // time takes D_b - 1 launches that stream all of X V and V each: 32 heads of 128 channels, 512 rows
-// 15.1 -> 2.3 ms, one problem of 1024 channels, 2048 rows 161 -> 25 ms.  Bound now by rotate_kernel, whose 32 dependent
-// rounds take 1.1 us each (128 KiB of LDS traffic, two barriers and the chain of the angles), 60 % of the time.
+// 15.1 -> 2.1 ms, one problem of 1024 channels, 2048 rows 161 -> 21 ms.  Bound by rotate_kernel (53 % of the time):
+// its 32 dependent rounds take 0.8 us each, the chain of the angles and two barriers.  With J updated in the same phase
+// as the inner products and every element in LDS a round took 1.1 us (33 against 42 us per launch).
 //
 // Columns are kept contiguous: Z[c] = [column c of X V (n_pad rows, zero padded) | row c of V^T].
 // A layer-wise rotation is one problem of dimension D; a head-wise one is D / 128 independent problems of
@@ -198,46 +199,87 @@ __global__ __launch_bounds__(1024) void rotate_kernel(PcaDev p, int round, int p
     if (all_pairs) p.diag2[blockIdx.x] = b;
   }
 
+  // J is not needed for the angles: it takes a round's rotations while the first wave computes the next round's angles.
   const int a = tid >> 5, b = tid & 31;
-  const int rounds = all_pairs ? kPcaPanel - 1 : kPcaBlock;
-  for (int r = 0; r < rounds; ++r) {
-    auto columns = [&](int k, int& x, int& y) {
-      if (all_pairs) tournament(kPcaPanel, r, k, x, y);
-      else { x = k; y = kPcaBlock + ((k + r) & (kPcaBlock - 1)); }
-    };
-    int pa, qa, pb, qb;
-    columns(a, pa, qa);
-    columns(b, pb, qb);
-    if (wave == 0) {                     // both halves of the wave compute the same
-      const double al = G[pb][pb], be = G[qb][qb], ga = G[pb][qb];
-      doublex2 v = {1.0, 0.0};
-      const double ab = al * be;
-      if (ab > 0.0 && ga * ga > 4.930380657631324e-32 * ab) {    // false too where one is NaN
-        const double d = be - al, g = 2.0 * ga;
-        const double h2 = __builtin_fma(d, d, g * g);
-        const double t = copysign(1.0, d) * g * fast_rcp(fabs(d) + h2 * fast_rsqrt(h2));
-        const double c = fast_rsqrt(__builtin_fma(t, t, 1.0));
-        v = doublex2{c, c * t};
-      }
-      if (lane < kPcaBlock) cs[b] = v;
+  auto angles = [&](int pb, int qb) {    // both halves of the wave compute the same
+    const double al = G[pb][pb], be = G[qb][qb], ga = G[pb][qb];
+    doublex2 v = {1.0, 0.0};
+    const double ab = al * be;
+    if (ab > 0.0 && ga * ga > 4.930380657631324e-32 * ab) {    // false too where one is NaN
+      const double d = be - al, g = 2.0 * ga;
+      const double h2 = __builtin_fma(d, d, g * g);
+      const double t = copysign(1.0, d) * g * fast_rcp(fabs(d) + h2 * fast_rsqrt(h2));
+      const double c = fast_rsqrt(__builtin_fma(t, t, 1.0));
+      v = doublex2{c, c * t};
     }
-    __syncthreads();
-    const doublex2 ra = cs[a], rb = cs[b];
-    const double pp = G[pa][pb], pq = G[pa][qb], qp = G[qa][pb], qq = G[qa][qb];
-    const double pp1 = rb.x * pp - rb.y * pq, pq1 = rb.y * pp + rb.x * pq;      // columns
+    if (lane < kPcaBlock) cs[b] = v;
+  };
+  // the 2 x 2 block (pp pq; qp qq): columns by rb, then rows by ra
+  auto turn = [](doublex2 ra, doublex2 rb, double& pp, double& pq, double& qp, double& qq) {
+    const double pp1 = rb.x * pp - rb.y * pq, pq1 = rb.y * pp + rb.x * pq;
     const double qp1 = rb.x * qp - rb.y * qq, qq1 = rb.y * qp + rb.x * qq;
-    G[pa][pb] = ra.x * pp1 - ra.y * qp1;                                        // rows
-    G[pa][qb] = ra.x * pq1 - ra.y * qq1;
-    G[qa][pb] = ra.y * pp1 + ra.x * qp1;
-    G[qa][qb] = ra.y * pq1 + ra.x * qq1;
+    pp = ra.x * pp1 - ra.y * qp1;
+    pq = ra.x * pq1 - ra.y * qq1;
+    qp = ra.y * pp1 + ra.x * qp1;
+    qq = ra.y * pq1 + ra.x * qq1;
+  };
+  if (all_pairs) {
+    int pj = 0, qj = 0;                  // rows of J and the rotation that they still have to take
+    doublex2 rj = {1.0, 0.0};
+    auto turn_j = [&]() {
 #pragma unroll
-    for (int i = b; i < kPcaPanel; i += 32) {
-      const double u = Jt[pa][i], v = Jt[qa][i];
-      Jt[pa][i] = ra.x * u - ra.y * v;
-      Jt[qa][i] = ra.y * u + ra.x * v;
+      for (int i = b; i < kPcaPanel; i += 32) {
+        const double u = Jt[pj][i], v = Jt[qj][i];
+        Jt[pj][i] = rj.x * u - rj.y * v;
+        Jt[qj][i] = rj.y * u + rj.x * v;
+      }
+    };
+    for (int r = 0; r < kPcaPanel - 1; ++r) {
+      int pa, qa, pb, qb;
+      tournament(kPcaPanel, r, a, pa, qa);
+      tournament(kPcaPanel, r, b, pb, qb);
+      if (wave == 0) angles(pb, qb);
+      if (r > 0) turn_j();
+      __syncthreads();
+      const doublex2 ra = cs[a], rb = cs[b];
+      double pp = G[pa][pb], pq = G[pa][qb], qp = G[qa][pb], qq = G[qa][qb];
+      turn(ra, rb, pp, pq, qp, qq);
+      G[pa][pb] = pp; G[pa][qb] = pq; G[qa][pb] = qp; G[qa][qb] = qq;
+      pj = pa; qj = qa; rj = ra;
+      __syncthreads();
     }
-    __syncthreads();
+    turn_j();
+  } else {
+    // column a of the first block meets a, a + 1, ... of the second: rows p_a of J and elements (p_a, p_b) stay in
+    // registers; of the latter the angles read the diagonal
+    double pp = G[a][b], u0 = Jt[a][b], u1 = Jt[a][b + 32];
+    int qj = 0;
+    doublex2 rj = {1.0, 0.0};
+    auto turn_j = [&]() {
+      const double v0 = Jt[qj][b], v1 = Jt[qj][b + 32];
+      Jt[qj][b] = rj.y * u0 + rj.x * v0;
+      Jt[qj][b + 32] = rj.y * u1 + rj.x * v1;
+      u0 = rj.x * u0 - rj.y * v0;
+      u1 = rj.x * u1 - rj.y * v1;
+    };
+    for (int r = 0; r < kPcaBlock; ++r) {
+      const int qa = kPcaBlock + ((a + r) & (kPcaBlock - 1)), qb = kPcaBlock + ((b + r) & (kPcaBlock - 1));
+      if (wave == 0) angles(b, qb);
+      if (r > 0) turn_j();
+      __syncthreads();
+      const doublex2 ra = cs[a], rb = cs[b];
+      double pq = G[a][qb], qp = G[qa][b], qq = G[qa][qb];
+      turn(ra, rb, pp, pq, qp, qq);
+      if (a == b) G[a][a] = pp;
+      G[a][qb] = pq; G[qa][b] = qp; G[qa][qb] = qq;
+      qj = qa; rj = ra;
+      __syncthreads();
+    }
+    turn_j();
+    Jt[a][b] = u0;
+    Jt[a][b + 32] = u1;
   }
+  __syncthreads();
   double* out = p.J + static_cast<size_t>(blockIdx.x) * (kPcaPanel * kPcaPanel);
   for (int i = tid; i < kPcaPanel * kPcaPanel; i += 1024) out[i] = Jt[i >> 6][i & 63];
 }
