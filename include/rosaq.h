@@ -284,7 +284,8 @@ int rosaq_stream_probe(const void* src_dev, size_t src_bytes, const void* shared
  *   "rot_splits"  the dense rotation of calls of 17 to 64 rows as n = 2-16 slabs of the contraction
  *             whose partial tiles a second launch adds (0, 1 = the single-launch rotation, the
  *             default; a count whose slabs exceed 32 k-steps also keeps the single launch)
- *   "wide"    the 128 x 256 tile kernel for many rows (main GEMM and dense rotation): 0 = heuristic, 1 = never,
+ *   "wide"    the kernels for many rows (128 x 256 tiles in the main GEMM and the dense rotation; whole heads
+ *             per workgroup in the head-wise rotation): 0 = heuristic, 1 = never,
  *             2 = every launch of more than 64 rows
  *   "stages"  3 = whole call (default), 1 = prologue kernels only, 2 = main GEMM only
  *             (2 reuses the rotated activations a previous call left in the workspace)

@@ -348,6 +348,15 @@ static int run_prologue(const rosaq_packed_t* p, const WsPlan& w, const void* x_
   // the first launch of a call clears the tickets of the GEMM launches behind it
   void* tickets = ws + w.tickets;
   const int n_tickets = 2 * kTicketsPerLaunch;
+  // Many rows: a workgroup per head and 64 rows takes 5.7 us however few there are, a workgroup per column tile less as
+  // long as the chip is not full.  us, per head / per column tile: 4096 channels at 256 rows (128 heads x blocks)
+  // 6.0 / 5.3, at 384 (192) 6.2 / 6.9, at 512 6.4 / 8.7, at 2048 15.8 / 26.2; 5120 at 256 rows (160) 6.1 / 6.0,
+  // at 2048 18.8 / 32.8; 1024 at 1024 rows (128) 6.1 / 5.2, at 2048 (256) 6.6 / 8.8.
+  const int64_t head_blocks = static_cast<int64_t>(c.D / kHeadDim) * ((M + kMBlock - 1) / kMBlock);
+  const bool many = g_tune_rot.wide == 2 ? M > kMBlock : (g_tune_rot.wide == 0 && M > kMBlock && head_blocks > 160);
+  if (c.q_mode == ROSAQ_Q_HEADWISE && many)
+    return launch_rotate_rows(x_dev, ldx, M, c.D, p->d_qf, p->d_perm, p->d_pos, ws + w.xf_a, tickets, n_tickets,
+                              hip_stream);
   if (c.q_mode == ROSAQ_Q_HEADWISE)
     return launch_rotate_headwise(x_dev, ldx, M, c.D, p->d_qf, p->d_pos, ws + w.xf_a, tickets, n_tickets,
                                   hip_stream);

@@ -124,6 +124,9 @@ int launch_gather(const void* x, int64_t ldx, int M, int D, const int32_t* perm_
 int launch_rotate_headwise(const void* x, int64_t ldx, int M, int D, const void* qh,
                            const int32_t* pos_dev, void* xf, void* zero_ptr, int zero_count,
                            void* stream);
+// the same for many rows (rosaq_rotate.hip); `perm_dev` is the inverse of `pos_dev`
+int launch_rotate_rows(const void* x, int64_t ldx, int M, int D, const void* qh, const int32_t* perm_dev,
+                       const int32_t* pos_dev, void* xf, void* zero_ptr, int zero_count, void* stream);
 
 // Dense rotation of up to 64 rows as slabs of the contraction plus a summing launch
 // (rosaq_rotate.hip).  pick_rotate_slabs: `forced` if slabs of that count fit the kernel, else 0;
