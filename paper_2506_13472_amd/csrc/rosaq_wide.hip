@@ -8,7 +8,7 @@
 // (128 channels) of the workgroup's 128 rows of xhat is fetched once, straight into a ring of three LDS buffers,
 // and read by all waves; a wave converts the weights of its own channels once per 128 rows (2.1 VALU
 // instructions per MFMA, 5 in gemm_kernel).  4096 -> 12288 INT4 at 2048 rows: 265 -> 174 us (0.78 -> 1.18 PFLOP/s),
-// 11008 -> 4096 226 -> 150 us (1.23); the fp16 form (the dense rotation) 4096 -> 4096 137 -> 64 us.
+// 11008 -> 4096 226 -> 150 us (1.23); the fp16 form (the dense rotation) 4096 -> 4096 137 -> 69 us.
 // Bound now: a unit takes 1.4 us (1.7 with the whole chip busy) where its MFMAs alone take 0.95, one barrier per
 // unit and the shared issue slots of two waves per SIMD are the difference.  Measured against it: 64 x 64
 // tiles per wave (half the LDS reads, 3.6 VALU instructions per MFMA) 10 % slower; 128 x 64 per wave with one wave
@@ -16,6 +16,7 @@
 #include <hip/hip_runtime.h>
 
 #include <string>
+#include <type_traits>
 
 #include "rosaq_gemm.h"
 #include "rosaq_internal.h"
@@ -102,6 +103,19 @@ __global__ __launch_bounds__(kWaves * 64, 1) void wide_gemm_kernel(GemmDev p) {
   for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) acc[nt][mt] = floatx4{0.f, 0.f, 0.f, 0.f};
+  // Sums are formed in two levels: MFMAs add up a short run of the contraction in tmp (a group of a low-bit layer; one or
+  // two units of fp16 channels), which is then added to acc.  In one chain of n MFMAs every step rounds at the size of
+  // the sum so far; gemm_kernel's eight waves make eight chains of n / 8.  With steps of independent sign the squared error
+  // of those is n^2 / 16 + 4.5 n rounding errors of one step, that of runs of eight 4 n + n^2 / 16.  Outputs that are not the
+  // correctly rounded sum of 4096 fp16 channels: one chain 1.9e-3, runs of eight 1.0e-3, gemm_kernel 1.3e-3.  The
+  // additions cost 3-5 % (4096 -> 4096 at 2048 rows 67 -> 69 us).  The groups of a low-bit layer are one chain of D / 128
+  // additions (4096 channels: 6.4e-4 against 6.0e-4 in gemm_kernel, 13824: 9.8e-4 against 7.1e-4; a third level does not
+  // fit the registers: 48 of them would spill).
+  floatx4 tmp[NT][MT];
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) tmp[nt][mt] = floatx4{0.f, 0.f, 0.f, 0.f};
 
   constexpr int kCw = BITS == 3 ? 3 : 4;
   struct Codes { uint32_t cw[NT][kCw], sz[NT]; };
@@ -164,7 +178,8 @@ __global__ __launch_bounds__(kWaves * 64, 1) void wide_gemm_kernel(GemmDev p) {
     wait_loads<0>();
     wide_barrier();
     read_a(a[0], 0, 0);
-    auto step = [&](Frags& c) {
+    // `first`: the run that tmp holds is complete; it is added while this unit's first k-step starts the next one
+    auto step = [&](Frags& c, auto first) {
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
         __builtin_amdgcn_sched_barrier(0);
@@ -174,7 +189,12 @@ __global__ __launch_bounds__(kWaves * 64, 1) void wide_gemm_kernel(GemmDev p) {
         for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
           for (int m = 0; m < HM; ++m) {
-            floatx4& d = acc[nt][(k & 1) * HM + m];
+            const int mt = (k & 1) * HM + m;
+            floatx4& d = tmp[nt][mt];
+            if (decltype(first)::value && k < 2) {
+              acc[nt][mt] += d;
+              d = floatx4{0.f, 0.f, 0.f, 0.f};
+            }
             d = mfma16(__builtin_bit_cast(half8, a[k & 1][m]), __builtin_bit_cast(half8, c.b[k >> 1][nt]), d);
           }
         if (k & 1) load_frags_t(c, u + 2, k >> 1);
@@ -183,7 +203,11 @@ __global__ __launch_bounds__(kWaves * 64, 1) void wide_gemm_kernel(GemmDev p) {
       buf = next(buf);
       return ++u < U;
     };
-    while (step(f[0]) && step(f[1])) {}
+    while (step(f[0], std::true_type{}) && step(f[1], std::false_type{})) {}
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) acc[nt][mt] += tmp[nt][mt];
   } else {
     Codes c[2];
     load_codes(c[0], 0);
@@ -201,7 +225,12 @@ __global__ __launch_bounds__(kWaves * 64, 1) void wide_gemm_kernel(GemmDev p) {
         for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
           for (int m = 0; m < HM; ++m) {
-            floatx4& d = acc[nt][(k & 1) * HM + m];
+            const int mt = (k & 1) * HM + m;
+            floatx4& d = tmp[nt][mt];
+            if (k < 2) {
+              acc[nt][mt] += d;
+              d = floatx4{0.f, 0.f, 0.f, 0.f};
+            }
             d = mfma16(__builtin_bit_cast(half8, a[0][m]), __builtin_bit_cast(half8, f.b[k >> 1][nt]), d);
           }
       }
@@ -220,14 +249,9 @@ __global__ __launch_bounds__(kWaves * 64, 1) void wide_gemm_kernel(GemmDev p) {
       }
     };
     half8 b[2][NT];
-    floatx4 tmp[NT][MT];
-    float s_prev[NT];
+    float s_prev[NT];                                 // tmp holds the last fp16 unit, or zero
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-      s_prev[nt] = 0.f;
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt) tmp[nt][mt] = floatx4{0.f, 0.f, 0.f, 0.f};
-    }
+    for (int nt = 0; nt < NT; ++nt) s_prev[nt] = 1.f;
     wait_loads<0>();
     wide_barrier();
 #pragma unroll

@@ -95,3 +95,27 @@ def test_wide_is_the_default_where_it_fills_the_chip():
     assert np.linalg.norm(y - y1) <= 1e-3 * np.linalg.norm(y1)
     assert not np.array_equal(y1.astype(np.float16).view(np.uint16), y.view(np.uint16))
     p.free()
+
+
+@pytest.mark.parametrize("K", [4096, 1024])
+def test_wide_fp16_sums_are_no_less_exact_than_gemm_kernels(K):
+    """Share of outputs that are not the correctly rounded fp64 sum, over 512 x 1024 outputs of 4096 channels, K of them
+    fp16.  A fp32 sum that is off by e rounds wrongly with a probability proportional to e; one chain of all fp16 MFMAs
+    gives 1.5 times gemm_kernel's share.  400 such outputs or more on either side: 25 % are more than three
+    standard deviations of the quotient."""
+    print(f"case wide sums K={K}", flush=True)
+    bits = 4
+    lay, _, lam = make_case(550, 512, 4096, 1024, 64, O.MODE_NONE)
+    p = B.rosaq_pack_weights(lay["W"], None, lam, K, bits, B.Q_NONE)
+    e = B.rosaq_packed_export(p)
+    order = np.concatenate([e["salient_idx"], np.setdiff1d(np.arange(4096), e["salient_idx"])])
+    s, z = (np.repeat(e[k].astype(np.float64), 128, axis=1) for k in ("scales", "zeros"))
+    w = np.concatenate([e["W_S"].astype(np.float64), (e["codes"] - z) * s], axis=1)
+    want = (lay["x"][:, order].astype(np.float64) @ w.T).astype(np.float16)
+    wrong = {}
+    for key in (2, 1):
+        B.rosaq_tune("wide", key)
+        wrong[key] = np.mean(run_gpu(p, lay["x"]).view(np.uint16) != want.view(np.uint16))
+    print(f"not correctly rounded: wide {wrong[2]:.3e}, gemm_kernel {wrong[1]:.3e}", flush=True)
+    assert wrong[2] <= 1.25 * wrong[1]
+    p.free()
