@@ -23,7 +23,7 @@ LIB_PATH = os.environ.get("ROSAQ_LIB") or os.path.join(os.path.dirname(os.path.a
 
 EXPORTED = ["rosaq_pack_weights", "rosaq_workspace_bytes", "rosaq_workspace_bytes_batch", "rosaq_workspace_bytes_min", "rosaq_linear", "rosaq_linear_headwise",
             "rosaq_linear_headwise_static", "rosaq_linear_batch", "rosaq_linear_swiglu", "rosaq_mlp_swiglu", "rosaq_workspace_bytes_mlp", "rosaq_stream_probe", "rosaq_packed_clone", "rosaq_pca_headwise", "rosaq_pca_full",
-            "rosaq_packed_info", "rosaq_packed_export", "rosaq_tune", "rosaq_launch_shape", "rosaq_block_map", "rosaq_packed_image", "rosaq_free",
+            "rosaq_packed_info", "rosaq_packed_export", "rosaq_tune", "rosaq_launch_shape", "rosaq_launch_many_rows", "rosaq_block_map", "rosaq_packed_image", "rosaq_free",
             "rosaq_last_error"]
 
 
@@ -98,6 +98,8 @@ def lib() -> C.CDLL:
         L.rosaq_tune.restype = C.c_int
         L.rosaq_launch_shape.argtypes = [i32, i32, i32, i32, C.POINTER(i32)]
         L.rosaq_launch_shape.restype = C.c_int
+        L.rosaq_launch_many_rows.argtypes = [i32, i32, i32, i32, i32, i32, C.POINTER(i32)]
+        L.rosaq_launch_many_rows.restype = C.c_int
         L.rosaq_packed_image.argtypes = [vp, i32, vp, C.POINTER(sz)]
         L.rosaq_packed_image.restype = C.c_int
         L.rosaq_block_map.argtypes = [i32, i32, i32, C.POINTER(i32), C.POINTER(i32)]
@@ -275,6 +277,13 @@ def rosaq_launch_shape(M: int, channels: int, in_features: int, bits: int):
     out = (C.c_int32 * 5)()
     _check(lib().rosaq_launch_shape(M, channels, in_features, bits, out))
     return tuple(out)
+
+
+def rosaq_launch_many_rows(M: int, channels: int, in_features: int, K: int, bits: int, q_mode: int = Q_NONE):
+    """(main GEMM, rotation): which launches of such a call take the kernels for many rows."""
+    uses = C.c_int32()
+    _check(lib().rosaq_launch_many_rows(M, channels, in_features, K, bits, q_mode, C.byref(uses)))
+    return bool(uses.value & 1), bool(uses.value & 2)
 
 
 def rosaq_packed_image(p: "Packed", which: int) -> np.ndarray:

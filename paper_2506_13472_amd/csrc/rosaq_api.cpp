@@ -341,6 +341,23 @@ static int run_main_gemm(const rosaq_packed_t* const* ps, int count, const GemmI
   return launch_gemm(a, g_tune, stream);
 }
 
+// Settings of the dense rotation's launch: "rot_splits" selects the slab launches, never a ticketed split (no room for
+// partial tiles is offered).
+static GemmTune rotation_tune() {
+  GemmTune tune = g_tune_rot;
+  tune.splits = 0;
+  return tune;
+}
+
+// The head-wise rotation of many rows: a workgroup per head and 64 rows takes 6 us and more as long as they find a compute
+// unit each, a workgroup per column tile less until the chip is full.  us, per head / per column tile: 4096 channels at
+// 256 rows (128 heads x blocks) 6.0 / 5.3, at 384 (192) 6.2 / 6.9, at 512 6.4 / 8.7, at 2048 15.8 / 26.2; 5120 at 256 rows
+// (160) 6.1 / 6.0, at 2048 18.8 / 32.8; 1024 at 1024 rows (128) 6.1 / 5.2, at 2048 (256) 6.6 / 8.8.
+static bool rotates_whole_heads(int D, int M) {
+  const int64_t head_blocks = static_cast<int64_t>(D / kHeadDim) * ((M + kMBlock - 1) / kMBlock);
+  return g_tune_rot.wide == 2 ? M > kMBlock : (g_tune_rot.wide == 0 && M > kMBlock && head_blocks > 160);
+}
+
 // x -> xhat fragments in the workspace (gather / head-wise blocks / dense rotation).
 static int run_prologue(const rosaq_packed_t* p, const WsPlan& w, const void* x_dev, int M,
                         int64_t ldx, char* ws, size_t ws_bytes, void* hip_stream) {
@@ -348,13 +365,7 @@ static int run_prologue(const rosaq_packed_t* p, const WsPlan& w, const void* x_
   // the first launch of a call clears the tickets of the GEMM launches behind it
   void* tickets = ws + w.tickets;
   const int n_tickets = 2 * kTicketsPerLaunch;
-  // Many rows: a workgroup per head and 64 rows takes 5.7 us however few there are, a workgroup per column tile less as
-  // long as the chip is not full.  us, per head / per column tile: 4096 channels at 256 rows (128 heads x blocks)
-  // 6.0 / 5.3, at 384 (192) 6.2 / 6.9, at 512 6.4 / 8.7, at 2048 15.8 / 26.2; 5120 at 256 rows (160) 6.1 / 6.0,
-  // at 2048 18.8 / 32.8; 1024 at 1024 rows (128) 6.1 / 5.2, at 2048 (256) 6.6 / 8.8.
-  const int64_t head_blocks = static_cast<int64_t>(c.D / kHeadDim) * ((M + kMBlock - 1) / kMBlock);
-  const bool many = g_tune_rot.wide == 2 ? M > kMBlock : (g_tune_rot.wide == 0 && M > kMBlock && head_blocks > 160);
-  if (c.q_mode == ROSAQ_Q_HEADWISE && many)
+  if (c.q_mode == ROSAQ_Q_HEADWISE && rotates_whole_heads(c.D, M))
     return launch_rotate_rows(x_dev, ldx, M, c.D, p->d_qf, p->d_perm, p->d_pos, ws + w.xf_a, tickets, n_tickets,
                               hip_stream);
   if (c.q_mode == ROSAQ_Q_HEADWISE)
@@ -393,10 +404,7 @@ static int run_prologue(const rosaq_packed_t* p, const WsPlan& w, const void* x_
   a.M = M;
   a.ks_s = c.D / kKStep; a.G = 0; a.KS = c.D / kKStep; a.KS_out = c.D / kKStep;
   a.bits = 4; a.out_frag = 1;
-  // "rot_splits" selects the slab launches above, never a ticketed split: no room for partial tiles is offered
-  GemmTune tune = g_tune_rot;
-  tune.splits = 0;
-  return launch_gemm(a, tune, hip_stream);
+  return launch_gemm(a, rotation_tune(), hip_stream);
 }
 
 static int run_call(const rosaq_packed_t* const* ps, int count, const void* x_dev, int M,
@@ -802,6 +810,23 @@ int rosaq_launch_shape(int32_t M, int32_t channels, int32_t in_features, int32_t
                                       part_room(M, channels), kTicketsPerLaunch);
   shape_out[0] = s.mt; shape_out[1] = s.nt; shape_out[2] = s.wpb; shape_out[3] = s.depth;
   shape_out[4] = s.splits;
+  return ROSAQ_OK;
+}
+
+int rosaq_launch_many_rows(int32_t M, int32_t channels, int32_t in_features, int32_t K, int32_t bits, int32_t q_mode,
+                           int32_t* uses_out) {
+  if (!uses_out) return fail(ROSAQ_ERR_NULL, "uses_out is NULL");
+  if (M < 1 || channels < 1 || channels % kTileN || in_features < kGroup || in_features % kGroup || K < 0 ||
+      K > in_features || K % kGroup)
+    return fail(ROSAQ_ERR_SHAPE, "M >= 1, channels a positive multiple of 16, in_features a positive multiple of 128, "
+                                 "K a multiple of 128 up to in_features");
+  if (bits != 3 && bits != 4) return fail(ROSAQ_ERR_ARG, "bits must be 3 or 4");
+  if (q_mode < ROSAQ_Q_NONE || q_mode > ROSAQ_Q_HEADWISE) return fail(ROSAQ_ERR_ARG, "unknown q_mode");
+  const int D = in_features;
+  int uses = prefers_wide(M, channels / kTileN, D, K, K == D ? 16 : bits, g_tune) ? 1 : 0;
+  if (q_mode == ROSAQ_Q_HEADWISE && rotates_whole_heads(D, M)) uses |= 2;
+  if (q_mode == ROSAQ_Q_FULL && prefers_wide(M, D / kTileN, D, D, 16, rotation_tune())) uses |= 2;
+  *uses_out = uses;
   return ROSAQ_OK;
 }
 

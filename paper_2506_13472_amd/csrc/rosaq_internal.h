@@ -116,6 +116,8 @@ size_t gemm_part_bytes(const GemmShape& s, int M, int ntiles);
 int launch_gemm(const GemmArgs& a, const GemmTune& tune, void* stream);
 // Host copy of the kernel's workgroup -> (channel chunk, row group) map: b < 0 returns the grid
 // size, otherwise 1 and the pair, or 0 for a padding workgroup that exits at once.
+// Whether launch_gemm takes the kernel for many rows (128 x 256 tiles).
+bool prefers_wide(int M, int ntiles, int D, int K, int bits, const GemmTune& tune);
 int block_map_host(int b, int chunks, int mgroups, int* chunk, int* mg);
 // both prologue launchers also clear `zero_count` 32-bit words at `zero_ptr` (the tickets of the
 // GEMM launches that follow in the same call)

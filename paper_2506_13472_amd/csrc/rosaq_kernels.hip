@@ -881,30 +881,44 @@ static int launch_gemm_shape(const GemmArgs& a, const GemmShape& sh, void* strea
 }
 
 // The 128 x 256 tiles of the kernel for many rows against the shape pick_unsplit chooses for gemm_kernel, by what both were
-// measured to take: a wide workgroup 1.7 us per 128 channels of the contraction plus 5 us, one per compute unit; a
-// round of gemm_kernel workgroups 1.2 x (inflow at 128 GB/s + VALU issue), plus 3 us (all-fp16: 2.1 x the inflow).  The
-// wide kernel needs enough rows and channels to fill the chip.  INT4, wide / gemm_kernel in us: 4096 -> 12288 at 256
-// rows 51 / 39, at 512 56 / 73; 5120 -> 27648 at 256 rows 70 / 105; 13824 -> 5120 at 512 rows 145 / 100 (80
-// workgroups), at 2048 321 / 338; fp16 4096 -> 4096 at 256 rows 44 / 19, at 2048 64 / 137.
-static bool prefers_wide(int M, int ntiles, int D, int bits, const GemmTune& tune) {
+// measured to take (2400 launches: D 1024 to 13824, 512 to 32000 channels, 65 to 2048 rows, INT4, INT3 and fp16, K 128 to D):
+//   wide         9.7 us a round + 1.35 us per low-bit unit of 128 channels (INT4 and INT3 alike) and 2.0 per salient unit
+//                (fp16 units in front of low-bit ones are not pipelined); all-fp16: 10 us + 1.27 per unit;
+//   gemm_kernel  3.0 us a round + 0.96 x inflow at 128 GB/s + 0.95 x VALU issue; all-fp16: 2.8 us + 1.5 x inflow.
+// A round is one workgroup on each of the eight compute units of a shader engine.  Workgroup b runs on XCD b % 8 and there
+// on shader engine (b / 8) % 4.  By map_block a channel chunk belongs to one XCD, and with more than four row groups a row
+// group to one engine, so the fullest engine sets the rounds: 5120 channels at 1536 rows are 240 wide workgroups in two
+// rounds (three of 20 chunks and three of 12 row groups on one engine: 9), 4608 at 1152 rows 162 in two as well.  (gemm_kernel's
+// small tiles share a compute unit, which evens the engines out.)
+// Both estimates are good to 6 to 10 % (rms) and the wide kernel has to promise 3 %: over the launches measured the choice is
+// 0.1 % slower than the faster kernel on average.  us, wide / gemm_kernel: INT4 4096 -> 12288 at 256 rows 52 / 39,
+// at 512 57 / 74, at 2048 186 / 301, with K = 2048 208 / 307; 5120 -> 5120 at 1536 rows 129 / 117, with K = 1024 139 / 120;
+// 13824 -> 5120 at 1536 rows 325 / 265; INT3 4096 -> 12288 at 2048 rows 176 / 285; fp16 4096 -> 4096 at 256 rows 47 / 20,
+// at 2048 65 / 132.
+bool prefers_wide(int M, int ntiles, int D, int K, int bits, const GemmTune& tune) {
   if (tune.wide == 2) return M > 64;
   if (M <= 64 || tune.wide == 1 || tune.mt || tune.nt || tune.wpb || tune.depth || tune.splits) return false;
   const GemmShape s = pick_unsplit(M, ntiles, D, bits, tune);
-  auto rounds = [](int wgs) { return static_cast<double>((wgs + 255) / 256); };
-  const int wide_wgs = ((ntiles + kWideChannels / 16 - 1) / (kWideChannels / 16)) * ((M + kWideRows - 1) / kWideRows);
-  const double wide = rounds(wide_wgs) * (D / 128 * 1.7 + 5.0);
-  const int wgs = ((ntiles + s.nt - 1) / s.nt) * (((M + 15) / 16 + s.mt - 1) / s.mt);
+  auto rounds = [](int chunks, int mgroups, bool alone) {
+    const int64_t cx = (chunks + 7) / 8;
+    return static_cast<double>(mgroups <= kMapRows || !alone ? (cx * mgroups + 31) / 32 : (cx * ((mgroups + 3) / 4) + 7) / 8);
+  };
+  const double units = D / 128, salient = K / 128;
+  const double wide = rounds((ntiles + kWideChannels / 16 - 1) / (kWideChannels / 16), (M + kWideRows - 1) / kWideRows, true) *
+                          (bits == 16 ? 10.0 + 1.27 * units : 9.7 + 1.35 * (units - salient) + 2.0 * salient) - 2.0;
   const double wbytes = bits == 16 ? 2.0 : (bits == 3 ? 0.46 : 0.58);
   const double inflow = (s.mt * 32.0 + s.nt * 16 * wbytes) * D / 128e3;
-  const double valu = (s.nt * ((bits == 3 ? 40 : 36) + 4 * s.mt) + 40) * (D / 128.0) / 2000.0;
-  return wide < (bits == 16 ? rounds(wgs) * inflow * 2.1 : rounds(wgs) * (inflow + valu) * 1.2 + 3.0);
+  const double valu = (s.nt * ((bits == 3 ? 40 : 36) + 4 * s.mt) + 40) * units / 2000.0;
+  const double narrow = rounds((ntiles + s.nt - 1) / s.nt, ((M + 15) / 16 + s.mt - 1) / s.mt, s.mt * s.nt > 4) *
+                            (bits == 16 ? 2.8 + 1.5 * inflow : 3.0 + 0.96 * inflow + 0.95 * valu) + 1.7;
+  return 1.03 * wide < narrow;
 }
 
 int launch_gemm(const GemmArgs& a, const GemmTune& tune, void* stream) {
   int tiles_total = 0;
   for (int i = 0; i < a.nseg; ++i) tiles_total += (a.seg[i].N + kTileN - 1) / kTileN;
   const int bits = a.G == 0 ? 16 : a.bits;
-  if (a.xrow == nullptr && prefers_wide(a.M, tiles_total, a.KS * kKStep, bits, tune)) {
+  if (a.xrow == nullptr && prefers_wide(a.M, tiles_total, a.KS * kKStep, a.ks_s * kKStep, bits, tune)) {
     const GemmDev d = fill_dev(a, &tiles_total);
     return launch_gemm_wide(d, bits, tiles_total, stream);
   }

@@ -291,6 +291,48 @@ def test_launch_shape_of_the_named_workloads():
     assert B.ERR_NAMES[e.value.code] == "ARG"
 
 
+def test_many_rows_rule_follows_what_was_measured():
+    """(M, channels, D, K, bits) with the measured us of the 128 x 256 tiles and of gemm_kernel: the rule takes the faster one
+    wherever they are 10 % apart.  Some launches need a second round only on one shader engine of some XCDs, some have many
+    salient channels, whose units cost the wide kernel more."""
+    measured = [
+        # 20 or 23 chunks of 256 channels over eight XCDs: 220 to 276 workgroups, up to 36 of them on one XCD
+        ((1536, 5120, 5120, 128, 4), 129.5, 117.3), ((1408, 5120, 5120, 128, 3), 127.1, 114.9),
+        ((1536, 5120, 13824, 128, 4), 324.5, 264.7), ((1408, 5120, 11008, 128, 3), 257.1, 214.7),
+        ((1408, 5888, 13824, 128, 3), 321.6, 290.0), ((1536, 5120, 5120, 1024, 4), 139.3, 120.0),
+        ((1408, 5120, 4096, 1024, 3), 113.6, 101.9),
+        # 162, 222 and 220 workgroups, nine or ten of them on one shader engine of eight compute units
+        ((1040, 4608, 5248, 128, 4), 128.4, 92.1), ((666, 9440, 12416, 0, 4), 280.0, 222.7),
+        ((1215, 5504, 3712, 128, 4), 97.4, 83.2),
+        # launches of few workgroups
+        ((256, 5120, 13824, 128, 4), 144.0, 56.5), ((128, 4096, 4096, 128, 4), 48.4, 11.0),
+        ((76, 11008, 4864, 128, 4), 57.4, 41.8),
+        # full rounds
+        ((2048, 12288, 4096, 128, 4), 185.8, 301.2), ((2048, 4096, 11008, 128, 3), 156.4, 232.6),
+        ((384, 32000, 1024, 128, 4), 39.4, 84.1), ((320, 32000, 5120, 128, 4), 130.3, 207.2),
+        ((368, 20864, 1536, 256, 4), 54.8, 73.1), ((160, 24016, 11136, 2688, 4), 142.3, 199.8),
+    ]
+    for (M, n, D, K, bits), wide, narrow in measured:
+        assert abs(wide / narrow - 1) > 0.1, "rows of the table decide"
+        assert B.rosaq_launch_many_rows(M, n, D, K, bits)[0] == (wide < narrow), (M, n, D, K, bits)
+    # all-fp16 layers and the dense rotation go by the same rule, the head-wise rotation by its number of workgroups
+    assert B.rosaq_launch_many_rows(2048, 4096, 4096, 4096, 4)[0]
+    assert B.rosaq_launch_many_rows(2048, 4096, 4096, 128, 4, B.Q_FULL)[1]
+    assert not B.rosaq_launch_many_rows(256, 4096, 4096, 128, 4, B.Q_FULL)[1]
+    assert B.rosaq_launch_many_rows(1030, 48, 1280, 128, 3, B.Q_HEADWISE) == (False, True)
+    assert not B.rosaq_launch_many_rows(1024, 48, 1280, 128, 3, B.Q_HEADWISE)[1]       # 160 heads x blocks
+    assert not any(B.rosaq_launch_many_rows(64, 32000, 13824, 128, 4, q) != (False, False) for q in range(3))
+    for key, value, want in (("wide", 1, (False, False)), ("wide", 2, (True, True))):
+        B.rosaq_tune(key, value)
+        try:
+            assert B.rosaq_launch_many_rows(2048, 4096, 4096, 128, 4, B.Q_FULL) == want
+        finally:
+            B.rosaq_tune(key, 0)
+    for bad, name in (((0, 4096, 4096, 128, 4), "SHAPE"), ((64, 4090, 4096, 128, 4), "SHAPE"), ((64, 4096, 4096, 4224, 4), "SHAPE"),
+                      ((64, 4096, 4096, 128, 5), "ARG"), ((64, 4096, 4096, 128, 4, 3), "ARG")):
+        assert B.ERR_NAMES[_code(lambda: B.rosaq_launch_many_rows(*bad))] == name
+
+
 def test_bench_traffic_table_holds_the_shapes_the_heuristic_picks():
     """bench.py reports measured HBM traffic only for launch shapes it has a profile for: the two
     launches of its default workload must be among them, or the default line would say null."""
