@@ -446,7 +446,12 @@ int rosaq_pack_weights(const rosaq_pack_desc* desc, void* hip_stream, rosaq_pack
         p->rot_fingerprint = rotation_hash_host(desc->Q, static_cast<size_t>(desc->in_features) *
                                                              (desc->q_mode == ROSAQ_Q_FULL ? desc->in_features : kHeadDim));
     } else {
-      rc = pack_device(*desc, static_cast<hipStream_t>(hip_stream), p);
+      try {
+        rc = pack_device(*desc, static_cast<hipStream_t>(hip_stream), p);
+      } catch (const std::exception&) { rc = fail(ROSAQ_ERR_NOMEM, "out of host memory"); }
+      // Without a GPU that could look (no device, no memory), the host does: bad input is named as such either way.
+      if ((rc == ROSAQ_ERR_HIP || rc == ROSAQ_ERR_NOMEM) && pack_validate(*desc, &err) != ROSAQ_OK)
+        rc = fail(ROSAQ_ERR_NONFINITE, err);
     }
   } catch (const std::exception&) { rc = fail(ROSAQ_ERR_NOMEM, "out of host memory"); }
   if (rc != ROSAQ_OK) { rosaq_free(p); return rc; }

@@ -50,8 +50,9 @@ struct Canonical {
   HostArray<uint16_t> zeros;          // [N x G] fp16 (integer valued)
 };
 
-// Pieces of the offline step that also serve the device path: the eigenvalue check, and the salient set
-// with the storage order (fills the shape fields, salient_idx, perm, pos).
+// Pieces of the offline step that also serve the device path: the checks for Inf / NaN (of the eigenvalues alone, and of
+// all inputs), and the salient set with the storage order (fills the shape fields, salient_idx, perm, pos).
+int pack_validate(const rosaq_pack_desc& d, std::string* err);
 int pack_validate_eigenvalues(const rosaq_pack_desc& d, std::string* err);
 void pack_select(const rosaq_pack_desc& d, Canonical* c);
 

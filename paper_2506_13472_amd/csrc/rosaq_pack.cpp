@@ -209,14 +209,14 @@ void pack_select(const rosaq_pack_desc& d, Canonical* c) {
   for (int p = 0; p < D; ++p) c->pos[c->perm[p]] = p;
 }
 
-// Input checks that need the data: every eigenvalue, weight and rotation entry finite.
 int pack_validate_eigenvalues(const rosaq_pack_desc& d, std::string* err) {
   for (int i = 0; i < d.in_features; ++i)
     if (!std::isfinite(d.eigenvalues[i])) { *err = "eigenvalues contain NaN/Inf"; return ROSAQ_ERR_NONFINITE; }
   return ROSAQ_OK;
 }
 
-static int pack_validate(const rosaq_pack_desc& d, std::string* err) {
+// Input checks that need the data: every eigenvalue, weight and rotation entry finite.
+int pack_validate(const rosaq_pack_desc& d, std::string* err) {
   const int N = d.out_features, D = d.in_features;
   const int rc = pack_validate_eigenvalues(d, err);
   if (rc != ROSAQ_OK) return rc;

@@ -80,6 +80,17 @@ def test_pack_rejects_nonfinite():
     assert _code(lambda: B.rosaq_pack_weights(Wf, Qo, lamf, K, bits, B.Q_FULL, host_only=True)) == -7
 
 
+@pytest.mark.parametrize("where", ["W", "Q", "eigenvalues"])
+def test_pack_names_nonfinite_input_with_or_without_a_gpu(where):
+    """The device path looks for Inf / NaN on the GPU; where there is none the same error comes from the host."""
+    D, N = 256, 40
+    a = {"W": np.ones((N, D), np.float16), "Q": np.eye(D, dtype=np.float32), "eigenvalues": np.ones(D)}
+    a[where].reshape(-1)[-1] = np.nan
+    with pytest.raises(B.RosaqError) as e:
+        B.rosaq_pack_weights(a["W"], a["Q"], a["eigenvalues"], 128, 4, B.Q_FULL)
+    assert B.ERR_NAMES[e.value.code] == "NONFINITE" and where in str(e.value)
+
+
 def test_call_argument_errors_on_host_only_handle():
     W, Q, lam, K, bits, mode = _good()
     p = B.rosaq_pack_weights(W, Q, lam, K, bits, mode, host_only=True)
