@@ -74,7 +74,8 @@ __device__ __forceinline__ int pair_columns(const PcaDev& p, int pair, int round
 // turned through LDS so that both sides move whole lines.
 __global__ __launch_bounds__(256) void pca_init_kernel(const _Float16* __restrict__ X, int64_t ldx, int n_cal, PcaDev p) {
   __shared__ _Float16 tile[64][66];
-  const int c0 = blockIdx.x * 64, r0 = blockIdx.y * 64;
+  const int groups = gridDim.x / (p.pitch / 64);            // of 64 columns; see apply_kernel for the order
+  const int c0 = blockIdx.x % groups * 64, r0 = blockIdx.x / groups * 64;
   if (r0 < p.n_pad) {
     for (int i = threadIdx.x; i < 64 * 64; i += 256) {
       const int r = i >> 6, c = i & 63;
@@ -285,15 +286,17 @@ __global__ __launch_bounds__(1024) void rotate_kernel(PcaDev p, int round, int p
 }
 
 // Columns c' of a pair <- sum over c of J[c][c'] column c, for 64 entries of Z: a wave owns 16 entries of all 64
-// columns, which it reads before it writes any.
-__global__ __launch_bounds__(256) void apply_kernel(PcaDev p, int round) {
+// columns, which it reads before it writes any.  Workgroups count pairs first, then steps of 64 entries, in one dimension:
+// the others of a grid end at 65536, four million rows of calibration data.
+__global__ __launch_bounds__(256) void apply_kernel(PcaDev p, int round, int pairs) {
   __shared__ double Jt[kPcaPanel][kPcaPanel + 2];
   int c0, c1;
-  if (p.done[pair_columns(p, blockIdx.x, round, c0, c1)]) return;
+  const int pair = blockIdx.x % pairs, step = blockIdx.x / pairs;
+  if (p.done[pair_columns(p, pair, round, c0, c1)]) return;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int i16 = lane & 15, q = lane >> 4;
-  const double* J = p.J + static_cast<size_t>(blockIdx.x) * (kPcaPanel * kPcaPanel);
-  const int row = blockIdx.y * 64 + wave * 16 + i16;
+  const double* J = p.J + static_cast<size_t>(pair) * (kPcaPanel * kPcaPanel);
+  const int row = step * 64 + wave * 16 + i16;
   auto column = [&](int c) { return p.Z + static_cast<size_t>((c < kPcaBlock ? c0 : c1 - kPcaBlock) + c) * p.pitch + row; };
   double z[16];                                       // columns 16 q + s of this entry
 #pragma unroll
@@ -394,7 +397,7 @@ __global__ __launch_bounds__(256) void pca_write_kernel(PcaDev p, const int* __r
                                                         const double* __restrict__ sign, float* __restrict__ Q) {
   __shared__ float tile[64][65];
   const int tiles = p.Db / 64;
-  const int problem = blockIdx.y / tiles, j0 = (blockIdx.y % tiles) * 64, i0 = blockIdx.x * 64;
+  const int problem = blockIdx.x / tiles, j0 = (blockIdx.x % tiles) * 64, i0 = blockIdx.y * 64;
   for (int k = threadIdx.x; k < 64 * 64; k += 256) {
     const int c = order[problem * p.Db + j0 + (k >> 6)];
     tile[k >> 6][k & 63] = static_cast<float>(sign[c] * p.Z[static_cast<size_t>(c) * p.pitch + p.n_pad + i0 + (k & 63)]);
@@ -457,7 +460,7 @@ static int pca_blocks_device(const void* X_dev, int n_cal, int D, int Db, int64_
   bool converged = false;
   e = hipMemsetAsync(p.done, 0, sizes[5], st);
   if (e == hipSuccess) {
-    hipLaunchKernelGGL(pca_init_kernel, dim3(D / 64, p.pitch / 64), dim3(256), 0, st,
+    hipLaunchKernelGGL(pca_init_kernel, dim3(static_cast<unsigned>(D / 64) * (p.pitch / 64)), dim3(256), 0, st,
                        static_cast<const _Float16*>(X_dev), ldx, n_cal, p);
     e = hipGetLastError();
   }
@@ -465,7 +468,7 @@ static int pca_blocks_device(const void* X_dev, int n_cal, int D, int Db, int64_
     for (int r = 0; r < rounds && e == hipSuccess; ++r) {
       hipLaunchKernelGGL(gram_kernel, dim3(pairs, p.chunks), dim3(256), 0, st, p, r);
       hipLaunchKernelGGL(rotate_kernel, dim3(pairs), dim3(1024), 0, st, p, r, pairs);
-      hipLaunchKernelGGL(apply_kernel, dim3(pairs, p.pitch / 64), dim3(256), 0, st, p, r);
+      hipLaunchKernelGGL(apply_kernel, dim3(static_cast<unsigned>(pairs) * (p.pitch / 64)), dim3(256), 0, st, p, r, pairs);
       e = hipGetLastError();
     }
     if (e != hipSuccess) break;
@@ -484,7 +487,7 @@ static int pca_blocks_device(const void* X_dev, int n_cal, int D, int Db, int64_
   if (e == hipSuccess && converged) {
     hipLaunchKernelGGL(pca_norms_kernel, dim3(D), dim3(256), 0, st, p, n_cal, lam, sign);
     hipLaunchKernelGGL(pca_order_kernel, dim3(D / 64), dim3(64), 0, st, lam, Db, order, eig);
-    hipLaunchKernelGGL(pca_write_kernel, dim3(Db / 64, D / 64), dim3(256), 0, st, p, order, sign, Q);
+    hipLaunchKernelGGL(pca_write_kernel, dim3(D / 64, Db / 64), dim3(256), 0, st, p, order, sign, Q);
     e = hipGetLastError();
     if (e == hipSuccess) e = hipMemcpyAsync(Q_host, Q, sizes[10], hipMemcpyDeviceToHost, st);
     if (e == hipSuccess) e = hipMemcpyAsync(eig_host, eig, sizes[8], hipMemcpyDeviceToHost, st);

@@ -35,3 +35,26 @@ def test_pca_block_edges(D, n_cal, full):
         assert np.max(np.abs(q.T @ q - np.eye(width))) <= 2e-6
         assert np.all(q[np.argmax(np.abs(q), axis=0), np.arange(width)] > 0)
         assert np.linalg.norm(q @ np.diag(lam[h]) @ q.T - C) <= 1e-5 * np.linalg.norm(C)
+
+
+def test_pca_of_more_rows_than_a_grid_dimension_holds():
+    """4194305 rows: more than 65536 steps of 64 rows, the limit of a grid's second dimension."""
+    n, D = 64 * 65536 + 1, 128
+    print(f"case pca rows D={D} n_cal={n}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(1001)
+    X = torch.empty((n, D), dtype=torch.float16, device="cuda")
+    C = torch.zeros((D, D), dtype=torch.float64, device="cuda")
+    scale = torch.exp(torch.randn(D, generator=g, device="cuda"))
+    for lo in range(0, n, 1 << 18):
+        x = (torch.randn((min(n - lo, 1 << 18), D), generator=g, device="cuda") * scale).to(torch.float16)
+        X[lo:lo + x.shape[0]] = x
+        x = x.double()
+        C += x.t().contiguous() @ x
+    X[-1] *= 64                                    # the last row alone changes the result
+    C += 4095 * torch.outer(X[-1].double(), X[-1].double()) / 4096
+    C = (C / n).cpu().numpy()
+    Q, lam = B.rosaq_pca_full(X.data_ptr(), n, D, D)
+    want = np.linalg.eigvalsh(C)[::-1]
+    assert np.max(np.abs(lam - want)) <= 1e-10 * want[0]
+    q = Q.astype(np.float64)
+    assert np.linalg.norm(q @ np.diag(lam) @ q.T - C) <= 1e-5 * np.linalg.norm(C)
