@@ -38,6 +38,38 @@ _HOST_NOISE = "'-packed-fp32-ops' is not a recognized feature for this target (i
 _PK_F32 = re.compile(r"\bv_pk_(?:add|mul|fma)_f32\b")
 
 
+# rosaq_wide.hip fetches LDS buffers ahead with hand-written loads and waits by count: in front of the pieces of a unit
+# (four loads into LDS), "all but the N youngest loads are done", where the N youngest are two units' loads of weights and
+# one unit's pieces.  How many loads of weights a unit has is the compiler's doing, so the assembly is counted.  A loop runs
+# over two units, after and before a wait for everything: 0 L..L W DDDD L..L W DDDD L..L 0, with the loads behind
+# the last pieces belonging to the first unit of the next turn.
+_WAIT_LOOP = re.compile(r"0(L*)W(\d+)D{4}(L*)W(\d+)D{4}(L*)0")
+
+
+def check_counted_waits(assembly: str) -> int:
+    """The number of loops found; raises where one of their waits would not cover what it is there for, and where code
+    of the compiler's uses m0, which the hand-written loads change without its knowledge."""
+    events, in_asm = [], False
+    for line in assembly.splitlines():
+        op = line.strip()
+        if op.startswith(";;#ASM"):
+            in_asm = op.startswith(";;#ASMSTART")
+        elif not in_asm and re.search(r"\bm0\b", op.split(";")[0]):
+            raise RuntimeError(f"m0 outside the hand-written loads: {op}")
+        elif "global_load_lds" in op:
+            events.append("D")
+        elif re.match(r"(global|flat|buffer)_load", op):
+            events.append("L")
+        elif in_asm and (m := re.match(r"s_waitcnt vmcnt\((\d+)\)$", op)):
+            events.append("0" if m.group(1) == "0" else "W" + m.group(1))
+    loops = _WAIT_LOOP.findall("".join(events))
+    for head, first, middle, second, tail in loops:
+        for loads, wait in ((len(head) + len(tail), int(first)), (len(middle), int(second))):
+            if 2 * loads + 4 < wait:
+                raise RuntimeError(f"vmcnt({wait}) counts on {(wait - 4) // 2} loads of weights in a unit, there are {loads}")
+    return len(loops)
+
+
 def _compile_hip(src: str, obj: str, common, verbose: bool) -> None:
     cmd = [hipcc(), "-x", "hip", "--offload-arch=gfx950", "-save-temps=obj",
            "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -59,7 +91,10 @@ def _compile_hip(src: str, obj: str, common, verbose: bool) -> None:
     n = 0
     for f in asm:
         with open(os.path.join(os.path.dirname(obj), f), "r", errors="replace") as fh:
-            n += len(_PK_F32.findall(fh.read()))
+            text = fh.read()
+        n += len(_PK_F32.findall(text))
+        if stem == "rosaq_wide" and check_counted_waits(text) != 3:      # INT4, INT3 and fp16
+            raise RuntimeError(f"{src}: the counted waits of the LDS ring are not where they are looked for")
     print(f"{os.path.basename(src)}: device pass for gfx950 holds {n} packed-fp32 instructions", flush=True)
     if n:
         raise RuntimeError(f"{src}: packed-fp32 arithmetic in the device code")

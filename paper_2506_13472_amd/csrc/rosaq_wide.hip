@@ -35,7 +35,8 @@ __device__ __forceinline__ void wide_barrier() {
 
 // Global memory to LDS without a register in between: lane l's 16 bytes from base + off go to lds + 16 l, both shifted
 // by OFFSET.  Written as assembly because the compiler, which cannot tell the ring's buffers apart, would
-// wait for every such load in flight before each LDS read; the waits are wait_loads() below.
+// wait for every such load in flight before each LDS read; the waits are wait_loads() below.  m0 cannot be declared as
+// changed (the compiler reserves it); the build checks that the compiler itself has no use for it in these kernels.
 template <int OFFSET> __device__ __forceinline__ void dma_16(const void* base, uint32_t off, uint32_t lds) {
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 offset:%3" ::"v"(off), "s"(base), "s"(lds),
                "n"(OFFSET)
@@ -117,6 +118,9 @@ __global__ __launch_bounds__(kWaves * 64, 1) void wide_gemm_kernel(GemmDev p) {
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) tmp[nt][mt] = floatx4{0.f, 0.f, 0.f, 0.f};
 
+  // Loads that load_codes issues per low-bit unit (codes, scale and zero of each tile) and load_frags_t per four k-steps:
+  // hand_over's wait counts on them, and the build checks its assembly for them (build.py).
+  constexpr int kUnitLoads = BITS == 16 ? 4 * NT : 2 * NT;
   constexpr int kCw = BITS == 3 ? 3 : 4;
   struct Codes { uint32_t cw[NT][kCw], sz[NT]; };
   auto load_codes = [&](Codes& c, int g) {
@@ -162,10 +166,11 @@ __global__ __launch_bounds__(kWaves * 64, 1) void wide_gemm_kernel(GemmDev p) {
       dst[m] = a_lds[b][row_tile >> 2][k >> 1][row_tile & 3][lane];
     }
   };
-  // (younger than the pieces of unit u + 1: those of u + 2 and two units of weights; the first three units are
-  // waited for before the loop)
+  // (younger than the pieces of unit u + 1: those of u + 2 and the loads of two units of weights; more loads than that
+  // would only wait longer, fewer would let the unit be read too early.  The first three units are waited for before
+  // the loop.)
   auto hand_over = [&]() {
-    wait_loads<(BITS == 16 ? 8 : 4) * NT + kDma>();
+    wait_loads<2 * kUnitLoads + kDma>();
     wide_barrier();
     load_a(u + 3, buf);
   };
