@@ -108,8 +108,8 @@ static int check_desc(const rosaq_pack_desc* d) {
 // What one offline step on the GPU holds besides the handle's own buffer; given back on every way out.
 struct PackScratch {
   char* mem = nullptr;
-  hipStream_t copies = nullptr;      // uploads and downloads run beside the kernels
   hipStream_t work = nullptr;        // the caller's stream
+  hipStream_t copies = nullptr;      // uploads and downloads: beside the kernels, or `work` itself for a single chunk
   std::vector<hipEvent_t> events;
   hipError_t event(hipEvent_t* e) {
     events.push_back(nullptr);
@@ -118,7 +118,7 @@ struct PackScratch {
     return r;
   }
   ~PackScratch() {
-    if (copies) { (void)hipStreamSynchronize(copies); (void)hipStreamDestroy(copies); }
+    if (copies != work) { (void)hipStreamSynchronize(copies); (void)hipStreamDestroy(copies); }
     if (mem) { (void)hipStreamSynchronize(work); (void)hipFree(mem); }
     for (hipEvent_t e : events) if (e) (void)hipEventDestroy(e);
   }
@@ -176,14 +176,19 @@ static int pack_device(const rosaq_pack_desc& d, hipStream_t st, rosaq_packed* p
   const size_t chunk = align_up(std::max<size_t>((N + 7) / 8, (size_t{4} << 20) / D), rotate && !headwise ? round_rows : 128);
   const size_t chunks = (N + chunk - 1) / chunk;
   PackScratch t;
-  t.work = st;
+  t.work = t.copies = st;
   t.events.reserve(2 * chunks);
   // scratch of this call: [W | What | Q | W_S | codes | scales | zeros | flags and hash]
   const size_t sizes[] = {N * D * 2, rotate ? N * D * 2 : 0, q_words * 4, N * K * 2, N * C, N * G * 2, N * G * 2, 256};
   size_t offs[8], tmp_total = 0;
   for (int i = 0; i < 8; ++i) { offs[i] = tmp_total; tmp_total += align_up(std::max<size_t>(sizes[i], 16), 256); }
   ROSAQ_HIP(hipMalloc(reinterpret_cast<void**>(&t.mem), tmp_total));
-  ROSAQ_HIP(hipStreamCreateWithFlags(&t.copies, hipStreamNonBlocking));
+  if (chunks > 1) {      // nothing to overlap within one chunk: creating a stream and its events takes longer than they save
+    hipStream_t copies;
+    ROSAQ_HIP(hipStreamCreateWithFlags(&copies, hipStreamNonBlocking));
+    t.copies = copies;
+  }
+  const bool beside = t.copies != st;
   char* const w_dev = t.mem + offs[0];
   char* const what = rotate ? t.mem + offs[1] : w_dev;
   char* const q_dev = t.mem + offs[2];
@@ -201,10 +206,12 @@ static int pack_device(const rosaq_pack_desc& d, hipStream_t st, rosaq_packed* p
     else
       ROSAQ_HIP(hipMemcpy2DAsync(w, D * 2, d.W + n0 * static_cast<size_t>(d.ldw), static_cast<size_t>(d.ldw) * 2, D * 2,
                                  rows, hipMemcpyHostToDevice, t.copies));
-    hipEvent_t uploaded;
-    ROSAQ_HIP(t.event(&uploaded));
-    ROSAQ_HIP(hipEventRecord(uploaded, t.copies));
-    ROSAQ_HIP(hipStreamWaitEvent(st, uploaded, 0));
+    if (beside) {
+      hipEvent_t uploaded;
+      ROSAQ_HIP(t.event(&uploaded));
+      ROSAQ_HIP(hipEventRecord(uploaded, t.copies));
+      ROSAQ_HIP(hipStreamWaitEvent(st, uploaded, 0));
+    }
     if (i == 0 && rotate && (rc = launch_check_rotation(q_dev, q_words, flags + 8, flags + 16, st)) != ROSAQ_OK) return rc;
     if (i == 0 && keep_q && (rc = launch_rotation_image(q_dev, c.D, headwise ? 1 : 0, p->d_perm, p->d_qf, st)) != ROSAQ_OK)
       return rc;
@@ -220,8 +227,10 @@ static int pack_device(const rosaq_pack_desc& d, hipStream_t st, rosaq_packed* p
     a.scales = t.mem + offs[5] + n0 * G * 2; a.zeros = t.mem + offs[6] + n0 * G * 2;
     a.flag = flags;
     if ((rc = launch_quantize_pack(a, st)) != ROSAQ_OK) return rc;
-    ROSAQ_HIP(t.event(&finished[i]));
-    ROSAQ_HIP(hipEventRecord(finished[i], st));
+    if (beside) {
+      ROSAQ_HIP(t.event(&finished[i]));
+      ROSAQ_HIP(hipEventRecord(finished[i], st));
+    }
   }
   struct Array { char* host; size_t dev, row_bytes; };
   const Array arrays[] = {{reinterpret_cast<char*>(c.codes.data()), offs[4], C}, {reinterpret_cast<char*>(c.W_S.data()), offs[3], K * 2},
@@ -235,7 +244,7 @@ static int pack_device(const rosaq_pack_desc& d, hipStream_t st, rosaq_packed* p
   }
   for (size_t i = 0; i < chunks; ++i) {
     const size_t n0 = i * chunk, rows = std::min(chunk, N - n0);
-    ROSAQ_HIP(hipStreamWaitEvent(t.copies, finished[i], 0));
+    if (beside) ROSAQ_HIP(hipStreamWaitEvent(t.copies, finished[i], 0));
     for (const Array& a : arrays)
       if (a.row_bytes)
         ROSAQ_HIP(hipMemcpyAsync(a.host + n0 * a.row_bytes, t.mem + a.dev + n0 * a.row_bytes, rows * a.row_bytes,
