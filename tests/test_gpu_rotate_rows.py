@@ -43,8 +43,10 @@ def test_rotate_rows(M, D, K, rule):
 
 
 def test_rotate_rows_is_the_default_where_it_fills_the_chip():
-    """10 heads x 17 blocks: the rule's own choice against rotate_headwise_kernel, with a padded row stride."""
+    """10 heads x 17 blocks: the rule takes the kernel for many rows by itself (and at 10 x 16 does not); against
+    rotate_headwise_kernel, with a padded row stride."""
     print("case rotate rows default", flush=True)
+    assert [B.rosaq_launch_many_rows(M, 48, 1280, 128, 3, B.Q_HEADWISE)[1] for M in (1024, 1030)] == [False, True]
     lay, Q, lam = make_case(710, 64, 1280, 48, 300, O.MODE_HEADWISE)
     p = B.rosaq_pack_weights(lay["W"], Q, lam, 128, 3, B.Q_HEADWISE)
     x = torch.full((1030, 1288), 7.0, dtype=torch.float16, device="cuda")[:, :1280]

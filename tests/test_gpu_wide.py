@@ -28,6 +28,8 @@ def wide():
                                                (O.MODE_HEADWISE, 4, 200, 384, 130, 128),
                                                (O.MODE_HEADWISE, 3, 320, 640, 600, 0),    # an odd number of 64-row blocks
                                                (O.MODE_FULL, 4, 300, 512, 512, 256),      # fp16 form as the dense rotation
+                                               (O.MODE_NONE, 4, 140, 768, 260, 512),      # four fp16 units, then low-bit ones:
+                                               (O.MODE_HEADWISE, 3, 130, 1280, 300, 640), # the ring wraps among the former
                                                (O.MODE_FULL, 3, 72, 384, 272, 384)])
 def test_wide_against_oracle(mode, bits, M, D, N, K):
     print(f"case wide mode={mode} bits={bits} M={M} D={D} N={N} K={K}", flush=True)
