@@ -132,7 +132,7 @@ struct PackScratch {
 // downloaded on a second stream, and the pages of the arrays they go to are touched by several threads
 // (a download into untouched memory runs at 4 GB/s, into touched memory at 16).  Inf / NaN in W and Q and the rotation's
 // fingerprint are found by kernels on the uploaded copies; a byte-wise hash of a 4096 x 4096 rotation on the host
-// alone took 54 ms.  11008 x 4096 INT3 with a dense rotation, export included: 79 -> 13 ms.
+// alone took 54 ms.  11008 x 4096 INT3 with a dense rotation, export included: 80 to 90 -> 12 to 17 ms from box to box.
 static int pack_device(const rosaq_pack_desc& d, hipStream_t st, rosaq_packed* p) {
   std::string err;
   int rc = pack_validate_eigenvalues(d, &err);
@@ -358,8 +358,8 @@ static GemmTune rotation_tune() {
   return tune;
 }
 
-// The head-wise rotation of many rows: a workgroup per head and 64 rows takes 6 us and more as long as they find a compute
-// unit each, a workgroup per column tile less until the chip is full.  us, per head / per column tile: 4096 channels at
+// The head-wise rotation of many rows: a launch of one workgroup per head and 64 rows takes 6.0 to 6.4 us until it has more
+// workgroups than compute units, one of a workgroup per column tile (eight times as many) less than that while it is small.  us, per head / per column tile: 4096 channels at
 // 256 rows (128 heads x blocks) 6.0 / 5.3, at 384 (192) 6.2 / 6.9, at 512 6.4 / 8.7, at 2048 15.8 / 26.2; 5120 at 256 rows
 // (160) 6.1 / 6.0, at 2048 18.8 / 32.8; 1024 at 1024 rows (128) 6.1 / 5.2, at 2048 (256) 6.6 / 8.8.
 static bool rotates_whole_heads(int D, int M) {

@@ -144,7 +144,8 @@ int launch_stream_probe(const void* src, const void* shared, int workgroups, int
                         int x_kib, int shared_kib, void* sink, void* stream);
 
 // Word i's share of a rotation's hash; the hash of a rotation is the sum over its fp32 words, modulo 2^64, so that
-// any number of threads can add it up (host and GPU give the same).
+// any number of threads can add it up (host and GPU give the same).  Each word goes with its index through the published
+// 64-bit finaliser of MurmurHash3 (fmix64, with its two constants).
 #ifdef __HIPCC__
 __host__ __device__
 #endif

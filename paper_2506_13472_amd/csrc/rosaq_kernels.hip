@@ -3,9 +3,11 @@
 // Data flow of one call:
 //   prologue   x [M x D] fp16  ->  xhat fragments in storage order
 //                NONE      gather_kernel (permutation only, R = I)
-//                HEADWISE  rotate_headwise_kernel (128x128 MFMA blocks, Eq. 6)
-//                FULL      gather_kernel (identity) + gemm_kernel on fp16(Q)^T
-//   main       gemm_kernel: y = xhat_S W_S^T + xhat_N ((q - z) s)^T, fp32 accumulate
+//                HEADWISE  rotate_headwise_kernel (128x128 MFMA blocks, Eq. 6), or for many rows
+//                          rotate_rows_kernel (rosaq_rotate.hip)
+//                FULL      gather_kernel (identity) + the all-fp16 form of the main kernel on fp16(Q)^T
+//   main       gemm_kernel, or for many rows wide_gemm_kernel (rosaq_wide.hip):
+//                y = xhat_S W_S^T + xhat_N ((q - z) s)^T, fp32 accumulate
 //
 // All matrix operands are kept in "fragment order": a fragment is what one
 // v_mfma_f32_16x16x32_f16 consumes, 64 lanes x 16 bytes, lane l holding 8 halves
@@ -167,8 +169,9 @@ void gemm_kernel(GemmDev p) {
         acc[nt][mt] = mfma16(as_h8(r.a[mt]), as_h8(r.b[nt]), acc[nt][mt]);
   };
   // Every workgroup walks the groups in the same order: the fp32 sum of an output element
-  // is then the same whatever the tile shape or batching of the launch (starting each
-  // workgroup at its own group was measured: 1-3 % faster, not worth that property).
+  // is then the same whatever the tile of eight waves or the batching of an unsplit launch of this
+  // kernel (starting each workgroup at its own group was measured: 1-3 % faster, not worth that
+  // property).  Splits, sixteen waves and wide_gemm_kernel add in other orders.
   auto load_group = [&](int g, GroupRegs& r) {
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {

@@ -1,3 +1,6 @@
+// Two rotations that have kernels of their own: the dense one of few rows as slabs of the contraction, and the
+// head-wise one of many rows (rotate_rows_kernel, at the end).
+//
 // Dense rotation xhat = x fp16(Q) for calls of up to 64 rows (Eq. 1 with the layer-wise PCA
 // rotation of Sec. 3.1): a skinny fp16 contraction whose cost is the stream of fp16(Q) from HBM
 // (2 D^2 bytes: 33.5 MB at D = 4096, 52 MB at D = 5120).

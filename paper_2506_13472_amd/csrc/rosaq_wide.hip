@@ -110,8 +110,10 @@ __global__ __launch_bounds__(kWaves * 64, 1) void wide_gemm_kernel(GemmDev p) {
   // of those is n^2 / 16 + 4.5 n rounding errors of one step, that of runs of eight 4 n + n^2 / 16.  Outputs that are not the
   // correctly rounded sum of 4096 fp16 channels: one chain 1.9e-3, runs of eight 1.0e-3, gemm_kernel 1.3e-3.  The
   // additions cost 3-5 % (4096 -> 4096 at 2048 rows 67 -> 69 us).  The groups of a low-bit layer are one chain of D / 128
-  // additions (4096 channels: 6.4e-4 against 6.0e-4 in gemm_kernel, 13824: 9.8e-4 against 7.1e-4; a third level does not
-  // fit the registers: 48 of them would spill).
+  // additions, wide / gemm_kernel: 1024 channels 4.5e-4 / 5.1e-4, 4096 6.3e-4 / 5.6e-4, 13824 10.3e-4 / 7.5e-4.  The error of
+  // the outputs, which is their rounding to fp16, is the same to six digits in all of these (2.068814e-4 / 2.068813e-4 of the
+  // norm at 13824).  A third level has no room: in registers 48 of them spill, and half in registers, half in the 64 KiB of
+  // LDS that are left, still 20 inside the loop, whose reloads would wait for the pieces in flight.
   floatx4 tmp[NT][MT];
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt)
