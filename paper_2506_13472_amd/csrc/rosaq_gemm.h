@@ -89,7 +89,7 @@ struct GemmSeg {
   _Float16* out;
   int64_t ldo;
   int N;
-  int tile_end;      // exclusive prefix sum of the layers' valid channel tiles, ceil(N / 16)
+  int tile_begin, tile_end;   // its part of the launch's list of valid channel tiles, ceil(N / 16) each
 };
 struct GemmDev {
   const uint4* xf;
@@ -98,6 +98,7 @@ struct GemmDev {
   GemmSeg seg[kMaxBatch];
   int nseg;
   int M, ks_s, G, KS, KS_out, out_frag, chunks, mgroups;
+  int grid3;              // gemm_kernel: the grid is [8][splits x row groups][chunks / 8], else one-dimensional (map_block)
   // split-K across workgroups: `splits` workgroups share one output tile, each over its own run
   // of the contraction; their fp32 partial tiles meet in `part`, and the workgroup that draws
   // the last ticket of a tile adds them up in split order and stores the result
@@ -171,35 +172,6 @@ __device__ __forceinline__ GemmSeg pick_seg(const GemmDev& p, int si) {
   for (int i = 1; i < kMaxBatch; ++i)
     if (si == i) sg = p.seg[i];
   return sg;
-}
-
-// Store one accumulator fragment of row tile `mtile` (16 rows) and channel tile T of the
-// launch's tile list: lane holds rows 4*(lane/16)+i, column lane%16.
-__device__ __forceinline__ void store_fragment(const GemmDev& p, float4 v, int mtile, int T, int lane) {
-  int si, tile;
-  locate_tile(p, T, si, tile);
-  const GemmSeg sg = pick_seg(p, si);
-  const int n = tile * kTileN + (lane & 15);
-  if (n >= sg.N) return;
-  const float vv[4] = {v.x, v.y, v.z, v.w};
-  _Float16* out = sg.out;
-  if (!p.out_frag) {
-    const int64_t ldo = sg.ldo;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int m = mtile * 16 + 4 * (lane >> 4) + i;
-      if (m < p.M) out[static_cast<int64_t>(m) * ldo + n] = static_cast<_Float16>(vv[i]);
-    }
-  } else {
-    const int ks = n >> 5, j = (n >> 3) & 3, e = n & 7;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int lane2 = 4 * (lane >> 4) + i + 16 * j;
-      const size_t off =
-          (((static_cast<size_t>(mtile >> 2) * p.KS_out + ks) * 4 + (mtile & 3)) * 64 + lane2) * 8 + e;
-      out[off] = static_cast<_Float16>(vv[i]);
-    }
-  }
 }
 
 // The kernel for many rows (rosaq_wide.hip): 128 x 256 outputs per workgroup.  Needs a contraction of whole units

@@ -58,6 +58,50 @@ __host__ __device__ __forceinline__ void split_cut(int s, int splits, int ks_s, 
   if (g > G) g = G;
 }
 
+// The layers of the launch in its argument buffer, which scalar loads can index (indexing the by-value argument would move
+// it to scratch memory).  GemmDev is the kernel's first argument.
+typedef const __attribute__((address_space(4))) GemmSeg* SegArgs;
+__device__ __forceinline__ SegArgs seg_args() {
+  const uint64_t args = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr();
+  return (SegArgs)(args + offsetof(GemmDev, seg));
+}
+
+// Store one accumulator fragment of row tile `mtile` (16 rows) and channel tile T of the
+// launch's tile list: lane holds rows 4*(lane/16)+i, column lane%16.
+__device__ __forceinline__ void store_fragment(const GemmDev& p, float4 v, int mtile, int T, int lane) {
+  int tile = T;
+  _Float16* out = p.seg[0].out;
+  int64_t ldo = p.seg[0].ldo;
+  int N = p.seg[0].N;
+  if (p.nseg != 1) {
+    if (T >= p.seg[kMaxBatch - 1].tile_end) return;       // past the end of the list
+    const SegArgs segs = seg_args();
+    const int si = (T >= p.seg[0].tile_end) + (T >= p.seg[1].tile_end) + (T >= p.seg[2].tile_end);
+    tile = T - segs[si].tile_begin;
+    out = segs[si].out;
+    ldo = segs[si].ldo;
+    N = segs[si].N;
+  }
+  const int n = tile * kTileN + (lane & 15), m0 = mtile * 16 + 4 * (lane >> 4);
+  if (n >= N) return;
+  const float vv[4] = {v.x, v.y, v.z, v.w};
+  if (!p.out_frag) {
+    const int rows = p.M - m0;
+    _Float16* q = out + m0 * ldo + n;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (i < rows) *q = static_cast<_Float16>(vv[i]);
+      q += ldo;
+    }
+  } else {
+    // fragment order: k-step n / 32, lane 16 ((n / 8) % 4) + m % 16, half n % 8
+    _Float16* q = out + (static_cast<size_t>(mtile >> 2) * (p.KS_out * 4u) + (mtile & 3)) * 512 +
+                  static_cast<unsigned>(n >> 5) * 2048u + (4 * (lane >> 4) + 16 * ((n >> 3) & 3)) * 8 + (n & 7);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) q[i * 8] = static_cast<_Float16>(vv[i]);
+  }
+}
+
 int block_map_host(int b, int chunks, int mgroups, int* chunk, int* mg) {
   if (b < 0) return map_grid(chunks, mgroups);          // the grid size
   return map_block(b, chunks, mgroups, *chunk, *mg) ? 1 : 0;
@@ -82,40 +126,63 @@ void gemm_kernel(GemmDev p) {
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  int chunk, mg;
-  // the workgroups of one output tile are neighbours on one XCD (blockIdx % 8 is the XCD)
-  const int splits = p.splits;
-  const int local = blockIdx.x >> 3;
-  const int split = splits > 1 ? local % splits : 0;
-  const int base_block = splits > 1 ? ((local / splits) << 3) | (blockIdx.x & 7) : blockIdx.x;
-  if (p.zero_ptr != nullptr && blockIdx.x == 0)
-    for (int i = threadIdx.x; i < p.zero_count; i += WPB * 64) p.zero_ptr[i] = 0u;
-  if (!map_block(base_block, p.chunks, p.mgroups, chunk, mg)) return;
+  // Which tile.  Nothing is loaded before this is known, and what stands in front of it is latency: a wave issues one
+  // instruction in about eight clocks, and an argument load takes some 200.  With the divisions of the one-dimensional map, a
+  // search for every tile of a batch and argument loads where the compiler places them (at their uses, one after another)
+  // the first load left 2900 (one layer) to 4300 clocks (three) after a wave's start, 1.2 to 1.8 us of every launch; it is 790
+  // and 1610 now.  So the grid of up to four row groups has the tile's coordinates, in the same order; a layer's place is read
+  // from the argument buffer by its index; and everything the addresses need is asked for at once.  Whole steps, us before
+  // and after: 8 attention blocks of 64 rows 273.2 -> 261.9, 4 decoder layers at one row 236.8 -> 222.8, at 64 381.5 -> 370.0.
+  const int grid3 = p.grid3, splits = p.splits, chunks = p.chunks, nseg = p.nseg, G = p.G, ks_s = p.ks_s, KS4 = p.KS * 4, swiglu = p.swiglu;
+  const int e0 = p.seg[0].tile_end, e1 = p.seg[1].tile_end, e2 = p.seg[2].tile_end, list_end = p.seg[kMaxBatch - 1].tile_end;
+  const uint4 *const xf = p.xf, *const wS_0 = p.seg[0].wS;
+  const uint32_t* const wq_0 = p.seg[0].wq;
+  asm volatile("" ::"s"(grid3), "s"(splits), "s"(chunks), "s"(nseg), "s"(G), "s"(ks_s), "s"(KS4), "s"(swiglu), "s"(e0), "s"(e1),
+               "s"(e2), "s"(list_end), "s"(xf), "s"(wS_0), "s"(wq_0), "s"(p.M));
+  int chunk, mg, split = 0;
+  if (__builtin_expect(grid3, 1)) {
+    chunk = blockIdx.x + 8 * blockIdx.z;   // blockIdx.x is the XCD
+    mg = blockIdx.y;
+    if (__builtin_expect(splits > 1, 0)) { split = mg % splits; mg /= splits; }   // an output tile's workgroups: neighbours on one XCD
+    if (chunk >= chunks) return;
+  } else {
+    const int local = blockIdx.x >> 3;
+    split = splits > 1 ? local % splits : 0;
+    const int base_block = splits > 1 ? ((local / splits) << 3) | (blockIdx.x & 7) : blockIdx.x;
+    if (!map_block(base_block, chunks, p.mgroups, chunk, mg)) return;
+  }
   const int tile0 = chunk * NT;   // first tile of the chunk in the launch's tile list
   const int mtile0 = mg * MT;
   // where each of the chunk's tiles lives (uniform over the workgroup): fp16 fragments and
-  // low-bit records of tile nt start at wS_t[nt] and wq_t[nt]
+  // low-bit records of tile nt start at wS_t[nt] and wq_t[nt]; past the end of the list: the last tile again
   const uint4* wS_t[NT];
   const uint32_t* wq_t[NT];
   constexpr int kRecDwordsT = (BITS == 4 ? 256 : 192) + 16;
-  if (p.nseg == 1) {   // one layer: no search, the tiles are consecutive
-    const int valid = (p.seg[0].N + kTileN - 1) / kTileN;
+  const unsigned wS_tile = ks_s * 64, wq_tile = G * kRecDwordsT;
+  if (__builtin_expect(nseg == 1, 1)) {   // one layer: the tiles are consecutive
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
-      const int tile = tile0 + nt < valid ? tile0 + nt : valid - 1;   // past the end: re-read the last tile
-      wS_t[nt] = p.seg[0].wS + static_cast<size_t>(tile) * p.ks_s * 64;
-      wq_t[nt] = p.seg[0].wq + static_cast<size_t>(tile) * p.G * kRecDwordsT;
+      const unsigned tile = min(tile0 + nt, e0 - 1);
+      wS_t[nt] = wS_0 + static_cast<uint64_t>(tile) * wS_tile;
+      wq_t[nt] = wq_0 + static_cast<uint64_t>(tile) * wq_tile;
     }
   } else {
+    const SegArgs segs = seg_args();
+    const int gated = -swiglu;             // a gated pair's two layers alternate
+    unsigned tile[NT];
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
-      int si, tile;
-      locate_tile(p, tile0 + nt, si, tile);
-      const GemmSeg sg = pick_seg(p, si);
-      const int valid = (sg.N + kTileN - 1) / kTileN;
-      if (tile >= valid) tile = valid - 1;
-      wS_t[nt] = sg.wS + static_cast<size_t>(tile) * p.ks_s * 64;
-      wq_t[nt] = sg.wq + static_cast<size_t>(tile) * p.G * kRecDwordsT;
+      const int T = min(tile0 + nt, list_end - 1);
+      const int by_end = (T >= e0) + (T >= e1) + (T >= e2), si = by_end ^ ((by_end ^ (T & 1)) & gated);
+      wS_t[nt] = segs[si].wS;
+      wq_t[nt] = segs[si].wq;
+      const int local = T - segs[si].tile_begin;
+      tile[nt] = local ^ ((local ^ (T >> 1)) & gated);
+    }
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+      wS_t[nt] += static_cast<uint64_t>(tile[nt]) * wS_tile;
+      wq_t[nt] += static_cast<uint64_t>(tile[nt]) * wq_tile;
     }
   }
 
@@ -125,13 +192,8 @@ void gemm_kernel(GemmDev p) {
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) acc[nt][mt] = floatx4{0.f, 0.f, 0.f, 0.f};
 
-  // xhat fragment of row tile mtile0+mt and k-step ks: xa[mt][ks * 256]
-  const uint4* xa[MT];
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt) {
-    const int mtile = mtile0 + mt;
-    xa[mt] = p.xf + (static_cast<size_t>(mtile >> 2) * p.KS * 4 + (mtile & 3)) * 64 + lane;
-  }
+  // xhat fragment of row tile mtile0+mt and k-step ks: xa[ks * 256 + mt * 64] (MT divides the four tiles of a 64-row block)
+  const uint4* const xa = xf + (static_cast<uint64_t>(static_cast<unsigned>(mtile0) >> 2) * static_cast<unsigned>(KS4) + (mtile0 & 3)) * 64;
   // Skinny inputs (single row tile per workgroup): lanes whose row is beyond M skip the
   // load, so a decode step with a few rows does not pull 16 rows of padding per k-step.
   const bool row_ok = MT > 1 || mtile0 * 16 + (lane & 15) < p.M;
@@ -156,10 +218,10 @@ void gemm_kernel(GemmDev p) {
   auto load_step = [&](int u, StepRegs& r) {
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt)
-      r.b[nt] = wS_t[nt][static_cast<size_t>(u) * 64 + lane];
+      r.b[nt] = (wS_t[nt] + static_cast<unsigned>(u) * 64u)[lane];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
-      r.a[mt] = row_ok ? xa[mt][static_cast<size_t>(u) * 256] : make_uint4(0, 0, 0, 0);
+      r.a[mt] = row_ok ? (xa + static_cast<unsigned>(u) * 256u + mt * 64)[lane] : make_uint4(0, 0, 0, 0);
   };
   auto compute_step = [&](const StepRegs& r) {
 #pragma unroll
@@ -176,7 +238,7 @@ void gemm_kernel(GemmDev p) {
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
       constexpr int kCodeDwords = BITS == 4 ? 256 : 192, kRecDwords = kCodeDwords + 16;
-      const uint32_t* rec = wq_t[nt] + static_cast<size_t>(g) * kRecDwords;
+      const uint32_t* rec = wq_t[nt] + static_cast<unsigned>(g) * static_cast<unsigned>(kRecDwords);
       if (BITS == 4) {
         const uint4 c = reinterpret_cast<const uint4*>(rec)[lane];
         r.cw[nt][0] = c.x; r.cw[nt][1] = c.y; r.cw[nt][2] = c.z; r.cw[nt][3] = c.w;
@@ -185,15 +247,15 @@ void gemm_kernel(GemmDev p) {
         r.cw[nt][0] = c.w0; r.cw[nt][1] = c.w1; r.cw[nt][2] = c.w2;
         r.cw[nt][3] = 0;
       }
-      r.sz[nt] = rec[kCodeDwords + (lane & 15)];
+      r.sz[nt] = (rec + kCodeDwords)[lane & 15];
     }
-    const size_t ks0 = static_cast<size_t>(p.ks_s + 4 * g);
+    const uint4* const x0 = xa + static_cast<unsigned>(ks_s + 4 * g) * 256u;
 #pragma unroll
     for (int t = 0; t < 4; ++t)
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) {
         r.a[t][mt] = make_uint4(0, 0, 0, 0);
-        if (row_ok) r.a[t][mt] = xa[mt][(ks0 + t) * 256];
+        if (row_ok) r.a[t][mt] = (x0 + t * 256 + mt * 64)[lane];
       }
   };
   auto compute_group = [&](const GroupRegs& r) {
@@ -223,7 +285,6 @@ void gemm_kernel(GemmDev p) {
     }
   };
 
-  const int ks_s = p.ks_s, G = p.G;
   // this workgroup's run of the contraction (everything when the launch is not split)
   int u_lo = 0, u_hi = ks_s, g_lo = 0, g_hi = G;
   if (splits > 1 && BITS != 16) {
@@ -242,7 +303,7 @@ void gemm_kernel(GemmDev p) {
       for (int t = 0; t < 4; ++t) {
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt)
-          r.b[t][nt] = wS_t[nt][static_cast<size_t>(4 * qd + t) * 64 + lane];
+          r.b[t][nt] = (wS_t[nt] + static_cast<unsigned>(4 * qd + t) * 64u)[lane];
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
           if (p.xrow != nullptr) {
@@ -253,7 +314,7 @@ void gemm_kernel(GemmDev p) {
               r.a[t][mt] = *reinterpret_cast<const uint4*>(p.xrow + static_cast<int64_t>(m) * p.ldx +
                                                            (4 * qd + t) * kKStep + (lane >> 4) * 8);
           } else {
-            r.a[t][mt] = row_ok ? xa[mt][static_cast<size_t>(4 * qd + t) * 256] : make_uint4(0, 0, 0, 0);
+            r.a[t][mt] = row_ok ? (xa + static_cast<unsigned>(4 * qd + t) * 256u + mt * 64)[lane] : make_uint4(0, 0, 0, 0);
           }
         }
       }
@@ -275,7 +336,7 @@ void gemm_kernel(GemmDev p) {
     // fp16 tiles are a power-of-two number of KiB apart when D is: workgroups that all walk
     // their tiles from k = 0 would camp on the same HBM channels.  Each workgroup starts
     // its walk at its own offset (the sum over k does not care where it starts).
-    const int skew = nquad ? (blockIdx.x * 5) % nquad : 0;
+    const int skew = nquad ? ((p.grid3 ? blockIdx.x + 8 * (blockIdx.y + gridDim.y * blockIdx.z) : blockIdx.x) * 5) % nquad : 0;
     auto at = [&](int i) { const int v = i + skew; return q_lo + (v >= nquad ? v - nquad : v); };
     QuadRegs q[DEPTH];
     int u = wave;
@@ -299,7 +360,7 @@ void gemm_kernel(GemmDev p) {
       }
   } else {
   int u = u_lo + wave;
-  int g = g_lo + (wave + WPB - (u_hi - u_lo) % WPB) % WPB;
+  int g = g_lo + ((wave - (u_hi - u_lo)) & (WPB - 1));   // unit ks_s + g belongs to wave (ks_s + g) % WPB
   StepRegs s0, s1;
   GroupRegs r[DEPTH];
   if (u < u_hi) load_step(u, s0);
@@ -325,6 +386,9 @@ void gemm_kernel(GemmDev p) {
     }
   }
   }   // BITS != 16
+
+  if (p.zero_ptr != nullptr && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0)
+    for (int i = threadIdx.x; i < p.zero_count; i += WPB * 64) p.zero_ptr[i] = 0u;
 
   // ---- gated pair: out = silu(gate) * up, both sums still in fp32, one rounding to fp16 ------
   if constexpr (kRedNT % 2 == 0) {
@@ -411,7 +475,10 @@ void gemm_kernel(GemmDev p) {
       }
     __syncthreads();
 
-    for (int slot = wave; slot < kSlots; slot += WPB) {
+#pragma unroll
+    for (int slot0 = 0; slot0 < kSlots; slot0 += WPB) {
+      const int slot = slot0 + wave;
+      if (slot >= kSlots) break;
       float4 v = red[0][slot][lane];
 #pragma unroll
       for (int w = 1; w < WPB; ++w) {
@@ -615,8 +682,13 @@ static int hip_fail(hipError_t e, const char* what) {
 
 template <int BITS, int MT, int NT, int WPB, int DEPTH>
 static int launch_gemm_t(const GemmDev& d, hipStream_t st) {
-  const int xblocks = map_grid(d.chunks, d.mgroups) * (d.splits > 1 ? d.splits : 1);
-  hipLaunchKernelGGL((gemm_kernel<BITS, MT, NT, WPB, DEPTH>), dim3(xblocks), dim3(WPB * 64), 0, st, d);
+  const int splits = d.splits > 1 ? d.splits : 1, octets = (d.chunks + 7) / 8;
+  GemmDev g = d;
+  // up to kMapRows row groups the order of map_block is plain chunk-major, which a grid can have by itself; the octets of
+  // chunks are its third dimension, which ends at 65535 (some eight million channels; beyond, map_block as for many rows)
+  g.grid3 = d.mgroups <= kMapRows && octets <= 65535;
+  const dim3 grid = g.grid3 ? dim3(8, splits * d.mgroups, octets) : dim3(map_grid(d.chunks, d.mgroups) * splits);
+  hipLaunchKernelGGL((gemm_kernel<BITS, MT, NT, WPB, DEPTH>), grid, dim3(WPB * 64), 0, st, g);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? ROSAQ_OK : hip_fail(e, "gemm_kernel launch");
 }
@@ -828,6 +900,7 @@ static GemmDev fill_dev(const GemmArgs& a, int* tiles_out) {
   int tiles = 0;   // in launch order
   for (int i = 0; i < kMaxBatch; ++i) {
     const GemmSegArgs& sa = a.seg[i < a.nseg ? i : 0];
+    d.seg[i].tile_begin = tiles;
     if (i < a.nseg) tiles += (sa.N + kTileN - 1) / kTileN;
     d.seg[i].wS = static_cast<const uint4*>(sa.wS);
     d.seg[i].wq = static_cast<const uint32_t*>(sa.wq);
@@ -836,7 +909,7 @@ static GemmDev fill_dev(const GemmArgs& a, int* tiles_out) {
     d.seg[i].N = sa.N;
     d.seg[i].tile_end = tiles;
   }
-  d.chunks = d.mgroups = 0;
+  d.chunks = d.mgroups = d.grid3 = 0;
   d.splits = 1;
   d.part = static_cast<float4*>(a.part);
   d.tickets = static_cast<unsigned*>(a.tickets);
