@@ -328,8 +328,8 @@ static GemmIO plan_io(const rosaq_packed& p0, const WsPlan& w, char* ws, size_t 
 }
 
 // y_i = xhat W_i^T for `count` layers that share the xhat fragments `io.xf`.
-static int run_main_gemm(const rosaq_packed_t* const* ps, int count, const GemmIO& io, int M,
-                         void* const* ys, const int64_t* ldys, void* stream, bool swiglu = false) {
+static GemmArgs main_gemm(const rosaq_packed_t* const* ps, int count, const GemmIO& io, int M,
+                          void* const* ys, const int64_t* ldys, bool swiglu = false) {
   const Canonical& c = ps[0]->c;
   GemmArgs a{};
   a.xf = io.xf;
@@ -347,8 +347,11 @@ static int run_main_gemm(const rosaq_packed_t* const* ps, int count, const GemmI
   a.tickets = io.tickets; a.ticket_count = kTicketsPerLaunch;
   a.zero_ptr = io.zero_ptr; a.zero_count = io.zero_count;
   a.swiglu = swiglu ? 1 : 0;
-  return launch_gemm(a, g_tune, stream);
+  return a;
 }
+// The words the first launch of a call clears: the tickets of the GEMM launches behind it, if there are any.  (Cleared
+// always, they were 32 KiB of stores in launches that are bound by the way of their stores to memory.)
+static int ticket_words(const GemmArgs& a, int words) { return gemm_uses_tickets(a, g_tune) ? words : 0; }
 
 // Settings of the dense rotation's launch: "rot_splits" selects the slab launches, never a ticketed split (no room for
 // partial tiles is offered).
@@ -369,11 +372,9 @@ static bool rotates_whole_heads(int D, int M) {
 
 // x -> xhat fragments in the workspace (gather / head-wise blocks / dense rotation).
 static int run_prologue(const rosaq_packed_t* p, const WsPlan& w, const void* x_dev, int M,
-                        int64_t ldx, char* ws, size_t ws_bytes, void* hip_stream) {
+                        int64_t ldx, char* ws, size_t ws_bytes, int n_tickets, void* hip_stream) {
   const Canonical& c = p->c;
-  // the first launch of a call clears the tickets of the GEMM launches behind it
   void* tickets = ws + w.tickets;
-  const int n_tickets = 2 * kTicketsPerLaunch;
   if (c.q_mode == ROSAQ_Q_HEADWISE && rotates_whole_heads(c.D, M))
     return launch_rotate_rows(x_dev, ldx, M, c.D, p->d_qf, p->d_perm, p->d_pos, ws + w.xf_a, tickets, n_tickets,
                               hip_stream);
@@ -401,8 +402,8 @@ static int run_prologue(const rosaq_packed_t* p, const WsPlan& w, const void* x_
     a.xrow = x_dev;        // skinny input: the rotation reads x in place, no fragment copy
     a.ldx = ldx;
     // no launch in front of the rotation: it runs unsplit and clears the main GEMM's tickets itself
-    a.zero_ptr = static_cast<char*>(tickets) + kTicketsPerLaunch * sizeof(uint32_t);
-    a.zero_count = kTicketsPerLaunch;
+    a.zero_ptr = n_tickets ? tickets : nullptr;
+    a.zero_count = n_tickets;
   } else {
     const int rc = launch_gather(x_dev, ldx, M, c.D, nullptr, ws + w.xf_a, tickets, n_tickets, hip_stream);
     if (rc != ROSAQ_OK) return rc;
@@ -419,12 +420,13 @@ static int run_prologue(const rosaq_packed_t* p, const WsPlan& w, const void* x_
 static int run_call(const rosaq_packed_t* const* ps, int count, const void* x_dev, int M,
                     int64_t ldx, void* const* ys, const int64_t* ldys, char* ws, size_t ws_bytes,
                     const WsPlan& w, void* hip_stream, bool swiglu = false) {
+  const GemmArgs a = main_gemm(ps, count, plan_io(*ps[0], w, ws, ws_bytes), M, ys, ldys, swiglu);
   if (g_tune_stages & 1) {
-    const int rc = run_prologue(ps[0], w, x_dev, M, ldx, ws, ws_bytes, hip_stream);
+    const int rc = run_prologue(ps[0], w, x_dev, M, ldx, ws, ws_bytes, ticket_words(a, 2 * kTicketsPerLaunch), hip_stream);
     if (rc != ROSAQ_OK) return rc;
   }
   if (!(g_tune_stages & 2)) return ROSAQ_OK;
-  return run_main_gemm(ps, count, plan_io(*ps[0], w, ws, ws_bytes), M, ys, ldys, hip_stream, swiglu);
+  return launch_gemm(a, g_tune, hip_stream);
 }
 
 static uint64_t fnv1a(uint64_t h, const void* data, size_t n) {
@@ -665,21 +667,12 @@ int rosaq_mlp_swiglu(const rosaq_packed_t* gate, const rosaq_packed_t* up, const
   const rosaq_packed_t* gu[2] = {gate, up};
   const rosaq_packed_t* all[3] = {gate, up, down};
   if (check_device(all, 3) != ROSAQ_OK) return ROSAQ_ERR_HOSTONLY;
-  // 1. xhat of the input (clears the gate / up launch's tickets)
+  // 1. xhat of the input
   if (g_tune_stages & 1) {
-    rc = run_prologue(gate, m.gate, x_dev, M, ldx, ws, m.gate.required, hip_stream);
+    rc = run_prologue(gate, m.gate, x_dev, M, ldx, ws, m.gate.required, 0, hip_stream);   // a gated launch is never split
     if (rc != ROSAQ_OK) return rc;
   }
   if (!(g_tune_stages & 2)) return ROSAQ_OK;
-  // 2. silu(gate) * up, written as down's input fragments at down's storage positions
-  GemmIO io = plan_io(*gate, m.gate, ws, m.gate.required);
-  io.part = nullptr; io.part_bytes = 0;
-  io.chain_pos = down->d_pos; io.chain_ks = down->c.D / kKStep;
-  io.zero_ptr = ws + m.down_tickets; io.zero_count = 2 * kTicketsPerLaunch;
-  void* hs[2] = {ws + m.down_xf, ws + m.down_xf};
-  const int64_t ldh[2] = {0, 0};
-  rc = run_main_gemm(gu, 2, io, M, hs, ldh, hip_stream, true);
-  if (rc != ROSAQ_OK) return rc;
   // 3. y = h What_down^T
   GemmIO dn{};
   dn.xf = ws + m.down_xf;
@@ -687,7 +680,17 @@ int rosaq_mlp_swiglu(const rosaq_packed_t* gate, const rosaq_packed_t* up, const
   dn.part = ws + m.part;
   dn.part_bytes = ws_bytes > m.part ? ws_bytes - m.part : 0;
   const int64_t ldys[1] = {ldy};
-  return run_main_gemm(&down, 1, dn, M, &y_dev, ldys, hip_stream);
+  const GemmArgs third = main_gemm(&down, 1, dn, M, &y_dev, ldys);
+  // 2. silu(gate) * up, written as down's input fragments at down's storage positions; clears that launch's tickets
+  GemmIO io = plan_io(*gate, m.gate, ws, m.gate.required);
+  io.part = nullptr; io.part_bytes = 0;
+  io.chain_pos = down->d_pos; io.chain_ks = down->c.D / kKStep;
+  io.zero_count = ticket_words(third, 2 * kTicketsPerLaunch);
+  io.zero_ptr = io.zero_count ? ws + m.down_tickets : nullptr;
+  void* hs[2] = {ws + m.down_xf, ws + m.down_xf};
+  const int64_t ldh[2] = {0, 0};
+  rc = launch_gemm(main_gemm(gu, 2, io, M, hs, ldh, true), g_tune, hip_stream);
+  return rc != ROSAQ_OK ? rc : launch_gemm(third, g_tune, hip_stream);
 }
 
 int rosaq_packed_info(const rosaq_packed_t* p, int32_t* N, int32_t* D, int32_t* K, int32_t* bits,

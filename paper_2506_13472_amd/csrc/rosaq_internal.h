@@ -115,6 +115,8 @@ GemmShape pick_gemm_shape(int M, int ntiles, int D, int bits, const GemmTune& tu
 // bytes of partial tiles a launch of this shape needs
 size_t gemm_part_bytes(const GemmShape& s, int M, int ntiles);
 int launch_gemm(const GemmArgs& a, const GemmTune& tune, void* stream);
+// Whether that launch is split over workgroups, so that its tickets have to be cleared in front of it.
+bool gemm_uses_tickets(const GemmArgs& a, const GemmTune& tune);
 // Host copy of the kernel's workgroup -> (channel chunk, row group) map: b < 0 returns the grid
 // size, otherwise 1 and the pair, or 0 for a padding workgroup that exits at once.
 // Whether launch_gemm takes the kernel for many rows (128 x 256 tiles).

@@ -549,20 +549,18 @@ void gemm_kernel(GemmDev p) {
 // ascending inside the salient and inside the remaining part, so most 8-channel
 // fragments are a run of consecutive channels: those are cut out of two aligned
 // 16-byte loads; the others are gathered element by element.
+// One workgroup per k-step and 64-row block, a wave per row tile (calls of up to 48 rows have fewer).
 __global__ __launch_bounds__(256) void gather_kernel(const _Float16* __restrict__ x, int64_t ldx,
-                                                     int M, int KS, const int32_t* __restrict__ perm,
-                                                     uint4* __restrict__ xf, int total,
+                                                     int M, const int32_t* __restrict__ perm,
+                                                     uint4* __restrict__ xf,
                                                      unsigned* __restrict__ zero_ptr, int zero_count) {
-  const int idx = blockIdx.x * 256 + threadIdx.x;
-  // tickets of the GEMM launches that follow in this call, spread over the launch's threads
-  for (int i = idx; i < zero_count; i += gridDim.x * 256) zero_ptr[i] = 0u;
-  if (idx >= total) return;
-  const int lane = idx & 63, mt = (idx >> 6) & 3;
-  const int ks = (idx >> 8) % KS, mb = (idx >> 8) / KS;
-  const int m = mb * kMBlock + mt * 16 + (lane & 15);
+  asm volatile("" ::"s"(x), "s"(ldx), "s"(M), "s"(perm), "s"(xf), "s"(zero_count));   // one wait for all arguments
+  const int lane = threadIdx.x & 63, mt = threadIdx.x >> 6;
+  const int ks = blockIdx.x, mb = blockIdx.y;
+  const int m = min(mb * kMBlock + mt * 16 + (lane & 15), M - 1);   // rows past M: the last one again
   const int p0 = ks * kKStep + (lane >> 4) * 8;
-  uint4 v = make_uint4(0, 0, 0, 0);
-  if (m < M) {
+  uint4 v;
+  {
     const _Float16* row = x + static_cast<int64_t>(m) * ldx;
     if (perm == nullptr) {
       v = *reinterpret_cast<const uint4*>(row + p0);
@@ -595,47 +593,53 @@ __global__ __launch_bounds__(256) void gather_kernel(const _Float16* __restrict_
       }
     }
   }
-  xf[idx] = v;
+  xf[((static_cast<size_t>(mb) * gridDim.x + ks) * 4 + mt) * 64 + lane] = v;
+  // tickets of the GEMM launches that follow in this call, spread over the launch's threads
+  for (int i = (mb * gridDim.x + ks) * blockDim.x + threadIdx.x; i < zero_count; i += gridDim.x * gridDim.y * blockDim.x)
+    zero_ptr[i] = 0u;
 }
 
 // Head-wise rotation (Eq. 6): xhat_h = x_h fp16(Q_h).  One workgroup per (head,
 // 16-channel column tile, 64-row block): wave w owns row tile w, issues every load
 // it needs at once (x, Q_h fragments, storage positions), runs 4 MFMAs and scatters
 // the tile to the storage position of each rotated channel.
+//
+// A launch is latency: its loads, the way of its stores to memory, and what stands in front of the loads.  2170 clocks went
+// by before the last load was issued (argument loads one after another, tickets cleared first, 64-bit addresses for each
+// access), 1000 until the data were there, 1900 until the stores were.  With one wait for the arguments, loads first, rows
+// clamped instead of tested and no tickets to clear unless the GEMM behind is split: 8 attention blocks of 64 rows (16
+// rotations) 261.7 -> 253.9 us.  A call of up to 48 rows has fewer waves.
 __global__ __launch_bounds__(256) void rotate_headwise_kernel(
     const _Float16* __restrict__ x, int64_t ldx, int M, int KS, int H, const uint4* __restrict__ qh,
     const int32_t* __restrict__ pos, _Float16* __restrict__ xf, unsigned* __restrict__ zero_ptr,
     int zero_count) {
-  // tickets of the GEMM launch that follows in this call, spread over the launch's threads
-  for (int i = (blockIdx.y * gridDim.x + blockIdx.x) * 256 + threadIdx.x; i < zero_count;
-       i += gridDim.x * gridDim.y * 256)
-    zero_ptr[i] = 0u;
-  const int lane = threadIdx.x & 63;
+  asm volatile("" ::"s"(x), "s"(ldx), "s"(M), "s"(KS), "s"(H), "s"(qh), "s"(pos), "s"(xf), "s"(zero_count));   // one wait for all
+  const unsigned lane = threadIdx.x & 63;
   const int mt = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // the eight column tiles of a head share x_h: keep them on one XCD (id % 8)
   const int h = (blockIdx.x & 7) + 8 * (blockIdx.x >> 6), ct = (blockIdx.x >> 3) & 7, mb = blockIdx.y;
   if (h >= H) return;
-  const int m = mb * kMBlock + mt * 16 + (lane & 15);
+  const int m = min(mb * kMBlock + mt * 16 + static_cast<int>(lane & 15), M - 1);   // rows past M: the last one again
   uint4 a[4], b[4];
+  const uint4* const q0 = qh + static_cast<size_t>(h * 8 + ct) * 256;
 #pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    a[t] = make_uint4(0, 0, 0, 0);
-    if (m < M)
-      a[t] = *reinterpret_cast<const uint4*>(x + static_cast<int64_t>(m) * ldx + h * kHeadDim +
-                                             t * kKStep + (lane >> 4) * 8);
-    b[t] = qh[((static_cast<size_t>(h) * 8 + ct) * 4 + t) * 64 + lane];
-  }
-  const int p = pos[h * kHeadDim + ct * 16 + (lane & 15)];
+  for (int t = 0; t < 4; ++t) b[t] = (q0 + t * 64)[lane];
+  const int p = (pos + h * kHeadDim + ct * 16)[lane & 15];
+  const _Float16* const x0 = x + static_cast<int64_t>(m) * ldx + (h * kHeadDim + static_cast<int>(lane >> 4) * 8);
+#pragma unroll
+  for (int t = 0; t < 4; ++t) a[t] = *reinterpret_cast<const uint4*>(x0 + t * kKStep);
   floatx4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int t = 0; t < 4; ++t) acc = mfma16(as_h8(a[t]), as_h8(b[t]), acc);
-  const int ks = p >> 5, j = (p >> 3) & 3, e = p & 7;
+  // position p of row r of the tile: k-step p / 32, lane r + 16 (p / 8 % 4), half p % 8
+  _Float16* const tile0 = xf + (static_cast<size_t>(mb) * KS * 4 + mt) * 512;
+  const unsigned off = static_cast<unsigned>(p >> 5) * 2048u + (4 * (lane >> 4) + 16 * ((p >> 3) & 3)) * 8 + (p & 7);
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int lane2 = 4 * (lane >> 4) + i + 16 * j;
-    xf[(((static_cast<size_t>(mb) * KS + ks) * 4 + mt) * 64 + lane2) * 8 + e] =
-        static_cast<_Float16>(acc[i]);
-  }
+  for (int i = 0; i < 4; ++i) (tile0 + i * 8)[off] = static_cast<_Float16>(acc[i]);
+  // tickets of the GEMM launch that follows in this call, spread over the launch's threads
+  for (int i = (blockIdx.y * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x; i < zero_count;
+       i += gridDim.x * gridDim.y * blockDim.x)
+    zero_ptr[i] = 0u;
 }
 
 // Measurement aid: a pure read stream.  Every wave reads `w_kib` KiB of its own from
@@ -990,6 +994,14 @@ bool prefers_wide(int M, int ntiles, int D, int K, int bits, const GemmTune& tun
   return 1.03 * wide < narrow;
 }
 
+bool gemm_uses_tickets(const GemmArgs& a, const GemmTune& tune) {
+  int tiles = 0;
+  for (int i = 0; i < a.nseg; ++i) tiles += (a.seg[i].N + kTileN - 1) / kTileN;
+  if (a.swiglu || a.M > kMBlock || !a.part || !a.tickets) return false;
+  if (tune.splits <= 1 && (a.M <= 32 || a.KS * kKStep < 8192)) return false;   // pick_gemm_shape's own rule, without its cost
+  return pick_gemm_shape(a.M, tiles, a.KS * kKStep, a.G == 0 ? 16 : a.bits, tune, a.part_bytes, a.ticket_count, a.ks_s).splits > 1;
+}
+
 int launch_gemm(const GemmArgs& a, const GemmTune& tune, void* stream) {
   int tiles_total = 0;
   for (int i = 0; i < a.nseg; ++i) tiles_total += (a.seg[i].N + kTileN - 1) / kTileN;
@@ -1041,13 +1053,15 @@ int launch_stream_probe(const void* src, const void* shared, int workgroups, int
   return e == hipSuccess ? ROSAQ_OK : hip_fail(e, "stream_probe_kernel launch");
 }
 
+// A wave per row tile of a 64-row block.  What no wave writes, rows past the last tile of a call, no one uses: a row of xhat
+// only enters the output row of the same number.
+static int prologue_threads(int M) { return 64 * std::min(4, (M + 15) / 16); }
+
 int launch_gather(const void* x, int64_t ldx, int M, int D, const int32_t* perm_dev, void* xf,
                   void* zero_ptr, int zero_count, void* stream) {
-  const int KS = D / kKStep, mblocks = (M + kMBlock - 1) / kMBlock;
-  const int total = mblocks * KS * 256;
-  hipLaunchKernelGGL(gather_kernel, dim3((total + 255) / 256), dim3(256), 0,
-                     static_cast<hipStream_t>(stream), static_cast<const _Float16*>(x), ldx, M, KS,
-                     perm_dev, static_cast<uint4*>(xf), total, static_cast<unsigned*>(zero_ptr), zero_count);
+  hipLaunchKernelGGL(gather_kernel, dim3(D / kKStep, (M + kMBlock - 1) / kMBlock), dim3(prologue_threads(M)), 0,
+                     static_cast<hipStream_t>(stream), static_cast<const _Float16*>(x), ldx, M,
+                     perm_dev, static_cast<uint4*>(xf), static_cast<unsigned*>(zero_ptr), zero_count);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? ROSAQ_OK : hip_fail(e, "gather_kernel launch");
 }
@@ -1056,7 +1070,7 @@ int launch_rotate_headwise(const void* x, int64_t ldx, int M, int D, const void*
                            const int32_t* pos_dev, void* xf, void* zero_ptr, int zero_count,
                            void* stream) {
   const int H = D / kHeadDim, mblocks = (M + kMBlock - 1) / kMBlock;
-  hipLaunchKernelGGL(rotate_headwise_kernel, dim3(((H + 7) / 8) * 64, mblocks), dim3(256), 0,
+  hipLaunchKernelGGL(rotate_headwise_kernel, dim3(((H + 7) / 8) * 64, mblocks), dim3(prologue_threads(M)), 0,
                      static_cast<hipStream_t>(stream), static_cast<const _Float16*>(x), ldx, M,
                      D / kKStep, H, static_cast<const uint4*>(qh), pos_dev,
                      static_cast<_Float16*>(xf), static_cast<unsigned*>(zero_ptr), zero_count);
