@@ -13,9 +13,8 @@
 //   apply_kernel   multiplies the pair's columns of X V and of V by J (fp64 MFMA).
 // That makes D_b / 32 - 1 rounds of three launches per sweep where rotating one pair of columns at a
 // time takes D_b - 1 launches that stream all of X V and V each: 32 heads of 128 channels, 512 rows
-// 15.1 -> 2.1 ms, one problem of 1024 channels, 2048 rows 161 -> 21 ms.  Bound by rotate_kernel (53 % of the time):
-// its 32 dependent rounds take 0.8 us each, the chain of the angles and two barriers.  With J updated in the same phase
-// as the inner products and every element in LDS a round took 1.1 us (33 against 42 us per launch).
+// 15.1 -> 1.9 ms, one problem of 1024 channels, 2048 rows 161 -> 19 ms.  Bound by rotate_kernel (45 % of the time):
+// see there.
 //
 // Columns are kept contiguous: Z[c] = [column c of X V (n_pad rows, zero padded) | row c of V^T].
 // A layer-wise rotation is one problem of dimension D; a head-wise one is D / 128 independent problems of
@@ -37,6 +36,7 @@ typedef double doublex4 __attribute__((ext_vector_type(4)));
 
 constexpr int kPcaBlock = 32;                // columns per block
 constexpr int kPcaPanel = 2 * kPcaBlock;     // columns of a pair of blocks
+constexpr int kPcaChunks = 8;                // most partial sums of a pair's inner products
 constexpr int kPcaTiles = 10;                // 16 x 16 tiles on and above the diagonal of the panel's matrix
 
 // One calibration set on the device.
@@ -157,59 +157,63 @@ __device__ __forceinline__ double fast_rcp(double x) {
 
 // The rotations of a pair of blocks.  With alpha = |y_p|^2, beta = |y_q|^2, gamma = y_p . y_q:
 //   d = beta - alpha, t = sign(d) 2 gamma / (|d| + sqrt(d^2 + 4 gamma^2)), c = 1 / sqrt(1 + t^2), s = c t,
-//   (y_p, y_q) <- (c y_p - s y_q, s y_p + c y_q);
-// columns that are orthogonal to round-off (|gamma| <= eps sqrt(alpha beta)) are left alone.  Of a round's 32 rotations
-// one wave computes the angles; then thread (a, b) turns the 2 x 2 block of rows (p_a, q_a) and columns (p_b, q_b).
-__global__ __launch_bounds__(1024) void rotate_kernel(PcaDev p, int round, int pairs) {
-  __shared__ double G[kPcaPanel][kPcaPanel];
-  __shared__ double Jt[kPcaPanel][kPcaPanel];
-  __shared__ doublex2 cs[kPcaBlock];
-  __shared__ double red[2][16];
-  int c0, c1;
-  if (p.done[pair_columns(p, blockIdx.x, round, c0, c1)]) return;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  {
-    const double* part = p.part + static_cast<size_t>(blockIdx.x) * p.chunks * (kPcaTiles * 256);
-    for (int i = tid; i < kPcaTiles * 256; i += 1024) {
-      double v = 0.0;
-      for (int ch = 0; ch < p.chunks; ++ch) v += part[static_cast<size_t>(ch) * (kPcaTiles * 256) + i];
-      // accumulator e of lane l of a 16 x 16 tile: row 4 e + l / 16, column l % 16
-      const int tile = i >> 8, e = (i >> 6) & 3, l = i & 63;
-      const int ta = tile < 4 ? 0 : (tile < 7 ? 1 : (tile < 9 ? 2 : 3));
-      const int tb = tile - (ta == 0 ? 0 : (ta == 1 ? 3 : (ta == 2 ? 5 : 6)));
-      const int r = ta * 16 + 4 * e + (l >> 4), c = tb * 16 + (l & 15);
-      G[r][c] = v;
-      G[c][r] = v;                       // inside a diagonal tile both orders of an element hold the same sum
+//   (y_p, y_q) <- (c y_p - s y_q, s y_p + c y_q), alpha <- alpha - t gamma, beta <- beta + t gamma;
+// columns that are orthogonal to round-off (|gamma| <= eps sqrt(alpha beta)) are left alone.
+//
+// A round is 32 rotations: ALL pairs of the panel's columns in 63 rounds of a tournament, or each column of one block with
+// each of the other in 32.  Its angles need the inner products as the round before leaves them, and the rest of
+// the work needs its angles: as two steps with a barrier each a round took 0.8 us, 33 us a launch.  But of those inner products the
+// angles need only the 32 of the pairs that meet next, each a combination of the four between two pairs of this
+// round.  So the first wave forms these by itself, from the matrix as it stands before the round, while seven and a half
+// waves turn the matrix from one buffer into the other (of the 32 x 32 blocks (pair a, pair b) those with a <= b: it is
+// symmetric) and eight turn J, with one barrier a round.  A launch of 32 rounds now takes 24.9 us (29.6 before, kernels alone),
+// one of 63 59.7 (67.3).  Of the 24.9, 9.8 are left without any rounds (launch, partial sums, the way of J to memory), 15.9 with
+// the angles alone, 18.4 with J and 18.9 with the matrix in place of both: issue slots and LDS are what the three share.
+template <bool ALL>
+struct PcaPairing {
+  static constexpr int kRounds = ALL ? kPcaPanel - 1 : kPcaBlock;
+  // columns of pair k of round r; in a tournament the last column stays and the others move one seat per round
+  static __device__ __forceinline__ void pair(int r, int k, int& P, int& Q) {
+    if constexpr (ALL) {
+      int x = k + r, y = kPcaPanel - 1 - k + r;
+      x -= x >= kPcaPanel - 1 ? kPcaPanel - 1 : 0;
+      y = k == 0 ? kPcaPanel - 1 : y - (y >= kPcaPanel - 1 ? kPcaPanel - 1 : 0);
+      P = min(x, y);
+      Q = max(x, y);
+    } else {
+      P = k;
+      Q = kPcaBlock + ((k + r) & (kPcaBlock - 1));
     }
-    for (int i = tid; i < kPcaPanel * kPcaPanel; i += 1024) Jt[i >> 6][i & 63] = (i >> 6) == (i & 63) ? 1.0 : 0.0;
   }
-  __syncthreads();
-  // what the convergence test needs, before anything is rotated: gamma^2 between the blocks, in a sweep's first round also
-  // inside them, and alpha^2
-  const bool all_pairs = round == 0;
-  double g2 = 0.0, d2 = 0.0;
-  for (int i = tid; i < kPcaPanel * kPcaPanel; i += 1024) {
-    const int r = i >> 6, c = i & 63;
-    const double v = G[r][c];
-    if (r < c && (all_pairs || (r < kPcaBlock && c >= kPcaBlock))) g2 = __builtin_fma(v, v, g2);
-    if (r == c) d2 = __builtin_fma(v, v, d2);
+  // the pair of round r that column v is in
+  static __device__ __forceinline__ int of(int r, int v) {
+    if constexpr (ALL) {
+      if (v == kPcaPanel - 1) return 0;
+      const int seat = v - r + (v < r ? kPcaPanel - 1 : 0);
+      return seat < kPcaBlock ? seat : kPcaPanel - 1 - seat;
+    } else {
+      return v < kPcaBlock ? v : (v - r) & (kPcaBlock - 1);
+    }
   }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) { g2 += __shfl_down(g2, o, 64); d2 += __shfl_down(d2, o, 64); }
-  if (lane == 0) { red[0][wave] = g2; red[1][wave] = d2; }
-  __syncthreads();
-  if (tid == 0) {
-    double a = 0.0, b = 0.0;
-    for (int w = 0; w < 16; ++w) { a += red[0][w]; b += red[1][w]; }
-    p.gamma2[static_cast<size_t>(round) * pairs + blockIdx.x] = a;
-    if (all_pairs) p.diag2[blockIdx.x] = b;
-  }
+};
 
-  // J is not needed for the angles: it takes a round's rotations while the first wave computes the next round's angles.
-  const int a = tid >> 5, b = tid & 31;
-  auto angles = [&](int pb, int qb) {    // both halves of the wave compute the same
-    const double al = G[pb][pb], be = G[qb][qb], ga = G[pb][qb];
+constexpr int kPcaPitch = kPcaPanel + 1;     // lanes on neighbouring rows of a column meet no bank twice
+struct PcaPanelLds {
+  double G[2][kPcaPanel * kPcaPitch];        // element (i, j) at min(i, j) * kPcaPitch + max(i, j)
+  alignas(16) double Jt[kPcaPanel][kPcaPanel + 2];
+  doublex2 cs[2][kPcaBlock];
+  double diag[kPcaPanel];
+  double red[2][16];
+};
+
+template <bool ALL>
+__device__ __forceinline__ void rotate_rounds(PcaPanelLds& m) {
+  using Pairing = PcaPairing<ALL>;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  auto at = [](int i, int j) { return min(i, j) * kPcaPitch + max(i, j); };
+  auto angle = [&](int r, int k, int P, int Q, double al, double be, double ga) {
     doublex2 v = {1.0, 0.0};
+    double shift = 0.0;
     const double ab = al * be;
     if (ab > 0.0 && ga * ga > 4.930380657631324e-32 * ab) {    // false too where one is NaN
       const double d = be - al, g = 2.0 * ga;
@@ -217,8 +221,14 @@ __global__ __launch_bounds__(1024) void rotate_kernel(PcaDev p, int round, int p
       const double t = copysign(1.0, d) * g * fast_rcp(fabs(d) + h2 * fast_rsqrt(h2));
       const double c = fast_rsqrt(__builtin_fma(t, t, 1.0));
       v = doublex2{c, c * t};
+      shift = t * ga;
     }
-    if (lane < kPcaBlock) cs[b] = v;
+    if (lane < kPcaBlock) {                                    // both halves of the wave compute the same
+      m.cs[r & 1][k] = v;
+      m.diag[P] = al - shift;
+      m.diag[Q] = be + shift;
+    }
+    __builtin_amdgcn_wave_barrier();
   };
   // the 2 x 2 block (pp pq; qp qq): columns by rb, then rows by ra
   auto turn = [](doublex2 ra, doublex2 rb, double& pp, double& pq, double& qp, double& qq) {
@@ -229,65 +239,151 @@ __global__ __launch_bounds__(1024) void rotate_kernel(PcaDev p, int round, int p
     qp = ra.y * pp1 + ra.x * qp1;
     qq = ra.y * pq1 + ra.x * qq1;
   };
-  if (all_pairs) {
-    int pj = 0, qj = 0;                  // rows of J and the rotation that they still have to take
-    doublex2 rj = {1.0, 0.0};
-    auto turn_j = [&]() {
-#pragma unroll
-      for (int i = b; i < kPcaPanel; i += 32) {
-        const double u = Jt[pj][i], v = Jt[qj][i];
-        Jt[pj][i] = rj.x * u - rj.y * v;
-        Jt[qj][i] = rj.y * u + rj.x * v;
+  if (wave == 0) {
+    __builtin_amdgcn_s_setprio(3);
+    const int k = lane & (kPcaBlock - 1);
+    m.diag[lane] = m.G[0][at(lane, lane)];
+    __builtin_amdgcn_wave_barrier();
+    int P, Q;
+    Pairing::pair(0, k, P, Q);
+    angle(0, k, P, Q, m.diag[P], m.diag[Q], m.G[0][at(P, Q)]);
+    __syncthreads();
+    auto look_ahead = [&](int r, const double* G, const doublex2* cs) {
+      if (r + 1 < Pairing::kRounds) {
+        int x, y;
+        Pairing::pair(r + 1, k, x, y);
+        const int i = Pairing::of(r, x), j = Pairing::of(r, y);
+        int Pi, Qi, Pj, Qj;
+        Pairing::pair(r, i, Pi, Qi);
+        Pairing::pair(r, j, Pj, Qj);
+        const double pp = G[at(Pi, Pj)], pq = G[at(Pi, Qj)], qp = G[at(Qi, Pj)], qq = G[at(Qi, Qj)];
+        const doublex2 ri = cs[i], rj = cs[j];
+        const double al = m.diag[x], be = m.diag[y];
+        // column p of a pair becomes c p - s q, column q becomes s p + c q
+        const double ip = x == Pi ? ri.x : ri.y, iq = x == Pi ? -ri.y : ri.x;
+        const double jp = y == Pj ? rj.x : rj.y, jq = y == Pj ? -rj.y : rj.x;
+        const double gp = __builtin_fma(jq, pq, jp * pp), gq = __builtin_fma(jq, qq, jp * qp);
+        angle(r + 1, k, x, y, al, be, __builtin_fma(iq, gq, ip * gp));
       }
+      __syncthreads();
     };
-    for (int r = 0; r < kPcaPanel - 1; ++r) {
-      int pa, qa, pb, qb;
-      tournament(kPcaPanel, r, a, pa, qa);
-      tournament(kPcaPanel, r, b, pb, qb);
-      if (wave == 0) angles(pb, qb);
-      if (r > 0) turn_j();
-      __syncthreads();
-      const doublex2 ra = cs[a], rb = cs[b];
-      double pp = G[pa][pb], pq = G[pa][qb], qp = G[qa][pb], qq = G[qa][qb];
-      turn(ra, rb, pp, pq, qp, qq);
-      G[pa][pb] = pp; G[pa][qb] = pq; G[qa][pb] = qp; G[qa][qb] = qq;
-      pj = pa; qj = qa; rj = ra;
-      __syncthreads();
+    for (int r = 0; r < Pairing::kRounds; r += 2) {          // even and odd rounds: the buffers are known at compile time
+      look_ahead(r, m.G[0], m.cs[0]);
+      if (r + 1 < Pairing::kRounds) look_ahead(r + 1, m.G[1], m.cs[1]);
     }
-    turn_j();
-  } else {
-    // column a of the first block meets a, a + 1, ... of the second: rows p_a of J and elements (p_a, p_b) stay in
-    // registers; of the latter the angles read the diagonal
-    double pp = G[a][b], u0 = Jt[a][b], u1 = Jt[a][b + 32];
-    int qj = 0;
-    doublex2 rj = {1.0, 0.0};
-    auto turn_j = [&]() {
-      const double v0 = Jt[qj][b], v1 = Jt[qj][b + 32];
-      Jt[qj][b] = rj.y * u0 + rj.x * v0;
-      Jt[qj][b + 32] = rj.y * u1 + rj.x * v1;
-      u0 = rj.x * u0 - rj.y * v0;
-      u1 = rj.x * u1 - rj.y * v1;
-    };
-    for (int r = 0; r < kPcaBlock; ++r) {
-      const int qa = kPcaBlock + ((a + r) & (kPcaBlock - 1)), qb = kPcaBlock + ((b + r) & (kPcaBlock - 1));
-      if (wave == 0) angles(b, qb);
-      if (r > 0) turn_j();
-      __syncthreads();
+    __builtin_amdgcn_s_setprio(0);
+    return;
+  }
+  // block (a, b) of the matrix: number n of 33 x 16, a row of 33 being rows i and 31 - i of the triangle a <= b
+  const int n = wave < 8 ? tid - 64 : (wave >= 14 ? 448 + tid - 896 : 528);
+  const bool has_block = n < 528;
+  const int ti = n / 33, tj = n - ti * 33;
+  const int a = tj < kPcaBlock - ti ? ti : kPcaBlock - 1 - ti, b = tj < kPcaBlock - ti ? ti + tj : tj - 1;
+  // two pairs of neighbouring entries of the rows of J of pair aj
+  const bool has_j = wave >= 8;
+  const int aj = (tid & 511) >> 4, cj = 2 * (tid & 15);
+  auto j_at = [&](int row, int e) -> doublex2& { return *reinterpret_cast<doublex2*>(&m.Jt[row][cj + kPcaBlock * e]); };
+  doublex2 u[2] = {};
+  double pp = 0.0;
+  // where column p of a pair stays, its row of J and the inner products of such columns stay in registers
+  if (has_j && !ALL) { u[0] = j_at(aj, 0); u[1] = j_at(aj, 1); }
+  if (has_block && !ALL) pp = m.G[0][at(a, b)];
+  const bool next_pair = ALL || b - a == 1 || b - a == kPcaBlock - 1;      // these the first wave looks at
+  __syncthreads();
+  auto round = [&](int r, const double* G, double* H, const doublex2* cs) {
+    if (has_block) {
+      int Pa, Qa, Pb, Qb;
+      Pairing::pair(r, a, Pa, Qa);
+      Pairing::pair(r, b, Pb, Qb);
+      const int o_pp = at(Pa, Pb), o_pq = at(Pa, Qb), o_qp = at(Qa, Pb), o_qq = at(Qa, Qb);
       const doublex2 ra = cs[a], rb = cs[b];
-      double pq = G[a][qb], qp = G[qa][b], qq = G[qa][qb];
+      if (ALL) pp = G[o_pp];
+      double pq = G[o_pq], qp = G[o_qp], qq = G[o_qq];
       turn(ra, rb, pp, pq, qp, qq);
-      if (a == b) G[a][a] = pp;
-      G[a][qb] = pq; G[qa][b] = qp; G[qa][qb] = qq;
-      qj = qa; rj = ra;
-      __syncthreads();
+      if (next_pair) H[o_pp] = pp;
+      if (a != b) H[o_qp] = qp;              // in a pair's own block that is pq
+      H[o_pq] = pq;
+      H[o_qq] = qq;
     }
-    turn_j();
-    Jt[a][b] = u0;
-    Jt[a][b + 32] = u1;
+    if (has_j) {
+      int P, Q;
+      Pairing::pair(r, aj, P, Q);
+      const doublex2 rj = cs[aj];
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        if (ALL) u[e] = j_at(P, e);
+        const doublex2 v = j_at(Q, e), w = u[e];
+        u[e] = rj.x * w - rj.y * v;
+        j_at(Q, e) = rj.y * w + rj.x * v;
+        if (ALL) j_at(P, e) = u[e];
+      }
+    }
+    __syncthreads();
+  };
+  for (int r = 0; r < Pairing::kRounds; r += 2) {
+    round(r, m.G[0], m.G[1], m.cs[0]);
+    if (r + 1 < Pairing::kRounds) round(r + 1, m.G[1], m.G[0], m.cs[1]);
+  }
+  if (has_j && !ALL) { j_at(aj, 0) = u[0]; j_at(aj, 1) = u[1]; }
+}
+
+__global__ __launch_bounds__(1024) void rotate_kernel(PcaDev p, int round, int pairs) {
+  __shared__ PcaPanelLds m;
+  int c0, c1;
+  if (p.done[pair_columns(p, blockIdx.x, round, c0, c1)]) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  {
+    const double* part = p.part + static_cast<size_t>(blockIdx.x) * p.chunks * (kPcaTiles * 256);
+    // all loads in flight at once (a chunk or element past the end: the last one again, not used)
+    constexpr int kEach = (kPcaTiles * 256 + 1023) / 1024;
+    double o[kEach][kPcaChunks];
+#pragma unroll
+    for (int j = 0; j < kEach; ++j)
+#pragma unroll
+      for (int k = 0; k < kPcaChunks; ++k)
+        o[j][k] = part[static_cast<size_t>(min(k, p.chunks - 1)) * (kPcaTiles * 256) + min(tid + 1024 * j, kPcaTiles * 256 - 1)];
+#pragma unroll
+    for (int j = 0; j < kEach; ++j) {
+      const int i = tid + 1024 * j;
+      if (i >= kPcaTiles * 256) break;
+      double v = 0.0;
+#pragma unroll
+      for (int k = 0; k < kPcaChunks; ++k) v += k < p.chunks ? o[j][k] : 0.0;
+      // accumulator e of lane l of a 16 x 16 tile: row 4 e + l / 16, column l % 16
+      const int tile = i >> 8, e = (i >> 6) & 3, l = i & 63;
+      const int ta = tile < 4 ? 0 : (tile < 7 ? 1 : (tile < 9 ? 2 : 3));
+      const int tb = tile - (ta == 0 ? 0 : (ta == 1 ? 3 : (ta == 2 ? 5 : 6)));
+      const int r = ta * 16 + 4 * e + (l >> 4), c = tb * 16 + (l & 15);
+      if (r <= c) m.G[0][r * kPcaPitch + c] = v;      // the tiles on the diagonal hold both orders of an element
+    }
+    for (int i = tid; i < kPcaPanel * kPcaPanel; i += 1024) m.Jt[i >> 6][i & 63] = (i >> 6) == (i & 63) ? 1.0 : 0.0;
   }
   __syncthreads();
+  // what the convergence test needs, before anything is rotated: gamma^2 between the blocks, in a sweep's first round also
+  // inside them, and alpha^2
+  const bool all_pairs = round == 0;
+  double g2 = 0.0, d2 = 0.0;
+  for (int i = tid; i < kPcaPanel * kPcaPanel; i += 1024) {
+    const int r = i >> 6, c = i & 63;
+    const double v = r <= c ? m.G[0][r * kPcaPitch + c] : 0.0;
+    if (r < c && (all_pairs || (r < kPcaBlock && c >= kPcaBlock))) g2 = __builtin_fma(v, v, g2);
+    if (r == c) d2 = __builtin_fma(v, v, d2);
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) { g2 += __shfl_down(g2, o, 64); d2 += __shfl_down(d2, o, 64); }
+  if (lane == 0) { m.red[0][wave] = g2; m.red[1][wave] = d2; }
+  __syncthreads();
+  if (tid == 1023) {                     // not in the wave of the angles
+    double a = 0.0, b = 0.0;
+    for (int w = 0; w < 16; ++w) { a += m.red[0][w]; b += m.red[1][w]; }
+    p.gamma2[static_cast<size_t>(round) * pairs + blockIdx.x] = a;
+    if (all_pairs) p.diag2[blockIdx.x] = b;
+  }
+  if (all_pairs) rotate_rounds<true>(m);
+  else rotate_rounds<false>(m);
+  __syncthreads();
   double* out = p.J + static_cast<size_t>(blockIdx.x) * (kPcaPanel * kPcaPanel);
-  for (int i = tid; i < kPcaPanel * kPcaPanel; i += 1024) out[i] = Jt[i >> 6][i & 63];
+  for (int i = tid; i < kPcaPanel * kPcaPanel; i += 1024) out[i] = m.Jt[i >> 6][i & 63];
 }
 
 // Columns c' of a pair <- sum over c of J[c][c'] column c, for 64 entries of Z: a wave owns 16 entries of all 64
@@ -433,8 +529,8 @@ static int pca_blocks_device(const void* X_dev, int n_cal, int D, int Db, int64_
   p.n_pad = (n_cal + 63) / 64 * 64;
   p.pitch = p.n_pad + Db;
   p.Db = Db;
-  // rows of a chunk: enough workgroups for the chip, no more than eight partial sums per pair
-  const int want = std::max(1, std::min(8, 512 / pairs));
+  // rows of a chunk: enough workgroups for the chip, no more than kPcaChunks partial sums per pair
+  const int want = std::max(1, std::min(kPcaChunks, 512 / pairs));
   p.chunk_rows = ((p.n_pad / 64 + want - 1) / want) * 64;
   p.chunks = (p.n_pad + p.chunk_rows - 1) / p.chunk_rows;
   const size_t sizes[] = {static_cast<size_t>(D) * p.pitch * 8, static_cast<size_t>(pairs) * p.chunks * kPcaTiles * 256 * 8,
