@@ -274,7 +274,7 @@ int rosaq_stream_probe(const void* src_dev, size_t src_bytes, const void* shared
 /* Tuning aid for benchmarks; affects later rosaq_linear* calls in this process.
  *   "mt", "nt"  16-row / 16-channel MFMA tiles per workgroup (0 = heuristic, 1, 2, 4; nt also 3 and 6
  *             for low-bit layers with mt >= 2)
- *   "rot_mt", "rot_nt", "rot_depth"  the same three knobs for the dense-rotation launch
+ *   "rot_mt", "rot_nt", "rot_depth"  the same three knobs for the dense-rotation launch (rot_nt also 3 and 5, not 6)
  *   "wpb"     waves per workgroup splitting the contraction (0 = default, 4, 8, 16; variants that
  *             would not fit the register file fall back to 8)
  *   "depth"   units (a group, or four fp16 k-steps) a wave keeps in flight (0 = default, 1-4; clamped to

@@ -119,7 +119,7 @@ template <int BITS, int MT, int NT, int WPB, int DEPTH>
 __global__ __launch_bounds__(WPB * 64, (DEPTH == 1 && MT * NT <= 4 ? (MT == 4 ? 2 : 4) : 1))
 void gemm_kernel(GemmDev p) {
   // the waves' partial tiles meet in LDS, in one pass or (large tiles) in two halves
-  constexpr int kRedPasses = WPB * NT * MT > 128 ? 2 : 1;
+  constexpr int kRedPasses = WPB * NT * MT <= 128 ? 1 : (NT % 2 == 0 ? 2 : NT);
   constexpr int kRedNT = NT / kRedPasses;
   static_assert(NT % kRedPasses == 0, "tile split");
   __shared__ float4 red[WPB][kRedNT * MT][64];
@@ -726,6 +726,13 @@ static int clamp_depth(int mt, int nt, int wpb, int depth) {
 
 static GemmShape pick_unsplit(int M, int ntiles, int D, int bits, const GemmTune& tune);
 
+// Rounds of a launch whose workgroups have a compute unit each, by the fullest XCD (32 of them) or, with more than four row
+// groups, shader engine (8): see prefers_wide.
+static int64_t full_rounds(int chunks, int mgroups) {
+  const int64_t cx = (chunks + 7) / 8;
+  return mgroups <= kMapRows ? (cx * mgroups + 31) / 32 : (cx * ((mgroups + 3) / 4) + 7) / 8;
+}
+
 // Split-K across workgroups (launches of up to 64 rows).  Measured on the 7B / 13B shapes at
 // M = 64, a split launch loses wherever the unsplit one already fills the chip: a 4096 x 4096 layer
 // takes 8.6 us as 256 tiles of 32 x 32 and 12.4 us as 64 tiles of 64 x 64 cut in 2, 3 or 4, because
@@ -832,11 +839,24 @@ static GemmShape pick_unsplit(int M, int ntiles, int D, int bits, const GemmTune
     };
     double best_alt = cost(s.mt, s.nt) * 0.97;
     if (cost(2, 3) < best_alt) { best_alt = cost(2, 3); s.mt = 2; s.nt = 3; }
-    if (mtiles >= 3 && cost(4, 3) < best_alt) { s.mt = 4; s.nt = 3; }
+    if (mtiles >= 3 && cost(4, 3) < best_alt) { best_alt = cost(4, 3); s.mt = 4; s.nt = 3; }
+    // 64 x 80: where it makes one round, counted on the fullest XCD or shader engine, of what is a good one and a half with 64 x
+    // 48.  Rotation with its copy launch, us, against 64 x 48 (of so many workgroups): 5120 at 256 rows 25.7 / 33.0 (428), 2560
+    // at 512 18.8 / 21.3 (432), 4992 at 202 30.3 / 34.4 (416), 1280 at 1024 15.5 / 17.0 (432), 6400 at 137 44.0 / 47.3 (402), 4736 at
+    // 254 31.5 / 33.9 (396).  With fewer the two rounds overlap as well: 4608 at 254 36.3 / 33.3 (384), 5632 at 163 39.2 /
+    // 39.2 (354); with long contractions the inflow is all: 9472 at 128 rows 77.2 / 76.0; where an XCD gets 33 workgroups
+    // it loses: 6656 at 150 rows 78 / 58.  (Low-bit layers gain nothing: their 80-channel tile spills, and 13824 -> 5120 at 256
+    // rows takes 54.4 us against 52.3.)
+    const int narrow = ((ntiles + 2) / 3) * ((mtiles + 3) / 4);
+    if (mtiles >= 3 && D <= 8192 && narrow >= 392 && full_rounds((ntiles + 4) / 5, (mtiles + 3) / 4) == 1 && cost(4, 5) < best_alt) {
+      s.mt = 4;
+      s.nt = 5;
+    }
   }
   if (tune.mt == 1 || tune.mt == 2 || tune.mt == 4) s.mt = tune.mt;
   if (tune.nt == 1 || tune.nt == 2 || tune.nt == 4) s.nt = tune.nt;
   if ((tune.nt == 3 || tune.nt == 6) && bits != 16 && s.mt >= 2) s.nt = tune.nt;
+  if (tune.nt == 5 && bits == 16 && s.mt == 4) s.nt = 5;
   if (tune.nt == 3 && bits == 16 && s.mt >= 2) s.nt = 3;
   s.wpb = 8;
   if (tune.wpb == 16 && s.mt * s.nt <= 2) s.wpb = 16;   // 16 waves leave 128 registers per lane
@@ -954,6 +974,7 @@ static int launch_gemm_shape(const GemmArgs& a, const GemmShape& sh, void* strea
   ROSAQ_WIDE(4)
   ROSAQ_WIDE(3)
   ROSAQ_CASE(16, 2, 3, 8) ROSAQ_CASE(16, 4, 3, 8)
+  if (bits == 16 && sh.mt == 4 && sh.nt == 5) return launch_gemm_t<16, 4, 5, 8, 1>(d, st);
 #undef ROSAQ_WIDE
 #undef ROSAQ_CASES
 #undef ROSAQ_CASE
@@ -981,7 +1002,7 @@ bool prefers_wide(int M, int ntiles, int D, int K, int bits, const GemmTune& tun
   const GemmShape s = pick_unsplit(M, ntiles, D, bits, tune);
   auto rounds = [](int chunks, int mgroups, bool alone) {
     const int64_t cx = (chunks + 7) / 8;
-    return static_cast<double>(mgroups <= kMapRows || !alone ? (cx * mgroups + 31) / 32 : (cx * ((mgroups + 3) / 4) + 7) / 8);
+    return static_cast<double>(alone ? full_rounds(chunks, mgroups) : (cx * mgroups + 31) / 32);
   };
   const double units = D / 128, salient = K / 128;
   const double wide = rounds((ntiles + kWideChannels / 16 - 1) / (kWideChannels / 16), (M + kWideRows - 1) / kWideRows, true) *
@@ -1021,7 +1042,7 @@ int launch_gemm(const GemmArgs& a, const GemmTune& tune, void* stream) {
     const GemmShape s0 = shape(t0);
     // 48-channel tiles become 32 x 96 ones (gate + up of a 7B MLP at M = 64: 26.9 us against 28.7 us
     // as 64 x 64 tiles, which need a second round of workgroups)
-    if (s0.nt == 3) { t0.nt = 6; t0.mt = 2; }
+    if (s0.nt == 3 && bits != 16) { t0.nt = 6; t0.mt = 2; }   // (all-fp16 layers have no 96-channel tiles)
     else if (s0.nt & 1) t0.nt = 2;
   }
   int rc = launch_gemm_shape(a, shape(t0), stream);
@@ -1031,7 +1052,7 @@ int launch_gemm(const GemmArgs& a, const GemmTune& tune, void* stream) {
     if (a.swiglu) {
       t1.splits = 1;
       const GemmShape s1 = shape(t1);
-      if (s1.nt == 3) { t1.nt = 6; t1.mt = 2; }
+      if (s1.nt == 3 && bits != 16) { t1.nt = 6; t1.mt = 2; }
       else if (s1.nt & 1) t1.nt = 2;
     }
     rc = launch_gemm_shape(a, shape(t1), stream);
