@@ -7,8 +7,15 @@ import torch
 from . import binding as B
 
 
+# The current stream's pointer alone takes 0.35 us, a Stream object made for it 2.7: a quarter of what issuing a small call
+# costs (one of four rows of a 1024 x 1024 layer 11.1 -> 7.9 us).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def current_stream_ptr() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    if _raw_stream is None or not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def alloc_workspace(p: B.Packed, M: int) -> torch.Tensor:
