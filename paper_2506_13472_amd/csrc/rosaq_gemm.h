@@ -18,26 +18,35 @@ __device__ __forceinline__ floatx4 mfma16(half8 a, half8 b, floatx4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
 }
 
-// (v & mask) | magic in one VALU op.  The compiler splits this into v_and + v_or with
-// two literals; VOP3 on gfx9 takes no literal, so the mask goes in an SGPR and the
-// magic constant in a VGPR.
+// (v & mask) | magic in one VALU op.  The compiler splits this into v_and + v_or with two literals; VOP3 on gfx9 takes no
+// literal, so the mask goes in an SGPR and the magic constant in a VGPR, as constants that the compiler cannot see through,
+// and it joins the two itself.  ASM: as one instruction of assembly, which pins its place between the MFMAs
+// (wide_gemm_kernel is 1 % faster so) but which the compiler does not count when it keeps vector writes away from the
+// registers of an MFMA under way: gemm_kernel's INT3 64 x 48 tile got one into the register that the MFMA in front of it reads.
+template <bool ASM>
 __device__ __forceinline__ uint32_t and_or(uint32_t v, uint32_t mask, uint32_t magic) {
-  uint32_t r;
-  asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(r) : "v"(v), "s"(mask), "v"(magic));
-  return r;
+  if constexpr (ASM) {
+    uint32_t r;
+    asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(r) : "v"(v), "s"(mask), "v"(magic));
+    return r;
+  }
+  asm("" : "+s"(mask));
+  asm("" : "+v"(magic));
+  return (v & mask) | magic;
 }
 
 // Eight 4-bit codes of one dword -> eight fp16 values (q - z), exactly.
 // 0x6400 | q is the fp16 number 1024 + q; 0x6400 | (q << 4) is 1024 + 16 q.
 // c_lo = -(1024 + z), c_hi = -(64 + z): both subtractions are exact in fp16.
+template <bool ASM = false>
 __device__ __forceinline__ half8 dequant4(uint32_t v, half2v c_lo, half2v c_hi) {
   const uint32_t kMagic = 0x64006400u;
   const half2v sixteenth = {(_Float16)0.0625f, (_Float16)0.0625f};
   const uint32_t v8 = v >> 8;
-  const half2v h0 = as_h2(and_or(v, 0x000f000fu, kMagic)) + c_lo;
-  const half2v h1 = __builtin_elementwise_fma(as_h2(and_or(v, 0x00f000f0u, kMagic)), sixteenth, c_hi);
-  const half2v h2 = as_h2(and_or(v8, 0x000f000fu, kMagic)) + c_lo;
-  const half2v h3 = __builtin_elementwise_fma(as_h2(and_or(v8, 0x00f000f0u, kMagic)), sixteenth, c_hi);
+  const half2v h0 = as_h2(and_or<ASM>(v, 0x000f000fu, kMagic)) + c_lo;
+  const half2v h1 = __builtin_elementwise_fma(as_h2(and_or<ASM>(v, 0x00f000f0u, kMagic)), sixteenth, c_hi);
+  const half2v h2 = as_h2(and_or<ASM>(v8, 0x000f000fu, kMagic)) + c_lo;
+  const half2v h3 = __builtin_elementwise_fma(as_h2(and_or<ASM>(v8, 0x00f000f0u, kMagic)), sixteenth, c_hi);
   return half8{h0.x, h0.y, h1.x, h1.y, h2.x, h2.y, h3.x, h3.y};
 }
 
@@ -52,6 +61,7 @@ __device__ __forceinline__ Dq3 dq3_consts(_Float16 z) {
   const _Float16 a = -(z + (_Float16)1024.0f), b = -(z + (_Float16)128.0f), c = -(z + (_Float16)16.0f);
   return Dq3{half2v{a, a}, half2v{b, b}, half2v{c, c}};
 }
+template <bool ASM = false>
 __device__ __forceinline__ half8 dequant3(uint32_t w0, uint32_t w1, uint32_t w2, int t, const Dq3& k) {
   const uint32_t kMagic = 0x64006400u;
   const half2v eighth = {(_Float16)0.125f, (_Float16)0.125f};
@@ -65,13 +75,13 @@ __device__ __forceinline__ half8 dequant3(uint32_t w0, uint32_t w1, uint32_t w2,
       const int s = P % 5;
       const uint32_t src = s < 3 ? w[P / 5] : w[P / 5] >> 9;
       const int o = s < 3 ? s : s - 3;
-      if (o == 0) h[i] = as_h2(and_or(src, 0x00070007u, kMagic)) + k.c0;
-      else if (o == 1) h[i] = __builtin_elementwise_fma(as_h2(and_or(src, 0x00380038u, kMagic)), eighth, k.c3);
-      else h[i] = __builtin_elementwise_fma(as_h2(and_or(src, 0x01c001c0u, kMagic)), sixty4th, k.c6);
+      if (o == 0) h[i] = as_h2(and_or<ASM>(src, 0x00070007u, kMagic)) + k.c0;
+      else if (o == 1) h[i] = __builtin_elementwise_fma(as_h2(and_or<ASM>(src, 0x00380038u, kMagic)), eighth, k.c3);
+      else h[i] = __builtin_elementwise_fma(as_h2(and_or<ASM>(src, 0x01c001c0u, kMagic)), sixty4th, k.c6);
     } else {
-      uint32_t r = and_or(w0 >> 15, 0x00010001u, kMagic);
-      r = and_or(w1 >> 14, 0x00020002u, r);
-      r = and_or(w2 >> 13, 0x00040004u, r);
+      uint32_t r = and_or<ASM>(w0 >> 15, 0x00010001u, kMagic);
+      r = and_or<ASM>(w1 >> 14, 0x00020002u, r);
+      r = and_or<ASM>(w2 >> 13, 0x00040004u, r);
       h[i] = as_h2(r) + k.c0;
     }
   }

@@ -249,10 +249,10 @@ __global__ __launch_bounds__(kWaves * 64, 1) void wide_gemm_kernel(GemmDev p) {
     auto convert = [&](const Codes& cc, int t, int nt) {
       const _Float16 z = as_h2(cc.sz[nt]).y;
       if constexpr (BITS == 3) {
-        return dequant3(cc.cw[nt][0], cc.cw[nt][1], cc.cw[nt][2], t, dq3_consts(z));
+        return dequant3<true>(cc.cw[nt][0], cc.cw[nt][1], cc.cw[nt][2], t, dq3_consts(z));
       } else {
         const _Float16 clo = -(z + (_Float16)1024.0f), chi = -(z + (_Float16)64.0f);
-        return dequant4(cc.cw[nt][t], half2v{clo, clo}, half2v{chi, chi});
+        return dequant4<true>(cc.cw[nt][t], half2v{clo, clo}, half2v{chi, chi});
       }
     };
     half8 b[2][NT];
