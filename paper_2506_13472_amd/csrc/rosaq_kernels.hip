@@ -618,7 +618,16 @@ __global__ __launch_bounds__(256) void rotate_headwise_kernel(
   const int mt = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // the eight column tiles of a head share x_h: keep them on one XCD (id % 8)
   const int h = (blockIdx.x & 7) + 8 * (blockIdx.x >> 6), ct = (blockIdx.x >> 3) & 7, mb = blockIdx.y;
-  if (h >= H) return;
+  // tickets of the GEMM launch that follows in this call, spread over all of the launch's threads, those without a head too
+  auto clear = [&]() {
+    for (int i = (blockIdx.y * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x; i < zero_count;
+         i += gridDim.x * gridDim.y * blockDim.x)
+      zero_ptr[i] = 0u;
+  };
+  if (h >= H) {
+    clear();
+    return;
+  }
   const int m = min(mb * kMBlock + mt * 16 + static_cast<int>(lane & 15), M - 1);   // rows past M: the last one again
   uint4 a[4], b[4];
   const uint4* const q0 = qh + static_cast<size_t>(h * 8 + ct) * 256;
@@ -636,10 +645,7 @@ __global__ __launch_bounds__(256) void rotate_headwise_kernel(
   const unsigned off = static_cast<unsigned>(p >> 5) * 2048u + (4 * (lane >> 4) + 16 * ((p >> 3) & 3)) * 8 + (p & 7);
 #pragma unroll
   for (int i = 0; i < 4; ++i) (tile0 + i * 8)[off] = static_cast<_Float16>(acc[i]);
-  // tickets of the GEMM launch that follows in this call, spread over the launch's threads
-  for (int i = (blockIdx.y * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x; i < zero_count;
-       i += gridDim.x * gridDim.y * blockDim.x)
-    zero_ptr[i] = 0u;
+  clear();
 }
 
 // Measurement aid: a pure read stream.  Every wave reads `w_kib` KiB of its own from
