@@ -1,6 +1,8 @@
 """Builds librosaq.so (host packer + C ABI + gfx950 kernels) in-tree with hipcc."""
 from __future__ import annotations
 
+import functools
+import heapq
 import os
 import re
 import subprocess
@@ -70,6 +72,83 @@ def check_counted_waits(assembly: str) -> int:
     return len(loops)
 
 
+# A vector, LDS or memory instruction may touch the registers of an MFMA under way only after so many wait states (one per
+# instruction, n + 1 for an s_nop n): a matrix instruction's result, whatever it is that touches it, and the sum that it
+# starts from, if a vector instruction writes there.  The hardware does not wait by itself.  The compiler counts for
+# the code that it makes, but it counts past a join of branches along one of the ways only, and inline assembly not at
+# all.  So the assembly is searched along every way.  The figures are what the compiler keeps in straight code.
+_MFMA_STATES = {            # (vector instruction at the result, LDS / memory instruction at it, vector write to the sum)
+    "v_mfma_f32_16x16x32_f16": (8, 8, 3),
+    "v_mfma_f64_16x16x4_f64": (19, 18, 0),
+}
+_REGISTERS = re.compile(r"\b([va])(?:\[(\d+):(\d+)\]|(\d+)\b)")
+_TOUCHES = ("v_", "ds_", "global_", "buffer_", "flat_", "scratch_")
+
+
+def _registers(operands: str) -> frozenset:
+    return frozenset((kind, i) for kind, lo, hi, one in _REGISTERS.findall(operands)
+                     for i in range(int(one or lo), int(one or hi) + 1))
+
+
+def check_mfma_distance(assembly: str) -> int:
+    """The number of MFMAs found; raises where the way from one to an instruction that touches its registers is short."""
+    program, labels = [], {}
+    for line in assembly.splitlines():
+        text = line.split(";")[0].split("//")[0].strip()
+        if text.endswith(":"):
+            labels[text[:-1]] = len(program)
+        elif text and not text.startswith("."):
+            op, _, operands = text.replace("\t", " ").partition(" ")
+            program.append((op, operands.strip()))
+
+    def successors(i):
+        op, operands = program[i]
+        if op == "s_branch":
+            return (labels[operands],)
+        if op == "s_endpgm":
+            return ()
+        if op in ("s_setpc_b64", "s_swappc_b64"):
+            raise RuntimeError(f"{op}: a way that cannot be followed")
+        after = (i + 1,) if i + 1 < len(program) else ()
+        return after + (labels[operands],) if op.startswith("s_cbranch") else after
+
+    @functools.lru_cache(maxsize=None)
+    def uses(i):                                   # (all registers, registers that a vector instruction writes)
+        op, operands = program[i]
+        if not op.startswith(_TOUCHES):
+            return frozenset(), frozenset()
+        written = operands if "swap" in op else operands.split(", ")[0]
+        return _registers(operands), _registers(written) if op.startswith("v_") else frozenset()
+
+    found = 0
+    for i, (op, operands) in enumerate(program):
+        if not op.startswith("v_mfma"):
+            continue
+        if op not in _MFMA_STATES:
+            raise RuntimeError(f"{op}: no wait states on file")
+        found += 1
+        vector, memory, write = _MFMA_STATES[op]
+        parts = [_registers(t) for t in operands.split(", ")[:4]]
+        result, summand = parts[0], parts[3]
+        seen, ways = set(), [(0, j) for j in successors(i)]
+        while ways:
+            states, j = heapq.heappop(ways)
+            if j in seen or states >= max(vector, memory, write):
+                continue
+            seen.add(j)
+            other, other_operands = program[j]
+            touched, written = uses(j)
+            if other.startswith("v_mfma"):         # the sum of the next product may be this one's result; its factors may not
+                touched, written = frozenset().union(*(_registers(t) for t in other_operands.split(", ")[1:3])), frozenset()
+            need = vector if other.startswith("v_") else memory
+            if (states < need and touched & result) or (states < write and written & summand):
+                raise RuntimeError(f"{states} wait states between {op} {operands} and {other} {other_operands}")
+            more = 1 + int(other_operands, 0) if other == "s_nop" else 1
+            for k in successors(j):
+                heapq.heappush(ways, (states + more, k))
+    return found
+
+
 def _compile_hip(src: str, obj: str, common, verbose: bool) -> None:
     cmd = [hipcc(), "-x", "hip", "--offload-arch=gfx950", "-save-temps=obj",
            "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -93,6 +172,7 @@ def _compile_hip(src: str, obj: str, common, verbose: bool) -> None:
         with open(os.path.join(os.path.dirname(obj), f), "r", errors="replace") as fh:
             text = fh.read()
         n += len(_PK_F32.findall(text))
+        check_mfma_distance(text)
         if stem == "rosaq_wide" and check_counted_waits(text) != 3:      # INT4, INT3 and fp16
             raise RuntimeError(f"{src}: the counted waits of the LDS ring are not where they are looked for")
     print(f"{os.path.basename(src)}: device pass for gfx950 holds {n} packed-fp32 instructions", flush=True)

@@ -21,8 +21,9 @@ __device__ __forceinline__ floatx4 mfma16(half8 a, half8 b, floatx4 c) {
 // (v & mask) | magic in one VALU op.  The compiler splits this into v_and + v_or with two literals; VOP3 on gfx9 takes no
 // literal, so the mask goes in an SGPR and the magic constant in a VGPR, as constants that the compiler cannot see through,
 // and it joins the two itself.  ASM: as one instruction of assembly, which pins its place between the MFMAs
-// (wide_gemm_kernel is 1 % faster so) but which the compiler does not count when it keeps vector writes away from the
-// registers of an MFMA under way: gemm_kernel's INT3 64 x 48 tile got one into the register that the MFMA in front of it reads.
+// (wide_gemm_kernel is 1 % faster so) but which the compiler does not count when it keeps vector writes away from the sum
+// that an MFMA under way starts from: gemm_kernel's INT3 64 x 48 tile got one there.  So the build searches the assembly
+// for such writes and fails on one (check_mfma_distance in build.py).
 template <bool ASM>
 __device__ __forceinline__ uint32_t and_or(uint32_t v, uint32_t mask, uint32_t magic) {
   if constexpr (ASM) {

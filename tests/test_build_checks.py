@@ -37,3 +37,62 @@ def test_counted_waits_of_the_built_kernel():
         pytest.skip("no assembly kept from the build")
     with open(kept[0]) as f:
         assert BU.check_counted_waits(f.read()) == 3
+
+
+_MFMA = "\tv_mfma_f32_16x16x32_f16 v[0:3], v[4:7], v[8:11], v[{}]\n".format
+
+
+def _states(n):
+    return f"\ts_nop {n - 1}\n" if n else ""
+
+
+@pytest.mark.parametrize("touch,need", [("v_add_f32_e32 v20, v3, v21", 8), ("v_mov_b32_e32 v0, 0", 8), ("v_cvt_f16_f32_e32 v9, v1", 8),
+                                        ("global_store_dwordx4 v30, v[0:3], s[0:1]", 8), ("ds_write_b64 v30, v[2:3]", 8),
+                                        ("v_mfma_f32_16x16x32_f16 v[12:15], v[0:3], v[8:11], 0", 8),
+                                        (";;#ASMSTART\n\tv_and_or_b32 v2, v20, s3, v21\n\t;;#ASMEND", 8),
+                                        ("v_mov_b32_e32 v17, 0", 3), ("v_swap_b32 v20, v17", 3)])
+def test_mfma_distance_in_straight_code(touch, need):
+    end = "\n\ts_endpgm\n"
+    assert BU.check_mfma_distance(_MFMA("16:19") + _states(need) + "\t" + touch + end) >= 1
+    with pytest.raises(RuntimeError):
+        BU.check_mfma_distance(_MFMA("16:19") + _states(need - 1) + "\t" + touch + end)
+
+
+def test_mfma_distance_ignores_what_may_follow_at_once():
+    for op in ("v_mov_b32_e32 v4, 0", "v_add_f32_e32 v20, v17, v21", "v_mfma_f32_16x16x32_f16 v[0:3], v[4:7], v[8:11], v[0:3]",
+               "s_mov_b32 s2, s3", "v_add_f32_e32 v12, a0, a1"):
+        assert BU.check_mfma_distance(_MFMA("16:19") + "\t" + op + "\n\ts_endpgm\n") >= 1
+
+
+def test_mfma_distance_along_every_way():
+    """The shorter of two ways to a join counts, and the way round a loop."""
+    def join(states):
+        return (_MFMA("0:3") + "\ts_cbranch_scc1 .LBB0_2\n" + _states(states) + ".LBB0_1:\n" + "\tv_add_f32_e32 v20, v0, v0\n\ts_endpgm\n"
+                ".LBB0_2:\n\ts_nop 7\n\ts_nop 7\n\ts_branch .LBB0_1\n")
+    assert BU.check_mfma_distance(join(7)) == 1                   # the branch itself is one
+    with pytest.raises(RuntimeError):
+        BU.check_mfma_distance(join(6))
+    loop = ".LBB1_0:\n\tv_cvt_f16_f32_e32 v20, v0\n\ts_nop 7\n{}" + _MFMA("0:3") + "{}\ts_cbranch_scc0 .LBB1_0\n\ts_endpgm\n"
+    assert BU.check_mfma_distance(loop.format("", _states(7))) == 1
+    with pytest.raises(RuntimeError):
+        BU.check_mfma_distance(loop.format(_states(8), _states(6)))
+
+
+def test_mfma_distance_takes_no_way_or_instruction_on_trust():
+    for text in (_MFMA("0:3") + "\ts_setpc_b64 s[30:31]\n", "\tv_mfma_f32_32x32x16_f16 v[0:15], v[16:19], v[20:23], v[0:15]\n\ts_endpgm\n"):
+        with pytest.raises(RuntimeError):
+            BU.check_mfma_distance(text)
+    f64 = "\tv_mfma_f64_16x16x4_f64 a[0:7], v[4:5], v[8:9], a[0:7]\n{}\tv_accvgpr_read_b32 v1, a7\n\ts_endpgm\n"
+    assert BU.check_mfma_distance(f64.format(_states(19))) == 1
+    with pytest.raises(RuntimeError):
+        BU.check_mfma_distance(f64.format(_states(18)))
+
+
+@pytest.mark.parametrize("source,least", [("rosaq_kernels", 1000), ("rosaq_wide", 100), ("rosaq_rotate", 100), ("rosaq_pca", 10),
+                                          ("rosaq_quant", 10)])
+def test_mfma_distance_of_the_built_kernels(source, least):
+    kept = glob.glob(os.path.join(BU.OBJ, source + "-hip-amdgcn*.s"))
+    if not kept:
+        pytest.skip("no assembly kept from the build")
+    with open(kept[0], errors="replace") as f:
+        assert BU.check_mfma_distance(f.read()) >= least
