@@ -288,7 +288,8 @@ int rosaq_stream_probe(const void* src_dev, size_t src_bytes, const void* shared
  *             per workgroup in the head-wise rotation): 0 = heuristic, 1 = never,
  *             2 = every launch of more than 64 rows
  *   "stages"  3 = whole call (default), 1 = prologue kernels only, 2 = main GEMM only
- *             (2 reuses the rotated activations a previous call left in the workspace)
+ *             (2 reuses the rotated activations a previous call left in the workspace; in front of a split
+ *             main GEMM it runs a small launch that clears the tickets)
  * For benchmarks and tests only: the settings are process-wide and not synchronised, so no other
  * thread may be inside a rosaq_linear* call while they change, and "stages" other than 3 makes
  * every later call skip part of its work while still returning ROSAQ_OK. */

@@ -421,10 +421,13 @@ static int run_call(const rosaq_packed_t* const* ps, int count, const void* x_de
                     int64_t ldx, void* const* ys, const int64_t* ldys, char* ws, size_t ws_bytes,
                     const WsPlan& w, void* hip_stream, bool swiglu = false) {
   const GemmArgs a = main_gemm(ps, count, plan_io(*ps[0], w, ws, ws_bytes), M, ys, ldys, swiglu);
-  if (g_tune_stages & 1) {
-    const int rc = run_prologue(ps[0], w, x_dev, M, ldx, ws, ws_bytes, ticket_words(a, 2 * kTicketsPerLaunch), hip_stream);
-    if (rc != ROSAQ_OK) return rc;
-  }
+  const int n_tickets = ticket_words(a, 2 * kTicketsPerLaunch);
+  int rc = ROSAQ_OK;
+  if (g_tune_stages & 1)
+    rc = run_prologue(ps[0], w, x_dev, M, ldx, ws, ws_bytes, n_tickets, hip_stream);
+  else if (n_tickets)    // what an earlier call left in the workspace are activations; its tickets it may not have used
+    rc = launch_clear(ws + w.tickets, n_tickets, hip_stream);
+  if (rc != ROSAQ_OK) return rc;
   if (!(g_tune_stages & 2)) return ROSAQ_OK;
   return launch_gemm(a, g_tune, hip_stream);
 }

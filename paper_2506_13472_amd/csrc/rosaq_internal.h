@@ -129,6 +129,7 @@ int launch_gather(const void* x, int64_t ldx, int M, int D, const int32_t* perm_
 int launch_rotate_headwise(const void* x, int64_t ldx, int M, int D, const void* qh,
                            const int32_t* pos_dev, void* xf, void* zero_ptr, int zero_count,
                            void* stream);
+int launch_clear(void* words, int count, void* stream);   // count >= 1 32-bit words to zero
 // the same for many rows (rosaq_rotate.hip); `perm_dev` is the inverse of `pos_dev`
 int launch_rotate_rows(const void* x, int64_t ldx, int M, int D, const void* qh, const int32_t* perm_dev,
                        const int32_t* pos_dev, void* xf, void* zero_ptr, int zero_count, void* stream);

@@ -648,6 +648,11 @@ __global__ __launch_bounds__(256) void rotate_headwise_kernel(
   clear();
 }
 
+// The tickets of a split GEMM launch without a launch in front of it (tuning aid "stages" = 2).
+__global__ __launch_bounds__(256) void clear_kernel(unsigned* p, int count) {
+  for (int i = blockIdx.x * 256 + threadIdx.x; i < count; i += gridDim.x * 256) p[i] = 0u;
+}
+
 // Measurement aid: a pure read stream.  Every wave reads `w_kib` KiB of its own from
 // `src` (1 KiB per load, eight loads in flight) and then `x_kib` KiB from a buffer
 // shared by all workgroups, and keeps nothing.  It shows what the memory system
@@ -1091,6 +1096,13 @@ int launch_gather(const void* x, int64_t ldx, int M, int D, const int32_t* perm_
                      perm_dev, static_cast<uint4*>(xf), static_cast<unsigned*>(zero_ptr), zero_count);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? ROSAQ_OK : hip_fail(e, "gather_kernel launch");
+}
+
+int launch_clear(void* words, int count, void* stream) {
+  hipLaunchKernelGGL(clear_kernel, dim3((count + 255) / 256), dim3(256), 0, static_cast<hipStream_t>(stream),
+                     static_cast<unsigned*>(words), count);
+  const hipError_t e = hipGetLastError();
+  return e == hipSuccess ? ROSAQ_OK : hip_fail(e, "clear_kernel launch");
 }
 
 int launch_rotate_headwise(const void* x, int64_t ldx, int M, int D, const void* qh,

@@ -51,3 +51,32 @@ def test_headwise_rotation_clears_every_ticket(M, D, N, nt):
 def test_other_prologues_clear_every_ticket(mode, M, rot_splits):
     print(f"case tickets mode={mode} M={M} rot_splits={rot_splits}", flush=True)
     _split_on_dirty_workspace(mode, M, 256, 5200, 1, 2, rot_splits)
+
+
+@pytest.mark.parametrize("mode,first", [(O.MODE_HEADWISE, 3), (O.MODE_NONE, 1), (O.MODE_FULL, 3)])
+def test_main_gemm_alone_splits_on_what_an_unsplit_call_left(mode, first):
+    """Tuning key "stages" = 2 takes the activations from the workspace, and nothing else."""
+    print(f"case tickets stages=2 mode={mode} first={first}", flush=True)
+    M, D, N = 40, 512, 200
+    lay, Q, lam = make_case(811, M, D, N, 300, mode)
+    ref = O.pack(lay["W"], Q, lam, 128, 4, mode)
+    p = B.rosaq_pack_weights(lay["W"], Q, lam, 128, 4, mode)
+    x = torch.from_numpy(lay["x"]).cuda()
+    y = torch.full((M, N), 3.0, dtype=torch.float16, device="cuda")
+    ws = T.alloc_workspace(p, M)
+    ws.fill_(DIRTY)
+    try:
+        B.rosaq_tune("stages", first)
+        B.rosaq_tune("splits", 1)
+        T.linear(p, x, y, ws)
+        y.fill_(3.0)
+        B.rosaq_tune("stages", 2)
+        B.rosaq_tune("splits", 3)
+        for _ in range(2):
+            T.linear(p, x, y, ws)
+        torch.cuda.synchronize()
+    finally:
+        B.rosaq_tune("stages", 3)
+        _reset()
+    check_output(y.cpu().numpy(), lay["x"], Q, ref)
+    p.free()
