@@ -859,7 +859,10 @@ static GemmShape pick_unsplit(int M, int ntiles, int D, int bits, const GemmTune
     // it loses: 6656 at 150 rows 78 / 58.  (Low-bit layers gain nothing: their 80-channel tile spills, and 13824 -> 5120 at 256
     // rows takes 54.4 us against 52.3.)
     const int narrow = ((ntiles + 2) / 3) * ((mtiles + 3) / 4);
-    if (mtiles >= 3 && D <= 8192 && narrow >= 392 && full_rounds((ntiles + 4) / 5, (mtiles + 3) / 4) == 1 && cost(4, 5) < best_alt) {
+    // 80 channels go with 64 rows only: not where other rows are forced.
+    const bool rows64 = tune.mt != 1 && tune.mt != 2;
+    if (rows64 && mtiles >= 3 && D <= 8192 && narrow >= 392 && full_rounds((ntiles + 4) / 5, (mtiles + 3) / 4) == 1 &&
+        cost(4, 5) < best_alt) {
       s.mt = 4;
       s.nt = 5;
     }

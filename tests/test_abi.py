@@ -302,6 +302,18 @@ def test_launch_shape_of_the_named_workloads():
     assert B.ERR_NAMES[e.value.code] == "ARG"
 
 
+@pytest.mark.parametrize("rows,shapes", [(0, 3 * [(4, 5)]), (4, 3 * [(4, 5)]), (2, [(2, 3), (2, 3), (2, 4)])])
+def test_forced_rows_keep_a_tile_that_a_kernel_exists_for(rows, shapes):
+    """The 80-channel tiles that the rule takes for all-fp16 layers exist with 64 rows only; with 32 forced rows the
+    choice is the one among the other tiles."""
+    try:
+        B.rosaq_tune("mt", rows)
+        for (M, N, D), shape in zip(((256, 5120, 256), (512, 2560, 2560), (137, 6400, 6400)), shapes):
+            assert B.rosaq_launch_shape(M, N, D, 16)[:2] == shape
+    finally:
+        B.rosaq_tune("mt", 0)
+
+
 def test_many_rows_rule_follows_what_was_measured():
     """(M, channels, D, K, bits) with the measured us of the 128 x 256 tiles and of gemm_kernel: the rule takes the faster one
     wherever they are 10 % apart.  Some launches need a second round only on one shader engine of some XCDs, some have many
