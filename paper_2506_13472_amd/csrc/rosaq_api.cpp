@@ -349,9 +349,9 @@ static GemmArgs main_gemm(const rosaq_packed_t* const* ps, int count, const Gemm
   a.swiglu = swiglu ? 1 : 0;
   return a;
 }
-// The words the first launch of a call clears: the tickets of the GEMM launches behind it, if there are any.  (Cleared
+// The words the first launch of a call clears: the tickets of the GEMM launch behind it, if that is split.  (Cleared
 // always, they were 32 KiB of stores in launches that are bound by the way of their stores to memory.)
-static int ticket_words(const GemmArgs& a, int words) { return gemm_uses_tickets(a, g_tune) ? words : 0; }
+static int ticket_words(const GemmPlan& plan) { return plan.shape.splits > 1 ? 2 * kTicketsPerLaunch : 0; }
 
 // Settings of the dense rotation's launch: "rot_splits" selects the slab launches, never a ticketed split (no room for
 // partial tiles is offered).
@@ -414,14 +414,15 @@ static int run_prologue(const rosaq_packed_t* p, const WsPlan& w, const void* x_
   a.M = M;
   a.ks_s = c.D / kKStep; a.G = 0; a.KS = c.D / kKStep; a.KS_out = c.D / kKStep;
   a.bits = 4; a.out_frag = 1;
-  return launch_gemm(a, rotation_tune(), hip_stream);
+  return launch_gemm(a, plan_gemm(a, rotation_tune()), hip_stream);
 }
 
 static int run_call(const rosaq_packed_t* const* ps, int count, const void* x_dev, int M,
                     int64_t ldx, void* const* ys, const int64_t* ldys, char* ws, size_t ws_bytes,
                     const WsPlan& w, void* hip_stream, bool swiglu = false) {
   const GemmArgs a = main_gemm(ps, count, plan_io(*ps[0], w, ws, ws_bytes), M, ys, ldys, swiglu);
-  const int n_tickets = ticket_words(a, 2 * kTicketsPerLaunch);
+  const GemmPlan plan = plan_gemm(a, g_tune);
+  const int n_tickets = ticket_words(plan);
   int rc = ROSAQ_OK;
   if (g_tune_stages & 1)
     rc = run_prologue(ps[0], w, x_dev, M, ldx, ws, ws_bytes, n_tickets, hip_stream);
@@ -429,7 +430,7 @@ static int run_call(const rosaq_packed_t* const* ps, int count, const void* x_de
     rc = launch_clear(ws + w.tickets, n_tickets, hip_stream);
   if (rc != ROSAQ_OK) return rc;
   if (!(g_tune_stages & 2)) return ROSAQ_OK;
-  return launch_gemm(a, g_tune, hip_stream);
+  return launch_gemm(a, plan, hip_stream);
 }
 
 static uint64_t fnv1a(uint64_t h, const void* data, size_t n) {
@@ -684,16 +685,18 @@ int rosaq_mlp_swiglu(const rosaq_packed_t* gate, const rosaq_packed_t* up, const
   dn.part_bytes = ws_bytes > m.part ? ws_bytes - m.part : 0;
   const int64_t ldys[1] = {ldy};
   const GemmArgs third = main_gemm(&down, 1, dn, M, &y_dev, ldys);
+  const GemmPlan third_plan = plan_gemm(third, g_tune);
   // 2. silu(gate) * up, written as down's input fragments at down's storage positions; clears that launch's tickets
   GemmIO io = plan_io(*gate, m.gate, ws, m.gate.required);
   io.part = nullptr; io.part_bytes = 0;
   io.chain_pos = down->d_pos; io.chain_ks = down->c.D / kKStep;
-  io.zero_count = ticket_words(third, 2 * kTicketsPerLaunch);
+  io.zero_count = ticket_words(third_plan);
   io.zero_ptr = io.zero_count ? ws + m.down_tickets : nullptr;
   void* hs[2] = {ws + m.down_xf, ws + m.down_xf};
   const int64_t ldh[2] = {0, 0};
-  rc = launch_gemm(main_gemm(gu, 2, io, M, hs, ldh, true), g_tune, hip_stream);
-  return rc != ROSAQ_OK ? rc : launch_gemm(third, g_tune, hip_stream);
+  const GemmArgs second = main_gemm(gu, 2, io, M, hs, ldh, true);
+  rc = launch_gemm(second, plan_gemm(second, g_tune), hip_stream);
+  return rc != ROSAQ_OK ? rc : launch_gemm(third, third_plan, hip_stream);
 }
 
 int rosaq_packed_info(const rosaq_packed_t* p, int32_t* N, int32_t* D, int32_t* K, int32_t* bits,

@@ -114,13 +114,20 @@ GemmShape pick_gemm_shape(int M, int ntiles, int D, int bits, const GemmTune& tu
                           size_t part_bytes = 0, int ticket_count = 0, int ks_s = -1);
 // bytes of partial tiles a launch of this shape needs
 size_t gemm_part_bytes(const GemmShape& s, int M, int ntiles);
-int launch_gemm(const GemmArgs& a, const GemmTune& tune, void* stream);
-// Whether that launch is split over workgroups, so that its tickets have to be cleared in front of it.
-bool gemm_uses_tickets(const GemmArgs& a, const GemmTune& tune);
+// What a launch runs as.  Decided once: a split launch (shape.splits > 1) finds its tickets cleared only because the launch
+// in front of it was told so from the same plan.
+struct GemmDev;
+struct GemmPlan {
+  bool wide = false;                                       // the kernel for many rows
+  GemmShape shape{1, 1, 8, 1, 1};                          // of gemm_kernel, if not
+  int (*run)(const GemmDev&, void* stream) = nullptr;      // its launcher, null where no kernel is built for the shape
+};
+GemmPlan plan_gemm(const GemmArgs& a, const GemmTune& tune);
+int launch_gemm(const GemmArgs& a, const GemmPlan& plan, void* stream);
+// Whether plan_gemm takes the kernel for many rows (128 x 256 tiles).
+bool prefers_wide(int M, int ntiles, int D, int K, int bits, const GemmTune& tune);
 // Host copy of the kernel's workgroup -> (channel chunk, row group) map: b < 0 returns the grid
 // size, otherwise 1 and the pair, or 0 for a padding workgroup that exits at once.
-// Whether launch_gemm takes the kernel for many rows (128 x 256 tiles).
-bool prefers_wide(int M, int ntiles, int D, int K, int bits, const GemmTune& tune);
 int block_map_host(int b, int chunks, int mgroups, int* chunk, int* mg);
 // both prologue launchers also clear `zero_count` 32-bit words at `zero_ptr` (the tickets of the
 // GEMM launches that follow in the same call)

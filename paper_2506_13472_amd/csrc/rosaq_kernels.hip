@@ -696,14 +696,14 @@ static int hip_fail(hipError_t e, const char* what) {
 }
 
 template <int BITS, int MT, int NT, int WPB, int DEPTH>
-static int launch_gemm_t(const GemmDev& d, hipStream_t st) {
+static int launch_gemm_t(const GemmDev& d, void* stream) {
   const int splits = d.splits > 1 ? d.splits : 1, octets = (d.chunks + 7) / 8;
   GemmDev g = d;
   // up to kMapRows row groups the order of map_block is plain chunk-major, which a grid can have by itself; the octets of
   // chunks are its third dimension, which ends at 65535 (some eight million channels; beyond, map_block as for many rows)
   g.grid3 = d.mgroups <= kMapRows && octets <= 65535;
   const dim3 grid = g.grid3 ? dim3(8, splits * d.mgroups, octets) : dim3(map_grid(d.chunks, d.mgroups) * splits);
-  hipLaunchKernelGGL((gemm_kernel<BITS, MT, NT, WPB, DEPTH>), grid, dim3(WPB * 64), 0, st, g);
+  hipLaunchKernelGGL((gemm_kernel<BITS, MT, NT, WPB, DEPTH>), grid, dim3(WPB * 64), 0, static_cast<hipStream_t>(stream), g);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? ROSAQ_OK : hip_fail(e, "gemm_kernel launch");
 }
@@ -958,22 +958,14 @@ static GemmDev fill_dev(const GemmArgs& a, int* tiles_out) {
   return d;
 }
 
-// 0 = launched, 1 = no kernel is instantiated for this shape, negative = error
-static int launch_gemm_shape(const GemmArgs& a, const GemmShape& sh, void* stream) {
-  int tiles;
-  GemmDev d = fill_dev(a, &tiles);
-  if (a.swiglu && (sh.nt & 1)) return 1;   // pairs of tiles need an even tile count per workgroup
-  d.chunks = (tiles + sh.nt - 1) / sh.nt;
-  d.mgroups = ((a.M + 15) / 16 + sh.mt - 1) / sh.mt;
-  d.splits = a.swiglu ? 1 : sh.splits;
-  const int bits = a.G == 0 ? 16 : a.bits;
-  hipStream_t st = static_cast<hipStream_t>(stream);
+// The launcher of the kernel instantiated for this shape, or null.
+static int (*kernel_for(int bits, const GemmShape& sh))(const GemmDev&, void*) {
 #define ROSAQ_CASE(B, MT_, NT_, W)                                              \
   if (bits == B && sh.mt == MT_ && sh.nt == NT_ && sh.wpb == W) {              \
-    if (sh.depth == 1) return launch_gemm_t<B, MT_, NT_, W, 1>(d, st);           \
-    if (sh.depth == 2) return launch_gemm_t<B, MT_, NT_, W, 2>(d, st);           \
-    if (sh.depth == 3) return launch_gemm_t<B, MT_, NT_, W, 3>(d, st);           \
-    return launch_gemm_t<B, MT_, NT_, W, 4>(d, st);                              \
+    if (sh.depth == 1) return launch_gemm_t<B, MT_, NT_, W, 1>;                  \
+    if (sh.depth == 2) return launch_gemm_t<B, MT_, NT_, W, 2>;                  \
+    if (sh.depth == 3) return launch_gemm_t<B, MT_, NT_, W, 3>;                  \
+    return launch_gemm_t<B, MT_, NT_, W, 4>;                                     \
   }
 #define ROSAQ_CASES(B)                                                          \
   ROSAQ_CASE(B, 1, 1, 8) ROSAQ_CASE(B, 1, 2, 8) ROSAQ_CASE(B, 1, 4, 8)          \
@@ -988,11 +980,11 @@ static int launch_gemm_shape(const GemmArgs& a, const GemmShape& sh, void* strea
   ROSAQ_WIDE(4)
   ROSAQ_WIDE(3)
   ROSAQ_CASE(16, 2, 3, 8) ROSAQ_CASE(16, 4, 3, 8)
-  if (bits == 16 && sh.mt == 4 && sh.nt == 5) return launch_gemm_t<16, 4, 5, 8, 1>(d, st);
+  if (bits == 16 && sh.mt == 4 && sh.nt == 5) return launch_gemm_t<16, 4, 5, 8, 1>;
 #undef ROSAQ_WIDE
 #undef ROSAQ_CASES
 #undef ROSAQ_CASE
-  return 1;
+  return nullptr;
 }
 
 // The 128 x 256 tiles of the kernel for many rows against the shape pick_unsplit chooses for gemm_kernel, by what both were
@@ -1029,53 +1021,48 @@ bool prefers_wide(int M, int ntiles, int D, int K, int bits, const GemmTune& tun
   return 1.03 * wide < narrow;
 }
 
-bool gemm_uses_tickets(const GemmArgs& a, const GemmTune& tune) {
+GemmPlan plan_gemm(const GemmArgs& a, const GemmTune& tune) {
   int tiles = 0;
   for (int i = 0; i < a.nseg; ++i) tiles += (a.seg[i].N + kTileN - 1) / kTileN;
-  if (a.swiglu || a.M > kMBlock || !a.part || !a.tickets) return false;
-  if (tune.splits <= 1 && (a.M <= 32 || a.KS * kKStep < 8192)) return false;   // pick_gemm_shape's own rule, without its cost
-  return pick_gemm_shape(a.M, tiles, a.KS * kKStep, a.G == 0 ? 16 : a.bits, tune, a.part_bytes, a.ticket_count, a.ks_s).splits > 1;
+  const int bits = a.G == 0 ? 16 : a.bits;
+  GemmPlan plan;
+  plan.wide = a.xrow == nullptr && prefers_wide(a.M, tiles, a.KS * kKStep, a.ks_s * kKStep, bits, tune);
+  if (plan.wide) return plan;
+  auto choose = [&](GemmTune t) {
+    auto shape = [&]() {
+      return pick_gemm_shape(a.M, tiles, a.KS * kKStep, bits, t, a.part ? a.part_bytes : 0,
+                             a.tickets ? a.ticket_count : 0, a.ks_s);
+    };
+    if (a.swiglu) t.splits = 1;        // a gated pair runs unsplit with an even number of channel tiles per workgroup
+    plan.shape = shape();
+    if (a.swiglu && (plan.shape.nt & 1)) {
+      // 48-channel tiles become 32 x 96 ones (gate + up of a 7B MLP at M = 64: 26.9 us against 28.7 us
+      // as 64 x 64 tiles, which need a second round of workgroups; all-fp16 layers have none of 96 channels)
+      const bool to96 = plan.shape.nt == 3 && bits != 16;
+      t.nt = to96 ? 6 : 2;
+      if (to96) t.mt = 2;
+      plan.shape = shape();
+    }
+    plan.run = a.swiglu && (plan.shape.nt & 1) ? nullptr : kernel_for(bits, plan.shape);
+  };
+  choose(tune);
+  // a forced combination that no kernel is built for falls back to the heuristic's choice
+  if (!plan.run) choose(GemmTune{});
+  return plan;
 }
 
-int launch_gemm(const GemmArgs& a, const GemmTune& tune, void* stream) {
-  int tiles_total = 0;
-  for (int i = 0; i < a.nseg; ++i) tiles_total += (a.seg[i].N + kTileN - 1) / kTileN;
-  const int bits = a.G == 0 ? 16 : a.bits;
-  if (a.xrow == nullptr && prefers_wide(a.M, tiles_total, a.KS * kKStep, a.ks_s * kKStep, bits, tune)) {
-    const GemmDev d = fill_dev(a, &tiles_total);
-    return launch_gemm_wide(d, bits, tiles_total, stream);
-  }
-  auto shape = [&](const GemmTune& t) {
-    return pick_gemm_shape(a.M, tiles_total, a.KS * kKStep, bits, t, a.part ? a.part_bytes : 0,
-                           a.tickets ? a.ticket_count : 0, a.ks_s);
-  };
-  GemmTune t0 = tune;
-  if (a.swiglu) {
-    // a gated pair runs unsplit with an even number of channel tiles per workgroup
-    t0.splits = 1;
-    const GemmShape s0 = shape(t0);
-    // 48-channel tiles become 32 x 96 ones (gate + up of a 7B MLP at M = 64: 26.9 us against 28.7 us
-    // as 64 x 64 tiles, which need a second round of workgroups)
-    if (s0.nt == 3 && bits != 16) { t0.nt = 6; t0.mt = 2; }   // (all-fp16 layers have no 96-channel tiles)
-    else if (s0.nt & 1) t0.nt = 2;
-  }
-  int rc = launch_gemm_shape(a, shape(t0), stream);
-  // a forced combination that no kernel is built for falls back to the heuristic's choice
-  if (rc == 1) {
-    GemmTune t1{};
-    if (a.swiglu) {
-      t1.splits = 1;
-      const GemmShape s1 = shape(t1);
-      if (s1.nt == 3 && bits != 16) { t1.nt = 6; t1.mt = 2; }
-      else if (s1.nt & 1) t1.nt = 2;
-    }
-    rc = launch_gemm_shape(a, shape(t1), stream);
-  }
-  if (rc == 1) {
+int launch_gemm(const GemmArgs& a, const GemmPlan& plan, void* stream) {
+  int tiles;
+  GemmDev d = fill_dev(a, &tiles);
+  if (plan.wide) return launch_gemm_wide(d, a.G == 0 ? 16 : a.bits, tiles, stream);
+  if (!plan.run) {
     set_error("no kernel for this bits / tile combination");
     return ROSAQ_ERR_ARG;
   }
-  return rc;
+  d.chunks = (tiles + plan.shape.nt - 1) / plan.shape.nt;
+  d.mgroups = ((a.M + 15) / 16 + plan.shape.mt - 1) / plan.shape.mt;
+  d.splits = plan.shape.splits;
+  return plan.run(d, stream);
 }
 
 int launch_stream_probe(const void* src, const void* shared, int workgroups, int threads, int w_kib,
