@@ -325,7 +325,8 @@ int rosaq_packed_image(const rosaq_packed_t* p, int32_t which, void* out_host, s
 
 /* Testing aid, host only: the main GEMM's map from workgroup index to (channel chunk, row group) for a
  * launch of `chunks` x `row_groups` tiles (workgroup % 8 is the XCD; inside an XCD consecutive workgroups
- * form blocks of 8 chunks x 4 row groups).  workgroup < 0: returns the grid size (>= chunks * row_groups;
+ * form blocks of 8 chunks x 4 row groups).  Launches of up to 4 row groups have a grid of (XCD, row group, chunk / 8)
+ * with the first index fastest: workgroups are numbered in that order.  workgroup < 0: returns the grid size (>= chunks * row_groups;
  * the surplus are padding workgroups that exit at once).  Otherwise returns 1 and the pair, or 0 (and -1,
  * -1) for a padding workgroup.  Errors (negative): ROSAQ_ERR_SHAPE, ROSAQ_ERR_NULL. */
 int rosaq_block_map(int32_t workgroup, int32_t chunks, int32_t row_groups, int32_t* chunk_out,

@@ -109,7 +109,7 @@ struct GemmDev {
   GemmSeg seg[kMaxBatch];
   int nseg;
   int M, ks_s, G, KS, KS_out, out_frag, chunks, mgroups;
-  int grid3;              // gemm_kernel: the grid is [8][splits x row groups][chunks / 8], else one-dimensional (map_block)
+  int grid3;              // gemm_kernel: the grid is that of grid_tile, else one-dimensional (map_block, unsplit)
   // split-K across workgroups: `splits` workgroups share one output tile, each over its own run
   // of the contraction; their fp32 partial tiles meet in `part`, and the workgroup that draws
   // the last ticket of a tile adds them up in split order and stores the result
@@ -133,11 +133,19 @@ struct GemmDev {
 // chunk and every row group (which at large M streams the whole activation matrix through
 // every L2 once per chunk).  For up to 4 row groups this is the plain order: chunk-major.
 constexpr int kMapCols = 8, kMapRows = 4;
+// The plain order as a grid of (XCD, row group, chunk / 8), the first fastest: gemm_kernel launches of up to 4 row groups
+// have it, and with it the coordinates without a division.  Workgroups that split a tile are neighbours in y.
+__host__ __device__ __forceinline__ void grid_tile(int x, int y, int z, int splits, int& chunk, int& mg, int& split) {
+  chunk = x + 8 * z;
+  mg = y;
+  split = 0;
+  if (__builtin_expect(splits > 1, 0)) { split = mg % splits; mg /= splits; }
+}
 __host__ __device__ __forceinline__ bool map_block(int b, int chunks, int mgroups, int& chunk, int& mg) {
   const int xcd = b & 7, local = b >> 3;
   if (mgroups <= kMapRows) {                              // plain chunk-major order
-    mg = local % mgroups;
-    chunk = xcd + 8 * (local / mgroups);
+    int split;
+    grid_tile(xcd, local % mgroups, local / mgroups, 1, chunk, mg, split);
     return chunk < chunks;
   }
   const int tr = kMapRows;

@@ -141,15 +141,10 @@ void gemm_kernel(GemmDev p) {
                "s"(e2), "s"(list_end), "s"(xf), "s"(wS_0), "s"(wq_0), "s"(p.M));
   int chunk, mg, split = 0;
   if (__builtin_expect(grid3, 1)) {
-    chunk = blockIdx.x + 8 * blockIdx.z;   // blockIdx.x is the XCD
-    mg = blockIdx.y;
-    if (__builtin_expect(splits > 1, 0)) { split = mg % splits; mg /= splits; }   // an output tile's workgroups: neighbours on one XCD
+    grid_tile(blockIdx.x, blockIdx.y, blockIdx.z, splits, chunk, mg, split);
     if (chunk >= chunks) return;
-  } else {
-    const int local = blockIdx.x >> 3;
-    split = splits > 1 ? local % splits : 0;
-    const int base_block = splits > 1 ? ((local / splits) << 3) | (blockIdx.x & 7) : blockIdx.x;
-    if (!map_block(base_block, chunks, p.mgroups, chunk, mg)) return;
+  } else if (!map_block(blockIdx.x, chunks, p.mgroups, chunk, mg)) {
+    return;
   }
   const int tile0 = chunk * NT;   // first tile of the chunk in the launch's tile list
   const int mtile0 = mg * MT;
@@ -699,10 +694,11 @@ template <int BITS, int MT, int NT, int WPB, int DEPTH>
 static int launch_gemm_t(const GemmDev& d, void* stream) {
   const int splits = d.splits > 1 ? d.splits : 1, octets = (d.chunks + 7) / 8;
   GemmDev g = d;
-  // up to kMapRows row groups the order of map_block is plain chunk-major, which a grid can have by itself; the octets of
-  // chunks are its third dimension, which ends at 65535 (some eight million channels; beyond, map_block as for many rows)
+  // up to kMapRows row groups the order of map_block is plain chunk-major, which a grid can have by itself (grid_tile); the
+  // octets of chunks are its third dimension, which ends at 65535 (some eight million channels; beyond, map_block as for
+  // many rows).  Split launches have at most 64 rows and kTicketsPerLaunch tiles, so always this grid.
   g.grid3 = d.mgroups <= kMapRows && octets <= 65535;
-  const dim3 grid = g.grid3 ? dim3(8, splits * d.mgroups, octets) : dim3(map_grid(d.chunks, d.mgroups) * splits);
+  const dim3 grid = g.grid3 ? dim3(8, splits * d.mgroups, octets) : dim3(map_grid(d.chunks, d.mgroups));
   hipLaunchKernelGGL((gemm_kernel<BITS, MT, NT, WPB, DEPTH>), grid, dim3(WPB * 64), 0, static_cast<hipStream_t>(stream), g);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? ROSAQ_OK : hip_fail(e, "gemm_kernel launch");
