@@ -118,7 +118,8 @@ int block_map_host(int b, int chunks, int mgroups, int* chunk, int* mg) {
 template <int BITS, int MT, int NT, int WPB, int DEPTH>
 __global__ __launch_bounds__(WPB * 64, (DEPTH == 1 && MT * NT <= 4 ? (MT == 4 ? 2 : 4) : 1))
 void gemm_kernel(GemmDev p) {
-  // the waves' partial tiles meet in LDS, in one pass or (large tiles) in two halves
+  // the waves' partial tiles meet in LDS, in one pass or (large tiles) in two halves, or in one pass per channel tile where
+  // their number is odd
   constexpr int kRedPasses = WPB * NT * MT <= 128 ? 1 : (NT % 2 == 0 ? 2 : NT);
   constexpr int kRedNT = NT / kRedPasses;
   static_assert(NT % kRedPasses == 0, "tile split");
@@ -852,8 +853,12 @@ static GemmShape pick_unsplit(int M, int ntiles, int D, int bits, const GemmTune
     // at 512 18.8 / 21.3 (432), 4992 at 202 30.3 / 34.4 (416), 1280 at 1024 15.5 / 17.0 (432), 6400 at 137 44.0 / 47.3 (402), 4736 at
     // 254 31.5 / 33.9 (396).  With fewer the two rounds overlap as well: 4608 at 254 36.3 / 33.3 (384), 5632 at 163 39.2 /
     // 39.2 (354); with long contractions the inflow is all: 9472 at 128 rows 77.2 / 76.0; where an XCD gets 33 workgroups
-    // it loses: 6656 at 150 rows 78 / 58.  (Low-bit layers gain nothing: their 80-channel tile spills, and 13824 -> 5120 at 256
-    // rows takes 54.4 us against 52.3.)
+    // it loses: 6656 at 150 rows 78 / 58.  Layers of K = D (67 launches of 1270 to 20480 channels, D 128 to 8192, with their
+    // copy launch) are 2 to 10 % faster up to D = 1024 (5120 channels of D = 256 at 256 rows 8.7 / 9.1), 5 to 39 % above
+    // (2560 of D = 8192 at 450 rows 48.5 / 67.2; 19400 of D = 8192 at 60 rows 68.7 / 82.5).  Where 32 x 64 tiles were the
+    // choice: 6400 at 146 rows 44.6 / 75.8; 65 to 96 rows of 9400 to 10240 channels, which leave a quarter to a half of the
+    // second row group empty, 0 to 11 % faster (D = 3200 24.3-26.1 / 23.8-26.0, D = 4352 31.8 / 35.0).
+    // (Low-bit layers gain nothing: their 80-channel tile spills, and 13824 -> 5120 at 256 rows takes 54.4 us against 52.3.)
     const int narrow = ((ntiles + 2) / 3) * ((mtiles + 3) / 4);
     // 80 channels go with 64 rows only: not where other rows are forced.
     const bool rows64 = tune.mt != 1 && tune.mt != 2;

@@ -164,9 +164,9 @@ __device__ __forceinline__ double fast_rcp(double x) {
 // each of the other in 32.  Its angles need the inner products as the round before leaves them, and the rest of
 // the work needs its angles: as two steps with a barrier each a round took 0.8 us, 33 us a launch.  But of those inner products the
 // angles need only the 32 of the pairs that meet next, each a combination of the four between two pairs of this
-// round.  So the first wave forms these by itself, from the matrix as it stands before the round, while seven and a half
-// waves turn the matrix from one buffer into the other (of the 32 x 32 blocks (pair a, pair b) those with a <= b: it is
-// symmetric) and eight turn J, with one barrier a round.  A launch of 32 rounds now takes 24.9 us (29.6 before, kernels alone),
+// round.  So the first wave forms these by itself, from the matrix as it stands before the round, while waves 1 to 7, 14 and
+// a quarter of 15 turn the matrix from one buffer into the other (of the 32 x 32 blocks (pair a, pair b) the 528 with a <= b:
+// it is symmetric) and waves 8 to 15 turn J, with one barrier a round.  A launch of 32 rounds now takes 24.9 us (29.6 before, kernels alone),
 // one of 63 59.7 (67.3).  Of the 24.9, 9.8 are left without any rounds (launch, partial sums, the way of J to memory), 15.9 with
 // the angles alone, 18.4 with J and 18.9 with the matrix in place of both: issue slots and LDS are what the three share.
 template <bool ALL>
