@@ -140,6 +140,10 @@ void gemm_kernel(GemmDev p) {
   const uint32_t* const wq_0 = p.seg[0].wq;
   asm volatile("" ::"s"(grid3), "s"(splits), "s"(chunks), "s"(nseg), "s"(G), "s"(ks_s), "s"(KS4), "s"(swiglu), "s"(e0), "s"(e1),
                "s"(e2), "s"(list_end), "s"(xf), "s"(wS_0), "s"(wq_0), "s"(p.M));
+  // Workgroups of an octet of chunks, for the skew below.  (As gridDim.y it is a load of its own that is waited for in front
+  // of the first unit: 4039 all-fp16 channels over 128 at 72 rows 5.66 -> 5.54 us.)
+  const int octet_groups = splits * p.mgroups;
+  if constexpr (BITS == 16) asm volatile("" ::"s"(octet_groups));
   int chunk, mg, split = 0;
   if (__builtin_expect(grid3, 1)) {
     grid_tile(blockIdx.x, blockIdx.y, blockIdx.z, splits, chunk, mg, split);
@@ -332,7 +336,7 @@ void gemm_kernel(GemmDev p) {
     // fp16 tiles are a power-of-two number of KiB apart when D is: workgroups that all walk
     // their tiles from k = 0 would camp on the same HBM channels.  Each workgroup starts
     // its walk at its own offset (the sum over k does not care where it starts).
-    const int skew = nquad ? ((p.grid3 ? blockIdx.x + 8 * (blockIdx.y + gridDim.y * blockIdx.z) : blockIdx.x) * 5) % nquad : 0;
+    const int skew = nquad ? ((grid3 ? blockIdx.x + 8 * (blockIdx.y + octet_groups * blockIdx.z) : blockIdx.x) * 5) % nquad : 0;
     auto at = [&](int i) { const int v = i + skew; return q_lo + (v >= nquad ? v - nquad : v); };
     QuadRegs q[DEPTH];
     int u = wave;

@@ -1,6 +1,7 @@
 """What the build checks in its own device assembly, on text with and without the fault."""
 import glob
 import os
+import re
 
 import pytest
 
@@ -96,3 +97,21 @@ def test_mfma_distance_of_the_built_kernels(source, least):
         pytest.skip("no assembly kept from the build")
     with open(kept[0], errors="replace") as f:
         assert BU.check_mfma_distance(f.read()) >= least
+
+
+def _built(source):
+    kept = glob.glob(os.path.join(BU.OBJ, source + "-hip-amdgcn*.s"))
+    if not kept:
+        pytest.skip("no assembly kept from the build")
+    with open(kept[0], errors="replace") as f:
+        return f.read()
+
+
+def test_gemm_kernel_loads_no_argument_but_its_own():
+    """The grid's size, for one, is an argument behind the kernel's own, and a wait of its own in front of the first unit."""
+    text = _built("rosaq_kernels")
+    kernels = re.findall(r"\.args:\n(.*?)\.symbol:\s+(_ZN5rosaq11gemm_kernel\S+)", text, re.S)
+    assert len(kernels) > 100
+    for args, name in kernels:
+        args = args.rsplit("    .args:", 1)[-1]
+        assert "by_value" in args and "hidden_" not in args, name
