@@ -298,6 +298,18 @@ void gemm_kernel(GemmDev p) {
       uint4 a[4][MT];
       uint4 b[4][NT];
     };
+    // Where a lane's A fragments are: k-step ks of row tile mt at a_lane[mt][ks * a_step], in fragment order or straight in
+    // row-major x (lane (row r, k-slice j) reads halves 32 ks + 8 j .. + 7 of row r; rows past M: the last one again).  One load
+    // for both: as two under a branch, each in its own way of addressing, a load's registers could be those of one still under
+    // way on the other side, and the compiler waited for everything in front of it.
+    const uint4* a_lane[MT];
+    const unsigned a_step = p.xrow != nullptr ? kKStep / 8 : 256;
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+      const int m = min((mtile0 + mt) * 16 + (lane & 15), p.M - 1);
+      a_lane[mt] = p.xrow != nullptr ? reinterpret_cast<const uint4*>(p.xrow + static_cast<int64_t>(m) * p.ldx) + (lane >> 4)
+                                     : xa + mt * 64 + lane;
+    }
     auto load_quad = [&](int qd, QuadRegs& r) {
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
@@ -305,18 +317,8 @@ void gemm_kernel(GemmDev p) {
         for (int nt = 0; nt < NT; ++nt)
           r.b[t][nt] = (wS_t[nt] + static_cast<unsigned>(4 * qd + t) * 64u)[lane];
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-          if (p.xrow != nullptr) {
-            // lane (row r, k-slice j) reads its 8 halves straight from x[m][32 (4 qd + t) + 8 j]
-            const int m = (mtile0 + mt) * 16 + (lane & 15);
-            r.a[t][mt] = make_uint4(0, 0, 0, 0);
-            if (m < p.M)
-              r.a[t][mt] = *reinterpret_cast<const uint4*>(p.xrow + static_cast<int64_t>(m) * p.ldx +
-                                                           (4 * qd + t) * kKStep + (lane >> 4) * 8);
-          } else {
-            r.a[t][mt] = row_ok ? (xa + static_cast<unsigned>(4 * qd + t) * 256u + mt * 64)[lane] : make_uint4(0, 0, 0, 0);
-          }
-        }
+        for (int mt = 0; mt < MT; ++mt)
+          r.a[t][mt] = row_ok ? a_lane[mt][static_cast<unsigned>(4 * qd + t) * a_step] : make_uint4(0, 0, 0, 0);
       }
     };
     auto compute_quad = [&](const QuadRegs& r) {

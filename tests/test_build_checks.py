@@ -115,3 +115,14 @@ def test_gemm_kernel_loads_no_argument_but_its_own():
     for args, name in kernels:
         args = args.rsplit("    .args:", 1)[-1]
         assert "by_value" in args and "hidden_" not in args, name
+
+
+@pytest.mark.parametrize("rows,channels,depth", [(2, 2, 3), (2, 3, 2), (2, 4, 2), (4, 2, 2), (4, 3, 1), (4, 4, 1), (4, 5, 1)])
+def test_all_fp16_units_are_fetched_without_waits(rows, channels, depth):
+    """The shapes that the rule takes: nothing in front of the first product waits for all loads under way."""
+    text = _built("rosaq_kernels")
+    name = f"_ZN5rosaq11gemm_kernelILi16ELi{rows}ELi{channels}ELi8ELi{depth}EEEvNS_7GemmDevE:"
+    start = text.index("\n" + name)
+    head = text[start:text.index("v_mfma", start)]
+    assert head.count("global_load_dwordx4") >= 4 * (rows + channels) * depth
+    assert 0 not in [int(n) for n in re.findall(r"vmcnt\((\d+)\)", head)]
