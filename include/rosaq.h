@@ -253,7 +253,7 @@ int rosaq_pca_headwise(const void* X_dev, int32_t n_cal, int32_t D, int64_t ldx,
  *   eigenvalues_host  HOST fp64 [D], descending, >= 0
  *   X_dev             DEVICE fp16 [n_cal x D], row r at X + r*ldx
  * D a multiple of 128 up to 8192 (a sweep is 3 (D / 32 - 1) launches; 2048 rows of a 1024-channel
- * layer take 19 ms, 4608 of a 4096-channel layer 0.42 s).  Allocates its own device scratch (8 D
+ * layer take 18 ms, 4608 of a 4096-channel layer 0.41 s).  Allocates its own device scratch (8 D
  * (n_cal + D) bytes, 4 D^2 bytes of results and about 3 KiB per channel) and waits for the result.  Errors: NULL, SHAPE, ALIGN, HIP, NOCONVERGE. */
 int rosaq_pca_full(const void* X_dev, int32_t n_cal, int32_t D, int64_t ldx, float* Q_host,
                    double* eigenvalues_host, void* hip_stream);
