@@ -74,3 +74,24 @@ def test_mlp_block_on_a_workspace_of_nan(mode):
         B.rosaq_tune("splits", 0)
         for p in (pg, pu, pd):
             p.free()
+
+
+@pytest.mark.parametrize("rot_mt", [0, 2, 4])
+def test_rotation_in_place_with_more_rows_a_workgroup_than_the_call_has(rot_mt):
+    """x is read in place up to 16 rows: rows past M of the workgroup's tiles stay inside x, which ends with its last row."""
+    print(f"case rotation in place rot_mt={rot_mt}", flush=True)
+    D, N = 512, 130
+    lay, Q, lam = make_case(833, 16, D, N, 300, O.MODE_FULL)
+    ref = O.pack(lay["W"], Q, lam, 128, 4, O.MODE_FULL)
+    p = B.rosaq_pack_weights(lay["W"], Q, lam, 128, 4, B.Q_FULL)
+    try:
+        B.rosaq_tune("rot_mt", rot_mt)
+        for M, pad in ((1, 0), (3, 8), (15, 0), (16, 264)):
+            x = torch.full((M, D + pad), float("nan"), dtype=torch.float16, device="cuda")[:, :D]
+            x.copy_(torch.from_numpy(lay["x"][:M]))
+            ws = T.alloc_workspace(p, M)
+            ws.fill_(255)
+            check_output(T.linear(p, x, None, ws).cpu().numpy(), lay["x"][:M], Q, ref)
+    finally:
+        B.rosaq_tune("rot_mt", 0)
+        p.free()
