@@ -80,6 +80,7 @@ def check_counted_waits(assembly: str) -> int:
 _MFMA_STATES = {            # (vector instruction at the result, LDS / memory instruction at it, vector write to the sum)
     "v_mfma_f32_16x16x32_f16": (8, 8, 3),
     "v_mfma_f64_16x16x4_f64": (19, 18, 0),
+    "v_mfma_f32_16x16x4_f32": (10, 10, 7),
 }
 _REGISTERS = re.compile(r"\b([va])(?:\[(\d+):(\d+)\]|(\d+)\b)")
 _TOUCHES = ("v_", "ds_", "global_", "buffer_", "flat_", "scratch_")

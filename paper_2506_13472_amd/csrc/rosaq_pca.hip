@@ -4,17 +4,24 @@
 // applied to pairs of columns of X until all columns are mutually orthogonal; the same rotations
 // accumulate in V.  C itself is never formed.
 //
-// The rotations are applied in blocks (block one-sided Jacobi).  The columns of a problem are cut into blocks of
-// 32; a round pairs the blocks (round-robin), and for every pair of blocks
-//   gram_kernel    forms the 64 x 64 matrix of inner products of the pair's columns (fp64 MFMA),
-//   rotate_kernel  finds the plane rotations from it: 32 rounds that meet each column of one block with each of
-//                  the other (63, all pairs, in a sweep's first round), applied to the 64 x 64 matrix from both sides
-//                  and accumulated into an orthogonal 64 x 64 matrix J, all in LDS,
-//   apply_kernel   multiplies the pair's columns of X V and of V by J (fp64 MFMA).
-// That makes D_b / 32 - 1 rounds of three launches per sweep where rotating one pair of columns at a
-// time takes D_b - 1 launches that stream all of X V and V each: 32 heads of 128 channels, 512 rows
-// 15.1 -> 1.9 ms, one problem of 1024 channels, 2048 rows 161 -> 19 ms.  Bound by rotate_kernel (45 % of the time):
-// see there.
+// What bounds it: a sweep over all pairs is D_b - 1 dependent rounds however the work is laid out, and eight to ten sweeps of
+// them in fp64 took 1.9 ms for 32 heads of 128 channels and 19 ms for one problem of 1024 (2048 rows).  So the sweeps are made
+// where a round is cheap, and fp64 is left with steps that turn all pairs at once:
+//   1. Start.  G = X^T X is made once (fp64 MFMA) and diagonalised in fp32 by block Jacobi from both sides.  The columns are cut
+//      into blocks of 32; a round pairs the blocks (round-robin), start_rotate_kernel finds the plane rotations of a pair's
+//      64 x 64 panel of G - 32 rounds that meet each column of one block with each of the other (63, all pairs, in a
+//      sweep's first round) - and their product J, start_apply_kernel forms J^T G J and V J.  Two launches a round, 27 us, where a
+//      round on X in fp64 takes three and 54 us.
+//   2. V is widened to fp64 and made orthogonal to its last place (Newton-Schulz, product_kernel); X V.
+//   3. Corrections.  The inner products of all columns of X V give every pair's angle.  While these are small taken together
+//      V <- the orthogonal matrix nearest to V (1 + T), T the skew matrix of tangents, squares them.  Two or three reach round-off,
+//      0.1 ms each for 32 heads, 0.37 ms for 1024 channels.
+//   4. Where they are not small (a second moment without full rank, eigenvalues that differ by less than fp32 resolves) a sweep of
+//      one-sided block Jacobi on X V in fp64 follows, and then step 3 again: gram_kernel forms the 64 x 64 inner products of a
+//      pair of blocks, rotate_kernel finds J from them, apply_kernel multiplies the columns of X V and V by J.
+// fp32 decides only where step 3 starts from: X V, its inner products, V and the eigenvalues are fp64 throughout.
+// 32 heads of 128 channels, 512 rows 1.89 -> 1.31 ms, 1024 channels, 2048 rows 19.0 -> 9.3 ms; largest relative error of an
+// eigenvalue against LAPACK's singular values 2.4e-14 -> 1.3e-14 and 3.3e-13 -> 1.8e-14 (fewer roundings).
 //
 // Columns are kept contiguous: Z[c] = [column c of X V (n_pad rows, zero padded) | row c of V^T].
 // A layer-wise rotation is one problem of dimension D; a head-wise one is D / 128 independent problems of
@@ -32,6 +39,8 @@
 namespace rosaq {
 
 typedef double doublex2 __attribute__((ext_vector_type(2)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef double doublex4 __attribute__((ext_vector_type(4)));
 
 constexpr int kPcaBlock = 32;                // columns per block
@@ -48,13 +57,27 @@ struct PcaDev {
   double* diag2;      // [pairs]: sum of squared squared norms, first round of a sweep
   int* done;          // [problems]: converged
   int n_pad, pitch, Db, chunk_rows, chunks;
+  // the rotation to start from (see above)
+  double* full;       // inner products of all columns of a problem: [full_chunks][D][Db]; Vt Vt^T in between
+  float* G;           // [D][Db]
+  float* Vt;          // [D][Db], row c = eigenvector c
+  double* turn;       // [D][Db]: tangents of all pairs' angles, T[i][j] = -T[j][i]
+  double* row_t2;     // [D]: a row's sum of squared tangents
+  double* row_cos;    // [D]: its largest cosine
+  double* skew;       // [problem][tiles on and above the diagonal]: largest entry of a tile of Vt Vt^T - 1
+  int* start_done;    // [problems]: 1 = near enough, 2 = not finite, 3 = held by round-off
+  double* start_off;  // [problems]: what was left off the diagonal in the sweep before
+  int* loose;         // [problems]: 0 = every pair orthogonal to round-off, 1 = all angles small, 2 = not, 3 = one correction left
+  int full_rows, full_chunks;
 };
 
 // Pair k of a round-robin tournament of `n` players in `round`: player n - 1 stays, the others move one seat
 // per round; seat k meets seat n - 1 - k.  Lower number first.
 __device__ __forceinline__ void tournament(int n, int round, int k, int& a, int& b) {
   const int other = n - 1 - k;
-  const int x = (k + round) % (n - 1), y = other == n - 1 ? n - 1 : (other + round) % (n - 1);
+  int x = k + round, y = other + round;                    // both below 2 (n - 1) where they move
+  x -= x >= n - 1 ? n - 1 : 0;
+  y = other == n - 1 ? n - 1 : y - (y >= n - 1 ? n - 1 : 0);
   a = x < y ? x : y;
   b = x < y ? y : x;
 }
@@ -154,8 +177,22 @@ __device__ __forceinline__ double fast_rcp(double x) {
   y = y * __builtin_fma(-x, y, 2.0);
   return y * __builtin_fma(-x, y, 2.0);
 }
+// fp32: the hardware's estimates are good to the last place
+__device__ __forceinline__ float fast_rsqrt(float x) { return __builtin_amdgcn_rsqf(x); }
+__device__ __forceinline__ float fast_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
+__device__ __forceinline__ double fused(double a, double b, double c) { return __builtin_fma(a, b, c); }
+__device__ __forceinline__ float fused(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+template <class T> struct PcaReal;
+template <> struct PcaReal<double> {
+  typedef doublex2 two;
+  static constexpr double kEps2 = 4.930380657631324e-32;      // (2^-52)^2
+};
+template <> struct PcaReal<float> {
+  typedef floatx2 two;
+  static constexpr float kEps2 = 1.4210854715202004e-14f;     // (2^-23)^2
+};
 
-// The rotations of a pair of blocks.  With alpha = |y_p|^2, beta = |y_q|^2, gamma = y_p . y_q:
+// The rotations of a pair of blocks, in fp64 or in fp32.  With alpha = |y_p|^2, beta = |y_q|^2, gamma = y_p . y_q:
 //   d = beta - alpha, t = sign(d) 2 gamma / (|d| + sqrt(d^2 + 4 gamma^2)), c = 1 / sqrt(1 + t^2), s = c t,
 //   (y_p, y_q) <- (c y_p - s y_q, s y_p + c y_q), alpha <- alpha - t gamma, beta <- beta + t gamma;
 // columns that are orthogonal to round-off (|gamma| <= eps sqrt(alpha beta)) are left alone.
@@ -164,11 +201,12 @@ __device__ __forceinline__ double fast_rcp(double x) {
 // each of the other in 32.  Its angles need the inner products as the round before leaves them, and the rest of
 // the work needs its angles: as two steps with a barrier each a round took 0.8 us, 33 us a launch.  But of those inner products the
 // angles need only the 32 of the pairs that meet next, each a combination of the four between two pairs of this
-// round.  So the first wave forms these by itself, from the matrix as it stands before the round, while waves 1 to 7, 14 and
-// a quarter of 15 turn the matrix from one buffer into the other (of the 32 x 32 blocks (pair a, pair b) the 528 with a <= b:
-// it is symmetric) and waves 8 to 15 turn J, with one barrier a round.  A launch of 32 rounds now takes 24.9 us (29.6 before, kernels alone),
-// one of 63 59.7 (67.3).  Of the 24.9, 9.8 are left without any rounds (launch, partial sums, the way of J to memory), 15.9 with
-// the angles alone, 18.4 with J and 18.9 with the matrix in place of both: issue slots and LDS are what the three share.
+// round.  So the first wave forms these by itself, from the matrix as it stands before the round, while waves 1 to 7, 12 and
+// a quarter of 13 turn the matrix from one buffer into the other (of the 32 x 32 blocks (pair a, pair b) the 528 with a <= b:
+// it is symmetric) and waves 8 to 11 turn half of J, with one barrier a round; the other half is a second workgroup's, which turns
+// the same matrix (pairs of blocks are few, compute units many).  In fp32 a launch of 32 rounds takes 16.1 us; 5.8 of
+// them are left without any rounds, 12.6 with the angles alone, 14.8 without J, and 20.4 were all of it in one workgroup: issue slots
+// and LDS are what the three share.
 template <bool ALL>
 struct PcaPairing {
   static constexpr int kRounds = ALL ? kPcaPanel - 1 : kPcaBlock;
@@ -197,30 +235,33 @@ struct PcaPairing {
   }
 };
 
+constexpr int kPcaThreads = 14 * 64;         // of a workgroup that rotates a panel
 constexpr int kPcaPitch = kPcaPanel + 1;     // lanes on neighbouring rows of a column meet no bank twice
+template <class T>
 struct PcaPanelLds {
-  double G[2][kPcaPanel * kPcaPitch];        // element (i, j) at min(i, j) * kPcaPitch + max(i, j)
-  alignas(16) double Jt[kPcaPanel][kPcaPanel + 2];
-  doublex2 cs[2][kPcaBlock];
-  double diag[kPcaPanel];
+  T G[2][kPcaPanel * kPcaPitch];        // element (i, j) at min(i, j) * kPcaPitch + max(i, j)
+  alignas(16) T Jt[kPcaPanel][kPcaBlock + 2];
+  typename PcaReal<T>::two cs[2][kPcaBlock];
+  T diag[kPcaPanel];
   double red[2][16];
 };
 
-template <bool ALL>
-__device__ __forceinline__ void rotate_rounds(PcaPanelLds& m) {
+template <bool ALL, class T>
+__device__ __forceinline__ void rotate_rounds(PcaPanelLds<T>& m) {
+  typedef typename PcaReal<T>::two two;
   using Pairing = PcaPairing<ALL>;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   auto at = [](int i, int j) { return min(i, j) * kPcaPitch + max(i, j); };
-  auto angle = [&](int r, int k, int P, int Q, double al, double be, double ga) {
-    doublex2 v = {1.0, 0.0};
-    double shift = 0.0;
-    const double ab = al * be;
-    if (ab > 0.0 && ga * ga > 4.930380657631324e-32 * ab) {    // false too where one is NaN
-      const double d = be - al, g = 2.0 * ga;
-      const double h2 = __builtin_fma(d, d, g * g);
-      const double t = copysign(1.0, d) * g * fast_rcp(fabs(d) + h2 * fast_rsqrt(h2));
-      const double c = fast_rsqrt(__builtin_fma(t, t, 1.0));
-      v = doublex2{c, c * t};
+  auto angle = [&](int r, int k, int P, int Q, T al, T be, T ga) {
+    two v = {T(1), T(0)};
+    T shift = 0;
+    const T ab = al * be;
+    if (ab > 0 && ga * ga > PcaReal<T>::kEps2 * ab) {    // false too where one is NaN
+      const T d = be - al, g = 2 * ga;
+      const T h2 = fused(d, d, g * g);
+      const T t = (d < 0 ? -g : g) * fast_rcp(fabs(d) + h2 * fast_rsqrt(h2));
+      const T c = fast_rsqrt(fused(t, t, T(1)));
+      v = two{c, c * t};
       shift = t * ga;
     }
     if (lane < kPcaBlock) {                                    // both halves of the wave compute the same
@@ -231,9 +272,9 @@ __device__ __forceinline__ void rotate_rounds(PcaPanelLds& m) {
     __builtin_amdgcn_wave_barrier();
   };
   // the 2 x 2 block (pp pq; qp qq): columns by rb, then rows by ra
-  auto turn = [](doublex2 ra, doublex2 rb, double& pp, double& pq, double& qp, double& qq) {
-    const double pp1 = rb.x * pp - rb.y * pq, pq1 = rb.y * pp + rb.x * pq;
-    const double qp1 = rb.x * qp - rb.y * qq, qq1 = rb.y * qp + rb.x * qq;
+  auto turn = [](two ra, two rb, T& pp, T& pq, T& qp, T& qq) {
+    const T pp1 = rb.x * pp - rb.y * pq, pq1 = rb.y * pp + rb.x * pq;
+    const T qp1 = rb.x * qp - rb.y * qq, qq1 = rb.y * qp + rb.x * qq;
     pp = ra.x * pp1 - ra.y * qp1;
     pq = ra.x * pq1 - ra.y * qq1;
     qp = ra.y * pp1 + ra.x * qp1;
@@ -248,7 +289,7 @@ __device__ __forceinline__ void rotate_rounds(PcaPanelLds& m) {
     Pairing::pair(0, k, P, Q);
     angle(0, k, P, Q, m.diag[P], m.diag[Q], m.G[0][at(P, Q)]);
     __syncthreads();
-    auto look_ahead = [&](int r, const double* G, const doublex2* cs) {
+    auto look_ahead = [&](int r, const T* G, const two* cs) {
       if (r + 1 < Pairing::kRounds) {
         int x, y;
         Pairing::pair(r + 1, k, x, y);
@@ -256,14 +297,14 @@ __device__ __forceinline__ void rotate_rounds(PcaPanelLds& m) {
         int Pi, Qi, Pj, Qj;
         Pairing::pair(r, i, Pi, Qi);
         Pairing::pair(r, j, Pj, Qj);
-        const double pp = G[at(Pi, Pj)], pq = G[at(Pi, Qj)], qp = G[at(Qi, Pj)], qq = G[at(Qi, Qj)];
-        const doublex2 ri = cs[i], rj = cs[j];
-        const double al = m.diag[x], be = m.diag[y];
+        const T pp = G[at(Pi, Pj)], pq = G[at(Pi, Qj)], qp = G[at(Qi, Pj)], qq = G[at(Qi, Qj)];
+        const two ri = cs[i], rj = cs[j];
+        const T al = m.diag[x], be = m.diag[y];
         // column p of a pair becomes c p - s q, column q becomes s p + c q
-        const double ip = x == Pi ? ri.x : ri.y, iq = x == Pi ? -ri.y : ri.x;
-        const double jp = y == Pj ? rj.x : rj.y, jq = y == Pj ? -rj.y : rj.x;
-        const double gp = __builtin_fma(jq, pq, jp * pp), gq = __builtin_fma(jq, qq, jp * qp);
-        angle(r + 1, k, x, y, al, be, __builtin_fma(iq, gq, ip * gp));
+        const T ip = x == Pi ? ri.x : ri.y, iq = x == Pi ? -ri.y : ri.x;
+        const T jp = y == Pj ? rj.x : rj.y, jq = y == Pj ? -rj.y : rj.x;
+        const T gp = fused(jq, pq, jp * pp), gq = fused(jq, qq, jp * qp);
+        angle(r + 1, k, x, y, al, be, fused(iq, gq, ip * gp));
       }
       __syncthreads();
     };
@@ -275,30 +316,30 @@ __device__ __forceinline__ void rotate_rounds(PcaPanelLds& m) {
     return;
   }
   // block (a, b) of the matrix: number n of 33 x 16, a row of 33 being rows i and 31 - i of the triangle a <= b
-  const int n = wave < 8 ? tid - 64 : (wave >= 14 ? 448 + tid - 896 : 528);
+  const int n = wave < 8 ? tid - 64 : (wave >= 12 ? 448 + tid - 768 : 528);
   const bool has_block = n < 528;
   const int ti = n / 33, tj = n - ti * 33;
   const int a = tj < kPcaBlock - ti ? ti : kPcaBlock - 1 - ti, b = tj < kPcaBlock - ti ? ti + tj : tj - 1;
   // two pairs of neighbouring entries of the rows of J of pair aj
-  const bool has_j = wave >= 8;
-  const int aj = (tid & 511) >> 4, cj = 2 * (tid & 15);
-  auto j_at = [&](int row, int e) -> doublex2& { return *reinterpret_cast<doublex2*>(&m.Jt[row][cj + kPcaBlock * e]); };
-  doublex2 u[2] = {};
-  double pp = 0.0;
+  const bool has_j = wave >= 8 && wave < 12;
+  const int aj = (tid & 255) >> 3, cj = 2 * (tid & 7);
+  auto j_at = [&](int row, int e) -> two& { return *reinterpret_cast<two*>(&m.Jt[row][cj + kPcaBlock / 2 * e]); };
+  two u[2] = {};
+  T pp = 0;
   // where column p of a pair stays, its row of J and the inner products of such columns stay in registers
   if (has_j && !ALL) { u[0] = j_at(aj, 0); u[1] = j_at(aj, 1); }
   if (has_block && !ALL) pp = m.G[0][at(a, b)];
   const bool next_pair = ALL || b - a == 1 || b - a == kPcaBlock - 1;      // these the first wave looks at
   __syncthreads();
-  auto round = [&](int r, const double* G, double* H, const doublex2* cs) {
+  auto round = [&](int r, const T* G, T* H, const two* cs) {
     if (has_block) {
       int Pa, Qa, Pb, Qb;
       Pairing::pair(r, a, Pa, Qa);
       Pairing::pair(r, b, Pb, Qb);
       const int o_pp = at(Pa, Pb), o_pq = at(Pa, Qb), o_qp = at(Qa, Pb), o_qq = at(Qa, Qb);
-      const doublex2 ra = cs[a], rb = cs[b];
+      const two ra = cs[a], rb = cs[b];
       if (ALL) pp = G[o_pp];
-      double pq = G[o_pq], qp = G[o_qp], qq = G[o_qq];
+      T pq = G[o_pq], qp = G[o_qp], qq = G[o_qq];
       turn(ra, rb, pp, pq, qp, qq);
       if (next_pair) H[o_pp] = pp;
       if (a != b) H[o_qp] = qp;              // in a pair's own block that is pq
@@ -308,11 +349,11 @@ __device__ __forceinline__ void rotate_rounds(PcaPanelLds& m) {
     if (has_j) {
       int P, Q;
       Pairing::pair(r, aj, P, Q);
-      const doublex2 rj = cs[aj];
+      const two rj = cs[aj];
 #pragma unroll
       for (int e = 0; e < 2; ++e) {
         if (ALL) u[e] = j_at(P, e);
-        const doublex2 v = j_at(Q, e), w = u[e];
+        const two v = j_at(Q, e), w = u[e];
         u[e] = rj.x * w - rj.y * v;
         j_at(Q, e) = rj.y * w + rj.x * v;
         if (ALL) j_at(P, e) = u[e];
@@ -327,24 +368,59 @@ __device__ __forceinline__ void rotate_rounds(PcaPanelLds& m) {
   if (has_j && !ALL) { j_at(aj, 0) = u[0]; j_at(aj, 1) = u[1]; }
 }
 
-__global__ __launch_bounds__(1024) void rotate_kernel(PcaDev p, int round, int pairs) {
-  __shared__ PcaPanelLds m;
-  int c0, c1;
-  if (p.done[pair_columns(p, blockIdx.x, round, c0, c1)]) return;
+// The panel's matrix lies in m.G[0]: what there is to rotate, and J^T of the rotations to J[pair], columns 32 part .. 32 part + 31
+// (workgroups 2 pair and 2 pair + 1 both turn the matrix).
+template <class T>
+__device__ __forceinline__ void rotate_panel(PcaPanelLds<T>& m, const PcaDev& p, int round, int pairs, T* __restrict__ J) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int pair = blockIdx.x >> 1, part = blockIdx.x & 1;
+  for (int i = tid; i < kPcaPanel * kPcaBlock; i += kPcaThreads) m.Jt[i >> 5][i & 31] = (i >> 5) == (i & 31) + kPcaBlock * part ? T(1) : T(0);
+  __syncthreads();
+  // what the convergence test needs, before anything is rotated: gamma^2 between the blocks, in a sweep's first round also
+  // inside them, and alpha^2
+  const bool all_pairs = round == 0;
+  double g2 = 0.0, d2 = 0.0;
+  for (int i = tid; i < kPcaPanel * kPcaPanel; i += kPcaThreads) {
+    const int r = i >> 6, c = i & 63;
+    const double v = r <= c ? m.G[0][r * kPcaPitch + c] : T(0);
+    if (r < c && (all_pairs || (r < kPcaBlock && c >= kPcaBlock))) g2 = __builtin_fma(v, v, g2);
+    if (r == c) d2 = __builtin_fma(v, v, d2);
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) { g2 += __shfl_down(g2, o, 64); d2 += __shfl_down(d2, o, 64); }
+  if (lane == 0) { m.red[0][wave] = g2; m.red[1][wave] = d2; }
+  __syncthreads();
+  if (part == 0 && tid == kPcaThreads - 1) {               // not in the wave of the angles
+    double a = 0.0, b = 0.0;
+    for (int w = 0; w < kPcaThreads / 64; ++w) { a += m.red[0][w]; b += m.red[1][w]; }
+    p.gamma2[static_cast<size_t>(round) * pairs + pair] = a;
+    if (all_pairs) p.diag2[pair] = b;
+  }
+  if (all_pairs) rotate_rounds<true>(m);
+  else rotate_rounds<false>(m);
+  __syncthreads();
+  T* out = J + static_cast<size_t>(pair) * (kPcaPanel * kPcaPanel) + kPcaBlock * part;
+  for (int i = tid; i < kPcaPanel * kPcaBlock; i += kPcaThreads) out[(i >> 5) * kPcaPanel + (i & 31)] = m.Jt[i >> 5][i & 31];
+}
+
+__global__ __launch_bounds__(kPcaThreads) void rotate_kernel(PcaDev p, int round, int pairs) {
+  __shared__ PcaPanelLds<double> m;
+  int c0, c1;
+  const int tid = threadIdx.x, pair = blockIdx.x >> 1;
+  const int done = p.done[pair_columns(p, pair, round, c0, c1)];
   {
-    const double* part = p.part + static_cast<size_t>(blockIdx.x) * p.chunks * (kPcaTiles * 256);
+    const double* part = p.part + static_cast<size_t>(pair) * p.chunks * (kPcaTiles * 256);
     // all loads in flight at once (a chunk or element past the end: the last one again, not used)
-    constexpr int kEach = (kPcaTiles * 256 + 1023) / 1024;
+    constexpr int kEach = (kPcaTiles * 256 + kPcaThreads - 1) / kPcaThreads;
     double o[kEach][kPcaChunks];
 #pragma unroll
     for (int j = 0; j < kEach; ++j)
 #pragma unroll
       for (int k = 0; k < kPcaChunks; ++k)
-        o[j][k] = part[static_cast<size_t>(min(k, p.chunks - 1)) * (kPcaTiles * 256) + min(tid + 1024 * j, kPcaTiles * 256 - 1)];
+        o[j][k] = part[static_cast<size_t>(min(k, p.chunks - 1)) * (kPcaTiles * 256) + min(tid + kPcaThreads * j, kPcaTiles * 256 - 1)];
 #pragma unroll
     for (int j = 0; j < kEach; ++j) {
-      const int i = tid + 1024 * j;
+      const int i = tid + kPcaThreads * j;
       if (i >= kPcaTiles * 256) break;
       double v = 0.0;
 #pragma unroll
@@ -356,34 +432,9 @@ __global__ __launch_bounds__(1024) void rotate_kernel(PcaDev p, int round, int p
       const int r = ta * 16 + 4 * e + (l >> 4), c = tb * 16 + (l & 15);
       if (r <= c) m.G[0][r * kPcaPitch + c] = v;      // the tiles on the diagonal hold both orders of an element
     }
-    for (int i = tid; i < kPcaPanel * kPcaPanel; i += 1024) m.Jt[i >> 6][i & 63] = (i >> 6) == (i & 63) ? 1.0 : 0.0;
   }
-  __syncthreads();
-  // what the convergence test needs, before anything is rotated: gamma^2 between the blocks, in a sweep's first round also
-  // inside them, and alpha^2
-  const bool all_pairs = round == 0;
-  double g2 = 0.0, d2 = 0.0;
-  for (int i = tid; i < kPcaPanel * kPcaPanel; i += 1024) {
-    const int r = i >> 6, c = i & 63;
-    const double v = r <= c ? m.G[0][r * kPcaPitch + c] : 0.0;
-    if (r < c && (all_pairs || (r < kPcaBlock && c >= kPcaBlock))) g2 = __builtin_fma(v, v, g2);
-    if (r == c) d2 = __builtin_fma(v, v, d2);
-  }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) { g2 += __shfl_down(g2, o, 64); d2 += __shfl_down(d2, o, 64); }
-  if (lane == 0) { m.red[0][wave] = g2; m.red[1][wave] = d2; }
-  __syncthreads();
-  if (tid == 1023) {                     // not in the wave of the angles
-    double a = 0.0, b = 0.0;
-    for (int w = 0; w < 16; ++w) { a += m.red[0][w]; b += m.red[1][w]; }
-    p.gamma2[static_cast<size_t>(round) * pairs + blockIdx.x] = a;
-    if (all_pairs) p.diag2[blockIdx.x] = b;
-  }
-  if (all_pairs) rotate_rounds<true>(m);
-  else rotate_rounds<false>(m);
-  __syncthreads();
-  double* out = p.J + static_cast<size_t>(blockIdx.x) * (kPcaPanel * kPcaPanel);
-  for (int i = tid; i < kPcaPanel * kPcaPanel; i += 1024) out[i] = m.Jt[i >> 6][i & 63];
+  if (done) return;                                        // asked for together with what it decides about
+  rotate_panel(m, p, round, pairs, p.J);
 }
 
 // Columns c' of a pair <- sum over c of J[c][c'] column c, for 64 entries of Z: a wave owns 16 entries of all 64
@@ -418,14 +469,9 @@ __global__ __launch_bounds__(256) void apply_kernel(PcaDev p, int round, int pai
     for (int e = 0; e < 4; ++e) *column(t * 16 + 4 * e + q) = acc[t][e];
 }
 
-// End of a sweep, one workgroup per problem: converged when the off-diagonal part of the implied second
-// moment is below tol times its norm (2 sum gamma^2 <= tol^2 (sum alpha^2 + 2 sum gamma^2), measured over the
-// sweep).  Every thread adds its strided share in order and the shares are added in a fixed tree, so the sums do not
-// depend on scheduling.  done: 1 = converged, 2 = not a number.
-__global__ __launch_bounds__(256) void pca_check_kernel(PcaDev p, int rounds, int half, int pairs, double tol) {
-  __shared__ double sh[2][256];
-  const int problem = blockIdx.x;
-  if (p.done[problem]) return;
+// A sweep's sums of gamma^2 and alpha^2 of one problem, to sh[0][0] and sh[1][0] for thread 0.  Every thread adds its
+// strided share in order and the shares are added in a fixed tree, so the sums do not depend on scheduling.
+__device__ __forceinline__ void sum_sweep(const PcaDev& p, int problem, int rounds, int half, int pairs, double (*sh)[256]) {
   double g = 0.0, d = 0.0;
   for (int i = threadIdx.x; i < rounds * half; i += 256)
     g += p.gamma2[static_cast<size_t>(i / half) * pairs + problem * half + i % half];
@@ -436,10 +482,371 @@ __global__ __launch_bounds__(256) void pca_check_kernel(PcaDev p, int rounds, in
     if (threadIdx.x < w) { sh[0][threadIdx.x] += sh[0][threadIdx.x + w]; sh[1][threadIdx.x] += sh[1][threadIdx.x + w]; }
     __syncthreads();
   }
+}
+
+// End of a sweep, one workgroup per problem: converged when the off-diagonal part of the implied second
+// moment is below tol times its norm (2 sum gamma^2 <= tol^2 (sum alpha^2 + 2 sum gamma^2), measured over the
+// sweep).  done: 1 = converged, 2 = not a number.
+__global__ __launch_bounds__(256) void pca_check_kernel(PcaDev p, int rounds, int half, int pairs, double tol) {
+  __shared__ double sh[2][256];
+  const int problem = blockIdx.x;
+  if (p.done[problem]) return;
+  sum_sweep(p, problem, rounds, half, pairs, sh);
   if (threadIdx.x == 0) {
     const double off2 = 2.0 * sh[0][0], norm2 = sh[1][0] + off2;
     if (!(off2 == off2)) p.done[problem] = 2;
     else if (off2 <= tol * tol * norm2) p.done[problem] = 1;
+  }
+}
+
+// ---- the rotation to start from -------------------------------------------------------------------------
+
+// The chunks' sums in order, a row per workgroup: to the first chunk's place, or (FIRST) to G, and Vt <- 1.
+template <bool FIRST>
+__global__ __launch_bounds__(256) void full_sum_kernel(PcaDev p) {
+  const int problem = blockIdx.x / p.Db, i = blockIdx.x - problem * p.Db;
+  if (p.done[problem]) return;
+  const size_t row = static_cast<size_t>(blockIdx.x) * p.Db, chunk = static_cast<size_t>(gridDim.x) * p.Db;
+  for (int j = threadIdx.x; j < p.Db; j += 256) {
+    double v = 0.0;
+    for (int k = 0; k < p.full_chunks; ++k) v += p.full[k * chunk + row + j];
+    if (FIRST) {
+      p.G[row + j] = static_cast<float>(v);
+      p.Vt[row + j] = i == j ? 1.0f : 0.0f;
+    } else {
+      p.full[row + j] = v;
+    }
+  }
+  if (FIRST && i == 0 && threadIdx.x == 0) p.start_off[problem] = 1.0;
+}
+
+// The angles of all pairs of columns at once, from their inner products as they stand (p.full, or G in fp32): a row's sum of squared
+// tangents, and from p.full also the tangents themselves and the row's largest cosine.  A workgroup per row.  Columns
+// below 1e-13 of the longest are what round-off has left of a null space: any orthonormal basis of it will do.
+template <class T>
+__global__ __launch_bounds__(256) void tangent_kernel(PcaDev p) {
+  __shared__ double red[3][4];
+  constexpr bool kFull = sizeof(T) == 8;
+  const int problem = blockIdx.x / p.Db, i = blockIdx.x - problem * p.Db;
+  if (kFull ? p.done[problem] : p.start_done[problem]) return;
+  const size_t base = static_cast<size_t>(problem) * p.Db * p.Db, row = base + static_cast<size_t>(i) * p.Db;
+  const T* S;
+  if constexpr (kFull) S = p.full; else S = p.G;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  double longest = 0.0;
+  for (int j = threadIdx.x; j < p.Db; j += 256) longest = fmax(longest, static_cast<double>(S[base + static_cast<size_t>(j) * p.Db + j]));
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) longest = fmax(longest, __shfl_xor(longest, o, 64));
+  if (lane == 0) red[0][wave] = longest;
+  __syncthreads();
+  const double nothing = 1e-26 * fmax(fmax(red[0][0], red[0][1]), fmax(red[0][2], red[0][3]));
+  const double al = S[row + i];
+  double t2 = 0.0, c2 = 0.0;
+  for (int j = threadIdx.x; j < p.Db; j += 256) {
+    const double be = S[base + static_cast<size_t>(j) * p.Db + j], ga = S[row + j], ab = al * be;
+    double t = 0.0;
+    if (i != j && !(fmin(al, be) <= nothing)) {
+      const double d = be - al, g = 2.0 * ga;
+      if (ga * ga > PcaReal<double>::kEps2 * ab) t = (d < 0.0 || (d == 0.0 && j < i) ? -g : g) / (fabs(d) + sqrt(d * d + g * g));
+      const double c = ga * ga / ab;
+      c2 = c <= c2 ? c2 : c;                       // a NaN stays
+      t2 = __builtin_fma(t, t, t2);
+    }
+    if (kFull) p.turn[row + j] = t;
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    t2 += __shfl_xor(t2, o, 64);
+    const double c = __shfl_xor(c2, o, 64);
+    c2 = c <= c2 ? c2 : c;
+  }
+  if (lane == 0) { red[1][wave] = t2; red[2][wave] = c2; }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < 4; ++w) { t2 += red[1][w]; c2 = red[2][w] <= c2 ? c2 : red[2][w]; }
+    p.row_t2[blockIdx.x] = t2;
+    if (kFull) p.row_cos[blockIdx.x] = sqrt(c2);
+  }
+}
+
+// The sum of a problem's rows' squared tangents over both halves, in a fixed order, to sh[0] for thread 0, and the largest cosine to sh[1].
+__device__ __forceinline__ void sum_tangents(const PcaDev& p, int problem, bool cosines, double (*sh)[256]) {
+  double t2 = 0.0, c = 0.0;
+  for (int i = threadIdx.x; i < p.Db; i += 256) {
+    t2 += p.row_t2[problem * p.Db + i];
+    if (cosines) { const double v = p.row_cos[problem * p.Db + i]; c = v <= c ? c : v; }
+  }
+  sh[0][threadIdx.x] = t2; sh[1][threadIdx.x] = c;
+  __syncthreads();
+  for (int w = 128; w > 0; w >>= 1) {
+    if (threadIdx.x < w) {
+      sh[0][threadIdx.x] += sh[0][threadIdx.x + w];
+      const double v = sh[1][threadIdx.x + w];
+      if (!(v <= sh[1][threadIdx.x])) sh[1][threadIdx.x] = v;
+    }
+    __syncthreads();
+  }
+}
+
+// What the angles say, one workgroup per problem.  Round-off: every cosine within tol or the angles within 1e-11, and V so near to orthogonal before the
+// last step of kNewton, which squares what is missing, that nothing is missing now.  Small: the singular values of 1 + T
+// are at most sqrt(1.5) (those of T come in pairs), where the step converges (it does up to sqrt(3)).  A correction squares the
+// angles too (|T| 0.13, 1.5e-3, 2e-7, 3e-13 for 1024 channels), so after one of 3e-7 nothing is left to look for.
+__global__ __launch_bounds__(256) void tangent_check_kernel(PcaDev p, double tol) {
+  __shared__ double sh[2][256];
+  const int problem = blockIdx.x, half = p.Db / 64;
+  if (p.done[problem]) return;
+  double skew = 0.0;
+  const int tiles = half * (half + 1) / 2;
+  for (int i = threadIdx.x; i < tiles; i += 256) {
+    const double v = p.skew[problem * tiles + i];
+    skew = v <= skew ? skew : v;
+  }
+  const bool orthogonal = !__syncthreads_or(!(skew <= 1e-9)), nearly = !__syncthreads_or(!(skew <= 1e-5));
+  sum_tangents(p, problem, true, sh);
+  if (threadIdx.x == 0)
+    p.loose[problem] = (sh[1][0] <= tol || sh[0][0] <= 1e-22) && orthogonal ? 0
+                       : (sh[0][0] <= 1e-13 && nearly ? 3 : (sh[0][0] <= 1.0 ? 1 : 2));
+}
+
+// A pair of blocks of G: its panel and the rotations, as rotate_kernel but in fp32.
+__global__ __launch_bounds__(kPcaThreads) void start_rotate_kernel(PcaDev p, int round, int pairs) {
+  __shared__ PcaPanelLds<float> m;
+  int c0, c1;
+  const int problem = pair_columns(p, blockIdx.x >> 1, round, c0, c1), base = problem * p.Db;
+  const int done = p.start_done[problem];
+  constexpr int kEach = (kPcaPanel * kPcaPanel + kPcaThreads - 1) / kPcaThreads;
+  float v[kEach];
+#pragma unroll
+  for (int j = 0; j < kEach; ++j) {
+    const int i = min(threadIdx.x + kPcaThreads * j, kPcaPanel * kPcaPanel - 1), r = i >> 6, c = i & 63;
+    v[j] = p.G[static_cast<size_t>((r < kPcaBlock ? c0 : c1 - kPcaBlock) + r) * p.Db + (c < kPcaBlock ? c0 : c1 - kPcaBlock) - base + c];
+  }
+  if (done) return;
+#pragma unroll
+  for (int j = 0; j < kEach; ++j) {
+    const int i = threadIdx.x + kPcaThreads * j, r = i >> 6, c = i & 63;
+    if (i < kPcaPanel * kPcaPanel && r <= c) m.G[0][r * kPcaPitch + c] = v[j];
+  }
+  rotate_panel(m, p, round, pairs, reinterpret_cast<float*>(p.J));
+}
+
+// G <- J^T G J and Vt <- J^T Vt for a round's rotations: a workgroup per 64 x 64 tile (rows of pair a, columns of pair b >= a)
+// of G, whose transpose it stores as well, and per tile of 64 channels of Vt.  A wave owns 16 columns of the tile.  Both
+// products in registers: the first one's accumulator is the second one's factor as it stands, with rows of J in that order.
+__global__ __launch_bounds__(256) void start_apply_kernel(PcaDev p, int round) {
+  const int half = p.Db / kPcaPanel, tiles = half * (half + 1) / 2, per = tiles + half * half;
+  const int problem = blockIdx.x / per, n = blockIdx.x - problem * per;
+  const int done = p.start_done[problem];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int i16 = lane & 15, q = lane >> 4;
+  const bool is_v = n >= tiles;
+  const int ti = n / (half + 1), tj = n - ti * (half + 1);        // see product_kernel
+  const int a = is_v ? (n - tiles) / half : (tj < half - ti ? ti : half - 1 - ti);
+  const int b = is_v ? (n - tiles) % half : (tj < half - ti ? ti + tj : tj - 1);
+  int a0, a1;
+  pair_columns(p, problem * half + a, round, a0, a1);
+  auto row_of = [&](int r) { return static_cast<size_t>((r < kPcaBlock ? a0 : a1 - kPcaBlock) + r) * p.Db; };
+  const float* Ja = reinterpret_cast<const float*>(p.J) + static_cast<size_t>(problem * half + a) * (kPcaPanel * kPcaPanel);
+  floatx4 ja[4][4];
+#pragma unroll
+  for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+    for (int rt = 0; rt < 4; ++rt)
+      ja[mt][rt] = *reinterpret_cast<const floatx4*>(Ja + (16 * mt + i16) * kPcaPanel + 16 * rt + 4 * q);
+  floatx4 u[4];                                   // rows 16 rt + 4 q + e of column 16 wave + i16
+  int column;
+  if (is_v) {
+    column = kPcaPanel * b + 16 * wave + i16;
+#pragma unroll
+    for (int rt = 0; rt < 4; ++rt)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) u[rt][e] = p.Vt[row_of(16 * rt + 4 * q + e) + column];
+  } else {
+    int b0, b1;
+    pair_columns(p, problem * half + b, round, b0, b1);
+    b0 -= problem * p.Db;
+    b1 -= problem * p.Db;
+    const float* Jb = reinterpret_cast<const float*>(p.J) + static_cast<size_t>(problem * half + b) * (kPcaPanel * kPcaPanel);
+    floatx4 jb[4], t[4][4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      jb[s] = *reinterpret_cast<const floatx4*>(Jb + (16 * wave + i16) * kPcaPanel + 16 * q + 4 * s);
+#pragma unroll
+      for (int rt = 0; rt < 4; ++rt)
+        t[rt][s] = *reinterpret_cast<const floatx4*>(p.G + row_of(16 * rt + i16) + (q < 2 ? b0 : b1 - kPcaBlock) + 16 * q + 4 * s);
+    }
+#pragma unroll
+    for (int rt = 0; rt < 4; ++rt) u[rt] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int s = 0; s < 16; ++s)
+#pragma unroll
+      for (int rt = 0; rt < 4; ++rt) u[rt] = __builtin_amdgcn_mfma_f32_16x16x4f32(t[rt][s >> 2][s & 3], jb[s >> 2][s & 3], u[rt], 0, 0, 0);
+    const int c = 16 * wave + i16;
+    column = (c < kPcaBlock ? b0 : b1 - kPcaBlock) + c;
+  }
+  if (done) return;                               // asked for together with what it decides about
+  __syncthreads();                                // the other waves have read the tile
+  floatx4 out[4];
+#pragma unroll
+  for (int mt = 0; mt < 4; ++mt) out[mt] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+  for (int s = 0; s < 16; ++s)
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt) out[mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(ja[mt][s >> 2][s & 3], u[s >> 2][s & 3], out[mt], 0, 0, 0);
+  float* dst = is_v ? p.Vt : p.G;
+#pragma unroll
+  for (int mt = 0; mt < 4; ++mt) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) dst[row_of(16 * mt + 4 * q + e) + column] = out[mt][e];
+    if (!is_v && a != b) {
+      const int r = 16 * mt + 4 * q;
+      *reinterpret_cast<floatx4*>(p.G + (static_cast<size_t>(problem) * p.Db + column) * p.Db + (r < kPcaBlock ? a0 : a1 - kPcaBlock) + r -
+                                  problem * p.Db) = out[mt];
+    }
+  }
+}
+
+// End of a sweep in fp32, one workgroup per problem.  Near enough: the angles that are left are small taken together, or
+// round-off holds what is off the diagonal where it is (a second moment without full rank).  Sums as in pca_check_kernel.
+__global__ __launch_bounds__(256) void start_check_kernel(PcaDev p, int rounds, int half, int pairs, double small) {
+  __shared__ double sh[2][256];
+  const int problem = blockIdx.x;
+  if (p.start_done[problem]) return;
+  sum_sweep(p, problem, rounds, half, pairs, sh);
+  const double off2 = 2.0 * sh[0][0], norm2 = sh[1][0] + off2;
+  __syncthreads();
+  sum_tangents(p, problem, false, sh);
+  if (threadIdx.x == 0) {
+    const double now = off2 / norm2, before = p.start_off[problem];
+    const bool held = now < 1e-6 && now > 0.25 * before;
+    int state = 0;
+    if (!(norm2 < 1e76)) state = 2;                              // an infinity or NaN among the inner products
+    else if (sh[0][0] <= small) state = 1;
+    else if (held) state = 3;
+    p.start_done[problem] = state;
+    p.start_off[problem] = now;
+  }
+}
+
+// Vt in 64 bits, the unit matrix where the search came to nothing.
+__global__ __launch_bounds__(256) void start_widen_kernel(PcaDev p, double* __restrict__ out) {
+  const int problem = blockIdx.x / p.Db, i = blockIdx.x - problem * p.Db;
+  const bool none = p.start_done[problem] == 2;
+  const size_t row = static_cast<size_t>(blockIdx.x) * p.Db;
+  for (int j = threadIdx.x; j < p.Db; j += 256) out[row + j] = none ? (i == j ? 1.0 : 0.0) : static_cast<double>(p.Vt[row + j]);
+}
+
+// 64 x 64 tiles of products of fp64 matrices of a problem (fp64 MFMA, a wave per 32 x 32, operands straight from memory, the
+// next 16 of the contraction under way behind the MFMAs of these):
+//   kGram     out[m][n] = sum_r A[m][r] A[n][r]       over a chunk of rows r (blockIdx.y); a row of A is a column of X V
+//   kNorms    out[m][n] = sum_k A[m][k] A[n][k]       and the tile's largest difference from 1; a row of A is one of Vt
+//   kNewton   out[m][n] = 1.5 A[m][n] - 0.5 sum_k W[m][k] A[k][n]      one step towards the nearest orthogonal matrix
+//   kTurn     out[m][n] = A[m][n] - sum_k W[m][k] A[k][n]              (1 + T)^T Vt; A alone where the angles are not small
+//   kProject  out[m][n] = sum_k A[m][k] X[n][k]       columns of X V; n counts rows of X
+// W has rows of Db.  The first two are symmetric: tiles on and above the diagonal are made and stored on both sides.
+enum PcaProduct { kGram, kNorms, kNewton, kTurn, kProject };
+template <PcaProduct MODE>
+__global__ __launch_bounds__(256) void product_kernel(PcaDev p, int problems, const double* __restrict__ A, int64_t lda,
+                                                      const double* __restrict__ W, const _Float16* __restrict__ X, int64_t ldx,
+                                                      int n_cal, double* __restrict__ out, int64_t ldo) {
+  constexpr bool kSymmetric = MODE == kGram || MODE == kNorms, kWeighted = MODE == kNewton || MODE == kTurn;
+  const int half = p.Db / 64;
+  int problem, mt, nt;
+  if constexpr (kSymmetric) {
+    const int tiles = half * (half + 1) / 2, n = blockIdx.x % tiles;
+    problem = blockIdx.x / tiles;
+    const int ti = n / (half + 1), tj = n - ti * (half + 1);      // half is even: rows i and half - 1 - i of the triangle
+    mt = tj < half - ti ? ti : half - 1 - ti;
+    nt = tj < half - ti ? ti + tj : tj - 1;
+  } else {
+    const int rest = blockIdx.x % (problems * half);
+    problem = rest / half;
+    mt = rest % half;
+    nt = blockIdx.x / (problems * half);
+  }
+  if (MODE == kGram && p.done[problem]) return;
+  if (MODE == kProject && p.start_done[problem] == 2) return;      // Z stays as it was
+  const bool turned = MODE == kTurn && !p.done[problem] && p.loose[problem] != 2;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int i16 = lane & 15, q = lane >> 4;
+  const int m0 = 64 * mt + 32 * (wave & 1), n0 = 64 * nt + 32 * (wave >> 1);
+  const double* Ap = A + static_cast<size_t>(problem) * p.Db * lda;
+  const double* Lp = kWeighted ? W + static_cast<size_t>(problem) * p.Db * p.Db : Ap;
+  const int64_t ldl = kWeighted ? p.Db : lda;
+  const int64_t lo = MODE == kGram ? static_cast<int64_t>(blockIdx.y) * p.full_rows : 0;
+  const int64_t hi = MODE == kGram ? min(lo + p.full_rows, static_cast<int64_t>(p.n_pad)) : p.Db;
+  const double *lp[2], *rp[2];
+  const _Float16* xp[2];
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    const int n = n0 + 16 * t + i16;
+    lp[t] = Lp + (m0 + 16 * t + i16) * ldl + 4 * q;
+    rp[t] = kWeighted ? Ap + 4 * q * lda + n : Ap + n * lda + 4 * q;
+    xp[t] = X + min(n, n_cal - 1) * ldx + problem * p.Db + 4 * q;
+  }
+  auto load = [&](int64_t k, doublex4* lf, doublex4* rf) {
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      lf[t] = *reinterpret_cast<const doublex4*>(lp[t] + k);
+      if constexpr (kSymmetric) {
+        rf[t] = *reinterpret_cast<const doublex4*>(rp[t] + k);
+      } else {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) rf[t][s] = kWeighted ? rp[t][(k + s) * lda] : static_cast<double>(xp[t][k + s]);
+      }
+    }
+  };
+  doublex4 acc[2][2], l[2][2], r[2][2];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) acc[i >> 1][i & 1] = doublex4{0.0, 0.0, 0.0, 0.0};
+  auto multiply = [&](const doublex4* lf, const doublex4* rf) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        acc[i >> 1][i & 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(lf[i >> 1][s], rf[i & 1][s], acc[i >> 1][i & 1], 0, 0, 0);
+  };
+  load(lo, l[0], r[0]);
+  for (int64_t k = lo; k < hi; k += 32) {                          // whole 64s
+    load(k + 16, l[1], r[1]);
+    multiply(l[0], r[0]);
+    load(min(k + 32, hi - 16), l[0], r[0]);
+    multiply(l[1], r[1]);
+  }
+  if (MODE == kGram) out += static_cast<size_t>(blockIdx.y) * problems * p.Db * p.Db;
+  double skew = 0.0;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int m = m0 + 16 * (i >> 1) + 4 * e + q, n = n0 + 16 * (i & 1) + i16;
+      double v = acc[i >> 1][i & 1][e];
+      if constexpr (MODE == kNewton) v = 1.5 * Ap[m * lda + n] - 0.5 * v;
+      if constexpr (MODE == kTurn) v = turned ? Ap[m * lda + n] - v : Ap[m * lda + n];
+      if constexpr (MODE == kProject) v = n < n_cal ? v : 0.0;
+      if constexpr (MODE == kNorms) {
+        const double d = fabs(v - (m == n ? 1.0 : 0.0));
+        skew = d <= skew ? skew : d;                               // a NaN stays
+      }
+      // a tile on the diagonal holds both orders of a pair: the upper one counts for both
+      if (kSymmetric && m > n && mt == nt) continue;
+      out[(static_cast<int64_t>(problem) * p.Db + m) * ldo + n] = v;
+      if (kSymmetric && m != n) out[(static_cast<int64_t>(problem) * p.Db + n) * ldo + m] = v;
+    }
+  if constexpr (MODE == kNorms) {
+    __shared__ double red[4];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      const double d = __shfl_xor(skew, o, 64);
+      skew = d <= skew ? skew : d;
+    }
+    if (lane == 0) red[wave] = skew;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      for (int w = 1; w < 4; ++w) skew = red[w] <= skew ? skew : red[w];
+      p.skew[blockIdx.x] = skew;
+    }
   }
 }
 
@@ -524,7 +931,7 @@ static int pca_blocks_device(const void* X_dev, int n_cal, int D, int Db, int64_
   hipStream_t st = static_cast<hipStream_t>(stream);
   const int problems = D / Db, blocks = Db / kPcaBlock, half = blocks / 2, rounds = blocks - 1;
   const int pairs = problems * half;
-  std::vector<int> done(problems);   // before anything is allocated on the device
+  std::vector<int> state(3 * problems);   // done, start_done, loose; before anything is allocated on the device
   PcaDev p{};
   p.n_pad = (n_cal + 63) / 64 * 64;
   p.pitch = p.n_pad + Db;
@@ -533,11 +940,19 @@ static int pca_blocks_device(const void* X_dev, int n_cal, int D, int Db, int64_
   const int want = std::max(1, std::min(kPcaChunks, 512 / pairs));
   p.chunk_rows = ((p.n_pad / 64 + want - 1) / want) * 64;
   p.chunks = (p.n_pad + p.chunk_rows - 1) / p.chunk_rows;
+  const int full_tiles = problems * (Db / 64) * (Db / 64 + 1) / 2;
+  const int full_want = std::max(1, std::min(kPcaChunks, 512 / full_tiles));
+  p.full_rows = ((p.n_pad / 64 + full_want - 1) / full_want) * 64;
+  p.full_chunks = (p.n_pad + p.full_rows - 1) / p.full_rows;
   const size_t sizes[] = {static_cast<size_t>(D) * p.pitch * 8, static_cast<size_t>(pairs) * p.chunks * kPcaTiles * 256 * 8,
                           static_cast<size_t>(pairs) * kPcaPanel * kPcaPanel * 8, static_cast<size_t>(rounds) * pairs * 8,
-                          static_cast<size_t>(pairs) * 8, static_cast<size_t>(problems) * 4, static_cast<size_t>(D) * 8,
+                          static_cast<size_t>(pairs) * 8, static_cast<size_t>(problems) * 12, static_cast<size_t>(D) * 8,
                           static_cast<size_t>(D) * 8, static_cast<size_t>(D) * 8, static_cast<size_t>(D) * 4,
-                          static_cast<size_t>(D) * Db * 4};
+                          static_cast<size_t>(D) * Db * 4,
+                          static_cast<size_t>(p.full_chunks) * D * Db * 8, static_cast<size_t>(D) * Db * 4,
+                          static_cast<size_t>(D) * Db * 4, static_cast<size_t>(D) * Db * 8, static_cast<size_t>(D) * Db * 8,
+                          static_cast<size_t>(problems) * 8, static_cast<size_t>(D) * 8, static_cast<size_t>(D) * 8,
+                          static_cast<size_t>(D / 64) * (Db / 64) * 8};
   constexpr int kParts = sizeof(sizes) / sizeof(sizes[0]);
   size_t offs[kParts], total = 0;
   for (int i = 0; i < kParts; ++i) { offs[i] = total; total += (sizes[i] + 255) / 256 * 256; }
@@ -555,37 +970,131 @@ static int pca_blocks_device(const void* X_dev, int n_cal, int D, int Db, int64_
   double* eig = reinterpret_cast<double*>(mem + offs[8]);
   int* order = reinterpret_cast<int*>(mem + offs[9]);
   float* Q = reinterpret_cast<float*>(mem + offs[10]);
+  p.start_done = p.done + problems;
+  p.loose = p.done + 2 * problems;
+  p.full = reinterpret_cast<double*>(mem + offs[11]);
+  p.G = reinterpret_cast<float*>(mem + offs[12]);
+  p.Vt = reinterpret_cast<float*>(mem + offs[13]);
+  double* const vt = reinterpret_cast<double*>(mem + offs[14]);
+  p.turn = reinterpret_cast<double*>(mem + offs[15]);
+  p.start_off = reinterpret_cast<double*>(mem + offs[16]);
+  p.row_t2 = reinterpret_cast<double*>(mem + offs[17]);
+  p.row_cos = reinterpret_cast<double*>(mem + offs[18]);
+  p.skew = reinterpret_cast<double*>(mem + offs[19]);
 
-  // The first five sweeps are queued without a look at `done`: calibration sets take about ten, and what converges sooner
-  // (one row, orthogonal columns) has its remaining launches return at once.
-  constexpr int kMaxSweeps = 60, kBlindSweeps = 5;
-  constexpr double kTol = 1e-13;
+  auto read = [&] {
+    hipError_t r = hipMemcpyAsync(state.data(), p.done, sizes[5], hipMemcpyDeviceToHost, st);
+    return r == hipSuccess ? hipStreamSynchronize(st) : r;
+  };
+  auto every = [&](auto&& test) {
+    for (int i = 0; i < problems; ++i)
+      if (!test(state[i], state[problems + i], state[2 * problems + i])) return false;
+    return true;
+  };
+  // products of a problem's matrices; see product_kernel
+  auto product = [&](auto* kernel, unsigned grid, unsigned chunks, const double* A, int64_t lda, const double* W, double* to, int64_t ldo) {
+    hipLaunchKernelGGL(kernel, dim3(grid, chunks), dim3(256), 0, st, p, problems, A, lda, W, static_cast<const _Float16*>(X_dev), ldx,
+                       n_cal, to, ldo);
+  };
+  const unsigned tiles = static_cast<unsigned>(problems) * (Db / 64) * (Db / 64);
+  auto full_gram = [&] { product(product_kernel<kGram>, full_tiles, p.full_chunks, p.Z, p.pitch, nullptr, p.full, Db); };
+
+  constexpr int kMaxSweeps = 60, kMaxCorrections = 12, kBlindCorrections = 1;
+  constexpr double kTol = 1e-13, kCosTol = 1e-14;
   bool converged = false;
   e = hipMemsetAsync(p.done, 0, sizes[5], st);
   if (e == hipSuccess) {
     hipLaunchKernelGGL(pca_init_kernel, dim3(static_cast<unsigned>(D / 64) * (p.pitch / 64)), dim3(256), 0, st,
                        static_cast<const _Float16*>(X_dev), ldx, n_cal, p);
+    full_gram();
+    hipLaunchKernelGGL(full_sum_kernel<true>, dim3(D), dim3(256), 0, st, p);
     e = hipGetLastError();
   }
-  for (int sweep = 0; e == hipSuccess && sweep < kMaxSweeps && !converged; ++sweep) {
+  // The search for a rotation to start from.  Calibration sets take five sweeps at least: these are queued without a look
+  // at `start_done`, and what needs fewer (one row, orthogonal columns) has its remaining launches return at once.
+  // A sweep squares the angles like a correction does; of 128 channels it costs as much (120 us), of more three times as much.
+  constexpr int kStartSweeps = 14, kBlindSweeps = 5;
+  const double kSmall = Db <= 256 ? 1e-4 : 0.5;
+  for (int sweep = 0; e == hipSuccess && sweep < kStartSweeps; ++sweep) {
+    for (int r = 0; r < rounds; ++r) {
+      hipLaunchKernelGGL(start_rotate_kernel, dim3(2 * pairs), dim3(kPcaThreads), 0, st, p, r, pairs);
+      hipLaunchKernelGGL(start_apply_kernel, dim3(static_cast<unsigned>(problems) * (half * (half + 1) / 2 + half * half)),
+                         dim3(256), 0, st, p, r);
+    }
+    hipLaunchKernelGGL(tangent_kernel<float>, dim3(D), dim3(256), 0, st, p);
+    hipLaunchKernelGGL(start_check_kernel, dim3(problems), dim3(256), 0, st, p, rounds, half, pairs, kSmall);
+    e = hipGetLastError();
+    if (e != hipSuccess || sweep + 1 < kBlindSweeps) continue;
+    e = read();
+    if (e == hipSuccess && every([](int, int start, int) { return start != 0; })) break;
+  }
+  // V, the rows of the right part of Z, towards the nearest orthogonal matrix
+  auto newton = [&](const double* A, int64_t lda, double* to, int64_t ldo) {
+    product(product_kernel<kNorms>, full_tiles, 1, A, lda, nullptr, p.full, Db);
+    product(product_kernel<kNewton>, tiles, 1, A, lda, p.full, to, ldo);
+  };
+  double* const zv = p.Z + p.n_pad;
+  auto project = [&] {
+    product(product_kernel<kProject>, static_cast<unsigned>(D / 64) * (p.n_pad / 64), 1, zv, p.pitch, nullptr, p.Z, p.pitch);
+  };
+  if (e == hipSuccess) {
+    hipLaunchKernelGGL(start_widen_kernel, dim3(D), dim3(256), 0, st, p, vt);
+    newton(vt, Db, p.turn, Db);
+    newton(p.turn, Db, zv, p.pitch);
+    project();
+    e = hipGetLastError();
+  }
+  // All pairs at once while the angles are small, else a sweep.
+  const int blind = every([](int, int start, int) { return start == 1; }) ? kBlindCorrections : 0;
+  int sweeps = 0, corrections = 0;
+  bool corrected = false;
+  while (e == hipSuccess && sweeps < kMaxSweeps && !converged) {
+    bool sweep = corrections >= kMaxCorrections, last = false;
+    if (!sweep) {
+      full_gram();
+      hipLaunchKernelGGL(full_sum_kernel<false>, dim3(D), dim3(256), 0, st, p);
+      hipLaunchKernelGGL(tangent_kernel<double>, dim3(D), dim3(256), 0, st, p);
+      hipLaunchKernelGGL(tangent_check_kernel, dim3(problems), dim3(256), 0, st, p, kCosTol);
+      e = hipGetLastError();
+      if (e == hipSuccess && corrections >= blind) {
+        e = read();
+        converged = every([](int d, int, int loose) { return d == 1 || (d == 0 && loose == 0); });
+        sweep = !every([](int d, int, int loose) { return d == 1 || loose != 2; });
+        last = every([](int d, int, int loose) { return d == 1 || (d == 0 && (loose == 0 || loose == 3)); });
+      }
+      if (e != hipSuccess || converged) break;
+    }
+    if (!sweep) {
+      product(product_kernel<kTurn>, tiles, 1, zv, p.pitch, p.turn, vt, Db);
+      newton(vt, Db, zv, p.pitch);
+      project();
+      e = hipGetLastError();
+      ++corrections;
+      corrected = true;
+      converged = last;
+      continue;
+    }
+    if (corrected) {                               // a sweep keeps V as orthogonal as it is
+      for (int i = 0; i < 4; ++i) {
+        newton(i & 1 ? vt : zv, i & 1 ? Db : p.pitch, i & 1 ? zv : vt, i & 1 ? p.pitch : Db);
+      }
+      project();
+      corrected = false;
+    }
     for (int r = 0; r < rounds && e == hipSuccess; ++r) {
       hipLaunchKernelGGL(gram_kernel, dim3(pairs, p.chunks), dim3(256), 0, st, p, r);
-      hipLaunchKernelGGL(rotate_kernel, dim3(pairs), dim3(1024), 0, st, p, r, pairs);
+      hipLaunchKernelGGL(rotate_kernel, dim3(2 * pairs), dim3(kPcaThreads), 0, st, p, r, pairs);
       hipLaunchKernelGGL(apply_kernel, dim3(static_cast<unsigned>(pairs) * (p.pitch / 64)), dim3(256), 0, st, p, r, pairs);
       e = hipGetLastError();
     }
+    ++sweeps;
     if (e != hipSuccess) break;
     hipLaunchKernelGGL(pca_check_kernel, dim3(problems), dim3(256), 0, st, p, rounds, half, pairs, kTol);
     e = hipGetLastError();
-    if (e != hipSuccess || sweep + 1 < kBlindSweeps) continue;
-    e = hipMemcpyAsync(done.data(), p.done, sizes[5], hipMemcpyDeviceToHost, st);
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    if (e == hipSuccess) e = read();
     if (e != hipSuccess) break;
-    converged = true;
-    for (int v : done) {
-      if (v == 2) { e = hipErrorUnknown; break; }
-      if (v == 0) converged = false;
-    }
+    if (!every([](int d, int, int) { return d != 2; })) e = hipErrorUnknown;
+    converged = every([](int d, int, int) { return d == 1; });
   }
   if (e == hipSuccess && converged) {
     hipLaunchKernelGGL(pca_norms_kernel, dim3(D), dim3(256), 0, st, p, n_cal, lam, sign);
