@@ -370,6 +370,13 @@ static bool rotates_whole_heads(int D, int M) {
   return g_tune_rot.wide == 2 ? M > kMBlock : (g_tune_rot.wide == 0 && M > kMBlock && head_blocks > 160);
 }
 
+// Whether the dense rotation reads row-major x itself, without a copy into fragments in front of it.  That saves a launch (1.5
+// us in a graph, more where the host issues it), but its loads then take 64 bytes of each of 16 rows where those of fragments
+// take 1 KiB in a row, which costs more the more of them there are.  us of a call with 512 channels behind the rotation,
+// copy / in place: 1024 channels at 17 rows 9.5 / 7.9, at 64 9.7 / 8.3; 1408 at 37 10.9 / 9.5; 2048 at 64 12.6 / 11.0; 4096 at 24 17.5 /
+// 15.7, at 48 19.7 / 19.3, at 64 19.9 / 21.1; 5120 at 24 25.9 / 25.9, at 32 26.3 / 28.8, at 37 27.4 / 24.9, at 64 28.2 / 29.9.
+static bool rotates_in_place(int D, int M) { return M <= (D <= 2048 ? 64 : (D <= 4096 ? 48 : 16)); }
+
 // x -> xhat fragments in the workspace (gather / head-wise blocks / dense rotation).
 static int run_prologue(const rosaq_packed_t* p, const WsPlan& w, const void* x_dev, int M,
                         int64_t ldx, char* ws, size_t ws_bytes, int n_tickets, void* hip_stream) {
@@ -398,8 +405,8 @@ static int run_prologue(const rosaq_packed_t* p, const WsPlan& w, const void* x_
   // storage order
   GemmArgs a{};
   a.xf = ws + w.xf_a;
-  if (M <= 16) {
-    a.xrow = x_dev;        // skinny input: the rotation reads x in place, no fragment copy
+  if (rotates_in_place(c.D, M)) {
+    a.xrow = x_dev;
     a.ldx = ldx;
     // no launch in front of the rotation: it runs unsplit and clears the main GEMM's tickets itself
     a.zero_ptr = n_tickets ? tickets : nullptr;
