@@ -424,11 +424,26 @@ static int run_prologue(const rosaq_packed_t* p, const WsPlan& w, const void* x_
   return launch_gemm(a, plan_gemm(a, rotation_tune()), hip_stream);
 }
 
+// Whether an output of the call lies in the memory between x's first and last element.
+static bool overlaps(const GemmArgs& a, const void* x_dev, int M, int64_t ldx) {
+  const uintptr_t x0 = reinterpret_cast<uintptr_t>(x_dev), x1 = x0 + 2 * (static_cast<uint64_t>(M - 1) * ldx + static_cast<uint64_t>(a.KS) * kKStep);
+  for (int i = 0; i < a.nseg; ++i) {
+    const uintptr_t y0 = reinterpret_cast<uintptr_t>(a.seg[i].out), y1 = y0 + 2 * (static_cast<uint64_t>(M - 1) * a.seg[i].ldo + a.seg[i].N);
+    if (x0 < y1 && y0 < x1) return true;
+  }
+  return false;
+}
+
 static int run_call(const rosaq_packed_t* const* ps, int count, const void* x_dev, int M,
                     int64_t ldx, void* const* ys, const int64_t* ldys, char* ws, size_t ws_bytes,
                     const WsPlan& w, void* hip_stream, bool swiglu = false) {
   const GemmArgs a = main_gemm(ps, count, plan_io(*ps[0], w, ws, ws_bytes), M, ys, ldys, swiglu);
   const GemmPlan plan = plan_gemm(a, g_tune);
+  const rosaq_packed& p0 = *ps[0];
+  // in one launch, x is read while outputs are stored: not where they share memory
+  if (p0.c.q_mode == ROSAQ_Q_HEADWISE && g_tune_stages == 3 && g_tune_rot.wide == 0 && !overlaps(a, x_dev, M, ldx) &&
+      fuses_rotation(a, plan, hip_stream))
+    return launch_rotate_gemm(a, x_dev, ldx, p0.d_qf, p0.d_pos, hip_stream);
   const int n_tickets = ticket_words(plan);
   int rc = ROSAQ_OK;
   if (g_tune_stages & 1)

@@ -124,6 +124,9 @@ struct GemmPlan {
 };
 GemmPlan plan_gemm(const GemmArgs& a, const GemmTune& tune);
 int launch_gemm(const GemmArgs& a, const GemmPlan& plan, void* stream);
+// The head-wise rotation of a few rows inside the GEMM's launch: whether it pays for what `plan` would run, and the launch.
+bool fuses_rotation(const GemmArgs& a, const GemmPlan& plan, void* stream);
+int launch_rotate_gemm(const GemmArgs& a, const void* x, int64_t ldx, const void* qh, const int32_t* pos_dev, void* stream);
 // Whether plan_gemm takes the kernel for many rows (128 x 256 tiles).
 bool prefers_wide(int M, int ntiles, int D, int K, int bits, const GemmTune& tune);
 // Host copy of the kernel's workgroup -> (channel chunk, row group) map: b < 0 returns the grid

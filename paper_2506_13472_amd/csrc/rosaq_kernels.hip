@@ -66,6 +66,9 @@ __device__ __forceinline__ SegArgs seg_args() {
   return (SegArgs)(args + offsetof(GemmDev, seg));
 }
 
+// Of rotate_gemm_kernel: sixteen waves, two for each head.
+constexpr int kFusedWaves = 16, kFusedHeads = kFusedWaves / 2;
+
 // Store one accumulator fragment of row tile `mtile` (16 rows) and channel tile T of the
 // launch's tile list: lane holds rows 4*(lane/16)+i, column lane%16.
 __device__ __forceinline__ void store_fragment(const GemmDev& p, float4 v, int mtile, int T, int lane) {
@@ -650,6 +653,103 @@ __global__ __launch_bounds__(256) void rotate_headwise_kernel(
   clear();
 }
 
+// Rotation and GEMM of a small head-wise layer and up to 16 rows in one launch: every workgroup, a 16 x 16 tile of the output,
+// rotates all of x for itself into LDS while the weights of its sixteen waves are under way, and goes on as
+// gemm_kernel<BITS, 1, 1, 16, 1> does, in the same order (the outputs are the same to the bit).  That repeats the rotation in
+// every workgroup, 32 KiB of Q per head from L2 (0.3 us; the lines a compute unit can have under way are what bounds it), so it
+// pays while heads and workgroups are few (fuses_rotation).  It saves a launch: 1.4 us in a graph, 3.3 us where the host issues it.
+// x goes through LDS a row per wave: as fragments from memory, each wave 64 bytes of 16 rows at a time, 16 rows of 1024 channels took
+// 0.6 us more.
+template <int BITS>
+__global__ __launch_bounds__(kFusedWaves * 64) void rotate_gemm_kernel(GemmDev p, int64_t ldx, int H, const uint4* __restrict__ qh,
+                                                                       const int32_t* __restrict__ pos) {
+  __shared__ __attribute__((aligned(16))) _Float16 xs[kFusedHeads * 4][64][8];   // [k-step][lane], as in memory
+  __shared__ float4 red[kFusedWaves][64];
+  __shared__ __attribute__((aligned(16))) _Float16 rows[16][kFusedHeads * kHeadDim + 8];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  int si, tile;
+  locate_tile(p, blockIdx.x, si, tile);
+  const GemmSeg sg = pick_seg(p, si);
+  constexpr int kCodeDwords = BITS == 4 ? 256 : 192, kRecDwords = kCodeDwords + 16;
+  // a wave's units: fp16 k-steps wave and wave + 16 (there are at most 32 and a group), and one low-bit group
+  const int g = (wave - p.ks_s) & (kFusedWaves - 1);
+  const uint4* const bs = sg.wS + static_cast<size_t>(tile) * p.ks_s * 64 + lane;
+  const uint32_t* const rec = sg.wq + (static_cast<size_t>(tile) * p.G + min(g, p.G - 1)) * kRecDwords;
+  uint4 b0 = make_uint4(0, 0, 0, 0), b1 = b0;
+  if (wave < p.ks_s) b0 = bs[wave * 64];
+  if (wave + kFusedWaves < p.ks_s) b1 = bs[(wave + kFusedWaves) * 64];
+  uint32_t cw[4] = {};
+  if (BITS == 4) {
+    const uint4 c = reinterpret_cast<const uint4*>(rec)[lane];
+    cw[0] = c.x; cw[1] = c.y; cw[2] = c.z; cw[3] = c.w;
+  } else {
+    const Code3 c = reinterpret_cast<const Code3*>(rec)[lane];
+    cw[0] = c.w0; cw[1] = c.w1; cw[2] = c.w2;
+  }
+  const half2v sz = as_h2(rec[kCodeDwords + (lane & 15)]);
+  // a wave's row of x (rows past M: whatever LDS holds, which only enters output rows that are not stored)
+  if (wave < p.M)
+    for (int c = 8 * lane; c < H * kHeadDim; c += 512)
+      *reinterpret_cast<uint4*>(&rows[wave][c]) = *reinterpret_cast<const uint4*>(p.xrow + wave * ldx + c);
+  // rotation: a wave takes half a head, four column tiles
+  const int h = wave >> 1;
+  uint4 q[4][4];
+  int at[4];
+  if (h < H)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int ct = 4 * (wave & 1) + j;
+      at[j] = (pos + h * kHeadDim + ct * 16)[lane & 15];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) q[j][t] = (qh + (static_cast<size_t>(h * 8 + ct) * 4 + t) * 64)[lane];
+    }
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");   // (a __syncthreads() would wait for Q and the weights)
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+  if (h < H) {
+    uint4 a[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) a[t] = *reinterpret_cast<const uint4*>(&rows[lane & 15][h * kHeadDim + t * kKStep + 8 * (lane >> 4)]);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      floatx4 v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int t = 0; t < 4; ++t) v = mfma16(as_h8(a[t]), as_h8(q[j][t]), v);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) xs[at[j] >> 5][4 * (lane >> 4) + i + 16 * ((at[j] >> 3) & 3)][at[j] & 7] = static_cast<_Float16>(v[i]);
+    }
+  }
+  __syncthreads();
+  auto xa = [&](int ks) { return *reinterpret_cast<const half8*>(&xs[ks][lane][0]); };
+  floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+  if (wave < p.ks_s) acc = mfma16(xa(wave), as_h8(b0), acc);
+  if (wave + kFusedWaves < p.ks_s) acc = mfma16(xa(wave + kFusedWaves), as_h8(b1), acc);
+  if (g < p.G) {
+    const _Float16 z = sz.y, clo = -(z + (_Float16)1024.0f), chi = -(z + (_Float16)64.0f);
+    const Dq3 k3 = dq3_consts(z);
+    floatx4 tmp = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      half8 b;
+      if (BITS == 4) b = dequant4(cw[t], half2v{clo, clo}, half2v{chi, chi});
+      else b = dequant3(cw[0], cw[1], cw[2], t, k3);
+      tmp = mfma16(xa(p.ks_s + 4 * g + t), b, tmp);
+    }
+    acc += static_cast<float>(sz.x) * tmp;
+  }
+  red[wave][lane] = make_float4(acc[0], acc[1], acc[2], acc[3]);
+  __syncthreads();
+  if (wave != 0) return;
+  float4 v = red[0][lane];
+#pragma unroll
+  for (int w = 1; w < kFusedWaves; ++w) {
+    const float4 o = red[w][lane];
+    v.x += o.x; v.y += o.y; v.z += o.z; v.w += o.w;
+  }
+  store_fragment(p, v, 0, blockIdx.x, lane);
+}
+
 // The tickets of a split GEMM launch without a launch in front of it (tuning aid "stages" = 2).
 __global__ __launch_bounds__(256) void clear_kernel(unsigned* p, int count) {
   for (int i = blockIdx.x * 256 + threadIdx.x; i < count; i += gridDim.x * 256) p[i] = 0u;
@@ -1070,6 +1170,40 @@ int launch_gemm(const GemmArgs& a, const GemmPlan& plan, void* stream) {
   d.mgroups = ((a.M + 15) / 16 + plan.shape.mt - 1) / plan.shape.mt;
   d.splits = plan.shape.splits;
   return plan.run(d, stream);
+}
+
+static bool is_captured(void* stream) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(static_cast<hipStream_t>(stream), &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();       // the default stream while another one is captured: the launch says so itself
+  return true;
+}
+
+// Up to 16 rows, as gemm_kernel would take them in 16 x 16 tiles of sixteen waves.  us a call, two launches / one, 1 and 16 rows: in
+// a graph 256 -> 2048 channels 5.1 / 3.6 and 5.3 / 3.9, 512 -> 1024 5.3 / 4.6 and 5.6 / 5.1, 512 -> 4096 5.7 / 5.2 and 5.8 / 5.6, but
+// 1024 -> 1024 5.6 / 6.5 and 5.9 / 7.2; called eagerly, where the host's second launch is what takes the time, 8.6 to 8.9 / 5.4 to 5.7 up to
+// 512 channels and 8.6 / 5.7 and 8.7 / 6.0 for 1024 -> 1024.  So up to 512 channels always, up to 1024 unless the call is captured.
+bool fuses_rotation(const GemmArgs& a, const GemmPlan& plan, void* stream) {
+  int tiles = 0;
+  for (int i = 0; i < a.nseg; ++i) tiles += (a.seg[i].N + kTileN - 1) / kTileN;
+  const GemmShape& s = plan.shape;
+  return !plan.wide && !a.swiglu && a.out_frag == 0 && a.zero_ptr == nullptr && a.M <= kTileN && a.G > 0 && a.KS <= kFusedHeads * 4 &&
+         tiles <= 256 && s.mt == 1 && s.nt == 1 && s.wpb == kFusedWaves && s.splits == 1 &&
+         (a.KS <= kFusedHeads * 2 || !is_captured(stream));
+}
+
+int launch_rotate_gemm(const GemmArgs& a, const void* x, int64_t ldx, const void* qh, const int32_t* pos_dev, void* stream) {
+  int tiles;
+  GemmDev d = fill_dev(a, &tiles);
+  d.xrow = static_cast<const _Float16*>(x);
+  const dim3 grid(tiles), block(kFusedWaves * 64);
+  const int H = a.KS * kKStep / kHeadDim;
+  if (a.bits == 4)
+    hipLaunchKernelGGL(rotate_gemm_kernel<4>, grid, block, 0, static_cast<hipStream_t>(stream), d, ldx, H, static_cast<const uint4*>(qh), pos_dev);
+  else
+    hipLaunchKernelGGL(rotate_gemm_kernel<3>, grid, block, 0, static_cast<hipStream_t>(stream), d, ldx, H, static_cast<const uint4*>(qh), pos_dev);
+  const hipError_t e = hipGetLastError();
+  return e == hipSuccess ? ROSAQ_OK : hip_fail(e, "rotate_gemm_kernel launch");
 }
 
 int launch_stream_probe(const void* src, const void* shared, int workgroups, int threads, int w_kib,
