@@ -17,6 +17,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "rosaq_gemm.h"
 #include "rosaq_internal.h"
@@ -237,7 +238,7 @@ void gemm_kernel(GemmDev p) {
   // is then the same whatever the tile of eight waves or the batching of an unsplit launch of this
   // kernel (starting each workgroup at its own group was measured: 1-3 % faster, not worth that
   // property).  Splits, sixteen waves and wide_gemm_kernel add in other orders.
-  auto load_group = [&](int g, GroupRegs& r) {
+  auto load_codes = [&](int g, GroupRegs& r) {
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
       constexpr int kCodeDwords = BITS == 4 ? 256 : 192, kRecDwords = kCodeDwords + 16;
@@ -252,6 +253,9 @@ void gemm_kernel(GemmDev p) {
       }
       r.sz[nt] = (rec + kCodeDwords)[lane & 15];
     }
+  };
+  auto load_group = [&](int g, GroupRegs& r) {
+    load_codes(g, r);
     const uint4* const x0 = xa + static_cast<unsigned>(ks_s + 4 * g) * 256u;
 #pragma unroll
     for (int t = 0; t < 4; ++t)
@@ -364,6 +368,9 @@ void gemm_kernel(GemmDev p) {
         compute_step(s0);
       }
   } else {
+  // 64 x 48 tiles: k-steps outside, channel tiles inside, so that a k-step's fragments of xhat are free for those of the next
+  // group as soon as it is multiplied: a wave keeps three quarters of a group under way while it computes.
+  constexpr bool kRefill = MT > 1 && WPB == 8 && DEPTH == 1 && 8 * MT * NT + 16 * MT + 10 * NT <= 200;
   int u = u_lo + wave;
   int g = g_lo + ((wave - (u_hi - u_lo)) & (WPB - 1));   // unit ks_s + g belongs to wave (ks_s + g) % WPB
   StepRegs s0, s1;
@@ -381,6 +388,59 @@ void gemm_kernel(GemmDev p) {
       if (u + 3 * WPB < u_hi) load_step(u + 3 * WPB, s1);
     }
   }
+  if constexpr (kRefill) {
+    auto round = [&](auto more, GroupRegs& c, GroupRegs& n) {
+      constexpr bool kMore = decltype(more)::value;
+      if constexpr (kMore) load_codes(g + WPB, n);
+      floatx4 tmp[NT][MT];
+      const uint4* const x1 = xa + static_cast<unsigned>(ks_s + 4 * (g + WPB)) * 256u;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+          const _Float16 z = as_h2(c.sz[nt]).y;
+          half8 b;
+          if (BITS == 4) {
+            const _Float16 clo = -(z + (_Float16)1024.0f), chi = -(z + (_Float16)64.0f);
+            b = dequant4(c.cw[nt][t], half2v{clo, clo}, half2v{chi, chi});
+          } else {
+            b = dequant3(c.cw[nt][0], c.cw[nt][1], c.cw[nt][2], t, dq3_consts(z));
+          }
+#pragma unroll
+          for (int mt = 0; mt < MT; ++mt) {
+            if (t == 0) tmp[nt][mt] = floatx4{0.f, 0.f, 0.f, 0.f};
+            tmp[nt][mt] = mfma16(as_h8(r[0].a[t][mt]), b, tmp[nt][mt]);
+          }
+        }
+        if constexpr (kMore) {
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int mt = 0; mt < MT; ++mt) r[0].a[t][mt] = (x1 + t * 256 + mt * 64)[lane];
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) acc[nt][mt] += static_cast<float>(as_h2(c.sz[nt]).x) * tmp[nt][mt];
+      g += WPB;
+    };
+    GroupRegs other;
+    if (g < g_hi) {
+      __builtin_amdgcn_s_waitcnt(0x0f70);       // vmcnt(0): the compiler's count of loads under way then is that of the loop alone
+      while (g + 2 * WPB < g_hi) {
+        round(std::true_type{}, r[0], other);
+        round(std::true_type{}, other, r[0]);
+      }
+      if (g + WPB < g_hi) {
+        round(std::true_type{}, r[0], other);
+        round(std::false_type{}, other, r[0]);
+      } else {
+        round(std::false_type{}, r[0], other);
+      }
+    }
+  } else
   for (; g < g_hi; g += DEPTH * WPB) {
 #pragma unroll
     for (int d = 0; d < DEPTH; ++d) {
