@@ -107,7 +107,10 @@ struct GemmArgs {
 };
 constexpr int kMaxSplits = 16;
 constexpr int kTicketsPerLaunch = 4096;   // ticket words per GEMM launch kept in the workspace
-struct GemmTune { int mt = 0, nt = 0, wpb = 0, depth = 0, splits = 0, wide = 0; };   // 0 = heuristic
+struct GemmTune {               // 0 = heuristic
+  int mt = 0, nt = 0, wpb = 0, depth = 0, splits = 0, wide = 0;
+  bool gated = false;           // a gated pair: channel tiles in twos
+};
 struct GemmShape { int mt, nt, wpb, depth, splits; };
 // `part_bytes` / `ticket_count`: what the caller can offer for split-K (0 = never split)
 GemmShape pick_gemm_shape(int M, int ntiles, int D, int bits, const GemmTune& tune,

@@ -238,9 +238,7 @@ void gemm_kernel(GemmDev p) {
   // is then the same whatever the tile of eight waves or the batching of an unsplit launch of this
   // kernel (starting each workgroup at its own group was measured: 1-3 % faster, not worth that
   // property).  Splits, sixteen waves and wide_gemm_kernel add in other orders.
-  auto load_codes = [&](int g, GroupRegs& r) {
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
+  auto load_code = [&](int g, GroupRegs& r, int nt) {
       constexpr int kCodeDwords = BITS == 4 ? 256 : 192, kRecDwords = kCodeDwords + 16;
       const uint32_t* rec = wq_t[nt] + static_cast<unsigned>(g) * static_cast<unsigned>(kRecDwords);
       if (BITS == 4) {
@@ -252,7 +250,10 @@ void gemm_kernel(GemmDev p) {
         r.cw[nt][3] = 0;
       }
       r.sz[nt] = (rec + kCodeDwords)[lane & 15];
-    }
+  };
+  auto load_codes = [&](int g, GroupRegs& r) {
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) load_code(g, r, nt);
   };
   auto load_group = [&](int g, GroupRegs& r) {
     load_codes(g, r);
@@ -265,7 +266,7 @@ void gemm_kernel(GemmDev p) {
         if (row_ok) r.a[t][mt] = (x0 + t * 256 + mt * 64)[lane];
       }
   };
-  auto compute_group = [&](const GroupRegs& r) {
+  auto compute_group = [&](const GroupRegs& r, const GroupRegs& x) {         // codes and activations
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
       const half2v sz2 = as_h2(r.sz[nt]);
@@ -284,7 +285,7 @@ void gemm_kernel(GemmDev p) {
         if (BITS == 4) b = dequant4(r.cw[nt][t], c_lo, c_hi);
         else b = dequant3(r.cw[nt][0], r.cw[nt][1], r.cw[nt][2], t, k3);
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) tmp[mt] = mfma16(as_h8(r.a[t][mt]), b, tmp[mt]);
+        for (int mt = 0; mt < MT; ++mt) tmp[mt] = mfma16(as_h8(x.a[t][mt]), b, tmp[mt]);
       }
       // the group scale is applied once per 128 channels, in fp32
 #pragma unroll
@@ -368,17 +369,24 @@ void gemm_kernel(GemmDev p) {
         compute_step(s0);
       }
   } else {
-  // 64 x 48 tiles: k-steps outside, channel tiles inside, so that a k-step's fragments of xhat are free for those of the next
-  // group as soon as it is multiplied: a wave keeps three quarters of a group under way while it computes.
-  constexpr bool kRefill = MT > 1 && WPB == 8 && DEPTH == 1 && 8 * MT * NT + 16 * MT + 10 * NT <= 200;
+  // The one-deep tiles fetch ahead: k-steps outside, channel tiles inside, so that a k-step's fragments of xhat are free for those
+  // of the wave's next group as soon as it is multiplied, and most of a group is under way while one is multiplied.  That takes
+  // the sums of all channel tiles of a group in registers.  The order of every addition is that of compute_group.  us, a group at a time /
+  // ahead: 8 attention blocks of 64 rows 251 / 237 (one layer of 4096 8.4 / 7.8), 4 decoder layers of 64 359 / 352.
+  // 64 x 80 tiles have no registers for that: half a group at a time, codes fetched again behind their last use.  (A group's two halves
+  // are scaled and added one by one: outputs that are not the correctly rounded sum 6.0e-4 -> 6.7e-4 of 5120 channels, 7.5e-4 -> 8.6e-4
+  // of 13824, wide_gemm_kernel 10.3e-4; the error of the outputs is the same to seven digits, 2.076507e-4 and 2.070580e-4 of the norm.)
+  constexpr bool kAhead = MT > 1 && WPB == 8 && DEPTH == 1 && (8 * MT * NT + 16 * MT + 10 * NT <= 200 || NT == 5);
+  constexpr int kSteps = NT == 5 ? 2 : 4;
   int u = u_lo + wave;
   int g = g_lo + ((wave - (u_hi - u_lo)) & (WPB - 1));   // unit ks_s + g belongs to wave (ks_s + g) % WPB
   StepRegs s0, s1;
-  GroupRegs r[DEPTH];
+  constexpr int kDepth = DEPTH == 0 ? 1 : DEPTH;
+  GroupRegs r[kDepth];
   if (u < u_hi) load_step(u, s0);
   if (u + WPB < u_hi) load_step(u + WPB, s1);
 #pragma unroll
-  for (int d = 0; d < DEPTH; ++d)
+  for (int d = 0; d < kDepth; ++d)
     if (g + d * WPB < g_hi) load_group(g + d * WPB, r[d]);
   for (; u < u_hi; u += 2 * WPB) {
     compute_step(s0);
@@ -388,65 +396,109 @@ void gemm_kernel(GemmDev p) {
       if (u + 3 * WPB < u_hi) load_step(u + 3 * WPB, s1);
     }
   }
-  if constexpr (kRefill) {
+  if constexpr (kAhead) {
     auto round = [&](auto more, GroupRegs& c, GroupRegs& n) {
       constexpr bool kMore = decltype(more)::value;
-      if constexpr (kMore) load_codes(g + WPB, n);
-      floatx4 tmp[NT][MT];
+      if constexpr (kMore && kSteps == 4) load_codes(g + WPB, n);
       const uint4* const x1 = xa + static_cast<unsigned>(ks_s + 4 * (g + WPB)) * 256u;
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-          const _Float16 z = as_h2(c.sz[nt]).y;
-          half8 b;
-          if (BITS == 4) {
-            const _Float16 clo = -(z + (_Float16)1024.0f), chi = -(z + (_Float16)64.0f);
-            b = dequant4(c.cw[nt][t], half2v{clo, clo}, half2v{chi, chi});
-          } else {
-            b = dequant3(c.cw[nt][0], c.cw[nt][1], c.cw[nt][2], t, dq3_consts(z));
-          }
-#pragma unroll
-          for (int mt = 0; mt < MT; ++mt) {
-            if (t == 0) tmp[nt][mt] = floatx4{0.f, 0.f, 0.f, 0.f};
-            tmp[nt][mt] = mfma16(as_h8(r[0].a[t][mt]), b, tmp[nt][mt]);
-          }
+      auto weights = [&](int nt, int t) {
+        const _Float16 z = as_h2(c.sz[nt]).y;
+        if (BITS == 4) {
+          const _Float16 clo = -(z + (_Float16)1024.0f), chi = -(z + (_Float16)64.0f);
+          return dequant4(c.cw[nt][t], half2v{clo, clo}, half2v{chi, chi});
         }
-        if constexpr (kMore) {
+        return dequant3(c.cw[nt][0], c.cw[nt][1], c.cw[nt][2], t, dq3_consts(z));
+      };
+      auto refill = [&](int t) {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) r[0].a[t][mt] = (x1 + t * 256 + mt * 64)[lane];
+      };
+      if constexpr (kSteps == 4) {
+        floatx4 tmp[NT][MT];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
           __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-          for (int mt = 0; mt < MT; ++mt) r[0].a[t][mt] = (x1 + t * 256 + mt * 64)[lane];
+          for (int nt = 0; nt < NT; ++nt) {
+            const half8 b = weights(nt, t);
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) {
+              if (t == 0) tmp[nt][mt] = floatx4{0.f, 0.f, 0.f, 0.f};
+              tmp[nt][mt] = mfma16(as_h8(r[0].a[t][mt]), b, tmp[nt][mt]);
+            }
+          }
+          __builtin_amdgcn_sched_barrier(0);
+          if constexpr (kMore) refill(t);
         }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+          for (int mt = 0; mt < MT; ++mt) acc[nt][mt] += static_cast<float>(as_h2(c.sz[nt]).x) * tmp[nt][mt];
+      } else {
+#pragma unroll
+        for (int t = 0; t < 4; t += 2) {
+          floatx4 tmp[2][MT];
+          float scale[2];
+#pragma unroll
+          for (int nt = 0; nt <= NT; ++nt) {
+            __builtin_amdgcn_sched_barrier(0);
+            if (nt < NT) {
+              const half8 b0 = weights(nt, t), b1 = weights(nt, t + 1);
+              scale[nt & 1] = static_cast<float>(as_h2(c.sz[nt]).x);
+#pragma unroll
+              for (int mt = 0; mt < MT; ++mt) tmp[nt & 1][mt] = mfma16(as_h8(r[0].a[t][mt]), b0, floatx4{0.f, 0.f, 0.f, 0.f});
+#pragma unroll
+              for (int mt = 0; mt < MT; ++mt) tmp[nt & 1][mt] = mfma16(as_h8(r[0].a[t + 1][mt]), b1, tmp[nt & 1][mt]);
+            }
+            if (nt > 0) {
+#pragma unroll
+              for (int mt = 0; mt < MT; ++mt) acc[nt - 1][mt] += scale[(nt - 1) & 1] * tmp[(nt - 1) & 1][mt];
+            }
+            if (kMore && nt < NT && t == 2) {
+              __builtin_amdgcn_sched_barrier(0);
+              load_code(g + WPB, c, nt);
+            }
+          }
+          __builtin_amdgcn_sched_barrier(0);
+          if constexpr (kMore) { refill(t); refill(t + 1); }
+        }
+        __builtin_amdgcn_sched_barrier(0);
       }
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) acc[nt][mt] += static_cast<float>(as_h2(c.sz[nt]).x) * tmp[nt][mt];
       g += WPB;
     };
     GroupRegs other;
     if (g < g_hi) {
-      __builtin_amdgcn_s_waitcnt(0x0f70);       // vmcnt(0): the compiler's count of loads under way then is that of the loop alone
-      while (g + 2 * WPB < g_hi) {
-        round(std::true_type{}, r[0], other);
-        round(std::true_type{}, other, r[0]);
-      }
-      if (g + WPB < g_hi) {
-        round(std::true_type{}, r[0], other);
-        round(std::false_type{}, other, r[0]);
+      if constexpr (kSteps == 4) {
+        if (g + 2 * WPB < g_hi) {
+          __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): the compiler's count of loads under way then is that of the loop alone
+          do {
+            round(std::true_type{}, r[0], other);
+            round(std::true_type{}, other, r[0]);
+          } while (g + 2 * WPB < g_hi);
+        }
+        if (g + WPB < g_hi) {
+          round(std::true_type{}, r[0], other);
+          compute_group(other, r[0]);
+        } else {
+          compute_group(r[0], r[0]);
+        }
       } else {
-        round(std::false_type{}, r[0], other);
+        if (g + WPB < g_hi) {
+          __builtin_amdgcn_s_waitcnt(0x0f70);
+          do round(std::true_type{}, r[0], r[0]);
+          while (g + WPB < g_hi);
+        }
+        round(std::false_type{}, r[0], r[0]);
       }
     }
   } else
-  for (; g < g_hi; g += DEPTH * WPB) {
+  for (; g < g_hi; g += kDepth * WPB) {
 #pragma unroll
-    for (int d = 0; d < DEPTH; ++d) {
+    for (int d = 0; d < kDepth; ++d) {
       if (g + d * WPB < g_hi) {
-        compute_group(r[d]);
-        if (g + (d + DEPTH) * WPB < g_hi) load_group(g + (d + DEPTH) * WPB, r[d]);
+        compute_group(r[d], r[d]);
+        if (g + (d + kDepth) * WPB < g_hi) load_group(g + (d + kDepth) * WPB, r[d]);
       }
     }
   }
@@ -866,7 +918,12 @@ static int launch_gemm_t(const GemmDev& d, void* stream) {
   // many rows).  Split launches have at most 64 rows and kTicketsPerLaunch tiles, so always this grid.
   g.grid3 = d.mgroups <= kMapRows && octets <= 65535;
   const dim3 grid = g.grid3 ? dim3(8, splits * d.mgroups, octets) : dim3(map_grid(d.chunks, d.mgroups));
-  hipLaunchKernelGGL((gemm_kernel<BITS, MT, NT, WPB, DEPTH>), grid, dim3(WPB * 64), 0, static_cast<hipStream_t>(stream), g);
+  auto kernel = gemm_kernel<BITS, MT, NT, WPB, DEPTH>;
+  // 64 x 48 tiles of up to two groups a wave (DEPTH 0: one at a time) have little to fetch ahead, and their last group waits for all of it
+  // either way: 2048 -> 12288 at 64 rows 9.5 us, 9.8 ahead; 2432 -> 6605 at 173 15.8 / 16.0.
+  if constexpr (BITS != 16 && MT == 4 && NT == 3 && WPB == 8 && DEPTH == 1)
+    if (d.G <= 2 * WPB) kernel = gemm_kernel<BITS, MT, NT, WPB, 0>;
+  hipLaunchKernelGGL(kernel, grid, dim3(WPB * 64), 0, static_cast<hipStream_t>(stream), g);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? ROSAQ_OK : hip_fail(e, "gemm_kernel launch");
 }
@@ -1002,6 +1059,26 @@ static GemmShape pick_unsplit(int M, int ntiles, int D, int bits, const GemmTune
       if (cost(2, 6) < best_alt) { best_alt = cost(2, 6); s.mt = 2; s.nt = 6; }
       if (mtiles >= 3 && cost(4, 3) < best_alt) { best_alt = cost(4, 3); s.mt = 4; s.nt = 3; }
     }
+    // Of the 64-row tiles, 48, 64 or 80 channels by the rounds of the fullest XCD or shader engine (these tiles have a compute unit
+    // each): a round of 64 x 48 takes 0.84 of one of 64 x 64, of 64 x 80 1.17 (main GEMM alone, contraction of 5120: 13.4, 16.0 and
+    // 18.7 us).  us, the shape chosen above / 64 x 80: 13824 -> 5120 at 256 rows 55.4 / 43.4 (428 of 64 x 48 / 256 workgroups), at 512 93.9 /
+    // 82.6 (640 of 64 x 64 / 512); 5120 -> 5120 at 256 21.8 / 18.8, at 320 38.2 / 34.0, at 512 39.4 / 35.5; 2048 -> 5120 at 256 13.8 / 11.7;
+    // where no round is saved they lose: 11008 -> 4096 at 256 28.5 / 31.8 (256 / 208), at 384 50.9 / 59.4, 4096 -> 8192 at 320 43.4 / 55.5.
+    // A gated pair has no odd numbers of tiles.
+    if (!tune.gated && mtiles >= 3 && s.mt == 4 && (s.nt == 3 || s.nt == 4) && tune.mt != 1 && tune.mt != 2) {
+      const int mgroups = (mtiles + 3) / 4;
+      // a last round that is not full costs about half way between its share and a whole one
+      auto price = [&](int nt) {
+        const int64_t cx = ((ntiles + nt - 1) / nt + 7) / 8;
+        const double share = mgroups <= kMapRows ? cx * mgroups / 32.0 : cx * ((mgroups + 3) / 4) / 8.0;
+        return (nt == 3 ? 0.84 : (nt == 4 ? 1.0 : 1.17)) * std::max(1.0, 0.5 * (share + std::ceil(share)));
+      };
+      const double chosen = price(s.nt);
+      double least = chosen;
+      if (full_rounds((ntiles + 4) / 5, mgroups) <= 6)     // with more rounds, what is saved of the last one is little
+        for (int nt : {4, 5})
+          if (price(nt) < least && price(nt) < (nt == 4 ? 0.95 : 0.88) * chosen) { least = price(nt); s.nt = nt; }
+    }
   }
   // The same for all-fp16 layers (the dense rotation), which have no conversion: 48-channel tiles
   // by rounds x inflow.  A 5120 x 5120 rotation at M = 64 is 160 workgroups of 32 x 64 but 214 of
@@ -1024,7 +1101,6 @@ static GemmShape pick_unsplit(int M, int ntiles, int D, int bits, const GemmTune
     // (2560 of D = 8192 at 450 rows 48.5 / 67.2; 19400 of D = 8192 at 60 rows 68.7 / 82.5).  Where 32 x 64 tiles were the
     // choice: 6400 at 146 rows 44.6 / 75.8; 65 to 96 rows of 9400 to 10240 channels, which leave a quarter to a half of the
     // second row group empty, 0 to 11 % faster (D = 3200 24.3-26.1 / 23.8-26.0, D = 4352 31.8 / 35.0).
-    // (Low-bit layers gain nothing: their 80-channel tile spills, and 13824 -> 5120 at 256 rows takes 54.4 us against 52.3.)
     const int narrow = ((ntiles + 2) / 3) * ((mtiles + 3) / 4);
     // 80 channels go with 64 rows only: not where other rows are forced.
     const bool rows64 = tune.mt != 1 && tune.mt != 2;
@@ -1071,6 +1147,7 @@ static GemmShape pick_unsplit(int M, int ntiles, int D, int bits, const GemmTune
   }
   s.depth = std::min(s.depth, max_depth);
   if (s.depth == 1 && s.mt * s.nt > 4 && s.mt * s.nt < 16) s.depth = 2;
+  if (bits != 16 && s.nt == 5) { s.wpb = 8; s.depth = 1; }
   if (s.nt == 3 || s.nt == 6) {
     // 48- and 96-channel tiles (they make 768- and 1376-tile launches fit one round of 256)
     if (s.mt == 4 && s.nt == 6) {
@@ -1148,6 +1225,8 @@ static int (*kernel_for(int bits, const GemmShape& sh))(const GemmDev&, void*) {
   ROSAQ_WIDE(3)
   ROSAQ_CASE(16, 2, 3, 8) ROSAQ_CASE(16, 4, 3, 8)
   if (bits == 16 && sh.mt == 4 && sh.nt == 5) return launch_gemm_t<16, 4, 5, 8, 1>;
+  if (bits == 4 && sh.mt == 4 && sh.nt == 5) return launch_gemm_t<4, 4, 5, 8, 1>;
+  if (bits == 3 && sh.mt == 4 && sh.nt == 5) return launch_gemm_t<3, 4, 5, 8, 1>;
 #undef ROSAQ_WIDE
 #undef ROSAQ_CASES
 #undef ROSAQ_CASE
@@ -1184,7 +1263,7 @@ bool prefers_wide(int M, int ntiles, int D, int K, int bits, const GemmTune& tun
   const double inflow = (s.mt * 32.0 + s.nt * 16 * wbytes) * D / 128e3;
   const double valu = (s.nt * ((bits == 3 ? 40 : 36) + 4 * s.mt) + 40) * units / 2000.0;
   const double narrow = rounds((ntiles + s.nt - 1) / s.nt, ((M + 15) / 16 + s.mt - 1) / s.mt, s.mt * s.nt > 4) *
-                            (bits == 16 ? 2.8 + 1.5 * inflow : 3.0 + 0.96 * inflow + 0.95 * valu) + 1.7;
+                            (bits == 16 ? 2.8 + 1.5 * inflow : (s.nt == 5 ? 1.12 : 1.0) * (3.0 + 0.96 * inflow + 0.95 * valu)) + 1.7;
   return 1.03 * wide < narrow;
 }
 
@@ -1193,9 +1272,12 @@ GemmPlan plan_gemm(const GemmArgs& a, const GemmTune& tune) {
   for (int i = 0; i < a.nseg; ++i) tiles += (a.seg[i].N + kTileN - 1) / kTileN;
   const int bits = a.G == 0 ? 16 : a.bits;
   GemmPlan plan;
-  plan.wide = a.xrow == nullptr && prefers_wide(a.M, tiles, a.KS * kKStep, a.ks_s * kKStep, bits, tune);
+  GemmTune asked = tune;
+  asked.gated = a.swiglu != 0;
+  plan.wide = a.xrow == nullptr && prefers_wide(a.M, tiles, a.KS * kKStep, a.ks_s * kKStep, bits, asked);
   if (plan.wide) return plan;
   auto choose = [&](GemmTune t) {
+    t.gated = asked.gated;
     auto shape = [&]() {
       return pick_gemm_shape(a.M, tiles, a.KS * kKStep, bits, t, a.part ? a.part_bytes : 0,
                              a.tickets ? a.ticket_count : 0, a.ks_s);
