@@ -228,9 +228,10 @@ int rosaq_packed_export(const rosaq_packed_t* p, int32_t* salient_idx, uint16_t*
 /* rosaq_pca_headwise - calibration step of the method on the GPU (Sec. 3.1 Eq. 4 applied per
  * attention head, Sec. 3.1.1): for every block of 128 input channels the eigenvectors of the
  * uncentred second moment C_h = X_h^T X_h / n_cal, found as the right singular vectors of X_h by
- * one-sided Jacobi rotations in fp64 (pairs of columns are rotated until all are mutually orthogonal;
- * C_h is never formed; eigenvalue c = |column c of X_h V|^2 / n_cal), until the off-diagonal norm of
- * the implied C_h is <= 1e-13 ||C_h||_F in every head.  Results, ready for rosaq_pack_weights:
+ * Jacobi rotations until the columns of X_h V are mutually orthogonal in fp64 (a search in fp32 on C_h only
+ * decides which V to start from; eigenvalue c = |column c of X_h V|^2 / n_cal): until every pair of columns has a
+ * cosine <= 1e-14, or all angles left are below 3e-7 taken together and are turned once more, or the off-diagonal norm
+ * of the implied C_h is <= 1e-13 ||C_h||_F, in every head.  Results, ready for rosaq_pack_weights:
  *   Q_host            HOST fp32 [D/128][128][128], eigenvectors as columns, sorted by eigenvalue
  *                     (descending; each column signed so that its largest entry is positive)
  *   eigenvalues_host  HOST fp64 [D], descending inside every head, >= 0
@@ -242,19 +243,16 @@ int rosaq_pca_headwise(const void* X_dev, int32_t n_cal, int32_t D, int64_t ldx,
 
 /* rosaq_pca_full - the same calibration step for a layer-wise rotation (Sec. 3.1, Eq. 4): the
  * eigenvectors of C = X^T X / n_cal over all D input channels, found as the right singular vectors
- * of X by one-sided Jacobi rotations in fp64 on the GPU (pairs of columns of X are rotated until
- * all are mutually orthogonal; C is never formed; eigenvalue c = |column c of X V|^2 / n_cal).
- * Stops when the off-diagonal norm of the implied C is <= 1e-13 ||C||_F.  Results as for
- * rosaq_pca_headwise:
+ * of X as rosaq_pca_headwise finds them for a head.  Results as there:
  *   Q_host            HOST fp32 [D x D] row-major, eigenvectors as columns (xhat = x Q), sorted by
  *                     eigenvalue descending, each signed so that its largest entry is positive; with
  *                     fewer calibration rows than channels the null space comes out as an orthonormal
  *                     completion (any one is valid)
  *   eigenvalues_host  HOST fp64 [D], descending, >= 0
  *   X_dev             DEVICE fp16 [n_cal x D], row r at X + r*ldx
- * D a multiple of 128 up to 8192 (a sweep is 3 (D / 32 - 1) launches; 2048 rows of a 1024-channel
- * layer take 18 ms, 4608 of a 4096-channel layer 0.41 s).  Allocates its own device scratch (8 D
- * (n_cal + D) bytes, 4 D^2 bytes of results and about 3 KiB per channel) and waits for the result.  Errors: NULL, SHAPE, ALIGN, HIP, NOCONVERGE. */
+ * D a multiple of 128 up to 8192 (2048 rows of a 1024-channel layer take 9 ms, 4608 of a 2048-channel
+ * layer 38 ms).  Allocates its own device scratch (8 D (n_cal + D) bytes, 4 D^2 bytes of results and about 3 KiB per channel, and
+ * 32 to 88 D^2 bytes more for the faster way, which it does without where that much is not free) and waits for the result.  Errors: NULL, SHAPE, ALIGN, HIP, NOCONVERGE. */
 int rosaq_pca_full(const void* X_dev, int32_t n_cal, int32_t D, int64_t ldx, float* Q_host,
                    double* eigenvalues_host, void* hip_stream);
 

@@ -953,11 +953,22 @@ static int pca_blocks_device(const void* X_dev, int n_cal, int D, int Db, int64_
                           static_cast<size_t>(D) * Db * 4, static_cast<size_t>(D) * Db * 8, static_cast<size_t>(D) * Db * 8,
                           static_cast<size_t>(problems) * 8, static_cast<size_t>(D) * 8, static_cast<size_t>(D) * 8,
                           static_cast<size_t>(D / 64) * (Db / 64) * 8};
-  constexpr int kParts = sizeof(sizes) / sizeof(sizes[0]);
+  constexpr int kParts = sizeof(sizes) / sizeof(sizes[0]), kSweepParts = 11;      // from p.full on: not for sweeps
   size_t offs[kParts], total = 0;
-  for (int i = 0; i < kParts; ++i) { offs[i] = total; total += (sizes[i] + 255) / 256 * 256; }
+  size_t lean_total = 0;
+  for (int i = 0; i < kParts; ++i) {
+    if (i == kSweepParts) lean_total = total;
+    offs[i] = total;
+    total += (sizes[i] + 255) / 256 * 256;
+  }
   char* mem = nullptr;
   hipError_t e = hipMalloc(reinterpret_cast<void**>(&mem), total);
+  // without memory for the start and the corrections, sweeps alone will do (step 4 from V = 1)
+  const bool lean = e == hipErrorOutOfMemory;
+  if (lean) {
+    (void)hipGetLastError();
+    e = hipMalloc(reinterpret_cast<void**>(&mem), lean_total);
+  }
   if (e != hipSuccess) return pca_fail(e, who);
   p.Z = reinterpret_cast<double*>(mem + offs[0]);
   p.part = reinterpret_cast<double*>(mem + offs[1]);
@@ -1006,8 +1017,10 @@ static int pca_blocks_device(const void* X_dev, int n_cal, int D, int Db, int64_
   if (e == hipSuccess) {
     hipLaunchKernelGGL(pca_init_kernel, dim3(static_cast<unsigned>(D / 64) * (p.pitch / 64)), dim3(256), 0, st,
                        static_cast<const _Float16*>(X_dev), ldx, n_cal, p);
-    full_gram();
-    hipLaunchKernelGGL(full_sum_kernel<true>, dim3(D), dim3(256), 0, st, p);
+    if (!lean) {
+      full_gram();
+      hipLaunchKernelGGL(full_sum_kernel<true>, dim3(D), dim3(256), 0, st, p);
+    }
     e = hipGetLastError();
   }
   // The search for a rotation to start from.  Calibration sets take five sweeps at least: these are queued without a look
@@ -1015,7 +1028,7 @@ static int pca_blocks_device(const void* X_dev, int n_cal, int D, int Db, int64_
   // A sweep squares the angles like a correction does; of 128 channels it costs as much (120 us), of more three times as much.
   constexpr int kStartSweeps = 14, kBlindSweeps = 5;
   const double kSmall = Db <= 256 ? 1e-4 : 0.5;
-  for (int sweep = 0; e == hipSuccess && sweep < kStartSweeps; ++sweep) {
+  for (int sweep = 0; e == hipSuccess && !lean && sweep < kStartSweeps; ++sweep) {
     for (int r = 0; r < rounds; ++r) {
       hipLaunchKernelGGL(start_rotate_kernel, dim3(2 * pairs), dim3(kPcaThreads), 0, st, p, r, pairs);
       hipLaunchKernelGGL(start_apply_kernel, dim3(static_cast<unsigned>(problems) * (half * (half + 1) / 2 + half * half)),
@@ -1037,7 +1050,7 @@ static int pca_blocks_device(const void* X_dev, int n_cal, int D, int Db, int64_
   auto project = [&] {
     product(product_kernel<kProject>, static_cast<unsigned>(D / 64) * (p.n_pad / 64), 1, zv, p.pitch, nullptr, p.Z, p.pitch);
   };
-  if (e == hipSuccess) {
+  if (e == hipSuccess && !lean) {
     hipLaunchKernelGGL(start_widen_kernel, dim3(D), dim3(256), 0, st, p, vt);
     newton(vt, Db, p.turn, Db);
     newton(p.turn, Db, zv, p.pitch);
@@ -1046,7 +1059,7 @@ static int pca_blocks_device(const void* X_dev, int n_cal, int D, int Db, int64_
   }
   // All pairs at once while the angles are small, else a sweep.
   const int blind = every([](int, int start, int) { return start == 1; }) ? kBlindCorrections : 0;
-  int sweeps = 0, corrections = 0;
+  int sweeps = 0, corrections = lean ? kMaxCorrections : 0;
   bool corrected = false;
   while (e == hipSuccess && sweeps < kMaxSweeps && !converged) {
     bool sweep = corrections >= kMaxCorrections, last = false;
