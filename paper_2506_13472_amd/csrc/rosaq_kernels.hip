@@ -205,11 +205,9 @@ void gemm_kernel(GemmDev p) {
   // Per-wave work list: fp16 k-steps u = wave, wave + WPB, ... and low-bit groups
   // g = g_first, g_first + WPB, ... (unit ks_s + g belongs to wave (ks_s + g) % WPB).
   // DEPTH units are requested ahead of the one being multiplied, and everything a wave needs
-  // first is requested before it waits for anything.  How much of that overlaps inside a wave
-  // is up to the compiler's wait placement (with the refills under conditions, as here, the first
-  // use of a unit waits for every load in flight); a variant with exact progressive waits was
-  // measured and was not faster: the launch is bound by what the L1 / L2 path delivers per
-  // compute unit, and latency is covered by the other waves.
+  // first is requested before it waits for anything.  With the refills under conditions the first
+  // use of a unit waits for every load in flight; where only one unit fits the registers its parts are
+  // asked for again one by one instead, with exact waits (kAhead below).
   struct StepRegs {
     uint4 a[MT];
     uint4 b[NT];
