@@ -522,7 +522,8 @@ __global__ __launch_bounds__(256) void full_sum_kernel(PcaDev p) {
 
 // The angles of all pairs of columns at once, from their inner products as they stand (p.full, or G in fp32): a row's sum of squared
 // tangents, and from p.full also the tangents themselves and the row's largest cosine.  A workgroup per row.  Columns
-// below 1e-13 of the longest are what round-off has left of a null space: any orthonormal basis of it will do.
+// below 1e-13 of the longest are what round-off has left of a null space: any orthonormal basis of it will do.  An inner product
+// that is not finite makes the sum NaN: it has no angle, and comparisons with it are false, those that pass columns over among them.
 template <class T>
 __global__ __launch_bounds__(256) void tangent_kernel(PcaDev p) {
   __shared__ double red[3][4];
@@ -545,6 +546,7 @@ __global__ __launch_bounds__(256) void tangent_kernel(PcaDev p) {
   for (int j = threadIdx.x; j < p.Db; j += 256) {
     const double be = S[base + static_cast<size_t>(j) * p.Db + j], ga = S[row + j], ab = al * be;
     double t = 0.0;
+    t2 = __builtin_fma(0.0, ga, t2);
     if (i != j && !(fmin(al, be) <= nothing)) {
       const double d = be - al, g = 2.0 * ga;
       if (ga * ga > PcaReal<double>::kEps2 * ab) t = (d < 0.0 || (d == 0.0 && j < i) ? -g : g) / (fabs(d) + sqrt(d * d + g * g));
@@ -591,7 +593,8 @@ __device__ __forceinline__ void sum_tangents(const PcaDev& p, int problem, bool 
 // What the angles say, one workgroup per problem.  Round-off: every cosine within tol or the angles within 1e-11, and V so near to orthogonal before the
 // last step of kNewton, which squares what is missing, that nothing is missing now.  Small: the singular values of 1 + T
 // are at most sqrt(1.5) (those of T come in pairs), where the step converges (it does up to sqrt(3)).  A correction squares the
-// angles too (|T| 0.13, 1.5e-3, 2e-7, 3e-13 for 1024 channels), so after one of 3e-7 nothing is left to look for.
+// angles too (|T| 0.13, 1.5e-3, 2e-7, 3e-13 for 1024 channels), so after one of 3e-7 nothing is left to look for.  Inner products that are
+// not finite go to the sweeps, whose check finds the same and ends the call.
 __global__ __launch_bounds__(256) void tangent_check_kernel(PcaDev p, double tol) {
   __shared__ double sh[2][256];
   const int problem = blockIdx.x, half = p.Db / 64;
@@ -605,8 +608,11 @@ __global__ __launch_bounds__(256) void tangent_check_kernel(PcaDev p, double tol
   const bool orthogonal = !__syncthreads_or(!(skew <= 1e-9)), nearly = !__syncthreads_or(!(skew <= 1e-5));
   sum_tangents(p, problem, true, sh);
   if (threadIdx.x == 0)
-    p.loose[problem] = (sh[1][0] <= tol || sh[0][0] <= 1e-22) && orthogonal ? 0
-                       : (sh[0][0] <= 1e-13 && nearly ? 3 : (sh[0][0] <= 1.0 ? 1 : 2));
+    p.loose[problem] = sh[0][0] != sh[0][0]                                      ? 2
+                       : (sh[1][0] <= tol || sh[0][0] <= 1e-22) && orthogonal    ? 0
+                       : sh[0][0] <= 1e-13 && nearly                             ? 3
+                       : sh[0][0] <= 1.0                                         ? 1
+                                                                                 : 2;
 }
 
 // A pair of blocks of G: its panel and the rotations, as rotate_kernel but in fp32.
@@ -881,17 +887,19 @@ __global__ __launch_bounds__(256) void pca_norms_kernel(PcaDev p, int n_cal, dou
   }
 }
 
-// Column c's place among its problem's eigenvalues, descending, ties in column order; eig sorted.
+// Column c's place among its problem's eigenvalues, descending, ties in column order; eig sorted.  A NaN comes last: the
+// places are a permutation whatever the values.
 __global__ __launch_bounds__(64) void pca_order_kernel(const double* __restrict__ lam, int Db, int* __restrict__ order,
                                                        double* __restrict__ eig) {
   __shared__ double sh[64];
   const int c = blockIdx.x * 64 + threadIdx.x;      // 64 columns of one problem
   const int base = c / Db * Db;
-  const double v = lam[c];
+  auto key = [&](int j) { const double l = lam[j]; return l >= 0.0 ? l : -1.0; };
+  const double v = key(c);
   int rank = 0;
   for (int j0 = base; j0 < base + Db; j0 += 64) {
     __syncthreads();
-    sh[threadIdx.x] = lam[j0 + threadIdx.x];
+    sh[threadIdx.x] = key(j0 + threadIdx.x);
     __syncthreads();
 #pragma unroll 16
     for (int j = 0; j < 64; ++j) rank += sh[j] > v || (sh[j] == v && j0 + j < c) ? 1 : 0;

@@ -1,5 +1,5 @@
 """Calibration sets on which the search for a starting rotation in fp32 ends differently: full rank with channels mixed or not,
-eigenvalues that are equal or nearly so, ranks that are missing, channels that are zero, and a NaN."""
+eigenvalues that are equal or nearly so, ranks that are missing, channels that are zero; and sets that are refused: NaN and infinities."""
 import numpy as np
 import pytest
 
@@ -51,10 +51,36 @@ def test_pca_of_sets_that_start_differently(kind, D, n, full):
             assert np.max(np.abs(lam[h] / want - 1)) <= 4 * width * 2.0 ** -53 * cond
 
 
-def test_pca_refuses_a_set_that_is_not_a_number():
-    print("case pca nan", flush=True)
-    x = torch.randn((200, 256), device="cuda", dtype=torch.float16)
-    x[17, 200] = float("nan")
+def _spoil(x, kind):
+    """What keeps a set from being numbers; where every inner product of a problem is lost, no angle is left to find that."""
+    nan, inf = float("nan"), float("inf")
+    if kind == "element":
+        x[17, 200] = nan
+    elif kind == "row":
+        x[17] = nan
+    elif kind == "head":                       # the channels of one head, in every row
+        x[:, 128:] = nan
+    elif kind == "all":
+        x[:] = nan
+    elif kind == "channel among zeros":
+        x[:] = 0.0
+        x[:, 200] = nan
+    elif kind == "infinity":
+        x[17, 200] = inf
+    elif kind == "infinity among zeros":
+        x[:] = 0.0
+        x[17, 200] = -inf
+    else:                                      # a row of infinities
+        x[17] = inf
+
+
+@pytest.mark.parametrize("n", [100, 300])
+@pytest.mark.parametrize("kind", ["element", "row", "head", "all", "channel among zeros", "infinity", "infinity among zeros", "row of infinities"])
+def test_pca_refuses_a_set_that_is_not_numbers(kind, n):
+    x = torch.randn((n, 256), device="cuda", generator=torch.Generator("cuda").manual_seed(5)).half()
+    _spoil(x, kind)
     for call in (B.rosaq_pca_full, B.rosaq_pca_headwise):
-        with pytest.raises(Exception):
-            call(x.data_ptr(), 200, 256, 256)
+        print(f"case pca not numbers {kind} n_cal={n} {call.__name__}", flush=True)
+        with pytest.raises(B.RosaqError) as error:
+            call(x.data_ptr(), n, 256, 256)
+        assert error.value.code == -8          # ROSAQ_ERR_HIP
