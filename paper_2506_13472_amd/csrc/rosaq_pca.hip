@@ -71,6 +71,9 @@ struct PcaDev {
   int full_rows, full_chunks;
 };
 
+// The larger of two, a NaN where either is one.
+__device__ __forceinline__ double larger(double a, double b) { return a >= b || a != a ? a : b; }
+
 // Pair k of a round-robin tournament of `n` players in `round`: player n - 1 stays, the others move one seat
 // per round; seat k meets seat n - 1 - k.  Lower number first.
 __device__ __forceinline__ void tournament(int n, int round, int k, int& a, int& b) {
@@ -550,8 +553,7 @@ __global__ __launch_bounds__(256) void tangent_kernel(PcaDev p) {
     if (i != j && !(fmin(al, be) <= nothing)) {
       const double d = be - al, g = 2.0 * ga;
       if (ga * ga > PcaReal<double>::kEps2 * ab) t = (d < 0.0 || (d == 0.0 && j < i) ? -g : g) / (fabs(d) + sqrt(d * d + g * g));
-      const double c = ga * ga / ab;
-      c2 = c <= c2 ? c2 : c;                       // a NaN stays
+      c2 = larger(c2, ga * ga / ab);
       t2 = __builtin_fma(t, t, t2);
     }
     if (kFull) p.turn[row + j] = t;
@@ -559,13 +561,12 @@ __global__ __launch_bounds__(256) void tangent_kernel(PcaDev p) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
     t2 += __shfl_xor(t2, o, 64);
-    const double c = __shfl_xor(c2, o, 64);
-    c2 = c <= c2 ? c2 : c;
+    c2 = larger(c2, __shfl_xor(c2, o, 64));
   }
   if (lane == 0) { red[1][wave] = t2; red[2][wave] = c2; }
   __syncthreads();
   if (threadIdx.x == 0) {
-    for (int w = 1; w < 4; ++w) { t2 += red[1][w]; c2 = red[2][w] <= c2 ? c2 : red[2][w]; }
+    for (int w = 1; w < 4; ++w) { t2 += red[1][w]; c2 = larger(c2, red[2][w]); }
     p.row_t2[blockIdx.x] = t2;
     if (kFull) p.row_cos[blockIdx.x] = sqrt(c2);
   }
@@ -576,15 +577,14 @@ __device__ __forceinline__ void sum_tangents(const PcaDev& p, int problem, bool 
   double t2 = 0.0, c = 0.0;
   for (int i = threadIdx.x; i < p.Db; i += 256) {
     t2 += p.row_t2[problem * p.Db + i];
-    if (cosines) { const double v = p.row_cos[problem * p.Db + i]; c = v <= c ? c : v; }
+    if (cosines) c = larger(c, p.row_cos[problem * p.Db + i]);
   }
   sh[0][threadIdx.x] = t2; sh[1][threadIdx.x] = c;
   __syncthreads();
   for (int w = 128; w > 0; w >>= 1) {
     if (threadIdx.x < w) {
       sh[0][threadIdx.x] += sh[0][threadIdx.x + w];
-      const double v = sh[1][threadIdx.x + w];
-      if (!(v <= sh[1][threadIdx.x])) sh[1][threadIdx.x] = v;
+      sh[1][threadIdx.x] = larger(sh[1][threadIdx.x], sh[1][threadIdx.x + w]);
     }
     __syncthreads();
   }
@@ -602,8 +602,7 @@ __global__ __launch_bounds__(256) void tangent_check_kernel(PcaDev p, double tol
   double skew = 0.0;
   const int tiles = half * (half + 1) / 2;
   for (int i = threadIdx.x; i < tiles; i += 256) {
-    const double v = p.skew[problem * tiles + i];
-    skew = v <= skew ? skew : v;
+    skew = larger(skew, p.skew[problem * tiles + i]);
   }
   const bool orthogonal = !__syncthreads_or(!(skew <= 1e-9)), nearly = !__syncthreads_or(!(skew <= 1e-5));
   sum_tangents(p, problem, true, sh);
@@ -832,8 +831,7 @@ __global__ __launch_bounds__(256) void product_kernel(PcaDev p, int problems, co
       if constexpr (MODE == kTurn) v = turned ? Ap[m * lda + n] - v : Ap[m * lda + n];
       if constexpr (MODE == kProject) v = n < n_cal ? v : 0.0;
       if constexpr (MODE == kNorms) {
-        const double d = fabs(v - (m == n ? 1.0 : 0.0));
-        skew = d <= skew ? skew : d;                               // a NaN stays
+        skew = larger(skew, fabs(v - (m == n ? 1.0 : 0.0)));
       }
       // a tile on the diagonal holds both orders of a pair: the upper one counts for both
       if (kSymmetric && m > n && mt == nt) continue;
@@ -844,13 +842,12 @@ __global__ __launch_bounds__(256) void product_kernel(PcaDev p, int problems, co
     __shared__ double red[4];
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
-      const double d = __shfl_xor(skew, o, 64);
-      skew = d <= skew ? skew : d;
+      skew = larger(skew, __shfl_xor(skew, o, 64));
     }
     if (lane == 0) red[wave] = skew;
     __syncthreads();
     if (threadIdx.x == 0) {
-      for (int w = 1; w < 4; ++w) skew = red[w] <= skew ? skew : red[w];
+      for (int w = 1; w < 4; ++w) skew = larger(skew, red[w]);
       p.skew[blockIdx.x] = skew;
     }
   }
