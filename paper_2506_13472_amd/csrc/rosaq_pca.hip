@@ -771,7 +771,6 @@ __global__ __launch_bounds__(256) void product_kernel(PcaDev p, int problems, co
     nt = blockIdx.x / (problems * half);
   }
   if (MODE == kGram && p.done[problem]) return;
-  if (MODE == kProject && p.start_done[problem] == 2) return;      // Z stays as it was
   const bool turned = MODE == kTurn && !p.done[problem] && p.loose[problem] != 2;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int i16 = lane & 15, q = lane >> 4;
