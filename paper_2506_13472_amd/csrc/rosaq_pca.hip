@@ -16,9 +16,12 @@
 //   3. Corrections.  The inner products of all columns of X V give every pair's angle.  While these are small taken together
 //      V <- the orthogonal matrix nearest to V (1 + T), T the skew matrix of tangents, squares them.  Two or three reach round-off,
 //      0.1 ms each for 32 heads, 0.37 ms for 1024 channels.
-//   4. Where they are not small (a second moment without full rank, eigenvalues that differ by less than fp32 resolves) a sweep of
-//      one-sided block Jacobi on X V in fp64 follows, and then step 3 again: gram_kernel forms the 64 x 64 inner products of a
-//      pair of blocks, rotate_kernel finds J from them, apply_kernel multiplies the columns of X V and V by J.
+//   4. Where angles between short columns are not small they are left out at first (kDim below): a null space needs nothing else.
+//   5. Where angles still are not small (columns shorter than fp32 resolves beside the longest) the search of step 1 goes on once
+//      from the inner products of X V, which fp64 has made good to the last place of the shortest column, and then steps 2 and 3.
+//   6. After that, or where the card has no memory for all this, sweeps of one-sided block Jacobi on X V in fp64, each followed by step
+//      3: gram_kernel forms the 64 x 64 inner products of a pair of blocks, rotate_kernel finds J from them, apply_kernel
+//      multiplies the columns of X V and V by J.
 // fp32 decides only where step 3 starts from: X V, its inner products, V and the eigenvalues are fp64 throughout.
 // 32 heads of 128 channels, 512 rows 1.89 -> 1.31 ms, 1024 channels, 2048 rows 19.0 -> 9.3 ms; largest relative error of an
 // eigenvalue against LAPACK's singular values 2.4e-14 -> 1.3e-14 and 3.3e-13 -> 1.8e-14 (fewer roundings).
@@ -63,12 +66,15 @@ struct PcaDev {
   float* Vt;          // [D][Db], row c = eigenvector c
   double* turn;       // [D][Db]: tangents of all pairs' angles, T[i][j] = -T[j][i]
   double* row_t2;     // [D]: a row's sum of squared tangents
+  double* row_faint;  // [2][D]: the same of pairs of faint columns and of pairs of dim ones, which row_t2 then leaves out
   double* row_cos;    // [D]: its largest cosine
   double* skew;       // [problem][tiles on and above the diagonal]: largest entry of a tile of Vt Vt^T - 1
   int* start_done;    // [problems]: 1 = near enough, 2 = not finite, 3 = held by round-off
   double* start_off;  // [problems]: what was left off the diagonal in the sweep before
-  int* loose;         // [problems]: 0 = every pair orthogonal to round-off, 1 = all angles small, 2 = not, 3 = one correction left
+  int* loose;         // [problems]: 0 = every pair orthogonal to round-off, 1 = all angles small, 2 = not, 3 = one correction left,
+                      // 4 = all small but those between faint columns, 5 = but those between dim ones
   int full_rows, full_chunks;
+  int faint_out;      // tangents between faint or dim columns are zero where loose is 4 or 5
 };
 
 // The larger of two, a NaN where either is one.
@@ -523,13 +529,35 @@ __global__ __launch_bounds__(256) void full_sum_kernel(PcaDev p) {
   if (FIRST && i == 0 && threadIdx.x == 0) p.start_off[problem] = 1.0;
 }
 
+// The largest of a problem's squared norms, for every thread.
+template <class T>
+__device__ __forceinline__ double longest_column(const T* S, int Db, double* red) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  double longest = 0.0;
+  for (int j = threadIdx.x; j < Db; j += 256) longest = fmax(longest, static_cast<double>(S[static_cast<size_t>(j) * Db + j]));
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) longest = fmax(longest, __shfl_xor(longest, o, 64));
+  if (lane == 0) red[wave] = longest;
+  __syncthreads();
+  return fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
+}
+
+// Columns by their squared norms, as shares of the longest one's.  Below kNothing they are what round-off has left of a null space: any
+// orthonormal basis of it will do.  Dim and faint ones, below kDim and kFaint, may be what fp32 has left of it: where V is off by 1e-6, X V has
+// columns of that length in place of zeros, at any angle to each other.  Sweeps take a dozen turns to make these orthogonal.  Corrections
+// that leave their angles alone and turn those to the longer columns bring them below kNothing instead, if that is what they are.  Faint
+// ones where all other angles are well below one, so that none of the null space's is among them (taken at up to one, 32 heads, 64 rows
+// repeated, 3.2 against 2.1 ms); else dim ones, which leaves the angles of columns that are dim by right for later (taken in any case, 1000
+// rows of 1024 channels 29 against 13 ms).  ms, angles of all columns by sweeps / this: 100 rows of 128 channels 3.4 / 1.4, 64 rows of
+// 32 heads 5.2 / 2.0, 200 rows of 512 channels 17.2 / 5.3, 512 of 1024 36.7 / 10.0, 1000 of 1024 26.0 / 12.9.
+constexpr double kNothing = 1e-26, kFaint = 1e-10, kDim = 1e-6;
+
 // The angles of all pairs of columns at once, from their inner products as they stand (p.full, or G in fp32): a row's sum of squared
-// tangents, and from p.full also the tangents themselves and the row's largest cosine.  A workgroup per row.  Columns
-// below 1e-13 of the longest are what round-off has left of a null space: any orthonormal basis of it will do.  An inner product
-// that is not finite makes the sum NaN: it has no angle, and comparisons with it are false, those that pass columns over among them.
+// tangents, and from p.full also the tangents themselves and the row's largest cosine.  A workgroup per row.  An inner
+// product that is not finite makes the sum NaN: it has no angle, and comparisons with it are false, those that pass columns over among them.
 template <class T>
 __global__ __launch_bounds__(256) void tangent_kernel(PcaDev p) {
-  __shared__ double red[3][4];
+  __shared__ double red[5][4];
   constexpr bool kFull = sizeof(T) == 8;
   const int problem = blockIdx.x / p.Db, i = blockIdx.x - problem * p.Db;
   if (kFull ? p.done[problem] : p.start_done[problem]) return;
@@ -537,54 +565,102 @@ __global__ __launch_bounds__(256) void tangent_kernel(PcaDev p) {
   const T* S;
   if constexpr (kFull) S = p.full; else S = p.G;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  double longest = 0.0;
-  for (int j = threadIdx.x; j < p.Db; j += 256) longest = fmax(longest, static_cast<double>(S[base + static_cast<size_t>(j) * p.Db + j]));
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) longest = fmax(longest, __shfl_xor(longest, o, 64));
-  if (lane == 0) red[0][wave] = longest;
-  __syncthreads();
-  const double nothing = 1e-26 * fmax(fmax(red[0][0], red[0][1]), fmax(red[0][2], red[0][3]));
+  const double longest = longest_column(S + base, p.Db, red[0]);
   const double al = S[row + i];
-  double t2 = 0.0, c2 = 0.0;
+  double t2 = 0.0, f2 = 0.0, d2 = 0.0, c2 = 0.0;
   for (int j = threadIdx.x; j < p.Db; j += 256) {
     const double be = S[base + static_cast<size_t>(j) * p.Db + j], ga = S[row + j], ab = al * be;
     double t = 0.0;
     t2 = __builtin_fma(0.0, ga, t2);
-    if (i != j && !(fmin(al, be) <= nothing)) {
+    if (i != j && !(fmin(al, be) <= kNothing * longest)) {
       const double d = be - al, g = 2.0 * ga;
       if (ga * ga > PcaReal<double>::kEps2 * ab) t = (d < 0.0 || (d == 0.0 && j < i) ? -g : g) / (fabs(d) + sqrt(d * d + g * g));
-      c2 = larger(c2, ga * ga / ab);
-      t2 = __builtin_fma(t, t, t2);
+      if constexpr (kFull) {
+        const double longer = fmax(al, be), tt = t * t;
+        c2 = larger(c2, ga * ga / ab);
+        f2 += longer <= kFaint * longest ? tt : 0.0;
+        d2 += longer > kFaint * longest && longer <= kDim * longest ? tt : 0.0;
+        t2 += longer <= kDim * longest ? 0.0 : tt;
+      } else {
+        t2 = __builtin_fma(t, t, t2);
+      }
     }
     if (kFull) p.turn[row + j] = t;
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
     t2 += __shfl_xor(t2, o, 64);
-    c2 = larger(c2, __shfl_xor(c2, o, 64));
+    if constexpr (kFull) {
+      f2 += __shfl_xor(f2, o, 64);
+      d2 += __shfl_xor(d2, o, 64);
+      c2 = larger(c2, __shfl_xor(c2, o, 64));
+    }
   }
-  if (lane == 0) { red[1][wave] = t2; red[2][wave] = c2; }
+  if (lane == 0) {
+    red[1][wave] = t2;
+    if constexpr (kFull) { red[2][wave] = c2; red[3][wave] = f2; red[4][wave] = d2; }
+  }
   __syncthreads();
   if (threadIdx.x == 0) {
-    for (int w = 1; w < 4; ++w) { t2 += red[1][w]; c2 = larger(c2, red[2][w]); }
+    for (int w = 1; w < 4; ++w) {
+      t2 += red[1][w];
+      if constexpr (kFull) { c2 = larger(c2, red[2][w]); f2 += red[3][w]; d2 += red[4][w]; }
+    }
     p.row_t2[blockIdx.x] = t2;
-    if (kFull) p.row_cos[blockIdx.x] = sqrt(c2);
+    if constexpr (kFull) {
+      p.row_cos[blockIdx.x] = sqrt(c2);
+      p.row_faint[blockIdx.x] = f2;
+      p.row_faint[gridDim.x + blockIdx.x] = d2;
+    }
   }
 }
 
-// The sum of a problem's rows' squared tangents over both halves, in a fixed order, to sh[0] for thread 0, and the largest cosine to sh[1].
-__device__ __forceinline__ void sum_tangents(const PcaDev& p, int problem, bool cosines, double (*sh)[256]) {
-  double t2 = 0.0, c = 0.0;
+// The search goes on, in problems whose angles are not small: G <- the inner products of X V as they stand, scaled so that the longest
+// column's is about 2^60 and none that counts leaves the range of fp32, and Vt <- 1.  A workgroup per row.
+__global__ __launch_bounds__(256) void again_kernel(PcaDev p) {
+  __shared__ double red[4];
+  const int problem = blockIdx.x / p.Db, i = blockIdx.x - problem * p.Db;
+  const bool search = !p.done[problem] && p.loose[problem] == 2;
+  const size_t base = static_cast<size_t>(problem) * p.Db * p.Db, row = base + static_cast<size_t>(i) * p.Db;
+  const int up = search ? 60 - ilogb(longest_column(p.full + base, p.Db, red)) : 0;
+  for (int j = threadIdx.x; j < p.Db; j += 256) {
+    if (search) p.G[row + j] = static_cast<float>(ldexp(p.full[row + j], up));
+    p.Vt[row + j] = i == j ? 1.0f : 0.0f;
+  }
+  if (i == 0 && threadIdx.x == 0) p.start_done[problem] = search ? 0 : 1;
+}
+
+// No angles between faint or dim columns, where these are what is not small.  A workgroup per row.
+__global__ __launch_bounds__(256) void faint_kernel(PcaDev p) {
+  __shared__ double red[4];
+  const int problem = blockIdx.x / p.Db, i = blockIdx.x - problem * p.Db;
+  const int loose = p.loose[problem];
+  if (p.done[problem] || loose < 4) return;
+  const size_t base = static_cast<size_t>(problem) * p.Db * p.Db, row = base + static_cast<size_t>(i) * p.Db;
+  const double faint = (loose == 4 ? kFaint : kDim) * longest_column(p.full + base, p.Db, red);
+  if (!(p.full[row + i] <= faint)) return;
+  for (int j = threadIdx.x; j < p.Db; j += 256)
+    if (p.full[base + static_cast<size_t>(j) * p.Db + j] <= faint) p.turn[row + j] = 0.0;
+}
+
+// The sum of a problem's rows' squared tangents over both halves, in a fixed order, to sh[0] for thread 0, and (FULL) the largest cosine
+// to sh[1] and the sums between faint and dim columns to sh[2] and sh[3].
+template <bool FULL>
+__device__ __forceinline__ void sum_tangents(const PcaDev& p, int problem, int D, double (*sh)[256]) {
+  double t2 = 0.0, f2 = 0.0, d2 = 0.0, c = 0.0;
   for (int i = threadIdx.x; i < p.Db; i += 256) {
     t2 += p.row_t2[problem * p.Db + i];
-    if (cosines) c = larger(c, p.row_cos[problem * p.Db + i]);
+    if (FULL) c = larger(c, p.row_cos[problem * p.Db + i]);
+    if (FULL) { f2 += p.row_faint[problem * p.Db + i]; d2 += p.row_faint[D + problem * p.Db + i]; }
   }
-  sh[0][threadIdx.x] = t2; sh[1][threadIdx.x] = c;
+  sh[0][threadIdx.x] = t2;
+  if (FULL) { sh[1][threadIdx.x] = c; sh[2][threadIdx.x] = f2; sh[3][threadIdx.x] = d2; }
   __syncthreads();
   for (int w = 128; w > 0; w >>= 1) {
     if (threadIdx.x < w) {
       sh[0][threadIdx.x] += sh[0][threadIdx.x + w];
-      sh[1][threadIdx.x] = larger(sh[1][threadIdx.x], sh[1][threadIdx.x + w]);
+      if (FULL) sh[1][threadIdx.x] = larger(sh[1][threadIdx.x], sh[1][threadIdx.x + w]);
+      if (FULL) { sh[2][threadIdx.x] += sh[2][threadIdx.x + w]; sh[3][threadIdx.x] += sh[3][threadIdx.x + w]; }
     }
     __syncthreads();
   }
@@ -596,7 +672,7 @@ __device__ __forceinline__ void sum_tangents(const PcaDev& p, int problem, bool 
 // angles too (|T| 0.13, 1.5e-3, 2e-7, 3e-13 for 1024 channels), so after one of 3e-7 nothing is left to look for.  Inner products that are
 // not finite go to the sweeps, whose check finds the same and ends the call.
 __global__ __launch_bounds__(256) void tangent_check_kernel(PcaDev p, double tol) {
-  __shared__ double sh[2][256];
+  __shared__ double sh[4][256];
   const int problem = blockIdx.x, half = p.Db / 64;
   if (p.done[problem]) return;
   double skew = 0.0;
@@ -605,13 +681,18 @@ __global__ __launch_bounds__(256) void tangent_check_kernel(PcaDev p, double tol
     skew = larger(skew, p.skew[problem * tiles + i]);
   }
   const bool orthogonal = !__syncthreads_or(!(skew <= 1e-9)), nearly = !__syncthreads_or(!(skew <= 1e-5));
-  sum_tangents(p, problem, true, sh);
-  if (threadIdx.x == 0)
-    p.loose[problem] = sh[0][0] != sh[0][0]                                      ? 2
-                       : (sh[1][0] <= tol || sh[0][0] <= 1e-22) && orthogonal    ? 0
-                       : sh[0][0] <= 1e-13 && nearly                             ? 3
-                       : sh[0][0] <= 1.0                                         ? 1
+  sum_tangents<true>(p, problem, gridDim.x * p.Db, sh);
+  if (threadIdx.x == 0) {
+    const double bright = sh[0][0], not_faint = bright + sh[3][0], all = not_faint + sh[2][0];
+    p.loose[problem] = all != all                                                ? 2
+                       : (sh[1][0] <= tol || all <= 1e-22) && orthogonal         ? 0
+                       : all <= 1e-13 && nearly                                  ? 3
+                       : all <= 1.0                                              ? 1
+                       : not_faint <= 0.01 && not_faint > 1e-22                  ? 4
+                       : bright <= 1.0 && bright > 1e-22                         ? 5
+                       : not_faint <= 1.0 && not_faint > 1e-22                   ? 4
                                                                                  : 2;
+  }
 }
 
 // A pair of blocks of G: its panel and the rotations, as rotate_kernel but in fp32.
@@ -713,18 +794,20 @@ __global__ __launch_bounds__(256) void start_apply_kernel(PcaDev p, int round) {
 }
 
 // End of a sweep in fp32, one workgroup per problem.  Near enough: the angles that are left are small taken together, or
-// round-off holds what is off the diagonal where it is (a second moment without full rank).  Sums as in pca_check_kernel.
-__global__ __launch_bounds__(256) void start_check_kernel(PcaDev p, int rounds, int half, int pairs, double small) {
+// round-off holds what is off the diagonal where it is: a second moment without full rank, or short columns, which are left to the
+// steps behind.  (Stopping at 1e-6 of the norm in any case saves these sets up to three sweeps, but long channels beside a second moment
+// of full rank then need the search twice: 1.4 -> 2.4 ms for 32 heads.)  When the search goes on, short columns are what it is about.  Sums as in pca_check_kernel.
+__global__ __launch_bounds__(256) void start_check_kernel(PcaDev p, int rounds, int half, int pairs, double small, bool again) {
   __shared__ double sh[2][256];
   const int problem = blockIdx.x;
   if (p.start_done[problem]) return;
   sum_sweep(p, problem, rounds, half, pairs, sh);
   const double off2 = 2.0 * sh[0][0], norm2 = sh[1][0] + off2;
   __syncthreads();
-  sum_tangents(p, problem, false, sh);
+  sum_tangents<false>(p, problem, gridDim.x * p.Db, sh);
   if (threadIdx.x == 0) {
     const double now = off2 / norm2, before = p.start_off[problem];
-    const bool held = now < 1e-6 && now > 0.25 * before;
+    const bool held = !again && now < 1e-6 && now > 0.25 * before;
     int state = 0;
     if (!(norm2 < 1e76)) state = 2;                              // an infinity or NaN among the inner products
     else if (sh[0][0] <= small) state = 1;
@@ -748,14 +831,15 @@ __global__ __launch_bounds__(256) void start_widen_kernel(PcaDev p, double* __re
 //   kNorms    out[m][n] = sum_k A[m][k] A[n][k]       and the tile's largest difference from 1; a row of A is one of Vt
 //   kNewton   out[m][n] = 1.5 A[m][n] - 0.5 sum_k W[m][k] A[k][n]      one step towards the nearest orthogonal matrix
 //   kTurn     out[m][n] = A[m][n] - sum_k W[m][k] A[k][n]              (1 + T)^T Vt; A alone where the angles are not small
+//   kCombine  out[m][n] = sum_k W[m][k] A[k][n]
 //   kProject  out[m][n] = sum_k A[m][k] X[n][k]       columns of X V; n counts rows of X
 // W has rows of Db.  The first two are symmetric: tiles on and above the diagonal are made and stored on both sides.
-enum PcaProduct { kGram, kNorms, kNewton, kTurn, kProject };
+enum PcaProduct { kGram, kNorms, kNewton, kTurn, kCombine, kProject };
 template <PcaProduct MODE>
 __global__ __launch_bounds__(256) void product_kernel(PcaDev p, int problems, const double* __restrict__ A, int64_t lda,
                                                       const double* __restrict__ W, const _Float16* __restrict__ X, int64_t ldx,
                                                       int n_cal, double* __restrict__ out, int64_t ldo) {
-  constexpr bool kSymmetric = MODE == kGram || MODE == kNorms, kWeighted = MODE == kNewton || MODE == kTurn;
+  constexpr bool kSymmetric = MODE == kGram || MODE == kNorms, kWeighted = MODE == kNewton || MODE == kTurn || MODE == kCombine;
   const int half = p.Db / 64;
   int problem, mt, nt;
   if constexpr (kSymmetric) {
@@ -771,7 +855,7 @@ __global__ __launch_bounds__(256) void product_kernel(PcaDev p, int problems, co
     nt = blockIdx.x / (problems * half);
   }
   if (MODE == kGram && p.done[problem]) return;
-  const bool turned = MODE == kTurn && !p.done[problem] && p.loose[problem] != 2;
+  const bool turned = MODE == kTurn && !p.done[problem] && p.loose[problem] != 2 && (p.loose[problem] < 4 || p.faint_out);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int i16 = lane & 15, q = lane >> 4;
   const int m0 = 64 * mt + 32 * (wave & 1), n0 = 64 * nt + 32 * (wave >> 1);
@@ -956,7 +1040,7 @@ static int pca_blocks_device(const void* X_dev, int n_cal, int D, int Db, int64_
                           static_cast<size_t>(p.full_chunks) * D * Db * 8, static_cast<size_t>(D) * Db * 4,
                           static_cast<size_t>(D) * Db * 4, static_cast<size_t>(D) * Db * 8, static_cast<size_t>(D) * Db * 8,
                           static_cast<size_t>(problems) * 8, static_cast<size_t>(D) * 8, static_cast<size_t>(D) * 8,
-                          static_cast<size_t>(D / 64) * (Db / 64) * 8};
+                          static_cast<size_t>(D / 64) * (Db / 64) * 8, static_cast<size_t>(D) * 16};
   constexpr int kParts = sizeof(sizes) / sizeof(sizes[0]), kSweepParts = 11;      // from p.full on: not for sweeps
   size_t offs[kParts], total = 0;
   size_t lean_total = 0;
@@ -996,6 +1080,7 @@ static int pca_blocks_device(const void* X_dev, int n_cal, int D, int Db, int64_
   p.row_t2 = reinterpret_cast<double*>(mem + offs[17]);
   p.row_cos = reinterpret_cast<double*>(mem + offs[18]);
   p.skew = reinterpret_cast<double*>(mem + offs[19]);
+  p.row_faint = reinterpret_cast<double*>(mem + offs[20]);
 
   auto read = [&] {
     hipError_t r = hipMemcpyAsync(state.data(), p.done, sizes[5], hipMemcpyDeviceToHost, st);
@@ -1027,24 +1112,29 @@ static int pca_blocks_device(const void* X_dev, int n_cal, int D, int Db, int64_
     }
     e = hipGetLastError();
   }
-  // The search for a rotation to start from.  Calibration sets take five sweeps at least: these are queued without a look
-  // at `start_done`, and what needs fewer (one row, orthogonal columns) has its remaining launches return at once.
+  // The search for a rotation to start from.  Calibration sets take five sweeps at least: these are queued without
+  // a look at `start_done`, and what needs fewer (one row, orthogonal columns) has its remaining launches return at once.  But a look takes
+  // 50 us and launches that return at once 2.5 us each, of 1024 channels 155 us a sweep: of more than 256 channels the third sweep is looked at.
   // A sweep squares the angles like a correction does; of 128 channels it costs as much (120 us), of more three times as much.
-  constexpr int kStartSweeps = 14, kBlindSweeps = 5;
+  constexpr int kStartSweeps = 14;
+  auto looked_at = [&](int sweeps) { return sweeps >= 5 || (sweeps == 3 && Db > 256); };
   const double kSmall = Db <= 256 ? 1e-4 : 0.5;
-  for (int sweep = 0; e == hipSuccess && !lean && sweep < kStartSweeps; ++sweep) {
-    for (int r = 0; r < rounds; ++r) {
-      hipLaunchKernelGGL(start_rotate_kernel, dim3(2 * pairs), dim3(kPcaThreads), 0, st, p, r, pairs);
-      hipLaunchKernelGGL(start_apply_kernel, dim3(static_cast<unsigned>(problems) * (half * (half + 1) / 2 + half * half)),
-                         dim3(256), 0, st, p, r);
+  auto search = [&](bool again) {
+    for (int sweep = 0; e == hipSuccess && sweep < kStartSweeps; ++sweep) {
+      for (int r = 0; r < rounds; ++r) {
+        hipLaunchKernelGGL(start_rotate_kernel, dim3(2 * pairs), dim3(kPcaThreads), 0, st, p, r, pairs);
+        hipLaunchKernelGGL(start_apply_kernel, dim3(static_cast<unsigned>(problems) * (half * (half + 1) / 2 + half * half)),
+                           dim3(256), 0, st, p, r);
+      }
+      hipLaunchKernelGGL(tangent_kernel<float>, dim3(D), dim3(256), 0, st, p);
+      hipLaunchKernelGGL(start_check_kernel, dim3(problems), dim3(256), 0, st, p, rounds, half, pairs, kSmall, again);
+      e = hipGetLastError();
+      if (e != hipSuccess || !looked_at(sweep + 1)) continue;
+      e = read();
+      if (e == hipSuccess && every([](int, int start, int) { return start != 0; })) break;
     }
-    hipLaunchKernelGGL(tangent_kernel<float>, dim3(D), dim3(256), 0, st, p);
-    hipLaunchKernelGGL(start_check_kernel, dim3(problems), dim3(256), 0, st, p, rounds, half, pairs, kSmall);
-    e = hipGetLastError();
-    if (e != hipSuccess || sweep + 1 < kBlindSweeps) continue;
-    e = read();
-    if (e == hipSuccess && every([](int, int start, int) { return start != 0; })) break;
-  }
+  };
+  if (e == hipSuccess && !lean) search(false);
   // V, the rows of the right part of Z, towards the nearest orthogonal matrix
   auto newton = [&](const double* A, int64_t lda, double* to, int64_t ldo) {
     product(product_kernel<kNorms>, full_tiles, 1, A, lda, nullptr, p.full, Db);
@@ -1061,12 +1151,13 @@ static int pca_blocks_device(const void* X_dev, int n_cal, int D, int Db, int64_
     project();
     e = hipGetLastError();
   }
-  // All pairs at once while the angles are small, else a sweep.
+  // All pairs at once while the angles are small, else the search again, else a sweep.
   const int blind = every([](int, int start, int) { return start == 1; }) ? kBlindCorrections : 0;
   int sweeps = 0, corrections = lean ? kMaxCorrections : 0;
-  bool corrected = false;
+  bool corrected = false, again = !every([](int, int start, int) { return start != 2; });
   while (e == hipSuccess && sweeps < kMaxSweeps && !converged) {
     bool sweep = corrections >= kMaxCorrections, last = false;
+    p.faint_out = 0;
     if (!sweep) {
       full_gram();
       hipLaunchKernelGGL(full_sum_kernel<false>, dim3(D), dim3(256), 0, st, p);
@@ -1076,12 +1167,16 @@ static int pca_blocks_device(const void* X_dev, int n_cal, int D, int Db, int64_
       if (e == hipSuccess && corrections >= blind) {
         e = read();
         converged = every([](int d, int, int loose) { return d == 1 || (d == 0 && loose == 0); });
-        sweep = !every([](int d, int, int loose) { return d == 1 || loose != 2; });
+        // not before the corrections of the other problems have come to an end: a sweep is for all of them
+        sweep = !every([](int d, int, int loose) { return d == 1 || loose != 2; }) &&
+                every([](int d, int, int loose) { return d == 1 || loose == 0 || loose == 2 || loose == 3; });
         last = every([](int d, int, int loose) { return d == 1 || (d == 0 && (loose == 0 || loose == 3)); });
       }
       if (e != hipSuccess || converged) break;
+      p.faint_out = corrections >= blind && !sweep && !every([](int d, int, int loose) { return d == 1 || loose < 4; });
     }
     if (!sweep) {
+      if (p.faint_out) hipLaunchKernelGGL(faint_kernel, dim3(D), dim3(256), 0, st, p);
       product(product_kernel<kTurn>, tiles, 1, zv, p.pitch, p.turn, vt, Db);
       newton(vt, Db, zv, p.pitch);
       project();
@@ -1089,6 +1184,19 @@ static int pca_blocks_device(const void* X_dev, int n_cal, int D, int Db, int64_
       ++corrections;
       corrected = true;
       converged = last;
+      continue;
+    }
+    if (!again && corrections < kMaxCorrections) {     // ms, by sweeps / so: 32 heads of rank 16 and fp16's rounding 4.7 / 3.5, 512 channels of rank 30 14.3 / 9.3
+      again = true;
+      hipLaunchKernelGGL(again_kernel, dim3(D), dim3(256), 0, st, p);
+      search(true);
+      if (e != hipSuccess) break;
+      hipLaunchKernelGGL(start_widen_kernel, dim3(D), dim3(256), 0, st, p, vt);
+      product(product_kernel<kCombine>, tiles, 1, zv, p.pitch, vt, p.turn, Db);
+      newton(p.turn, Db, vt, Db);
+      newton(vt, Db, zv, p.pitch);
+      project();
+      e = hipGetLastError();
       continue;
     }
     if (corrected) {                               // a sweep keeps V as orthogonal as it is

@@ -1,5 +1,5 @@
 """Calibration sets on which the search for a starting rotation in fp32 ends differently: full rank with channels mixed or not,
-eigenvalues that are equal or nearly so, ranks that are missing, channels that are zero; and sets that are refused: NaN and infinities."""
+eigenvalues that are equal or nearly so, ranks that are missing, fewer rows than channels, channels that are zero or short; and sets that are refused: NaN and infinities."""
 import numpy as np
 import pytest
 
@@ -22,13 +22,20 @@ def _set(kind, n, D, rng):
         X = X @ rng.standard_normal((D, D // 2)) @ rng.standard_normal((D // 2, D)) / D
     elif kind == "zeros":
         X[:, ::3] = 0.0
+    elif kind == "repeated":                            # a few rows, again and again: rank n / 8
+        X = X[np.arange(n) % (n // 8)]
+    elif kind == "few long":                            # rank 8 and what rounding to fp16 adds
+        X = X[:, :8] @ rng.standard_normal((8, D))
+    elif kind == "one long":                            # short columns of full rank, not along the channels, beside a long one
+        X = X @ np.linalg.qr(rng.standard_normal((D, D)))[0] * 2e-5
+        X[:, 5] = 100.0 * rng.standard_normal(n)
     elif kind == "wide":                                # channels from 6e-5 to 6e4
         X = rng.standard_normal((n, D)) * np.logspace(-4, 4, D)
     return X.astype(np.float16)
 
 
-@pytest.mark.parametrize("kind", ["plain", "mixed", "equal", "close", "rank", "zeros", "wide"])
-@pytest.mark.parametrize("D,n,full", [(256, 300, False), (256, 257, True), (384, 900, True)])
+@pytest.mark.parametrize("kind", ["plain", "mixed", "equal", "close", "rank", "zeros", "wide", "repeated", "few long", "one long"])
+@pytest.mark.parametrize("D,n,full", [(256, 300, False), (256, 257, True), (384, 900, True), (256, 50, False), (384, 100, True), (512, 500, True)])
 def test_pca_of_sets_that_start_differently(kind, D, n, full):
     print(f"case pca start {kind} D={D} n_cal={n} full={full}", flush=True)
     X = _set(kind, n, D, np.random.default_rng(77 + D + n))
@@ -38,7 +45,8 @@ def test_pca_of_sets_that_start_differently(kind, D, n, full):
     Q, lam = np.asarray(Q).reshape(-1, width, width).astype(np.float64), np.asarray(lam).reshape(-1, width)
     for h in range(D // width):
         x = X[:, h * width:(h + 1) * width].astype(np.float64)
-        want = np.linalg.svd(x, compute_uv=False) ** 2 / n
+        want = np.zeros(width)
+        want[:min(n, width)] = np.linalg.svd(x, compute_uv=False) ** 2 / n
         # LAPACK's singular values and these are good to width * 2^-53 of the largest each
         assert np.max(np.abs(lam[h] - want)) <= 4 * width * 2.0 ** -53 * want[0]
         q = Q[h]
@@ -46,7 +54,7 @@ def test_pca_of_sets_that_start_differently(kind, D, n, full):
         y = x @ q                                                        # columns orthogonal up to that rounding
         c = y.T @ y / n
         assert np.max(np.abs(c - np.diag(np.diag(c)))) <= 2.0 ** -24 * 8 * want[0]
-        if kind in ("plain", "mixed", "close"):                          # full rank: relative accuracy of every eigenvalue
+        if n >= width and kind in ("plain", "mixed", "close"):                          # full rank: relative accuracy of every eigenvalue
             cond = np.sqrt(want[0] / want[-1])
             assert np.max(np.abs(lam[h] / want - 1)) <= 4 * width * 2.0 ** -53 * cond
 
