@@ -297,7 +297,8 @@ int rosaq_tune(const char* key, int32_t value);
  * would get: M rows, `channels` output channels in total over the layers of the launch (each layer
  * rounded up to whole 16-channel tiles by the caller: pass the sum of 16 * ceil(N_i / 16)),
  * `in_features` = D, `bits` 3 or 4 (16 for an all-fp16 layer), under the current rosaq_tune settings.
- * (Calls of many rows may run as the fixed 128 x 256 tiles of tune key "wide" instead: rosaq_launch_many_rows.)
+ * (Calls of many rows may run as the fixed 128 x 256 tiles of tune key "wide" instead: rosaq_launch_many_rows.
+ * Not a gated pair's (rosaq_linear_swiglu, rosaq_mlp_swiglu), which is never split and takes even numbers of channel tiles.)
  * shape_out (HOST, 5 ints) receives mt, nt (tiles of 16 rows / 16 channels per workgroup), waves per
  * workgroup, units in flight per wave and the number of workgroups that split one tile's contraction
  * (given a workspace of rosaq_workspace_bytes_batch size).  Errors: ROSAQ_ERR_NULL, ROSAQ_ERR_SHAPE (M, channels < 1,
@@ -306,7 +307,7 @@ int rosaq_launch_shape(int32_t M, int32_t channels, int32_t in_features, int32_t
 
 /* Reports, without launching anything (no GPU needed), which launches of a call of M rows take the kernels for many
  * rows (tune key "wide"): *uses_out is a sum of 1 = the main GEMM, 2 = the rotation of q_mode.  `channels` and
- * `in_features` as for rosaq_launch_shape, K and bits as packed.  Errors: ROSAQ_ERR_NULL, ROSAQ_ERR_SHAPE, ROSAQ_ERR_ARG. */
+ * `in_features` as for rosaq_launch_shape (not for a gated pair either), K and bits as packed.  Errors: ROSAQ_ERR_NULL, ROSAQ_ERR_SHAPE, ROSAQ_ERR_ARG. */
 int rosaq_launch_many_rows(int32_t M, int32_t channels, int32_t in_features, int32_t K, int32_t bits, int32_t q_mode,
                            int32_t* uses_out);
 

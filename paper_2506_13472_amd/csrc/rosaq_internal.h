@@ -107,14 +107,12 @@ struct GemmArgs {
 };
 constexpr int kMaxSplits = 16;
 constexpr int kTicketsPerLaunch = 4096;   // ticket words per GEMM launch kept in the workspace
-struct GemmTune {               // 0 = heuristic
-  int mt = 0, nt = 0, wpb = 0, depth = 0, splits = 0, wide = 0;
-  bool gated = false;           // a gated pair: channel tiles in twos
-};
+struct GemmTune { int mt = 0, nt = 0, wpb = 0, depth = 0, splits = 0, wide = 0; };   // 0 = heuristic
 struct GemmShape { int mt, nt, wpb, depth, splits; };
-// `part_bytes` / `ticket_count`: what the caller can offer for split-K (0 = never split)
+// `part_bytes` / `ticket_count`: what the caller can offer for split-K (0 = never split); `gated`: a gated pair, which takes channel
+// tiles in twos
 GemmShape pick_gemm_shape(int M, int ntiles, int D, int bits, const GemmTune& tune,
-                          size_t part_bytes = 0, int ticket_count = 0, int ks_s = -1);
+                          size_t part_bytes = 0, int ticket_count = 0, int ks_s = -1, bool gated = false);
 // bytes of partial tiles a launch of this shape needs
 size_t gemm_part_bytes(const GemmShape& s, int M, int ntiles);
 // What a launch runs as.  Decided once: a split launch (shape.splits > 1) finds its tickets cleared only because the launch
@@ -131,7 +129,7 @@ int launch_gemm(const GemmArgs& a, const GemmPlan& plan, void* stream);
 bool fuses_rotation(const GemmArgs& a, const GemmPlan& plan, void* stream);
 int launch_rotate_gemm(const GemmArgs& a, const void* x, int64_t ldx, const void* qh, const int32_t* pos_dev, void* stream);
 // Whether plan_gemm takes the kernel for many rows (128 x 256 tiles).
-bool prefers_wide(int M, int ntiles, int D, int K, int bits, const GemmTune& tune);
+bool prefers_wide(int M, int ntiles, int D, int K, int bits, const GemmTune& tune, bool gated = false);
 // Host copy of the kernel's workgroup -> (channel chunk, row group) map: b < 0 returns the grid
 // size, otherwise 1 and the pair, or 0 for a padding workgroup that exits at once.
 int block_map_host(int b, int chunks, int mgroups, int* chunk, int* mg);

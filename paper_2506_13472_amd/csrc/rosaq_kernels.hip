@@ -953,7 +953,7 @@ static int clamp_depth(int mt, int nt, int wpb, int depth) {
   return std::min(depth, max_depth);
 }
 
-static GemmShape pick_unsplit(int M, int ntiles, int D, int bits, const GemmTune& tune);
+static GemmShape pick_unsplit(int M, int ntiles, int D, int bits, const GemmTune& tune, bool gated);
 
 // Rounds of a launch whose workgroups have a compute unit each, by the fullest XCD (32 of them) or, with more than four row
 // groups, shader engine (8): see prefers_wide.
@@ -971,8 +971,8 @@ static int64_t full_rounds(int chunks, int mgroups) {
 // 160 workgroups of 32 x 64 in 25.9 us, as 80 x 3 workgroups of 64 x 64 in 22.4 us.  The default
 // therefore splits only such launches; rosaq_tune("splits", n) forces any count for tests.
 GemmShape pick_gemm_shape(int M, int ntiles, int D, int bits, const GemmTune& tune, size_t part_bytes,
-                          int ticket_count, int ks_s) {
-  GemmShape base = pick_unsplit(M, ntiles, D, bits, tune);
+                          int ticket_count, int ks_s, bool gated) {
+  GemmShape base = pick_unsplit(M, ntiles, D, bits, tune, gated);
   base.splits = 1;
   const int mtiles = (M + 15) / 16;
   if (tune.splits == 1 || part_bytes == 0 || ticket_count <= 0 || mtiles > 4) return base;
@@ -1015,7 +1015,7 @@ GemmShape pick_gemm_shape(int M, int ntiles, int D, int bits, const GemmTune& tu
   return base;
 }
 
-static GemmShape pick_unsplit(int M, int ntiles, int D, int bits, const GemmTune& tune) {
+static GemmShape pick_unsplit(int M, int ntiles, int D, int bits, const GemmTune& tune, bool gated) {
   GemmShape s;
   const int mtiles = (M + 15) / 16;
   const double k = static_cast<double>(D);
@@ -1063,7 +1063,7 @@ static GemmShape pick_unsplit(int M, int ntiles, int D, int bits, const GemmTune
     // 82.6 (640 of 64 x 64 / 512); 5120 -> 5120 at 256 21.8 / 18.8, at 320 38.2 / 34.0, at 512 39.4 / 35.5; 2048 -> 5120 at 256 13.8 / 11.7;
     // where no round is saved they lose: 11008 -> 4096 at 256 28.5 / 31.8 (256 / 208), at 384 50.9 / 59.4, 4096 -> 8192 at 320 43.4 / 55.5.
     // A gated pair has no odd numbers of tiles.
-    if (!tune.gated && mtiles >= 3 && s.mt == 4 && (s.nt == 3 || s.nt == 4) && tune.mt != 1 && tune.mt != 2) {
+    if (!gated && mtiles >= 3 && s.mt == 4 && (s.nt == 3 || s.nt == 4) && tune.mt != 1 && tune.mt != 2) {
       const int mgroups = (mtiles + 3) / 4;
       // a last round that is not full costs about half way between its share and a whole one
       auto price = [&](int nt) {
@@ -1246,10 +1246,10 @@ static int (*kernel_for(int bits, const GemmShape& sh))(const GemmDev&, void*) {
 // at 512 57 / 74, at 2048 186 / 301, with K = 2048 208 / 307; 5120 -> 5120 at 1536 rows 129 / 117, with K = 1024 139 / 120;
 // 13824 -> 5120 at 1536 rows 325 / 265; INT3 4096 -> 12288 at 2048 rows 176 / 285; fp16 4096 -> 4096 at 256 rows 47 / 20,
 // at 2048 65 / 132.
-bool prefers_wide(int M, int ntiles, int D, int K, int bits, const GemmTune& tune) {
+bool prefers_wide(int M, int ntiles, int D, int K, int bits, const GemmTune& tune, bool gated) {
   if (tune.wide == 2) return M > 64;
   if (M <= 64 || tune.wide == 1 || tune.mt || tune.nt || tune.wpb || tune.depth || tune.splits) return false;
-  const GemmShape s = pick_unsplit(M, ntiles, D, bits, tune);
+  const GemmShape s = pick_unsplit(M, ntiles, D, bits, tune, gated);
   auto rounds = [](int chunks, int mgroups, bool alone) {
     const int64_t cx = (chunks + 7) / 8;
     return static_cast<double>(alone ? full_rounds(chunks, mgroups) : (cx * mgroups + 31) / 32);
@@ -1270,19 +1270,17 @@ GemmPlan plan_gemm(const GemmArgs& a, const GemmTune& tune) {
   for (int i = 0; i < a.nseg; ++i) tiles += (a.seg[i].N + kTileN - 1) / kTileN;
   const int bits = a.G == 0 ? 16 : a.bits;
   GemmPlan plan;
-  GemmTune asked = tune;
-  asked.gated = a.swiglu != 0;
-  plan.wide = a.xrow == nullptr && prefers_wide(a.M, tiles, a.KS * kKStep, a.ks_s * kKStep, bits, asked);
+  const bool gated = a.swiglu != 0;
+  plan.wide = a.xrow == nullptr && prefers_wide(a.M, tiles, a.KS * kKStep, a.ks_s * kKStep, bits, tune, gated);
   if (plan.wide) return plan;
   auto choose = [&](GemmTune t) {
-    t.gated = asked.gated;
     auto shape = [&]() {
       return pick_gemm_shape(a.M, tiles, a.KS * kKStep, bits, t, a.part ? a.part_bytes : 0,
-                             a.tickets ? a.ticket_count : 0, a.ks_s);
+                             a.tickets ? a.ticket_count : 0, a.ks_s, gated);
     };
-    if (a.swiglu) t.splits = 1;        // a gated pair runs unsplit with an even number of channel tiles per workgroup
+    if (gated) t.splits = 1;        // a gated pair runs unsplit with an even number of channel tiles per workgroup
     plan.shape = shape();
-    if (a.swiglu && (plan.shape.nt & 1)) {
+    if (gated && (plan.shape.nt & 1)) {
       // 48-channel tiles become 32 x 96 ones (gate + up of a 7B MLP at M = 64: 26.9 us against 28.7 us
       // as 64 x 64 tiles, which need a second round of workgroups; all-fp16 layers have none of 96 channels)
       const bool to96 = plan.shape.nt == 3 && bits != 16;
@@ -1290,7 +1288,7 @@ GemmPlan plan_gemm(const GemmArgs& a, const GemmTune& tune) {
       if (to96) t.mt = 2;
       plan.shape = shape();
     }
-    plan.run = a.swiglu && (plan.shape.nt & 1) ? nullptr : kernel_for(bits, plan.shape);
+    plan.run = gated && (plan.shape.nt & 1) ? nullptr : kernel_for(bits, plan.shape);
   };
   choose(tune);
   // a forced combination that no kernel is built for falls back to the heuristic's choice
