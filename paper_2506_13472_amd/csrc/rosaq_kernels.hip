@@ -1317,17 +1317,22 @@ static bool is_captured(void* stream) {
   return true;
 }
 
-// Up to 16 rows, as gemm_kernel would take them in 16 x 16 tiles of sixteen waves.  us a call, two launches / one, 1 and 16 rows: in
+// Up to 16 rows, as gemm_kernel would take them in 16 x 16 tiles of sixteen waves.  us a call, two launches / one, 1 and 16 rows.  In
 // a graph 256 -> 2048 channels 5.1 / 3.6 and 5.3 / 3.9, 512 -> 1024 5.3 / 4.6 and 5.6 / 5.1, 512 -> 4096 5.7 / 5.2 and 5.8 / 5.6, but
-// 1024 -> 1024 5.6 / 6.5 and 5.9 / 7.2; called eagerly, where the host's second launch is what takes the time, 8.6 to 8.9 / 5.4 to 5.7 up to
-// 512 channels and 8.6 / 5.7 and 8.7 / 6.0 for 1024 -> 1024.  So up to 512 channels always, up to 1024 unless the call is captured.
+// 1024 -> 1024 5.6 / 6.5 and 5.9 / 7.2: so up to 512 channels.  Called eagerly it also counts what the host takes, and from here it cannot be seen which
+// of the two sets the pace.  Where it is the host, one launch saves 3: 9.0 to 9.3 / 5.5 to 6.3 from 512 to 1024 channels.  Where calls queue up
+// behind other work it is as in a graph: 512 -> 4096 5.6 / 5.0 and 5.8 / 5.3, 640 -> 1024 5.5 / 5.2 and 5.7 / 5.7, 640 -> 4096 5.6 / 5.6 and
+// 5.8 / 6.1, 768 -> 1024 5.8 / 5.7 and 5.9 / 6.1, 768 -> 4096 5.7 / 5.9 and 6.1 / 6.5, 1024 -> 64 5.7 / 6.3 and 5.8 / 6.7, 1024 -> 1024
+// 5.9 / 6.4 and 6.0 / 6.8, but 896 -> 4096 5.8 / 6.6 and 6.2 / 7.1, 1024 -> 2048 5.8 / 6.4 and 6.0 / 7.0, 1024 -> 4096 5.8 / 6.9 and 6.3 / 7.3.
+// So one launch up to 768 channels, and up to 1024 where a quarter of the compute units have a workgroup at most: the line is at a loss
+// behind other work of a quarter of what the host saves.
 bool fuses_rotation(const GemmArgs& a, const GemmPlan& plan, void* stream) {
   int tiles = 0;
   for (int i = 0; i < a.nseg; ++i) tiles += (a.seg[i].N + kTileN - 1) / kTileN;
   const GemmShape& s = plan.shape;
   return !plan.wide && !a.swiglu && a.out_frag == 0 && a.zero_ptr == nullptr && a.M <= kTileN && a.G > 0 && a.KS <= kFusedHeads * 4 &&
          tiles <= 256 && s.mt == 1 && s.nt == 1 && s.wpb == kFusedWaves && s.splits == 1 &&
-         (a.KS <= kFusedHeads * 2 || !is_captured(stream));
+         (a.KS <= kFusedHeads * 2 || ((a.KS <= kFusedHeads * 3 || tiles <= 64) && !is_captured(stream)));
 }
 
 int launch_rotate_gemm(const GemmArgs& a, const void* x, int64_t ldx, const void* qh, const int32_t* pos_dev, void* stream) {
