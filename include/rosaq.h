@@ -269,7 +269,7 @@ int rosaq_stream_probe(const void* src_dev, size_t src_bytes, const void* shared
                        size_t shared_bytes, size_t shared_bytes_per_workgroup, int32_t workgroups,
                        int32_t threads, void* sink_dev, size_t sink_bytes, void* hip_stream);
 
-/* Tuning aid for benchmarks; affects later rosaq_linear* calls in this process.
+/* Tuning aid for benchmarks; affects later rosaq_linear* and rosaq_pca_* calls in this process.
  *   "mt", "nt"  16-row / 16-channel MFMA tiles per workgroup (0 = heuristic, 1, 2, 4; nt also 3 and 6
  *             for low-bit layers with mt >= 2)
  *   "rot_mt", "rot_nt", "rot_depth"  the same three knobs for the dense-rotation launch (rot_nt also 3 and 5, not 6)
@@ -288,8 +288,10 @@ int rosaq_stream_probe(const void* src_dev, size_t src_bytes, const void* shared
  *   "stages"  3 = whole call (default), 1 = prologue kernels only, 2 = main GEMM only
  *             (2 reuses the rotated activations a previous call left in the workspace; in front of a split
  *             main GEMM it runs a small launch that clears the tickets)
+ *   "pca_sweeps"  1 = calibration by sweeps in fp64 alone, what rosaq_pca_headwise and rosaq_pca_full fall back to
+ *             without memory for the faster way (0 = default)
  * For benchmarks and tests only: the settings are process-wide and not synchronised, so no other
- * thread may be inside a rosaq_linear* call while they change, and "stages" other than 3 makes
+ * thread may be inside a rosaq_linear* or rosaq_pca_* call while they change, and "stages" other than 3 makes
  * every later call skip part of its work while still returning ROSAQ_OK. */
 int rosaq_tune(const char* key, int32_t value);
 

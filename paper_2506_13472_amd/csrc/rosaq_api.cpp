@@ -839,6 +839,10 @@ int rosaq_tune(const char* key, int32_t value) {
       return fail(ROSAQ_ERR_ARG, "tile counts must be 0, 1, 2 or 4 (nt also 3 or 6)");
     (key[0] == 'm' ? g_tune.mt : g_tune.nt) = value; return ROSAQ_OK;
   }
+  if (!std::strcmp(key, "pca_sweeps")) {
+    if (value < 0 || value > 1) return fail(ROSAQ_ERR_ARG, "pca_sweeps must be 0 or 1");
+    g_tune_pca_sweeps = value == 1; return ROSAQ_OK;
+  }
   if (!std::strcmp(key, "stages")) {
     if (value < 1 || value > 3) return fail(ROSAQ_ERR_ARG, "stages must be 1, 2 or 3");
     g_tune_stages = value; return ROSAQ_OK;

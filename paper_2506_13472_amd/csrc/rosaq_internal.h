@@ -193,6 +193,7 @@ int launch_check_rotation(const void* Q_dev, size_t words, void* flag, void* has
 int launch_rotation_image(const void* Q_dev, int D, int headwise, const int32_t* perm_dev, void* qf_image,
                           void* stream);
 
+extern bool g_tune_pca_sweeps;      // calibration by sweeps in fp64 alone, as where its scratch memory is not to be had
 int pca_headwise_device(const void* X_dev, int n_cal, int D, int64_t ldx, float* Q_host,
                         double* eig_host, void* stream);
 int pca_full_device(const void* X_dev, int n_cal, int D, int64_t ldx, float* Q_host, double* eig_host,

@@ -1004,6 +1004,8 @@ __global__ __launch_bounds__(256) void pca_write_kernel(PcaDev p, const int* __r
     out[static_cast<size_t>(i0 + (k >> 6)) * p.Db + j0 + (k & 63)] = tile[k & 63][k >> 6];
 }
 
+bool g_tune_pca_sweeps = false;
+
 static int pca_fail(hipError_t e, const char* what) {
   set_error(std::string(what) + ": " + hipGetErrorString(e));
   return ROSAQ_ERR_HIP;
@@ -1050,11 +1052,11 @@ static int pca_blocks_device(const void* X_dev, int n_cal, int D, int Db, int64_
     total += (sizes[i] + 255) / 256 * 256;
   }
   char* mem = nullptr;
-  hipError_t e = hipMalloc(reinterpret_cast<void**>(&mem), total);
-  // without memory for the start and the corrections, sweeps alone will do (step 4 from V = 1)
+  hipError_t e = g_tune_pca_sweeps ? hipErrorOutOfMemory : hipMalloc(reinterpret_cast<void**>(&mem), total);
+  // without memory for the start and the corrections, sweeps alone will do (step 6 from V = 1)
   const bool lean = e == hipErrorOutOfMemory;
   if (lean) {
-    (void)hipGetLastError();
+    if (!g_tune_pca_sweeps) (void)hipGetLastError();
     e = hipMalloc(reinterpret_cast<void**>(&mem), lean_total);
   }
   if (e != hipSuccess) return pca_fail(e, who);

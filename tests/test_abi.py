@@ -172,6 +172,7 @@ def test_tune_keys():
     assert _code(lambda: B.rosaq_tune("wpb", 3)) == -3
     assert _code(lambda: B.rosaq_tune("depth", 5)) == -3
     assert _code(lambda: B.rosaq_tune("stages", 0)) == -3
+    assert _code(lambda: B.rosaq_tune("pca_sweeps", 2)) == -3
     assert _code(lambda: B.rosaq_tune("nope", 1)) == -3
 
 

@@ -38,17 +38,34 @@ def _set(kind, n, D, rng):
 @pytest.mark.parametrize("D,n,full", [(256, 300, False), (256, 257, True), (384, 900, True), (256, 50, False), (384, 100, True), (512, 500, True)])
 def test_pca_of_sets_that_start_differently(kind, D, n, full):
     print(f"case pca start {kind} D={D} n_cal={n} full={full}", flush=True)
+    _check(kind, D, n, full)
+
+
+@pytest.mark.parametrize("kind", ["plain", "mixed", "rank", "one long"])
+@pytest.mark.parametrize("D,n,full", [(256, 300, False), (384, 900, True), (384, 100, True)])
+def test_pca_by_sweeps_alone(kind, D, n, full):
+    print(f"case pca sweeps alone {kind} D={D} n_cal={n} full={full}", flush=True)
+    B.rosaq_tune("pca_sweeps", 1)                       # as without memory for the search
+    try:
+        # up to 20 sweeps pass every column through width / 32 - 1 products of 64 terms, each good to 8 (the root of 64) 2^-53
+        # of the column's length, and an eigenvalue is its square
+        _check(kind, D, n, full, 2 * 20 * ((D if full else 128) // 32 - 1) * 8 * 2.0 ** -53)
+    finally:
+        B.rosaq_tune("pca_sweeps", 0)
+
+
+def _check(kind, D, n, full, good_to=None):
     X = _set(kind, n, D, np.random.default_rng(77 + D + n))
     xd = torch.from_numpy(X).cuda()
     Q, lam = (B.rosaq_pca_full if full else B.rosaq_pca_headwise)(xd.data_ptr(), n, D, D)
     width = D if full else 128
+    good_to = good_to or 4 * width * 2.0 ** -53      # LAPACK's singular values and these are good to width * 2^-53 of the largest each
     Q, lam = np.asarray(Q).reshape(-1, width, width).astype(np.float64), np.asarray(lam).reshape(-1, width)
     for h in range(D // width):
         x = X[:, h * width:(h + 1) * width].astype(np.float64)
         want = np.zeros(width)
         want[:min(n, width)] = np.linalg.svd(x, compute_uv=False) ** 2 / n
-        # LAPACK's singular values and these are good to width * 2^-53 of the largest each
-        assert np.max(np.abs(lam[h] - want)) <= 4 * width * 2.0 ** -53 * want[0]
+        assert np.max(np.abs(lam[h] - want)) <= good_to * want[0]
         q = Q[h]
         assert np.max(np.abs(q.T @ q - np.eye(width))) <= 2e-6           # the rounding of Q to fp32
         y = x @ q                                                        # columns orthogonal up to that rounding
@@ -56,7 +73,7 @@ def test_pca_of_sets_that_start_differently(kind, D, n, full):
         assert np.max(np.abs(c - np.diag(np.diag(c)))) <= 2.0 ** -24 * 8 * want[0]
         if n >= width and kind in ("plain", "mixed", "close"):                          # full rank: relative accuracy of every eigenvalue
             cond = np.sqrt(want[0] / want[-1])
-            assert np.max(np.abs(lam[h] / want - 1)) <= 4 * width * 2.0 ** -53 * cond
+            assert np.max(np.abs(lam[h] / want - 1)) <= good_to * cond
 
 
 def _spoil(x, kind):
@@ -88,7 +105,12 @@ def test_pca_refuses_a_set_that_is_not_numbers(kind, n):
     x = torch.randn((n, 256), device="cuda", generator=torch.Generator("cuda").manual_seed(5)).half()
     _spoil(x, kind)
     for call in (B.rosaq_pca_full, B.rosaq_pca_headwise):
-        print(f"case pca not numbers {kind} n_cal={n} {call.__name__}", flush=True)
-        with pytest.raises(B.RosaqError) as error:
-            call(x.data_ptr(), n, 256, 256)
-        assert error.value.code == -8          # ROSAQ_ERR_HIP
+        for sweeps in (0, 1):
+            print(f"case pca not numbers {kind} n_cal={n} {call.__name__} sweeps alone {sweeps}", flush=True)
+            B.rosaq_tune("pca_sweeps", sweeps)
+            try:
+                with pytest.raises(B.RosaqError) as error:
+                    call(x.data_ptr(), n, 256, 256)
+            finally:
+                B.rosaq_tune("pca_sweeps", 0)
+            assert error.value.code == -8          # ROSAQ_ERR_HIP
