@@ -235,7 +235,9 @@ void gemm_kernel(GemmDev p) {
   // Every workgroup walks the groups in the same order: the fp32 sum of an output element
   // is then the same whatever the tile of eight waves or the batching of an unsplit launch of this
   // kernel (starting each workgroup at its own group was measured: 1-3 % faster, not worth that
-  // property).  Splits, sixteen waves and wide_gemm_kernel add in other orders.
+  // property).  The exceptions are 64 x 80 tiles of low-bit layers, which scale and add a group in two halves (kAhead below), splits,
+  // sixteen waves and wide_gemm_kernel: as pick_unsplit takes 64 x 80 tiles by the channels of the whole launch, a layer of 33 rows on may
+  // differ in the last bit from itself in a batch.
   auto load_code = [&](int g, GroupRegs& r, int nt) {
       constexpr int kCodeDwords = BITS == 4 ? 256 : 192, kRecDwords = kCodeDwords + 16;
       const uint32_t* rec = wq_t[nt] + static_cast<unsigned>(g) * static_cast<unsigned>(kRecDwords);
@@ -1042,7 +1044,7 @@ static GemmShape pick_unsplit(int M, int ntiles, int D, int bits, const GemmTune
   // to scale, 40 per group otherwise).  q/k/v of a 7B attention block in one launch at M = 64:
   // 192 workgroups of 64 x 64 take 16.2 us, 256 of 32 x 96 15.0, 256 of 64 x 48 14.5; gate + up
   // of a 7B MLP 28.7 / 26.9 / 26.3 us, at M = 32 32 x 96 tiles make it one round (19.7 -> 16.2).
-  // Eight waves like every default shape: the summation order stays the same.
+  // Eight waves like every default shape: the summation order stays the same, but for the 64 x 80 tiles of the rule behind.
   if (bits != 16 && mtiles >= 2) {
     const double groups = k / 128.0;
     auto cost = [&](int mt, int nt) {
