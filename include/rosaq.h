@@ -231,13 +231,14 @@ int rosaq_packed_export(const rosaq_packed_t* p, int32_t* salient_idx, uint16_t*
  * Jacobi rotations until the columns of X_h V are mutually orthogonal in fp64 (a search in fp32 on C_h only
  * decides which V to start from; eigenvalue c = |column c of X_h V|^2 / n_cal): until every pair of columns has a
  * cosine <= 1e-14, or all angles left are below 3e-7 taken together and are turned once more, or the off-diagonal norm
- * of the implied C_h is <= 1e-13 ||C_h||_F, in every head.  Results, ready for rosaq_pack_weights:
+ * of the implied C_h is <= 1e-13 ||C_h||_F, in every head (columns below 1e-13 of the longest are a null space, and any orthonormal
+ * basis of it will do).  Results, ready for rosaq_pack_weights:
  *   Q_host            HOST fp32 [D/128][128][128], eigenvectors as columns, sorted by eigenvalue
  *                     (descending; each column signed so that its largest entry is positive)
  *   eigenvalues_host  HOST fp64 [D], descending inside every head, >= 0
  *   X_dev             DEVICE fp16 [n_cal x D] calibration activations, row r at X + r*ldx
  * Allocates its own device scratch and waits for the result (calibration time, not the hot path).
- * Errors: NULL, SHAPE, ALIGN, HIP, NOCONVERGE (tolerance not reached within 60 sweeps). */
+ * Errors: NULL, SHAPE, ALIGN, HIP (also where X holds NaN or Inf), NOCONVERGE (tolerance not reached within 60 sweeps). */
 int rosaq_pca_headwise(const void* X_dev, int32_t n_cal, int32_t D, int64_t ldx, float* Q_host,
                        double* eigenvalues_host, void* hip_stream);
 
@@ -250,8 +251,8 @@ int rosaq_pca_headwise(const void* X_dev, int32_t n_cal, int32_t D, int64_t ldx,
  *                     completion (any one is valid)
  *   eigenvalues_host  HOST fp64 [D], descending, >= 0
  *   X_dev             DEVICE fp16 [n_cal x D], row r at X + r*ldx
- * D a multiple of 128 up to 8192 (2048 rows of a 1024-channel layer take 9 ms, 4608 of a 2048-channel
- * layer 38 ms).  Allocates its own device scratch (8 D (n_cal + D) bytes, 4 D^2 bytes of results and about 3 KiB per channel, and
+ * D a multiple of 128 up to 8192 (2048 rows of a 1024-channel layer take 9 ms, 4608 of a 2048- and of a
+ * 4096-channel layer 40 and 241, 8704 of 8192 channels 2.1 s).  Allocates its own device scratch (8 D (n_cal + D) bytes, 4 D^2 bytes of results and about 3 KiB per channel, and
  * 32 to 88 D^2 bytes more for the faster way, which it does without where that much is not free) and waits for the result.  Errors: NULL, SHAPE, ALIGN, HIP, NOCONVERGE. */
 int rosaq_pca_full(const void* X_dev, int32_t n_cal, int32_t D, int64_t ldx, float* Q_host,
                    double* eigenvalues_host, void* hip_stream);
