@@ -372,10 +372,14 @@ static bool rotates_whole_heads(int D, int M) {
 
 // Whether the dense rotation reads row-major x itself, without a copy into fragments in front of it.  That saves a launch (1.5
 // us in a graph, more where the host issues it), but its loads then take 64 bytes of each of 16 rows where those of fragments
-// take 1 KiB in a row, which costs more the more of them there are.  us of a call with 512 channels behind the rotation,
-// copy / in place: 1024 channels at 17 rows 9.5 / 7.9, at 64 9.7 / 8.3; 1408 at 37 10.9 / 9.5; 2048 at 64 12.6 / 11.0; 4096 at 24 17.5 /
-// 15.7, at 48 19.7 / 19.3, at 64 19.9 / 21.1; 5120 at 24 25.9 / 25.9, at 32 26.3 / 28.8, at 37 27.4 / 24.9, at 64 28.2 / 29.9.
-static bool rotates_in_place(int D, int M) { return M <= (D <= 2048 ? 64 : (D <= 4096 ? 48 : 16)); }
+// take 1 KiB in a row, which costs more the more of them there are.  The lines are where it is faster both with Q from memory and with Q in
+// a cache, which leaves less time to hide those loads in.  us of a call with 512 channels behind the rotation, in a graph, copy / in place, Q from
+// memory and (one layer) in a cache: 1408 channels at 17 rows 10.1 / 8.5 and 8.8 / 7.5, at 64 10.6 / 9.2 and 9.1 / 8.0; 2048 at 64 12.8 / 11.4 and 10.3 /
+// 9.2; 2560 at 48 14.4 / 13.2 and 10.7 / 9.9, at 56 15.8 / 15.2 and 11.3 / 12.1; 3072 at 32 15.4 / 14.4 and 11.7 / 11.1, at 37 16.7 / 15.8 and 12.9 /
+// 13.7; 4096 at 32 18.5 / 17.5 and 13.8 / 12.9, at 37 20.1 / 19.7 and 15.2 / 16.8, at 64 20.5 / 21.4 and 15.5 / 16.3.  Above, Q out of the last-level cache:
+// 5120 at 17 26.3 / 24.6, at 24 24.4 / 24.9, at 32 24.6 / 27.5, at 37 25.6 / 23.6, at 48 26.3 / 25.7, at 64 26.5 / 28.6; 6144 at 17 30.6 / 28.6, at 32
+// 29.6 / 32.5, at 37 29.8 / 29.4, at 64 30.4 / 32.8; 8192 at 17 38.5 / 36.8, at 32 39.2 / 44.0, at 37 58.0 / 53.6, at 64 58.4 / 57.9.
+static bool rotates_in_place(int D, int M) { return M <= (D <= 2048 ? 64 : (D <= 2560 ? 48 : (D <= 4096 ? 32 : 16))); }
 
 // x -> xhat fragments in the workspace (gather / head-wise blocks / dense rotation).
 static int run_prologue(const rosaq_packed_t* p, const WsPlan& w, const void* x_dev, int M,

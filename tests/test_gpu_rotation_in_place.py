@@ -12,7 +12,7 @@ from test_gpu_parity import check_output
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("D,rows", [(128, (17, 33, 64, 65)), (2048, (17, 48, 49, 64, 65)), (2176, (32, 47, 48, 49)), (4224, (16, 17, 64))])
+@pytest.mark.parametrize("D,rows", [(128, (17, 33, 64, 65)), (2048, (17, 48, 49, 64, 65)), (2176, (32, 47, 48, 49)), (2560, (48, 49)), (2688, (31, 32, 33, 48)), (4096, (32, 33)), (4224, (16, 17, 64))])
 def test_dense_rotation_of_few_rows(D, rows):
     rng = np.random.default_rng(D)
     Q, lam = synth.random_orthogonal_dense(76, D), synth.descending_spectrum(77, D)
