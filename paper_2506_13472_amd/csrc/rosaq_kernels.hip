@@ -1060,24 +1060,25 @@ static GemmShape pick_unsplit(int M, int ntiles, int D, int bits, const GemmTune
       if (mtiles >= 3 && cost(4, 3) < best_alt) { best_alt = cost(4, 3); s.mt = 4; s.nt = 3; }
     }
     // Of the 64-row tiles, 48, 64 or 80 channels by the rounds of the fullest XCD or shader engine (these tiles have a compute unit
-    // each): a round of 64 x 48 takes 0.84 of one of 64 x 64, of 64 x 80 1.17 (main GEMM alone, contraction of 5120: 13.4, 16.0 and
-    // 18.7 us).  us, the shape chosen above / 64 x 80: 13824 -> 5120 at 256 rows 55.4 / 43.4 (428 of 64 x 48 / 256 workgroups), at 512 93.9 /
-    // 82.6 (640 of 64 x 64 / 512); 5120 -> 5120 at 256 21.8 / 18.8, at 320 38.2 / 34.0, at 512 39.4 / 35.5; 2048 -> 5120 at 256 13.8 / 11.7;
-    // where no round is saved they lose: 11008 -> 4096 at 256 28.5 / 31.8 (256 / 208), at 384 50.9 / 59.4, 4096 -> 8192 at 320 43.4 / 55.5.
-    // A gated pair has no odd numbers of tiles.
+    // each): estimates fitted to 340 launches (512 to 13824 -> 512 to 32000 channels, 33 to 1200 rows, INT4 and INT3, K up to 256), 7 % rms.
+    // Over 190 of them whose shape this changes it gains 12 % with the weights in a cache and 13 % from memory; three lose 1.5 to 3 %.  With one
+    // price a round for all contractions (0.84 : 1 : 1.17) and a last round by half its share 15 of 150 lost up to 10 % (1792 -> 12392 at 237
+    // rows INT3 31.1 / 33.6 us, 1536 -> 1156 at 1149 24.4 / 27.0).  us, the shape chosen above / 64 x 80: 13824 -> 5120 at 256
+    // rows 55.4 / 43.4 (428 of 64 x 48 / 256 workgroups), at 512 93.9 / 82.6 (640 of 64 x 64 / 512); 5120 -> 5120 at 256 21.8 / 18.8, at 320 38.2 /
+    // 34.0, at 512 39.4 / 35.5; 2048 -> 5120 at 256 13.8 / 11.7; where no round is saved they lose: 11008 -> 4096 at 256 28.5 / 31.8 (256 /
+    // 208), at 384 50.9 / 59.4, 4096 -> 8192 at 320 43.4 / 55.5.  A gated pair has no odd numbers of tiles.
     if (!gated && mtiles >= 3 && s.mt == 4 && (s.nt == 3 || s.nt == 4) && tune.mt != 1 && tune.mt != 2) {
       const int mgroups = (mtiles + 3) / 4;
-      // a last round that is not full costs about half way between its share and a whole one
-      auto price = [&](int nt) {
+      auto us = [&](int nt) {
         const int64_t cx = ((ntiles + nt - 1) / nt + 7) / 8;
         const double share = mgroups <= kMapRows ? cx * mgroups / 32.0 : cx * ((mgroups + 3) / 4) / 8.0;
-        return (nt == 3 ? 0.84 : (nt == 4 ? 1.0 : 1.17)) * std::max(1.0, 0.5 * (share + std::ceil(share)));
+        const double rounds = std::ceil(share);
+        return nt == 3 ? 4.4 + rounds * (2.6 + 0.00193 * D) : (nt == 4 ? 5.7 + rounds * (2.6 + 0.00234 * D) : 5.4 + rounds * (4.25 + 0.00304 * D));
       };
-      const double chosen = price(s.nt);
-      double least = chosen;
+      double least = us(s.nt);
       if (full_rounds((ntiles + 4) / 5, mgroups) <= 6)     // with more rounds, what is saved of the last one is little
         for (int nt : {4, 5})
-          if (price(nt) < least && price(nt) < (nt == 4 ? 0.95 : 0.88) * chosen) { least = price(nt); s.nt = nt; }
+          if (us(nt) < least) { least = us(nt); s.nt = nt; }
     }
   }
   // The same for all-fp16 layers (the dense rotation), which have no conversion: 48-channel tiles
