@@ -919,9 +919,10 @@ static int launch_gemm_t(const GemmDev& d, void* stream) {
   g.grid3 = d.mgroups <= kMapRows && octets <= 65535;
   const dim3 grid = g.grid3 ? dim3(8, splits * d.mgroups, octets) : dim3(map_grid(d.chunks, d.mgroups));
   auto kernel = gemm_kernel<BITS, MT, NT, WPB, DEPTH>;
-  // 64 x 48 tiles of up to two groups a wave (DEPTH 0: one at a time) have little to fetch ahead, and their last group waits for all of it
-  // either way: 2048 -> 12288 at 64 rows 9.5 us, 9.8 ahead; 2432 -> 6605 at 173 15.8 / 16.0.
-  if constexpr (BITS != 16 && MT == 4 && NT == 3 && WPB == 8 && DEPTH == 1)
+  // 64 x 48 and 32 x 96 tiles of up to two groups a wave (DEPTH 0: one at a time) have little to fetch ahead, and their last group waits for all of
+  // it either way: 64 x 48, 2048 -> 12288 at 64 rows 9.5 us, 9.8 ahead; 2432 -> 6605 at 173 15.8 / 16.0; 32 x 96, 90 launches of 8 to 16
+  // groups 0 to 3 % slower ahead with the weights in a cache, 0 to 5 % from memory (1792 -> 8670 at 135 rows 23.4 / 24.1).
+  if constexpr (BITS != 16 && ((MT == 4 && NT == 3) || (MT == 2 && NT == 6)) && WPB == 8 && DEPTH == 1)
     if (d.G <= 2 * WPB) kernel = gemm_kernel<BITS, MT, NT, WPB, 0>;
   hipLaunchKernelGGL(kernel, grid, dim3(WPB * 64), 0, static_cast<hipStream_t>(stream), g);
   const hipError_t e = hipGetLastError();
