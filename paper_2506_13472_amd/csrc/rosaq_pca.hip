@@ -576,11 +576,11 @@ __global__ __launch_bounds__(256) void tangent_kernel(PcaDev p) {
       const double d = be - al, g = 2.0 * ga;
       if (ga * ga > PcaReal<double>::kEps2 * ab) t = (d < 0.0 || (d == 0.0 && j < i) ? -g : g) / (fabs(d) + sqrt(d * d + g * g));
       if constexpr (kFull) {
-        const double longer = fmax(al, be), tt = t * t;
+        const double longer = fmax(al, be);
         c2 = larger(c2, ga * ga / ab);
-        f2 += longer <= kFaint * longest ? tt : 0.0;
-        d2 += longer > kFaint * longest && longer <= kDim * longest ? tt : 0.0;
-        t2 += longer <= kDim * longest ? 0.0 : tt;
+        if (longer <= kFaint * longest) f2 = __builtin_fma(t, t, f2);
+        else if (longer <= kDim * longest) d2 = __builtin_fma(t, t, d2);
+        else t2 = __builtin_fma(t, t, t2);
       } else {
         t2 = __builtin_fma(t, t, t2);
       }
@@ -590,10 +590,13 @@ __global__ __launch_bounds__(256) void tangent_kernel(PcaDev p) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
     t2 += __shfl_xor(t2, o, 64);
-    if constexpr (kFull) {
+    if constexpr (kFull) c2 = larger(c2, __shfl_xor(c2, o, 64));
+  }
+  if (kFull && __any(f2 != 0.0 || d2 != 0.0)) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
       f2 += __shfl_xor(f2, o, 64);
       d2 += __shfl_xor(d2, o, 64);
-      c2 = larger(c2, __shfl_xor(c2, o, 64));
     }
   }
   if (lane == 0) {
