@@ -1,8 +1,7 @@
 // PCA of the calibration activations on the GPU (Sec. 3.1 Eq. 4; per attention head Sec. 3.1.1,
 // Eq. 6): the eigenvectors of C = X^T X / n_cal are the right singular vectors of X, its
-// eigenvalues the squared column norms of X V / n_cal.  One-sided Jacobi: plane rotations are
-// applied to pairs of columns of X until all columns are mutually orthogonal; the same rotations
-// accumulate in V.  C itself is never formed.
+// eigenvalues the squared column norms of X V / n_cal.  Pairs of columns of X V are
+// turned until all are mutually orthogonal; V accumulates the turns.  C itself, n_cal times, only serves to find a V to start from.
 //
 // What bounds it: a sweep over all pairs is D_b - 1 dependent rounds however the work is laid out, and eight to ten sweeps of
 // them in fp64 took 1.9 ms for 32 heads of 128 channels and 19 ms for one problem of 1024 (2048 rows).  So the sweeps are made
